@@ -63,8 +63,7 @@ size_t ne_workspace_bytes(int32_t dim, int64_t max_batch, int32_t max_negatives)
  *   seed keys every random draw made through this handle.
  *   workspace_dev : device scratch for ne_train_batch, 256-byte aligned, at least
  *                   ne_workspace_bytes(dim, max_batch, max_negatives) bytes, caller-owned, used only
- *                   through this handle until the handle is destroyed; it is cleared on the stream
- *                   here.  Pass NULL with max_batch = 0 for a handle that is only evaluated.
+ *                   through this handle until the handle is destroyed; it needs no initialisation.  Pass NULL with max_batch = 0 for a handle that is only evaluated.
  *   1 <= max_batch <= NE_MAX_BATCH, 0 <= max_negatives <= NE_MAX_NEGATIVES when training.
  * *out receives a handle to free with ne_destroy_tables.  Errors: NE_ERR_ARG, NE_ERR_NOMEM, NE_ERR_HIP.
  */
@@ -103,16 +102,15 @@ ne_status ne_build_neg_alias(ne_alias** out, const uint32_t* degree_host, int64_
  *   vertex[src] += lr * sum_j g_j c_j,   context[id_j] += lr * g_j x,
  * contributions to the same row summed (in fp32; the order of the sum is not fixed).
  * Accuracy: a row that one reference of the batch names is updated with one rounding per element.  A row
- * that n references name has their n deltas added one after the other in fp32, so its update carries an
- * accumulation error of up to about n * 2^-24 of the summed magnitudes: typically sqrt(n) * 2^-24, close
- * to the bound when many of the contributions are identical (the same source row against the same context
- * row many times).  Up to n of about 1700 that is inside a relative error of 1e-4 per row; a hub row that
- * tens of thousands of samples of one batch name can exceed it (1.7e-4 measured at n = 4e5).
- * Calls on one handle must be ordered by the stream and must not overlap: the handle's workspace
- * carries state from one call to the next.  Errors: NE_ERR_ARG, NE_ERR_STATE, NE_ERR_HIP.  After
- * NE_ERR_HIP from a training call (a kernel launch failed part-way through its batches) the handle stays
- * usable: the next training call clears the workspace again before it starts; the tables may hold the
- * batches that were enqueued before the failure and part of the failing one.
+ * that n references name has their n deltas added in fp32, eight at a time and those sums one after the
+ * other, so its update carries an accumulation error of up to about n / 8 * 2^-24 of the summed magnitudes:
+ * typically sqrt(n / 8) * 2^-24, close to the bound when many of the contributions are identical (the same
+ * source row against the same context row many times).  Up to n of about 13 000 that is inside a relative
+ * error of 1e-4 per row.
+ * Calls on one handle must be ordered by the stream and must not overlap: they use the handle's
+ * workspace.  Errors: NE_ERR_ARG, NE_ERR_STATE, NE_ERR_HIP.  After NE_ERR_HIP from a training call (a kernel
+ * launch failed part-way through its batches) the handle stays usable; the tables may hold the batches
+ * that were enqueued before the failure and part of the failing one.
  */
 ne_status ne_train_batch(ne_tables* tables, const ne_alias* alias, const int32_t* pairs_dev, int64_t B,
                          int32_t K, float lr, uint64_t sample_base, int32_t* neg_out_dev,
@@ -124,8 +122,8 @@ ne_status ne_train_batch(ne_tables* tables, const ne_alias* alias, const int32_t
  * Algorithm 1 on one sample block with one negative-sampling table (Sec. III-C: a GPU trains its
  * vertex embeddings on a sample block against its fixed context partition).  The result is the same
  * as calling ne_train_batch once per batch with lr = lr_host[i] and sample_base + i*B; the call
- * exists because the id-only work of batch i+1 (negative draws, detection of rows named more than
- * once) then runs inside the kernels of batch i: two kernel launches per batch instead of four.
+ * exists because the id-only work of later batches (negative draws, detection of rows named more than
+ * once) then runs inside the train kernels of earlier ones: two kernel launches per batch instead of four.
  *   pairs_dev   : device, int32[n_pairs][2]; must stay unchanged until the enqueued work is done.
  *   lr_host     : host, float[ceil(n_pairs / B)], read during the call only.
  *   neg_out_dev : NULL, or device int32[n_pairs][K].
@@ -139,8 +137,8 @@ ne_status ne_train_block(ne_tables* tables, const ne_alias* alias, const int32_t
  * Train on a sequence of runs, each a run of consecutive batches as in ne_train_block on its own sample
  * block with its own negative-sampling table: what one GPU does over an epoch when it visits its sample
  * blocks one after the other (Sec. III-C, 2D partition of the samples).  Same result as one
- * ne_train_block call per run, in order; the call exists because the id-only work of a run's first batch
- * then rides in the kernels of the previous run's last batch, where separate calls would launch it on its
+ * ne_train_block call per run, in order; the call exists because the id-only work of a run's first batches
+ * then rides in the kernels of the previous run's last ones, where separate calls would launch it on its
  * own (two extra kernel launches per run).
  *   runs_host : host, ne_run[n_runs], read during the call only.  Per run: alias (may be NULL if K == 0),
  *               pairs_dev (device, int32[n_pairs][2], 8-byte aligned), n_pairs (0 = the run is skipped),
@@ -162,7 +160,7 @@ ne_status ne_train_runs(ne_tables* tables, const ne_run* runs_host, int64_t n_ru
 /*
  * ne_train_block on samples that stay in pinned host memory (the paper's training pipeline, Sec. IV-A:
  * the host-to-device copy of the next sample batches is hidden behind training).  Same batches, same
- * result as ne_train_block; the pairs of batch i+2 are copied into a ring of three batch buffers by a few
+ * result as ne_train_block; the pairs of batch i+3 are copied into a ring of three batch buffers by a few
  * helper workgroups inside the launch that trains batch i, so no second stream and no event is involved
  * (copies on a second stream ordered by events, whether memcpys or kernels, were measured to cost 6-25 % of
  * the training rate; riding along costs 3 %).
@@ -263,10 +261,10 @@ ne_status ne_train_batch_shared_static(ne_tables* tables, const ne_alias* alias,
  *     values before the call and values already updated inside it, where ne_train_batch uses the values
  *     before the call for all of them and a sequential loop the fully updated ones.
  * The result depends on timing wherever rows are shared inside a call and is not reproducible bit for bit;
- * it equals ne_train_batch (up to fp32 rounding) when no row is named twice in the call.  No delta slots,
- * no second pass over the shared rows: the call costs the train kernel plus a small id-only launch per batch.
- * ne_train_block_async takes a run of batches like ne_train_block (the id-only work of batch i+1 rides in
- * the kernels of batch i); ne_train_batch_async is one batch.  Both need the training workspace of
+ * it equals ne_train_batch (up to fp32 rounding) when no row is named twice in the call.  No delta
+ * buffer, no second pass over the shared rows: one launch per batch, and two small id-only ones per call.
+ * ne_train_block_async takes a run of batches like ne_train_block (the id-only work of later batches rides
+ * in the train kernels of earlier ones); ne_train_batch_async is one batch.  Both need the training workspace of
  * ne_create_tables (they find out which rows are shared the way ne_train_batch does).
  * Negatives, arguments and errors as for ne_train_block / ne_train_batch.
  */
@@ -312,17 +310,10 @@ ne_status ne_score_pairs(const ne_tables* tables, const int32_t* pairs_dev, int6
                          int32_t second_from_context, float* scores_dev, void* hip_stream);
 
 /*
- * Tuning of the exact step (ne_train_batch, ne_train_block, ne_train_block_pinned, ne_train_walks); the
- * results are the same sums either way.  The paper fixes neither choice (it never describes its kernel).
- *   list_cap          how a row that several references of a batch name ("shared row") collects
- *                     their deltas: its first list_cap
- *                     references (0..8) store them with plain stores, one buffer row per reference,
- *                     and the rest add to the row's accumulator with atomics.  0 = atomics only.
- *                     -1 = automatic: 8 when the tables are small next to the batch
- *                     (num_nodes <= min(20, 1500 / dim) * rows named per batch), else 0.
- *   sweep_per_thread  hash positions each thread of the apply kernel sweeps: 2, 4 or 8; 0 = automatic
- *                     (2 with the list path, else 4).
- * Takes effect from the next training call on this handle.  Errors: NE_ERR_ARG.
+ * Former tuning of the exact step: how a row that several references of a batch name collected their
+ * deltas (list_cap: -1 or 0..8) and how finely hash positions were swept (sweep_per_thread: 0, 2, 4 or 8).
+ * Neither choice exists any more: such a row has one buffer row per reference, and nothing is swept.  The
+ * arguments are checked as before and change nothing.  Errors: NE_ERR_ARG.
  */
 ne_status ne_set_tuning(ne_tables* tables, int32_t list_cap, int32_t sweep_per_thread);
 
@@ -334,11 +325,11 @@ ne_status ne_validate_pairs(const ne_tables* tables, const int32_t* pairs_dev, i
                             unsigned long long* bad_count_dev, void* hip_stream);
 
 /*
- * Debug helper: the home position the exact step's duplicate detection gives a row key in a table of
- * `positions` hash positions (a power of two in [2, 2^31]; 0xFFFFFFFF is returned otherwise): the top
- * log2(positions) bits of key * 0x9E3779B1 mod 2^32.  key = row id, with bit 31 set for context rows.
- * A batch uses the smallest power of two >= max(2048, 2 * references) positions, references = B * (K + 2)
- * <= 2^28, so at most 2^29.  Host-only; exists so that the spread of home positions can be checked
+ * Debug helper: the home position that the library's hash gives a row key in a table of `positions`
+ * positions (a power of two in [2, 2^31]; 0xFFFFFFFF is returned otherwise): the top log2(positions) bits of
+ * key * 0x9E3779B1 mod 2^32.  key = row id, with bit 31 set for context rows.  The detection of rows that
+ * several references of a batch name uses it to spread the references over bins (the exact step) and over
+ * the positions of a table (the shared-negative step).  Host-only; exists so that the spread can be checked
  * without a GPU.
  */
 uint32_t ne_hash_position(uint32_t key, uint32_t positions);

@@ -392,8 +392,8 @@ def ne_score_pairs(tables: Tables, pairs: torch.Tensor, scores: torch.Tensor, se
 
 
 def ne_set_tuning(tables: Tables, list_cap: int = -1, sweep_per_thread: int = 0) -> None:
-    """How the exact step collects the deltas of rows that several references name (list_cap: -1 automatic,
-    0 atomics only, up to 8 listed references per row) and how finely the apply kernel sweeps (0 automatic, 2, 4, 8)."""
+    """Former tuning of the exact step: the arguments are checked (list_cap -1 .. 8, sweep_per_thread 0, 2, 4 or 8)
+    and change nothing."""
     _check(lib().ne_set_tuning(tables.handle, list_cap, sweep_per_thread))
 
 

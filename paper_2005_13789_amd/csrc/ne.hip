@@ -3,41 +3,37 @@
 // One batch of the embedding-training loop (Algorithm 1; Sec. II-A "Training Process") has four
 // phases:
 //
-//   claim, resolve (ids only)  one thread per row reference (src, ctx and the K negatives of every
-//          pair).  claim draws the negative (Philox + alias table) and stores (key, reference
-//          index) at the key's hash position with a plain 8-byte store; whichever store lands last
-//          owns the position.  resolve reads the position back: a reference whose key owns it but
-//          whose index differs has found a second reference of the same row and flags the row as
-//          shared; references whose key lost the position (a different row hashed there) fall back
-//          to compare-and-swap probing.  Returning atomics retire slowly on this chip, so only that
-//          minority uses them.
+//   claim, resolve (ids only)  find out which rows several references of the batch name (a reference:
+//          the source, the context or one of the K negatives of a pair).  claim takes the references
+//          tile by tile: draws the negatives (Philox + alias table) and writes the tile's (key,
+//          reference) entries sorted by a hash of the key into bins.  resolve takes one bin per
+//          workgroup: all entries of a row meet in one hash table in LDS.  A row with n > 1 references
+//          gets n consecutive rows of the delta buffer, one per reference (its tag), and ceil(n / 8)
+//          work items for the apply kernel.  Nothing goes through atomics in memory but one counter
+//          per bin, and no state has to be cleared between batches.
 //   train  one lane group per pair: gathers x = vertex[src] and the K+1 context rows (dwordx4),
 //          reduces the K+1 dot products with DPP, forms g_j and the deltas.  A row that only this
 //          pair names is rewritten in place from registers (old + delta, one plain store: the row
 //          costs one read and one write).  A shared row is left untouched - other pairs must still
-//          read its pre-batch value - and its delta is added to the row's slot (indexed by hash
-//          position) with fp32 atomics.  Where most rows are shared the atomics' rate would bound
-//          the kernel; there the first references to arrive at a row (ranked by a returning
-//          counter, which is cheap) instead store their delta with plain stores in a buffer row
-//          of their own and enter the row's member list.
-//   apply  adds each shared row's slot, and the buffer rows of its member list, to the table row,
-//          zeroes the slot and the counter; the hash positions of the batch are emptied.
+//          read its pre-batch value - and the delta goes to the reference's row of the delta buffer.
+//   apply  one lane group per work item: sums up to 8 consecutive rows of the delta buffer and adds
+//          them to the table row (with atomics where a row has several items).
 //
 // This is exactly minibatch-synchronous: no row that a second reference could read is written
 // before the apply phase, and all contributions to a row are summed.  fp32 atomics on gfx950
 // retire one dword per L2 channel clock, far below the rate of plain row stores, which is why only
-// shared rows go through them.
+// rows with more than 8 references see any, one per element and 8 references.
 //
 // claim and resolve never touch the tables, so for a run of batches (ne_train_block) they ride
-// along in the kernels of the batch before: kernel A = train(t) + claim(t+1), kernel B = apply(t) +
-// resolve(t+1), two launches per batch, with two sets of hash state used alternately.
+// along in the train kernels of the batches before: kernel A = train(t) + resolve(t+1) + claim(t+2),
+// kernel B = apply(t), two launches per batch (one in the per-sample mode).
 //
 // The same four phases serve three shapes of batch: pairs (ne_train_batch, ne_train_block), and walks
 // (ne_train_walks: on-device augmentation) by entries or by segments, which differ only in how the
 // references are laid out (claim) and in what a lane group or workgroup keeps on chip (train).
 // Beside the exact step: the per-sample mode (ne_train_block_async: the same launches, but a shared
 // row's deltas are added to the table row itself with atomics while other pairs may still read it, and
-// the apply phase has no row work), the loss and pair-score kernels for evaluation, and table
+// there is no apply phase), the loss and pair-score kernels for evaluation, and table
 // initialisation.
 #include "ne_internal.h"
 
@@ -50,15 +46,6 @@ ne_status fail(ne_status st, const std::string& msg)
 }
 
 namespace {
-
-// ---------------------------------------------------------------------------------------------
-// small fills (hipMemsetAsync is avoided so that callers may capture the stream)
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v)
-{
-    const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-    for (size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
-}
 
 // ---------------------------------------------------------------------------------------------
 // table initialisation: vertex ~ U(-0.5/d, 0.5/d), context = 0.  One float4 per thread-iteration.
@@ -85,13 +72,53 @@ __global__ __launch_bounds__(256) void init_tables_kernel(float4* __restrict__ X
 }
 
 // ---------------------------------------------------------------------------------------------
-// claim + resolve kernels: one thread per row reference.  Reference j of pair b: j = 0 the source
-// row (vertex table), j = 1 the positive context row, j = 2.. negative j-2 (context table).
-// key = row | (context table ? 1 << 31 : 0).
-// ---------------------------------------------------------------------------------------------
-constexpr unsigned long long kEmptySlot = ~0ull;
+// claim + resolve kernels.  Reference j of pair b: j = 0 the source row (vertex table), j = 1 the
+// positive context row, j = 2.. negative j-2 (context table).
+// key = row | (context table ? 1 << 31 : 0); rows are below 2^31 - 1, so no key is ~0.
+//
+// Detection of shared rows by partition instead of by one hash table in memory: a table entry that
+// two compute dies touch costs a 64-byte transaction per store and per load, and a returning atomic
+// for every lost position (measured at 458 752 references: 28 us of a 134 us batch, plus a linear pass
+// that emptied the table again).  Here an entry is written once into a tile-local run of its bin and
+// read once from there, runs of a few entries are one transaction, and everything that needs an
+// atomic happens in LDS.  Bound by the latency of four dependent accesses per workgroup (segment words,
+// entries, the counter, nothing after it); riding in the train launch both phases together add 22 us to
+// its 76 us (32 M nodes, dim 128, 65 536 pairs), of which the random reads of the alias table are about half.
+// 65 536 pairs, K = 5: 1 M nodes 175 -> 140 us a batch, 32 M nodes 144 -> 126 us; 4096 pairs in one call 40 -> 33 us.
+constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
-__device__ __forceinline__ uint32_t hash_key(uint32_t key, uint32_t mask) { return hash_position(key, mask); }
+// How the references of a batch are binned.
+//   bins   a power of two.  512 .. 1024 references per bin where the batch is large, so that the distinct
+//          rows among them half fill a table of 2048 slots (16 KB of LDS, which a train launch can give to
+//          every workgroup without losing one; 2048 references and 4096 slots cost such a batch 6 %, 512 and
+//          1024 twice as many segments and 8 %); a smaller batch gets up to 256 bins, one per compute unit,
+//          of 128 .. 256 references, because a bin is one chain of dependent accesses (64 .. 128: 6 % slower
+//          on batches of 28 000 references).  More than 2^kMaxBinBits bins would make the claim phase's
+//          counters too large: the bins of batches beyond 4 M references are longer, and resolved in several
+//          ranges of the hash.
+//   tile   references per claim workgroup: at least 4 per bin, so that runs of a bin's entries are worth an
+//          access and the segment table stays a quarter of the entries.
+//   slots  of a bin's LDS table, and the distinct rows (full) at which it counts as too small: each of the
+//          256 threads may add one more after that, and one slot has to stay empty.
+struct Binning { uint32_t bits, tile, tiles, slot_bits, full; };
+constexpr uint32_t kMaxBinBits = 12;
+constexpr uint32_t kMinTile = 1024;
+constexpr uint64_t kFewRefs = 256, kManyRefs = 1024;   // most references per bin, on average, below and from 256 bins on
+inline Binning binning(uint64_t refs)
+{
+    Binning b;
+    b.bits = 0;
+    while (b.bits < 8 && (kFewRefs << b.bits) < refs) ++b.bits;
+    while (b.bits < kMaxBinBits && (kManyRefs << b.bits) < refs) ++b.bits;
+    b.tile = (4u << b.bits) > kMinTile ? (4u << b.bits) : kMinTile;
+    b.tiles = static_cast<uint32_t>((refs + b.tile - 1) / b.tile);
+    const uint64_t mean = refs >> b.bits;
+    b.slot_bits = mean <= 128 ? 9 : mean <= 400 ? 10 : 11;
+    b.full = b.slot_bits == 9 ? 255u : (5u << b.slot_bits) / 8u;
+    return b;
+}
+// Segment words that a batch of up to `refs` references can need.
+inline uint64_t max_segs(uint64_t refs) { return refs / 4 + (1u << kMaxBinBits); }
 
 struct PrepArgs {
     const int2* pairs;    // pair mode: the batch's pairs
@@ -99,7 +126,6 @@ struct PrepArgs {
     int32_t walk_len, window;
     uint32_t refs;        // references of the batch; 0 = nothing to prepare
     uint32_t R;           // references per pair (K + 2) / per walk entry (1 + window * (K + 1)) / per walk segment
-    uint32_t xrefs;       // how many references at the front of each group of R name the vertex table (1; segment mode: entries per segment)
     uint32_t seg_entries; // walk mode: 0 = one reference group per walk entry; else entries per segment
     uint32_t segs_per_walk;
     int32_t K;
@@ -108,12 +134,13 @@ struct PrepArgs {
     const uint2* alias;
     uint64_t alias_n;
     int32_t alias_base;
-    unsigned long long* slots;
-    uint32_t mask;        // cap - 1
-    uint8_t* shared;      // per hash position: the row there is named more than once (what the apply sweep reads)
-    uint8_t* refshared;   // per reference: the same fact, where the train kernel reads it without a dependent lookup
+    Binning bin;
     int32_t* ids;
-    uint32_t* posbuf;
+    uint32_t* tag;
+    uint2* items;
+    unsigned long long* totals;
+    unsigned long long* entries;
+    uint32_t* segs;
     int32_t* neg_out;
     // sample prefetch riding along (ne_train_block_pinned): fetch_blocks helper workgroups copy fetch_n
     // pairs from pinned host memory (fetch_src: its device address) into the staging ring (fetch_dst)
@@ -123,50 +150,49 @@ struct PrepArgs {
     uint32_t fetch_blocks;
 };
 
-// Both phases are chains of dependent memory accesses with next to no arithmetic, so each thread
-// runs kPrepUnroll references at once: a block covers 256 * kPrepUnroll consecutive references.
+__device__ __forceinline__ uint32_t bin_of(uint32_t key, uint32_t bits) { return bits ? hash_bits(key) >> (32u - bits) : 0u; }
+
+// Drawing a reference's id is a chain of dependent memory accesses with next to no arithmetic, so each
+// thread runs kPrepUnroll references at once: 256 * kPrepUnroll consecutive references per step.
 constexpr int kPrepUnroll = 4;
 
-__device__ __forceinline__ void claim_pair_refs(const PrepArgs& a, unsigned block, unsigned tid)
+// The references first + u * 256 + tid < last, u < kPrepUnroll: their keys (kNoKey where there is none); ids and
+// requested negatives go to memory.
+__device__ __forceinline__ void claim_pair_refs(const PrepArgs& a, uint32_t first, uint32_t last, unsigned tid, uint32_t (&key)[kPrepUnroll])
 {
     const uint32_t R = a.R;
-    uint32_t t[kPrepUnroll], b[kPrepUnroll];
-    int j[kPrepUnroll];
-    int32_t id[kPrepUnroll];
-    uint4 rnd[kPrepUnroll];
-    uint2 entry[kPrepUnroll];
-    uint64_t draw_slot[kPrepUnroll];
+    // per reference: a negative's alias entry, slot and third Philox word; else the pair, and which half of it.
+    // (A wavefront has references of every kind, so all lanes draw, and one load serves both kinds.)
+    uint2 e[kPrepUnroll];
+    uint32_t slot[kPrepUnroll], keep[kPrepUnroll];
 #pragma unroll
     for (int u = 0; u < kPrepUnroll; ++u) {
-        t[u] = (block * kPrepUnroll + u) * 256u + tid;
-        b[u] = t[u] / R;
-        j[u] = static_cast<int>(t[u] - b[u] * R);
-        id[u] = 0;
-        if (t[u] < a.refs) {
-            if (j[u] < 2) {
-                const int2 pr = a.pairs[b[u]];
-                id[u] = j[u] == 0 ? pr.x : pr.y;
-            } else {
-                const uint64_t sample = a.sample_base + b[u];
-                rnd[u] = philox4x32_10(make_uint4(static_cast<uint32_t>(sample), static_cast<uint32_t>(sample >> 32),
-                                                  static_cast<uint32_t>(j[u] - 2), kStreamNegative), a.k0, a.k1);
-                draw_slot[u] = __umul64hi((static_cast<uint64_t>(rnd[u].x) << 32) | rnd[u].y, a.alias_n);
-                entry[u] = a.alias[draw_slot[u]];
-            }
-        }
+        const uint32_t t = min(first + u * 256u + tid, last - 1u);
+        const uint32_t b = t / R, j = t - b * R;
+        const uint64_t sample = a.sample_base + b;
+        const uint4 rnd = philox4x32_10(make_uint4(static_cast<uint32_t>(sample), static_cast<uint32_t>(sample >> 32),
+                                                   j - 2u, kStreamNegative), a.k0, a.k1);
+        slot[u] = static_cast<uint32_t>(__umul64hi((static_cast<uint64_t>(rnd.x) << 32) | rnd.y, a.alias_n));   // (n < 2^31)
+        keep[u] = rnd.z;
+        const uint2* from = j < 2u ? reinterpret_cast<const uint2*>(a.pairs) + b : a.alias + slot[u];
+        e[u] = *from;
+        __builtin_amdgcn_sched_barrier(0);   // one draw's registers at a time; the loads stay in flight
     }
 #pragma unroll
     for (int u = 0; u < kPrepUnroll; ++u) {
-        if (t[u] < a.refs) {
-            if (j[u] >= 2) {
-                id[u] = a.alias_base + static_cast<int32_t>(rnd[u].z < entry[u].x ? static_cast<uint32_t>(draw_slot[u]) : entry[u].y);
-                if (a.neg_out) a.neg_out[static_cast<int64_t>(b[u]) * a.K + (j[u] - 2)] = id[u];
+        const uint32_t t = first + u * 256u + tid;
+        key[u] = kNoKey;
+        if (t < last) {
+            const uint32_t b = t / R, j = t - b * R;
+            uint32_t id = j == 0u ? e[u].x : e[u].y;
+            if (j >= 2u) {
+                id = static_cast<uint32_t>(a.alias_base) + (keep[u] < e[u].x ? slot[u] : e[u].y);
+                if (a.neg_out) a.neg_out[static_cast<int64_t>(b) * a.K + (j - 2u)] = static_cast<int32_t>(id);
             }
-            a.ids[t[u]] = id[u];
-            a.refshared[t[u]] = 0;   // resolve sets it, one launch later
-            const uint32_t key = static_cast<uint32_t>(id[u]) | (j[u] == 0 ? 0u : 0x80000000u);
-            a.slots[hash_key(key, a.mask)] = (static_cast<unsigned long long>(key) << 32) | t[u];
+            a.ids[t] = static_cast<int32_t>(id);
+            key[u] = id | (j == 0u ? 0u : 0x80000000u);
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -176,8 +202,8 @@ __device__ __forceinline__ void claim_pair_refs(const PrepArgs& a, unsigned bloc
 //   0                          the source row (vertex table), present if the position has a pair
 //   1 + (j-1)(K+1)             the context row of pair j
 //   1 + (j-1)(K+1) + 1 + k     negative k of pair j, drawn for sample index sample_base + p*window + (j-1)
-// Absent references get id -1 and claim nothing.
-__device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, unsigned block, unsigned tid)
+// Absent references get id -1 and no key.
+__device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, uint32_t first, uint32_t last, unsigned tid, uint32_t (&key)[kPrepUnroll])
 {
     const uint32_t R = a.R;
     const uint32_t L = static_cast<uint32_t>(a.walk_len), W = static_cast<uint32_t>(a.window), K1 = static_cast<uint32_t>(a.K + 1);
@@ -185,18 +211,18 @@ __device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, unsigned bloc
     int kk[kPrepUnroll];     // -2: source, -1: context, >= 0: negative k
     int32_t id[kPrepUnroll];
     bool valid[kPrepUnroll];
-    uint4 rnd[kPrepUnroll];
+    uint32_t keep[kPrepUnroll];
     uint2 entry[kPrepUnroll];
-    uint64_t draw_slot[kPrepUnroll];
+    uint32_t draw_slot[kPrepUnroll];   // (the table has fewer than 2^31 entries)
 #pragma unroll
     for (int u = 0; u < kPrepUnroll; ++u) {
-        t[u] = (block * kPrepUnroll + u) * 256u + tid;
+        t[u] = first + u * 256u + tid;
         id[u] = -1;
         valid[u] = false;
         kk[u] = -2;
         jj[u] = 0;
         p[u] = 0;
-        if (t[u] < a.refs) {
+        if (t[u] < last) {
             p[u] = t[u] / R;
             const uint32_t q = t[u] - p[u] * R;
             const uint32_t r = p[u] / L, i = p[u] - r * L;
@@ -216,9 +242,10 @@ __device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, unsigned bloc
                 id[u] = ctx;
                 if (valid[u] && kk[u] >= 0) {
                     const uint64_t sample = a.sample_base + static_cast<uint64_t>(p[u]) * W + jj[u];
-                    rnd[u] = philox4x32_10(make_uint4(static_cast<uint32_t>(sample), static_cast<uint32_t>(sample >> 32),
+                    const uint4 rnd = philox4x32_10(make_uint4(static_cast<uint32_t>(sample), static_cast<uint32_t>(sample >> 32),
                                                       static_cast<uint32_t>(kk[u]), kStreamNegative), a.k0, a.k1);
-                    draw_slot[u] = __umul64hi((static_cast<uint64_t>(rnd[u].x) << 32) | rnd[u].y, a.alias_n);
+                    draw_slot[u] = static_cast<uint32_t>(__umul64hi((static_cast<uint64_t>(rnd.x) << 32) | rnd.y, a.alias_n));
+                    keep[u] = rnd.z;
                     entry[u] = a.alias[draw_slot[u]];
                 }
             }
@@ -226,18 +253,15 @@ __device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, unsigned bloc
     }
 #pragma unroll
     for (int u = 0; u < kPrepUnroll; ++u) {
-        if (t[u] >= a.refs) continue;
+        key[u] = kNoKey;
+        if (t[u] >= last) continue;
         if (valid[u] && kk[u] >= 0) {
-            id[u] = a.alias_base + static_cast<int32_t>(rnd[u].z < entry[u].x ? static_cast<uint32_t>(draw_slot[u]) : entry[u].y);
+            id[u] = a.alias_base + static_cast<int32_t>(keep[u] < entry[u].x ? draw_slot[u] : entry[u].y);
             if (a.neg_out) a.neg_out[(static_cast<int64_t>(p[u]) * W + jj[u]) * a.K + kk[u]] = id[u];
         }
         if (!valid[u]) id[u] = -1;
         a.ids[t[u]] = id[u];
-        a.refshared[t[u]] = 0;
-        if (valid[u]) {
-            const uint32_t key = static_cast<uint32_t>(id[u]) | (kk[u] == -2 ? 0u : 0x80000000u);
-            a.slots[hash_key(key, a.mask)] = (static_cast<unsigned long long>(key) << 32) | t[u];
-        }
+        if (valid[u]) key[u] = static_cast<uint32_t>(id[u]) | (kk[u] == -2 ? 0u : 0x80000000u);
     }
 }
 
@@ -250,7 +274,7 @@ __device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, unsigned bloc
 //                            entries has it as a sample's context (the last window-1 of them belong
 //                            to the next segment's entries too: both segments name them)
 //   E + CT + (e*window + j-1)*K + k   negative k of sample (entry p0 + e, offset j)
-__device__ __forceinline__ void claim_seg_refs(const PrepArgs& a, unsigned block, unsigned tid)
+__device__ __forceinline__ void claim_seg_refs(const PrepArgs& a, uint32_t first, uint32_t last, unsigned tid, uint32_t (&key)[kPrepUnroll])
 {
     const uint32_t R = a.R, E = a.seg_entries;
     const uint32_t L = static_cast<uint32_t>(a.walk_len), W = static_cast<uint32_t>(a.window), K = static_cast<uint32_t>(a.K);
@@ -259,17 +283,17 @@ __device__ __forceinline__ void claim_seg_refs(const PrepArgs& a, unsigned block
     int kk[kPrepUnroll];     // -2: vertex row, -1: context row, >= 0: negative k
     int32_t id[kPrepUnroll];
     bool valid[kPrepUnroll];
-    uint4 rnd[kPrepUnroll];
+    uint32_t keep[kPrepUnroll];
     uint2 entry[kPrepUnroll];
-    uint64_t draw_slot[kPrepUnroll];
+    uint32_t draw_slot[kPrepUnroll];   // (the table has fewer than 2^31 entries)
 #pragma unroll
     for (int u = 0; u < kPrepUnroll; ++u) {
-        t[u] = (block * kPrepUnroll + u) * 256u + tid;
+        t[u] = first + u * 256u + tid;
         id[u] = -1;
         valid[u] = false;
         kk[u] = -2;
         samp[u] = 0;
-        if (t[u] < a.refs) {
+        if (t[u] < last) {
             const uint32_t seg = t[u] / R, q = t[u] - seg * R;
             const uint32_t r = seg / a.segs_per_walk, p0 = (seg - r * a.segs_per_walk) * E;
             const int32_t* wk = a.walks + static_cast<int64_t>(r) * L;
@@ -301,9 +325,10 @@ __device__ __forceinline__ void claim_seg_refs(const PrepArgs& a, unsigned block
                     samp[u] = (r * L + i) * W + (j - 1);
                     if (valid[u]) {
                         const uint64_t sample = a.sample_base + samp[u];
-                        rnd[u] = philox4x32_10(make_uint4(static_cast<uint32_t>(sample), static_cast<uint32_t>(sample >> 32),
+                        const uint4 rnd = philox4x32_10(make_uint4(static_cast<uint32_t>(sample), static_cast<uint32_t>(sample >> 32),
                                                           static_cast<uint32_t>(kk[u]), kStreamNegative), a.k0, a.k1);
-                        draw_slot[u] = __umul64hi((static_cast<uint64_t>(rnd[u].x) << 32) | rnd[u].y, a.alias_n);
+                        draw_slot[u] = static_cast<uint32_t>(__umul64hi((static_cast<uint64_t>(rnd.x) << 32) | rnd.y, a.alias_n));
+                        keep[u] = rnd.z;
                         entry[u] = a.alias[draw_slot[u]];
                     }
                 }
@@ -312,84 +337,273 @@ __device__ __forceinline__ void claim_seg_refs(const PrepArgs& a, unsigned block
     }
 #pragma unroll
     for (int u = 0; u < kPrepUnroll; ++u) {
-        if (t[u] >= a.refs) continue;
+        key[u] = kNoKey;
+        if (t[u] >= last) continue;
         if (valid[u] && kk[u] >= 0) {
-            id[u] = a.alias_base + static_cast<int32_t>(rnd[u].z < entry[u].x ? static_cast<uint32_t>(draw_slot[u]) : entry[u].y);
+            id[u] = a.alias_base + static_cast<int32_t>(keep[u] < entry[u].x ? draw_slot[u] : entry[u].y);
             if (a.neg_out) a.neg_out[static_cast<int64_t>(samp[u]) * a.K + kk[u]] = id[u];
         }
         if (!valid[u]) id[u] = -1;
         a.ids[t[u]] = id[u];
-        a.refshared[t[u]] = 0;
-        if (valid[u]) {
-            const uint32_t key = static_cast<uint32_t>(id[u]) | (kk[u] == -2 ? 0u : 0x80000000u);
-            a.slots[hash_key(key, a.mask)] = (static_cast<unsigned long long>(key) << 32) | t[u];
-        }
+        if (valid[u]) key[u] = static_cast<uint32_t>(id[u]) | (kk[u] == -2 ? 0u : 0x80000000u);
     }
 }
 
-__device__ __forceinline__ void claim_refs(const PrepArgs& a, unsigned block, unsigned tid)
+// Exclusive prefix sum over the 256 threads of a workgroup; *total receives the sum.  part: 4 words of LDS.
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* part, uint32_t* total)
 {
-    if (a.pairs) claim_pair_refs(a, block, tid);
-    else if (a.seg_entries) claim_seg_refs(a, block, tid);
-    else claim_walk_refs(a, block, tid);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t inc = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += o;
+    }
+    __syncthreads();            // part may still be read from an earlier scan
+    if (lane == 63) part[wave] = inc;
+    __syncthreads();
+    uint32_t before = 0, sum = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const uint32_t p = part[w];
+        if (w < wave) before += p;
+        sum += p;
+    }
+    *total = sum;
+    return before + inc - v;
 }
 
-__device__ __forceinline__ void resolve_refs(const PrepArgs& a, unsigned block)
+// LDS of the claim phase: a counter per bin and the scan's four words.
+inline size_t claim_lds_bytes(const Binning& b) { return ((static_cast<size_t>(1) << b.bits) + 4) * sizeof(uint32_t); }
+
+// Layout of a batch's references.
+enum RefMode { kPairRefs, kWalkRefs, kSegRefs };
+
+// One tile of references: draw, count by bin, then write the entries of each bin side by side.
+// All 256 threads of the workgroup call this together; hist: claim_lds_bytes() of LDS.
+template <RefMode MODE>
+__device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uint32_t* hist)
 {
-    const uint32_t R = a.R;
-    uint32_t t[kPrepUnroll], key[kPrepUnroll], pos[kPrepUnroll];
-    bool live[kPrepUnroll];   // walk mode leaves holes (id -1) where a walk has no pair
-    unsigned long long owner[kPrepUnroll];
+    const unsigned tid = threadIdx.x;
+    const uint32_t bits = a.bin.bits, bins = 1u << bits;
+    uint32_t* part = hist + bins;
+    if (tile == 0 && tid == 0) *a.totals = 0ull;      // resolve, one launch later, counts from zero
+    for (uint32_t i = tid; i < bins; i += 256) hist[i] = 0u;
+    __syncthreads();
+    const uint32_t first = tile * a.bin.tile;
+    const uint32_t last = min(first + a.bin.tile, a.refs);   // (refs is at most 2^28)
+    uint32_t key[kPrepUnroll];
+    uint32_t step = first;
+    for (;; step += 256 * kPrepUnroll) {
+        if (MODE == kPairRefs) claim_pair_refs(a, step, last, tid, key);
+        else if (MODE == kSegRefs) claim_seg_refs(a, step, last, tid, key);
+        else claim_walk_refs(a, step, last, tid, key);
 #pragma unroll
-    for (int u = 0; u < kPrepUnroll; ++u) {
-        t[u] = (block * kPrepUnroll + u) * 256u + threadIdx.x;
-        key[u] = 0;
-        live[u] = false;
-        if (t[u] < a.refs) {
-            const int32_t id = a.ids[t[u]];
-            live[u] = id >= 0;
-            key[u] = static_cast<uint32_t>(id) | ((t[u] % R) < a.xrefs ? 0u : 0x80000000u);
+        for (int u = 0; u < kPrepUnroll; ++u) {
+            const uint32_t t = step + u * 256u + tid;
+            if (t < last) a.tag[t] = 0u;             // resolve overwrites it where the row is shared
+            if (key[u] != kNoKey) atomicAdd(&hist[bin_of(key[u], bits)], 1u);
+        }
+        if (step + 256 * kPrepUnroll >= last) break;
+    }
+    __syncthreads();
+    // where each bin's entries start in the tile
+    const uint32_t per = (bins + 255u) >> 8;         // consecutive bins per thread
+    uint32_t mine = 0;
+    for (uint32_t i = 0; i < per; ++i) {
+        const uint32_t p = tid * per + i;
+        if (p < bins) mine += hist[p];
+    }
+    uint32_t total;
+    uint32_t at = block_exclusive_scan(mine, part, &total);
+    for (uint32_t i = 0; i < per; ++i) {
+        const uint32_t p = tid * per + i;
+        if (p < bins) {
+            const uint32_t n = hist[p];
+            a.segs[static_cast<size_t>(tile) * bins + p] = at | (n << 16);
+            hist[p] = at;
+            at += n;
         }
     }
+    __syncthreads();
+    // the last step's keys are still in registers; earlier ones are rebuilt from the ids
+    for (;;) {
 #pragma unroll
-    for (int u = 0; u < kPrepUnroll; ++u) {
-        pos[u] = hash_key(key[u], a.mask);
-        owner[u] = live[u] ? a.slots[pos[u]] : 0ull;
-    }
-#pragma unroll
-    for (int u = 0; u < kPrepUnroll; ++u) {
-        if (!live[u]) continue;
-        uint32_t p = pos[u];
-        if (static_cast<uint32_t>(owner[u] >> 32) == key[u]) {
-            // my row owns its home position; any reference but the one whose store landed last
-            // proves that the row is named at least twice
-            if (static_cast<uint32_t>(owner[u]) != t[u]) {
-                a.shared[p] = 1;
-                a.refshared[t[u]] = 1;
-                a.refshared[static_cast<uint32_t>(owner[u])] = 1;   // the owner cannot tell by itself
+        for (int u = 0; u < kPrepUnroll; ++u) {
+            if (key[u] != kNoKey) {
+                const uint32_t t = step + u * 256u + tid;
+                const uint32_t p = atomicAdd(&hist[bin_of(key[u], bits)], 1u);
+                a.entries[first + p] = (static_cast<unsigned long long>(key[u]) << 32) | t;
             }
+        }
+        if (step == first) break;
+        step -= 256 * kPrepUnroll;
+#pragma unroll
+        for (int u = 0; u < kPrepUnroll; ++u) {
+            const uint32_t t = step + u * 256u + tid;
+            const int32_t id = a.ids[t];
+            const uint32_t q = t % a.R;
+            const bool vertex_row = q < (MODE == kSegRefs ? a.seg_entries : 1u);
+            key[u] = id < 0 ? kNoKey : static_cast<uint32_t>(id) | (vertex_row ? 0u : 0x80000000u);
+        }
+    }
+}
+
+// One bin of references: all entries of a row are in it.  An LDS hash table counts each row's entries;
+// rows with more than one get their place in the delta buffer and their work items; then every entry of
+// such a row takes the next of the row's places.  A bin whose distinct rows do not fit the table is
+// gone through in ranges of the hash, halved until they fit: the hash is a bijection of the key, so a range
+// of 2^k values holds at most 2^k rows and the halving ends.
+constexpr uint32_t kItemRefs = 8;                        // references per work item
+struct ResolveLds {
+    uint32_t part[4];
+    uint32_t distinct, pad;
+    unsigned long long base;
+    // then key[slots], and cnt[slots]: references of the row; later its next place in the delta buffer (~0: not shared)
+};
+inline size_t resolve_lds_bytes(const Binning& b) { return sizeof(ResolveLds) + (static_cast<size_t>(8) << b.slot_bits); }
+
+// work item: x = key, y = first row in the delta buffer << 4 | (row has several items) << 3 | rows - 1
+__device__ __forceinline__ uint2 make_item(uint32_t key, uint32_t begin, uint32_t several, uint32_t n)
+{
+    return make_uint2(key, (begin << 4) | (several << 3) | (n - 1));
+}
+
+// A share of a bin's entries: 8 lanes per tile segment, kSegsPerLane segments each, the first 8 entries of
+// every segment in registers.  Fetching a share takes two dependent accesses, whatever its size; 256 tiles
+// are all there are up to 512 bins (with half as many, and so two fetches per pass: +1 .. 2 % of a batch).
+constexpr int kSegsPerLane = 8;
+constexpr uint32_t kShareTiles = 32 * kSegsPerLane;      // tile segments per share
+struct BinShare {
+    unsigned long long e[kSegsPerLane];
+    uint32_t seg[kSegsPerLane];       // start in the tile | entries << 16
+};
+
+__device__ __forceinline__ void fetch_share(const PrepArgs& a, uint32_t bin, uint32_t tile0, BinShare& s)
+{
+    const uint32_t g = threadIdx.x >> 3, l = threadIdx.x & 7;
+    const uint32_t bins = 1u << a.bin.bits;
+#pragma unroll
+    for (int i = 0; i < kSegsPerLane; ++i) {
+        const uint32_t t = tile0 + g + 32u * i;
+        s.seg[i] = t < a.bin.tiles ? a.segs[static_cast<size_t>(t) * bins + bin] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < kSegsPerLane; ++i) {
+        const uint32_t t = tile0 + g + 32u * i;
+        s.e[i] = l < (s.seg[i] >> 16) ? a.entries[t * a.bin.tile + (s.seg[i] & 0xFFFFu) + l] : ~0ull;
+    }
+}
+
+// f(key, reference) for every entry of the share
+template <class F>
+__device__ __forceinline__ void for_share(const PrepArgs& a, uint32_t tile0, const BinShare& s, F f)
+{
+    const uint32_t g = threadIdx.x >> 3, l = threadIdx.x & 7;
+#pragma unroll
+    for (int i = 0; i < kSegsPerLane; ++i) {
+        if (tile0 + 32u * i >= a.bin.tiles) break;
+        // (opaque to the optimiser, which would otherwise keep every entry's hash and address from one pass to
+        // the next: twice the registers, half the wavefronts of the kernel this rides in)
+        uint32_t key = static_cast<uint32_t>(s.e[i] >> 32), seg = s.seg[i];
+        asm volatile("" : "+v"(key), "+v"(seg));
+        const uint32_t n = seg >> 16;
+        if (l < n) f(key, static_cast<uint32_t>(s.e[i]));
+        for (uint32_t q = l + 8; q < n; q += 8) {
+            const unsigned long long v = a.entries[(tile0 + g + 32u * i) * a.bin.tile + (seg & 0xFFFFu) + q];
+            f(static_cast<uint32_t>(v >> 32), static_cast<uint32_t>(v));
+        }
+    }
+}
+
+__device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, unsigned char* lds)
+{
+    const unsigned tid = threadIdx.x;
+    ResolveLds& s = *reinterpret_cast<ResolveLds*>(lds);
+    const uint32_t slots = 1u << a.bin.slot_bits, mask = slots - 1u, per = slots >> 8;   // per: slots per thread
+    uint32_t* skey = reinterpret_cast<uint32_t*>(lds + sizeof(ResolveLds));
+    uint32_t* scnt = skey + slots;
+    uint32_t lo = 0, halvings = 0;      // range of the hash below the bin's bits: [lo, lo + 2^(32 - halvings))
+    BinShare share;
+    if (a.bin.tiles <= kShareTiles) fetch_share(a, bin, 0, share);    // all there is, once
+    auto for_bin_entries = [&](auto f) {
+        if (a.bin.tiles <= kShareTiles) {
+            for_share(a, 0, share, f);
         } else {
-            // another row owns the home position: probe onwards.  Positions only ever go from empty
-            // to occupied here, and the table holds at most half as many keys as positions, so the walk ends.
-            const unsigned long long mine = (static_cast<unsigned long long>(key[u]) << 32) | t[u];
+            for (uint32_t t0 = 0; t0 < a.bin.tiles; t0 += kShareTiles) {
+                fetch_share(a, bin, t0, share);
+                for_share(a, t0, share, f);
+            }
+        }
+    };
+    for (;;) {
+        for (uint32_t i = tid; i < slots; i += 256) { skey[i] = kNoKey; scnt[i] = 0u; }
+        if (tid == 0) s.distinct = 0u;
+        __syncthreads();
+        auto home = [&](uint32_t key, uint32_t* pos) {
+            const uint32_t x = (hash_bits(key) << a.bin.bits) - lo;
+            if (halvings && (x >> (32u - halvings))) return false;     // another range's
+            *pos = (x << halvings) >> (32u - a.bin.slot_bits);
+            return true;
+        };
+        for_bin_entries([&](uint32_t key, uint32_t) {
+            uint32_t p;
+            if (!home(key, &p)) return;
             while (true) {
-                p = (p + 1) & a.mask;
-                const unsigned long long prev = atomicCAS(&a.slots[p], kEmptySlot, mine);
-                if (prev == kEmptySlot) break;
-                if (static_cast<uint32_t>(prev >> 32) == key[u]) {
-                    a.shared[p] = 1;
-                    a.refshared[t[u]] = 1;
-                    a.refshared[static_cast<uint32_t>(prev)] = 1;
-                    break;
+                // (no new row once the range is given up, so an empty slot is left and every probe ends)
+                uint32_t k = *const_cast<volatile uint32_t*>(&skey[p]);
+                if (k == kNoKey) {
+                    if (*const_cast<volatile uint32_t*>(&s.distinct) > a.bin.full) return;
+                    k = atomicCAS(&skey[p], kNoKey, key);
+                    if (k == kNoKey) { atomicAdd(&s.distinct, 1u); k = key; }
+                }
+                if (k == key) { atomicAdd(&scnt[p], 1u); return; }
+                p = (p + 1) & mask;
+            }
+        });
+        __syncthreads();
+        if (s.distinct > a.bin.full) {       // (uniform: nobody writes it between the barriers)
+            __syncthreads();
+            halvings += 1;
+            continue;
+        }
+        // places and work items of the shared rows among my slots
+        uint32_t items = 0, rows = 0;
+        for (uint32_t i = 0; i < per; ++i) {
+            const uint32_t n = scnt[tid * per + i];
+            if (n > 1) { items += (n + kItemRefs - 1) / kItemRefs; rows += n; }
+        }
+        uint32_t items_all, rows_all;
+        uint32_t item = block_exclusive_scan(items, s.part, &items_all);
+        uint32_t row = block_exclusive_scan(rows, s.part, &rows_all);
+        if (rows_all) {                         // (uniform)
+            if (tid == 0) s.base = atomicAdd(a.totals, (static_cast<unsigned long long>(items_all) << 32) | rows_all);
+            __syncthreads();
+            item += static_cast<uint32_t>(s.base >> 32);
+            row += static_cast<uint32_t>(s.base);
+            for (uint32_t i = 0; i < per; ++i) {
+                const uint32_t p = tid * per + i, n = scnt[p], key = skey[p];
+                scnt[p] = n > 1 ? row : kNoKey;
+                if (n > 1) {
+                    for (uint32_t q = 0; q < n; q += kItemRefs)
+                        a.items[item++] = make_item(key, row + q, n > kItemRefs ? 1u : 0u, min(kItemRefs, n - q));
+                    row += n;
                 }
             }
+            __syncthreads();
+            for_bin_entries([&](uint32_t key, uint32_t ref) {
+                uint32_t p;
+                if (!home(key, &p)) return;
+                while (skey[p] != key) p = (p + 1) & mask;
+                if (scnt[p] != kNoKey) a.tag[ref] = 1u + atomicAdd(&scnt[p], 1u);
+            });
         }
-        a.posbuf[t[u]] = p;
+        if (halvings == 0) return;
+        lo += 1u << (32u - halvings);
+        if (lo == 0) return;
+        __syncthreads();
     }
 }
-
-// Number of blocks either phase needs for `refs` references.
-inline unsigned prep_blocks(uint32_t refs) { return (refs + 256u * kPrepUnroll - 1u) / (256u * kPrepUnroll); }
 
 // ---------------------------------------------------------------------------------------------
 // sample prefetch (ne_train_block_pinned): a few workgroups copy the pairs of a later batch from
@@ -424,62 +638,73 @@ __global__ __launch_bounds__(256) void fetch_pairs_kernel(const int2* __restrict
                 static_cast<int64_t>(gridDim.x) * blockDim.x);
 }
 
-// Placement of `extra` helper blocks among `total` blocks of a fused launch: every period-th block is
-// a helper until they run out, so helpers and main blocks are resident together from the start.
-__device__ __forceinline__ bool fused_block(unsigned extra, unsigned period, unsigned* index)
+// LDS of the kernels: counters of a claiming workgroup, hash table of a resolving one, staged rows of a training one.
+extern __shared__ __align__(16) unsigned char dynamic_lds[];
+
+// The id-only work for later batches that rides in a launch: the launch's first workgroups, because theirs are
+// chains of dependent accesses, which hide behind the other workgroups only if they start first.
+struct Helpers {
+    unsigned resolves, claims, fetches;   // workgroups of each kind: bins of `resolve`, tiles of `claim`
+    PrepArgs resolve;     // next batch
+    PrepArgs claim;       // the one after that; its fetch fields: pairs of the batch after that one
+    unsigned count() const { return resolves + claims + fetches; }
+    size_t lds_bytes() const
+    {
+        const size_t r = resolves ? resolve_lds_bytes(resolve.bin) : 0, c = claims ? claim_lds_bytes(claim.bin) : 0;
+        return r > c ? r : c;
+    }
+};
+
+// False for a workgroup that has other work to do; *block is then its index among those.
+template <RefMode MODE>
+__device__ __forceinline__ bool helper_block(const Helpers& h, unsigned* block)
 {
-    const unsigned i = blockIdx.x;
-    if (extra && i % period == 0 && i / period < extra) { *index = i / period; return true; }
-    const unsigned before = extra ? min(extra, (i + period - 1) / period) : 0u;
-    *index = i - before;
+    unsigned i = blockIdx.x;
+    if (i < h.resolves) {
+        // neighbouring bins share cache lines (a tile's segment words and entries lie bin after bin), and
+        // workgroups go to the eight dies in turn: each die takes a run of consecutive bins
+        resolve_bin(h.resolve, h.resolves >= 8 ? (i & 7u) * (h.resolves >> 3) + (i >> 3) : i, dynamic_lds);
+        return true;
+    }
+    i -= h.resolves;
+    if (i < h.claims) { claim_tile<MODE>(h.claim, i, reinterpret_cast<uint32_t*>(dynamic_lds)); return true; }
+    i -= h.claims;
+    if (i < h.fetches) {
+        fetch_pairs(h.claim.fetch_src, h.claim.fetch_dst, h.claim.fetch_n, static_cast<int64_t>(i) * 256 + threadIdx.x,
+                    static_cast<int64_t>(h.fetches) * 256);
+        return true;
+    }
+    *block = i - h.fetches;
     return false;
 }
 
-__global__ __launch_bounds__(256) void claim_kernel(PrepArgs a) { claim_refs(a, blockIdx.x, threadIdx.x); }
-__global__ __launch_bounds__(256) void resolve_kernel(PrepArgs a) { resolve_refs(a, blockIdx.x); }
+// The same work on its own, for the first batches of a call.
+template <RefMode MODE>
+__global__ __launch_bounds__(256) void prepare_kernel(Helpers h)
+{
+    unsigned block;
+    helper_block<MODE>(h, &block);
+}
 
 // ---------------------------------------------------------------------------------------------
 // train kernel.  G lanes per pair, NCH float4 chunks per lane (chunk index = lg + i*G, valid while
 // < d4), JB context rows in flight at a time.
+// DIRECT: the per-sample mode (ne_train_block_async): a shared row's deltas go straight to the table row
+// with atomics instead of to the delta buffer, so pairs that read the row later see them, and nothing is
+// left for the apply phase.
 // ---------------------------------------------------------------------------------------------
 struct TrainArgs {
     float4* X;
     float4* C;
-    int64_t B;            // pairs (pair mode) / walk positions (walk mode)
+    int64_t B;            // pairs (pair mode) / walk positions or segments (walk mode)
     int32_t window;       // walk mode: pairs per position
     int32_t K;
     int32_t d4;
     float lr;
     const int32_t* ids;
-    const uint32_t* posbuf;
-    const uint8_t* refshared;   // per reference: its row is named by another reference too
-    float* delta;
-    // shared rows, list path: the first list_cap references to arrive at a row (0 = path off)
-    uint32_t list_cap;
-    uint32_t* count;      // [positions] references of the row that have arrived (zero between batches)
-    uint32_t* members;    // [positions][kListCap] reference indices of the first arrivals
-    float4* dbuf;         // [references][d4] their deltas
-    // per-sample mode (ne_train_block_async): a shared row's deltas go straight to the table row with atomics
-    // instead of to a slot, so pairs that read the row later see them; nothing is left for the apply phase
-    int32_t direct;
+    const uint32_t* tag;  // per reference: 0 = sole reference of its row, else 1 + its row in dbuf
+    float4* dbuf;         // [..][d4] deltas of references to shared rows
 };
-
-// Longest member list of a shared row.
-constexpr uint32_t kListCap = 8;
-
-// Rank of a reference among those arriving at its shared row (~0 with the list path off).  The
-// returning atomic is cheap next to a row's traffic and is issued early, so its latency hides
-// behind the row gathers.
-template <int G>
-__device__ __forceinline__ uint32_t arrival_rank(const TrainArgs& a, uint32_t pos, int lg)
-{
-    uint32_t r = ~0u;
-    if (a.list_cap) {
-        if (lg == 0) r = atomicAdd(&a.count[pos], 1u);
-        r = __shfl(r, 0, G);
-    }
-    return r;
-}
 
 // Element e = lg + m*G of a row, for m < 4*NCH: the layout in which one atomic instruction of a lane
 // group covers consecutive dwords.  The float4-chunk layout is turned into it through LDS.
@@ -494,47 +719,29 @@ __device__ __forceinline__ void to_consecutive(const float4 (&v)[NCH], float (&o
     __builtin_amdgcn_wave_barrier();
 }
 
-// Delta dv of reference `ref` to the shared row at hash position pos.  A reference that arrived among
-// the first list_cap stores it with plain stores in its own row of dbuf and enters the row's member
-// list (the apply kernel sums the list); a later one adds it to the row's slot with atomics, which
-// retire one dword per memory channel clock and would otherwise bound batches with many shared rows.
+// row += delta in place, or the delta to its place in the delta buffer.
 template <int G, int NCH>
-__device__ __forceinline__ void shared_row_delta(const TrainArgs& a, uint32_t pos, uint32_t ref, uint32_t rank,
-                                                 const float4 (&dv)[NCH], float* lds_row, int lg, int d4, float4* row)
+__device__ __forceinline__ void write_row(const TrainArgs& a, float4* row, uint32_t tag, const float4 (&old)[NCH],
+                                          const float4 (&dv)[NCH], int lg, int d4)
 {
-    if (rank < a.list_cap) {
-        float4* out = a.dbuf + static_cast<int64_t>(ref) * d4;
+    float4* out = tag ? a.dbuf + static_cast<int64_t>(tag - 1u) * d4 : row;
 #pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-            const int ci = lg + i * G;
-            if (ci < d4) out[ci] = dv[i];
-        }
-        if (lg == 0) a.members[static_cast<int64_t>(pos) * kListCap + rank] = ref;
-    } else {
-        float t[4 * NCH];
-        to_consecutive<G, NCH>(dv, t, lds_row, lg);
-        float* slot = a.direct ? reinterpret_cast<float*>(row) : a.delta + static_cast<int64_t>(pos) * (d4 * 4);
-#pragma unroll
-        for (int m = 0; m < 4 * NCH; ++m) {
-            const int e = lg + m * G;
-            if (e < d4 * 4) unsafeAtomicAdd(slot + e, t[m]);
-        }
+    for (int i = 0; i < NCH; ++i) {
+        const int ci = lg + i * G;
+        if (ci < d4) out[ci] = tag ? dv[i] : make_float4(old[i].x + dv[i].x, old[i].y + dv[i].y, old[i].z + dv[i].z, old[i].w + dv[i].w);
     }
 }
 
 // K+1 context rows of one pair (rows 0..K; with POS_FIRST row 0 is the positive, every other row a
 // negative), JB at a time: gather, score against x, form g_j, add g_j c_j to dx, and update the row:
-// rewritten in place if only this reference names it, else its delta goes to the reference's buffer
-// row (list path, first arrivals) or to the row's slot with atomics.  Lane j + LANE0 of the group holds
-// reference j's id, hash position, shared flag and index in the batch.
-template <int G, int NCH, int JB, int LANE0, bool POS_FIRST = true>
-__device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, int d4, int d, const float4 (&xr)[NCH],
+// rewritten in place if only this reference names it, else its delta goes to the delta buffer (DIRECT:
+// to the row with atomics; xt is x in consecutive-dword layout).  Lane j + LANE0 of the group holds
+// reference j's id and tag.
+template <int G, int NCH, int JB, int LANE0, bool POS_FIRST = true, bool DIRECT = false>
+__device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, int d4, const float4 (&xr)[NCH],
                                                      const float (&xt)[4 * NCH], float4 (&dx)[NCH], int32_t id_mine,
-                                                     uint32_t pos_mine, int shared_mine, uint32_t ref_mine, int lg)
+                                                     uint32_t tag_mine, int lg)
 {
-    // ranks of this pair's references to shared rows, all in one returning atomic
-    uint32_t rank_mine = ~0u;
-    if (a.list_cap && shared_mine) rank_mine = atomicAdd(&a.count[pos_mine], 1u);
     for (int j0 = 0; j0 <= K; j0 += JB) {
         float4 cr[JB][NCH];
         float part[JB];
@@ -565,32 +772,28 @@ __device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, 
             if (j <= K) {
                 const float sg = sigmoidf(part[jj]);
                 const float g = a.lr * ((POS_FIRST && j == 0) ? 1.0f - sg : -sg);
-                const int shared = __shfl(shared_mine, j + LANE0, G);
-                const uint32_t pos = __shfl(pos_mine, j + LANE0, G);
-                const uint32_t rank = __shfl(rank_mine, j + LANE0, G);
-                const uint32_t ref = __shfl(ref_mine, j + LANE0, G);
+                const uint32_t tag = __shfl(tag_mine, j + LANE0, G);
 #pragma unroll
                 for (int i = 0; i < NCH; ++i) dx[i] = axpy4(g, cr[jj][i], dx[i]);
-                if (!shared) {
+                if (DIRECT && tag) {
+                    float* row = reinterpret_cast<float*>(crow[jj]);
 #pragma unroll
-                    for (int i = 0; i < NCH; ++i) {
-                        const int ci = lg + i * G;
-                        if (ci < d4) crow[jj][ci] = axpy4(g, xr[i], cr[jj][i]);
+                    for (int m = 0; m < 4 * NCH; ++m) {
+                        const int e = lg + m * G;
+                        if (e < d4 * 4) unsafeAtomicAdd(row + e, g * xt[m]);
                     }
-                } else if (rank < a.list_cap) {
-                    float4* out = a.dbuf + static_cast<int64_t>(ref) * d4;
+                } else if (tag) {
+                    float4* out = a.dbuf + static_cast<int64_t>(tag - 1u) * d4;
 #pragma unroll
                     for (int i = 0; i < NCH; ++i) {
                         const int ci = lg + i * G;
                         if (ci < d4) out[ci] = make_float4(g * xr[i].x, g * xr[i].y, g * xr[i].z, g * xr[i].w);
                     }
-                    if (lg == 0) a.members[static_cast<int64_t>(pos) * kListCap + rank] = ref;
                 } else {
-                    float* slot = a.direct ? reinterpret_cast<float*>(crow[jj]) : a.delta + static_cast<int64_t>(pos) * d;
 #pragma unroll
-                    for (int m = 0; m < 4 * NCH; ++m) {
-                        const int e = lg + m * G;
-                        if (e < d) unsafeAtomicAdd(slot + e, g * xt[m]);
+                    for (int i = 0; i < NCH; ++i) {
+                        const int ci = lg + i * G;
+                        if (ci < d4) crow[jj][ci] = axpy4(g, xr[i], cr[jj][i]);
                     }
                 }
             }
@@ -599,28 +802,14 @@ __device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, 
 
 }
 
-#ifndef NE_TRAIN_THREADS
-#define NE_TRAIN_THREADS 256
-#endif
-constexpr int kTrainThreads = NE_TRAIN_THREADS;   // threads per block of the train kernel (a claim block's 256-thread share is looped)
+constexpr int kTrainThreads = 256;   // threads per block of the train kernels
 
-template <int G, int NCH, int JB>
-__global__ __launch_bounds__(kTrainThreads) void train_kernel(TrainArgs a, PrepArgs next, unsigned claim_blocks, unsigned period)
+template <int G, int NCH, int JB, bool DIRECT>
+__global__ __launch_bounds__(kTrainThreads) void train_kernel(TrainArgs a, Helpers helpers)
 {
     constexpr int GROUPS = kTrainThreads / G;
-    __shared__ float lds[GROUPS][4 * G * NCH];
-    // some blocks do the id-only claim phase of the next batch
     unsigned block;
-    if (fused_block(claim_blocks, period, &block)) {
-        if (block < next.fetch_blocks) {   // sample prefetch for the batch after the next
-            fetch_pairs(next.fetch_src, next.fetch_dst, next.fetch_n, static_cast<int64_t>(block) * kTrainThreads + threadIdx.x,
-                        static_cast<int64_t>(next.fetch_blocks) * kTrainThreads);
-            return;
-        }
-        block -= next.fetch_blocks;
-        for (unsigned tid = threadIdx.x; tid < 256u; tid += kTrainThreads) claim_refs(next, block, tid);
-        return;
-    }
+    if (helper_block<kPairRefs>(helpers, &block)) return;
     const int lg = threadIdx.x & (G - 1);
     const int grp = threadIdx.x / G;
     const int64_t b = static_cast<int64_t>(block) * GROUPS + grp;
@@ -628,49 +817,41 @@ __global__ __launch_bounds__(kTrainThreads) void train_kernel(TrainArgs a, PrepA
     const int K = a.K;
     const int R = K + 2;
     const int d4 = a.d4;
-    const int d = d4 * 4;
 
-    // lane j < R owns reference j: id, delta slot, shared flag
+    // lane j < R owns reference j: id and tag
     int32_t id_mine = 0;
-    uint32_t pos_mine = 0;
-    int shared_mine = 0;
-    const uint32_t ref_mine = static_cast<uint32_t>(b * R + lg);
+    uint32_t tag_mine = 0;
     if (lg < R) {
-        id_mine = a.ids[ref_mine];
-        pos_mine = a.posbuf[ref_mine];
-        shared_mine = a.refshared[ref_mine];
+        id_mine = a.ids[b * R + lg];
+        tag_mine = a.tag[b * R + lg];
     }
-    const int shared0 = __shfl(shared_mine, 0, G);
-    const uint32_t pos0 = __shfl(pos_mine, 0, G);
-    const uint32_t rank0 = shared0 ? arrival_rank<G>(a, pos0, lg) : ~0u;
-
-    const int32_t src = __shfl(id_mine, 0, G);
-    float4* xrow = a.X + static_cast<int64_t>(src) * d4;
+    const uint32_t tag0 = __shfl(tag_mine, 0, G);
+    float4* xrow = a.X + static_cast<int64_t>(__shfl(id_mine, 0, G)) * d4;
     float4 xr[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
         const int ci = lg + i * G;
         xr[i] = (ci < d4) ? xrow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    float xt[4 * NCH];   // x in consecutive-dword layout, for the atomic path
-    to_consecutive<G, NCH>(xr, xt, lds[grp], lg);
+    float xt[4 * NCH];   // x in consecutive-dword layout, for the atomics
+    float* lds_row = reinterpret_cast<float*>(dynamic_lds) + grp * (4 * G * NCH);
+    if (DIRECT) to_consecutive<G, NCH>(xr, xt, lds_row, lg);
 
     float4 dx[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) dx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 
-    // (lane 0's reference, the vertex row, has been ranked above)
-    context_rows_of_pair<G, NCH, JB, 1>(a, K, d4, d, xr, xt, dx, id_mine, pos_mine, lg >= 1 ? shared_mine : 0, ref_mine, lg);
+    context_rows_of_pair<G, NCH, JB, 1, true, DIRECT>(a, K, d4, xr, xt, dx, id_mine, tag_mine, lg);
 
-    if (!shared0) {
+    if (DIRECT && tag0) {
+        to_consecutive<G, NCH>(dx, xt, lds_row, lg);
 #pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-            const int ci = lg + i * G;
-            if (ci < d4)
-                xrow[ci] = make_float4(xr[i].x + dx[i].x, xr[i].y + dx[i].y, xr[i].z + dx[i].z, xr[i].w + dx[i].w);
+        for (int m = 0; m < 4 * NCH; ++m) {
+            const int e = lg + m * G;
+            if (e < d4 * 4) unsafeAtomicAdd(reinterpret_cast<float*>(xrow) + e, xt[m]);
         }
     } else {
-        shared_row_delta<G, NCH>(a, pos0, static_cast<uint32_t>(b * R), rank0, dx, lds[grp], lg, d4, xrow);
+        write_row<G, NCH>(a, xrow, tag0, xr, dx, lg, d4);
     }
 }
 
@@ -680,36 +861,23 @@ __global__ __launch_bounds__(kTrainThreads) void train_kernel(TrainArgs a, PrepA
 // and written once.  Each pair's K+1 context rows are handled exactly as in the pair mode.
 // ---------------------------------------------------------------------------------------------
 template <int G, int NCH, int JB>
-__global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, PrepArgs next, unsigned claim_blocks, unsigned period)
+__global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, Helpers helpers)
 {
     constexpr int GROUPS = kTrainThreads / G;
-    __shared__ float lds[GROUPS][4 * G * NCH];
     unsigned block;
-    if (fused_block(claim_blocks, period, &block)) {
-        if (block < next.fetch_blocks) {   // sample prefetch for the batch after the next
-            fetch_pairs(next.fetch_src, next.fetch_dst, next.fetch_n, static_cast<int64_t>(block) * kTrainThreads + threadIdx.x,
-                        static_cast<int64_t>(next.fetch_blocks) * kTrainThreads);
-            return;
-        }
-        block -= next.fetch_blocks;
-        for (unsigned tid = threadIdx.x; tid < 256u; tid += kTrainThreads) claim_refs(next, block, tid);
-        return;
-    }
+    if (helper_block<kWalkRefs>(helpers, &block)) return;
     const int lg = threadIdx.x & (G - 1);
     const int grp = threadIdx.x / G;
     const int64_t p = static_cast<int64_t>(block) * GROUPS + grp;
     if (p >= a.B) return;   // whole groups leave together; groups never communicate below
     const int K = a.K;
     const int d4 = a.d4;
-    const int d = d4 * 4;
     const int64_t R = 1 + static_cast<int64_t>(a.window) * (K + 1);
     const int64_t ref0 = p * R;
 
     const int32_t src = a.ids[ref0];
     if (src < 0) return;    // no pair starts at this position (uniform over the group)
-    const uint32_t pos0 = a.posbuf[ref0];
-    const int shared0 = a.refshared[ref0];
-    const uint32_t rank0 = shared0 ? arrival_rank<G>(a, pos0, lg) : ~0u;
+    const uint32_t tag0 = a.tag[ref0];
 
     float4* xrow = a.X + static_cast<int64_t>(src) * d4;
     float4 xr[NCH];
@@ -718,8 +886,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
         const int ci = lg + i * G;
         xr[i] = (ci < d4) ? xrow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    float xt[4 * NCH];   // x in consecutive-dword layout, for the atomic path
-    to_consecutive<G, NCH>(xr, xt, lds[grp], lg);
+    const float xt[4 * NCH] = {};
 
     float4 dx[NCH];
 #pragma unroll
@@ -728,30 +895,16 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
     for (int j = 0; j < a.window; ++j) {
         // lane l <= K owns context reference l of pair j
         int32_t id_mine = -1;
-        uint32_t pos_mine = 0;
-        int shared_mine = 0;
+        uint32_t tag_mine = 0;
         const int64_t ref = ref0 + 1 + static_cast<int64_t>(j) * (K + 1) + lg;
         if (lg <= K) {
             id_mine = a.ids[ref];
-            if (id_mine >= 0) {
-                pos_mine = a.posbuf[ref];
-                shared_mine = a.refshared[ref];
-            }
+            tag_mine = a.tag[ref];
         }
         if (__shfl(id_mine, 0, G) < 0) continue;   // the walk has no pair j here; a pair's references exist together
-        context_rows_of_pair<G, NCH, JB, 0>(a, K, d4, d, xr, xt, dx, id_mine, pos_mine, shared_mine, static_cast<uint32_t>(ref), lg);
+        context_rows_of_pair<G, NCH, JB, 0>(a, K, d4, xr, xt, dx, id_mine, tag_mine, lg);
     }
-
-    if (!shared0) {
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-            const int ci = lg + i * G;
-            if (ci < d4)
-                xrow[ci] = make_float4(xr[i].x + dx[i].x, xr[i].y + dx[i].y, xr[i].z + dx[i].z, xr[i].w + dx[i].w);
-        }
-    } else {
-        shared_row_delta<G, NCH>(a, pos0, static_cast<uint32_t>(ref0), rank0, dx, lds[grp], lg, d4, xrow);
-    }
+    write_row<G, NCH>(a, xrow, tag0, xr, dx, lg, d4);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -766,54 +919,38 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
 //            entries of this segment: sums dc in registers.
 // The positive score of a sample is therefore computed twice (both ends need its coefficient); the
 // rows are what costs.  Every row is then written once: in place if no other reference names it,
-// else to its slot with atomics (the context rows next to a segment boundary get contributions
+// else its delta to the delta buffer (the context rows next to a segment boundary get contributions
 // from both segments and are always of that kind).
 // ---------------------------------------------------------------------------------------------
 template <int G, int NCH, int JB>
-__global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, PrepArgs next, unsigned claim_blocks, unsigned period)
+__global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, Helpers helpers)
 {
     constexpr int E = kTrainThreads / G;
     constexpr int ROW = 4 * G * NCH;              // floats per staged row (>= d)
-    extern __shared__ float seg_lds[];
-    float* scratch = seg_lds;                      // [E][ROW]        layout changes for the atomic path
-    float* xs = scratch + E * ROW;                 // [E][ROW]        vertex rows of the entries
-    float* cs = xs + E * ROW;                      // [E + window - 1][ROW]  context rows
+    float* xs = reinterpret_cast<float*>(dynamic_lds);   // [E][ROW]        vertex rows of the entries
+    float* cs = xs + E * ROW;                            // [E + window - 1][ROW]  context rows
     const int CT = E + a.window - 1;
     int32_t* cid = reinterpret_cast<int32_t*>(cs + CT * ROW);   // [CT] ids of the context rows (-1: absent)
     int32_t* xid = cid + CT;                                    // [E]  ids of the vertex rows (-1: absent)
     unsigned block;
-    if (fused_block(claim_blocks, period, &block)) {
-        if (block < next.fetch_blocks) {   // sample prefetch for the batch after the next
-            fetch_pairs(next.fetch_src, next.fetch_dst, next.fetch_n, static_cast<int64_t>(block) * kTrainThreads + threadIdx.x,
-                        static_cast<int64_t>(next.fetch_blocks) * kTrainThreads);
-            return;
-        }
-        block -= next.fetch_blocks;
-        for (unsigned tid = threadIdx.x; tid < 256u; tid += kTrainThreads) claim_refs(next, block, tid);
-        return;
-    }
+    if (helper_block<kSegRefs>(helpers, &block)) return;
     const int lg = threadIdx.x & (G - 1);
     const int grp = threadIdx.x / G;
     const int K = a.K;
     const int W = a.window;
     const int d4 = a.d4;
-    const int d = d4 * 4;
     const int64_t R = E + CT + static_cast<int64_t>(E) * W * K;
     if (static_cast<int64_t>(block) >= a.B) return;             // a.B = segments of the batch (uniform over the workgroup)
     const int64_t ref0 = static_cast<int64_t>(block) * R;
 
     // my entry's vertex row, and the context rows grp and grp + E of the segment's list
     const int32_t src = a.ids[ref0 + grp];
-    uint32_t pos_x = 0, rank_x = ~0u;
-    int shared_x = 0;
+    const uint32_t tag_x = a.tag[ref0 + grp];
     float4 xr[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) xr[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     float4* xrow = a.X;
     if (src >= 0) {
-        pos_x = a.posbuf[ref0 + grp];
-        shared_x = a.refshared[ref0 + grp];
-        if (shared_x) rank_x = arrival_rank<G>(a, pos_x, lg);
         xrow = a.X + static_cast<int64_t>(src) * d4;
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
@@ -839,8 +976,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, P
 
     // ---- source part
     if (src >= 0) {
-        float xt[4 * NCH];   // x in consecutive-dword layout, for the atomic path
-        to_consecutive<G, NCH>(xr, xt, scratch + grp * ROW, lg);
+        const float xt[4 * NCH] = {};
         float4 dx[NCH];
 #pragma unroll
         for (int i = 0; i < NCH; ++i) dx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -861,28 +997,16 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, P
             if (K > 0) {
                 // lane k < K owns negative k of this sample
                 int32_t id_mine = -1;
-                uint32_t pos_mine = 0;
-                int shared_mine = 0;
+                uint32_t tag_mine = 0;
                 const int64_t ref = ref0 + E + CT + (static_cast<int64_t>(grp) * W + (j - 1)) * K + lg;
                 if (lg < K) {
                     id_mine = a.ids[ref];
-                    pos_mine = a.posbuf[ref];
-                    shared_mine = a.refshared[ref];
+                    tag_mine = a.tag[ref];
                 }
-                context_rows_of_pair<G, NCH, JB, 0, false>(a, K - 1, d4, d, xr, xt, dx, id_mine, pos_mine, shared_mine,
-                                                           static_cast<uint32_t>(ref), lg);
+                context_rows_of_pair<G, NCH, JB, 0, false>(a, K - 1, d4, xr, xt, dx, id_mine, tag_mine, lg);
             }
         }
-        if (!shared_x) {
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                const int ci = lg + i * G;
-                if (ci < d4)
-                    xrow[ci] = make_float4(xr[i].x + dx[i].x, xr[i].y + dx[i].y, xr[i].z + dx[i].z, xr[i].w + dx[i].w);
-            }
-        } else {
-            shared_row_delta<G, NCH>(a, pos_x, static_cast<uint32_t>(ref0 + grp), rank_x, dx, scratch + grp * ROW, lg, d4, xrow);
-        }
+        write_row<G, NCH>(a, xrow, tag_x, xr, dx, lg, d4);
     }
 
     // ---- context part: context row `row` is entry p0 + 1 + row; its sources in this segment are the
@@ -890,10 +1014,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, P
     for (int row = grp; row < CT; row += E) {
         const int32_t id = cid[row];
         if (id < 0) continue;
-        const int64_t ref = ref0 + E + row;
-        const uint32_t pos_c = a.posbuf[ref];
-        const int shared_c = a.refshared[ref];
-        const uint32_t rank_c = shared_c ? arrival_rank<G>(a, pos_c, lg) : ~0u;
+        const uint32_t tag_c = a.tag[ref0 + E + row];
         float4 cr[NCH], dc[NCH];
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
@@ -915,147 +1036,77 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, P
 #pragma unroll
             for (int i = 0; i < NCH; ++i) dc[i] = axpy4(g0, xv[i], dc[i]);
         }
-        if (!shared_c) {
-            float4* crow = a.C + static_cast<int64_t>(id) * d4;
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                const int ci = lg + i * G;
-                if (ci < d4)
-                    crow[ci] = make_float4(cr[i].x + dc[i].x, cr[i].y + dc[i].y, cr[i].z + dc[i].z, cr[i].w + dc[i].w);
-            }
-        } else {
-            shared_row_delta<G, NCH>(a, pos_c, static_cast<uint32_t>(ref), rank_c, dc, scratch + grp * ROW, lg, d4,
-                                     a.C + static_cast<int64_t>(id) * d4);
-        }
+        write_row<G, NCH>(a, a.C + static_cast<int64_t>(id) * d4, tag_c, cr, dc, lg, d4);
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// apply kernel.  Two kinds of blocks:
-//   resolve_blocks of them (spread over the grid): resolve phase of the next batch (other set of
-//                         hash state)
-//   the rest              sweep the batch's hash positions in order, 8 per thread: read the shared
-//                         flags, empty the positions and clear the flags with full-width stores
-//                         (a linear pass is far cheaper than one partial store per reference), collect
-//                         the shared rows in LDS, then 16-lane groups add each row's deltas - the
-//                         buffer rows of its member list, the slot if references beyond the list
-//                         used it - to the table row and zero what they used.
+// apply kernel: one lane group per work item of the batch: up to 8 rows of the delta buffer, which lie
+// side by side, are summed and added to the table row.  A row with more references has several items,
+// which may meet: they use atomics.
 // ---------------------------------------------------------------------------------------------
-// Positions per sweep thread are a launch choice (2, 4 or 8): fewer give the row work more workgroups,
-// more make the sweep itself cheaper.  Position counts are multiples of the largest block's span.
-constexpr int kSweepPerBlock = 256 * 8;
-
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
 struct ApplyArgs {
     float4* X;
     float4* C;
     int32_t d4;
-    float4* delta;
-    uint32_t positions;   // hash positions in use for this batch (a power of two, multiple of 2048)
-    unsigned long long* slots;
-    uint8_t* shared;
-    uint32_t list_cap;    // as in TrainArgs
-    uint32_t* count;
-    const uint32_t* members;
+    const uint2* items;
+    const unsigned long long* totals;
     const float4* dbuf;
-    int32_t direct;       // per-sample mode: the train kernel has already added the shared rows' deltas to the tables
 };
 
-template <int kSweepPerThread, int GL, int CH>
-__global__ __launch_bounds__(256) void apply_kernel(ApplyArgs a, PrepArgs next, unsigned resolve_blocks,
-                                                    unsigned period)
+template <int GL, int CH>
+__global__ __launch_bounds__(256) void apply_kernel(ApplyArgs a)
 {
-    constexpr int kSpan = 256 * kSweepPerThread;   // positions per workgroup
-    __shared__ uint2 todo_list[kSpan];   // (position, key) of the shared rows of this block's span
-    __shared__ int todo_count;
-    unsigned block;
-    if (fused_block(resolve_blocks, period, &block)) {
-        resolve_refs(next, block);
-        return;
-    }
-    if (threadIdx.x == 0) todo_count = 0;
-    __syncthreads();
-    const uint32_t first = block * kSpan + threadIdx.x * kSweepPerThread;
-    using flags_t = std::conditional_t<kSweepPerThread == 8, uint64_t, std::conditional_t<kSweepPerThread == 4, uint32_t, uint16_t>>;
-    static_assert(kSweepPerThread == 8 || kSweepPerThread == 4 || kSweepPerThread == 2, "flags are read as one word");
-    const uint64_t flags = *reinterpret_cast<const flags_t*>(a.shared + first);
-    if (flags) {
-        *reinterpret_cast<flags_t*>(a.shared + first) = 0;
-#pragma unroll
-        for (int i = 0; i < kSweepPerThread; ++i) {
-            if ((flags >> (8 * i)) & 0xFFull) {
-                const uint32_t key = static_cast<uint32_t>(a.slots[first + i] >> 32);
-                todo_list[atomicAdd(&todo_count, 1)] = make_uint2(first + i, key);
-            }
-        }
-    }
-    {
-        ulonglong2* out = reinterpret_cast<ulonglong2*>(a.slots + first);
-        const ulonglong2 empty2 = make_ulonglong2(kEmptySlot, kEmptySlot);
-#pragma unroll
-        for (int i = 0; i < kSweepPerThread / 2; ++i) out[i] = empty2;
-    }
-    __syncthreads();
-    const int n = a.direct ? 0 : todo_count;
+    constexpr uint32_t GROUPS = 256 / GL;
+    constexpr uint32_t MB = CH >= static_cast<int>(kItemRefs) ? 1 : kItemRefs / CH;   // delta rows in flight
+    const uint32_t n = static_cast<uint32_t>(*a.totals >> 32);
     const int lg = threadIdx.x & (GL - 1);
-    for (int e = threadIdx.x / GL; e < n; e += 256 / GL) {
-        const uint2 item = todo_list[e];
-        float4* row = ((item.y & 0x80000000u) ? a.C : a.X) + static_cast<int64_t>(item.y & 0x7FFFFFFFu) * a.d4;
-        float4* slot = a.delta + static_cast<int64_t>(item.x) * a.d4;
-        // list path: the row's first arrivals left their deltas in dbuf; only later ones used the slot
-        uint32_t listed = 0, member = 0;
-        bool use_slot = true;
-        if (a.list_cap) {
-            const uint32_t arrived = a.count[item.x];
-            // (entries past the list's end hold stale indices; they are not used)
-            if (static_cast<uint32_t>(lg) < kListCap) member = a.members[static_cast<int64_t>(item.x) * kListCap + lg];
-            listed = arrived < a.list_cap ? arrived : a.list_cap;
-            use_slot = arrived > listed;
-            if (lg == 0) a.count[item.x] = 0u;
+    for (uint32_t e = blockIdx.x * GROUPS + threadIdx.x / GL; e < n; e += gridDim.x * GROUPS) {
+        const uint2 item = a.items[e];
+        float4* row = ((item.x & 0x80000000u) ? a.C : a.X) + static_cast<int64_t>(item.x & 0x7FFFFFFFu) * a.d4;
+        const float4* src = a.dbuf + static_cast<int64_t>(item.y >> 4) * a.d4;
+        const uint32_t refs = (item.y & 7u) + 1u;
+        if (item.y & 8u) {
+            // several items add to this row: consecutive dwords per atomic instruction
+            for (int c = lg; c < a.d4 * 4; c += GL) {
+                const float* s = reinterpret_cast<const float*>(src) + c;
+                float v[kItemRefs], sum = 0.0f;
+#pragma unroll
+                for (uint32_t r = 0; r < kItemRefs; ++r) v[r] = r < refs ? s[static_cast<int64_t>(r) * (a.d4 * 4)] : 0.0f;
+#pragma unroll
+                for (uint32_t r = 0; r < kItemRefs; ++r) sum += v[r];
+                unsafeAtomicAdd(reinterpret_cast<float*>(row) + c, sum);
+            }
+            continue;
         }
-        // CH chunks of a row per lane and pass, all of a pass's loads issued before its stores (a
-        // 2 KB row in passes of 2 chunks would pay four dependent round trips instead of one)
         for (int c0 = 0; c0 < a.d4; c0 += GL * CH) {
-            float4 acc[CH];
+            float4 old[CH], sum[CH];
             bool valid[CH];
 #pragma unroll
             for (int i = 0; i < CH; ++i) {
                 const int ci = c0 + lg + GL * i;
                 valid[i] = ci < a.d4;
-                acc[i] = valid[i] ? row[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
+                old[i] = valid[i] ? row[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
+                sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
-            if (use_slot) {
-                float4 sv[CH];
-#pragma unroll
-                for (int i = 0; i < CH; ++i) sv[i] = valid[i] ? slot[c0 + lg + GL * i] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                for (int i = 0; i < CH; ++i) acc[i] = add4(acc[i], sv[i]);
-            }
-            // the list's buffer rows, MB members' loads in flight together
-            constexpr uint32_t MB = CH >= 16 ? 1 : (16 / CH < kListCap ? 16 / CH : kListCap);
-            for (uint32_t r0 = 0; r0 < listed; r0 += MB) {
+            for (uint32_t r0 = 0; r0 < refs; r0 += MB) {
                 float4 dv[MB][CH];
-#pragma unroll
-                for (uint32_t r = 0; r < MB; ++r) {
-                    const float4* src = a.dbuf + static_cast<int64_t>(__shfl(member, static_cast<int>((r0 + r) & (kListCap - 1)), GL)) * a.d4;
-#pragma unroll
-                    for (int i = 0; i < CH; ++i)
-                        dv[r][i] = (r0 + r < listed && valid[i]) ? src[c0 + lg + GL * i] : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
 #pragma unroll
                 for (uint32_t r = 0; r < MB; ++r)
 #pragma unroll
-                    for (int i = 0; i < CH; ++i) acc[i] = add4(acc[i], dv[r][i]);
+                    for (int i = 0; i < CH; ++i)
+                        dv[r][i] = (r0 + r < refs && valid[i]) ? src[static_cast<int64_t>(r0 + r) * a.d4 + c0 + lg + GL * i]
+                                                               : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (uint32_t r = 0; r < MB; ++r)
+#pragma unroll
+                    for (int i = 0; i < CH; ++i) sum[i] = add4(sum[i], dv[r][i]);
             }
 #pragma unroll
             for (int i = 0; i < CH; ++i)
-                if (valid[i]) row[c0 + lg + GL * i] = acc[i];
-            if (use_slot) {
-#pragma unroll
-                for (int i = 0; i < CH; ++i)
-                    if (valid[i]) slot[c0 + lg + GL * i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+                if (valid[i]) row[c0 + lg + GL * i] = add4(old[i], sum[i]);
         }
     }
 }
@@ -1192,20 +1243,23 @@ bool pick_shape(int32_t d4, int32_t K, Shape* out)
 
 #define NE_FOR_EACH_SHAPE(M) M(8, 1) M(16, 1) M(32, 1) M(64, 1) M(64, 2) M(64, 4)
 
-hipError_t launch_train(const Shape& s, const TrainArgs& a, const PrepArgs& next, hipStream_t st)
+// Grid and LDS of a train launch with `blocks` training workgroups that need `own` bytes of LDS.
+struct TrainGrid { unsigned grid; size_t lds; };
+inline TrainGrid train_grid(const Helpers& h, int64_t blocks, size_t own)
+{
+    const size_t lds = h.lds_bytes();
+    return {h.count() + static_cast<unsigned>(blocks), own > lds ? own : lds};
+}
+
+hipError_t launch_train(const Shape& s, const TrainArgs& a, const Helpers& h, bool direct, hipStream_t st)
 {
     const int groups = kTrainThreads / s.G;
-    const unsigned claim_blocks = prep_blocks(next.refs) + next.fetch_blocks;   // helper workgroups
-    const unsigned grid = claim_blocks + static_cast<unsigned>((a.B + groups - 1) / groups);
-    const unsigned period = claim_blocks ? grid / claim_blocks : 1u;
-    // context rows gathered together per lane group: 2 measured +1.3 % over 6 at dim 128 (fewer registers,
-    // more wavefronts resident; the kernel is bound by throughput, not by one group's latency), except with
-    // the list path, where 6 is 1.5 % ahead
-    const bool few = a.list_cap == 0;
+    const TrainGrid g = train_grid(h, (a.B + groups - 1) / groups, direct ? static_cast<size_t>(kTrainThreads) * s.NCH * sizeof(float4) : 0);
+    // context rows gathered together per lane group: 2, as 3 and more; one costs 1 - 2 % (dim 128)
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
-        if (few) hipLaunchKernelGGL((train_kernel<G_, N_, 2>), dim3(grid), dim3(kTrainThreads), 0, st, a, next, claim_blocks, period); \
-        else hipLaunchKernelGGL((train_kernel<G_, N_, 6>), dim3(grid), dim3(kTrainThreads), 0, st, a, next, claim_blocks, period); \
+        if (direct) hipLaunchKernelGGL((train_kernel<G_, N_, 2, true>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
+        else hipLaunchKernelGGL((train_kernel<G_, N_, 2, false>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
         return hipGetLastError();                                                                \
     }
     NE_FOR_EACH_SHAPE(NE_CASE)
@@ -1213,15 +1267,13 @@ hipError_t launch_train(const Shape& s, const TrainArgs& a, const PrepArgs& next
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_train_walk(const Shape& s, const TrainArgs& a, const PrepArgs& next, hipStream_t st)
+hipError_t launch_train_walk(const Shape& s, const TrainArgs& a, const Helpers& h, hipStream_t st)
 {
     const int groups = kTrainThreads / s.G;
-    const unsigned claim_blocks = prep_blocks(next.refs) + next.fetch_blocks;   // helper workgroups
-    const unsigned grid = claim_blocks + static_cast<unsigned>((a.B + groups - 1) / groups);
-    const unsigned period = claim_blocks ? grid / claim_blocks : 1u;
+    const TrainGrid g = train_grid(h, (a.B + groups - 1) / groups, 0);
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
-        hipLaunchKernelGGL((train_walk_kernel<G_, N_, 6>), dim3(grid), dim3(kTrainThreads), 0, st, a, next, claim_blocks, period); \
+        hipLaunchKernelGGL((train_walk_kernel<G_, N_, 6>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
         return hipGetLastError();                                                                \
     }
     NE_FOR_EACH_SHAPE(NE_CASE)
@@ -1229,22 +1281,47 @@ hipError_t launch_train_walk(const Shape& s, const TrainArgs& a, const PrepArgs&
     return hipErrorInvalidValue;
 }
 
-// LDS of the segment kernel: scratch, vertex rows and context rows of a segment, and their ids
+// LDS of the segment kernel: vertex rows and context rows of a segment, and their ids
 size_t seg_lds_bytes(const Shape& s, int window)
 {
     const size_t E = kTrainThreads / s.G, row = 4 * static_cast<size_t>(s.G) * s.NCH, CT = E + window - 1;
-    return (2 * E + CT) * row * 4 + (CT + E) * 4;
+    return (E + CT) * row * 4 + (CT + E) * 4;
 }
 
-hipError_t launch_train_seg(const Shape& s, const TrainArgs& a, const PrepArgs& next, unsigned segments, hipStream_t st)
+hipError_t launch_train_seg(const Shape& s, const TrainArgs& a, const Helpers& h, hipStream_t st)
 {
-    const unsigned claim_blocks = prep_blocks(next.refs) + next.fetch_blocks;   // helper workgroups
-    const unsigned grid = claim_blocks + segments;
-    const unsigned period = claim_blocks ? grid / claim_blocks : 1u;
-    const size_t lds = seg_lds_bytes(s, a.window);
+    const TrainGrid g = train_grid(h, a.B, seg_lds_bytes(s, a.window));   // one workgroup per segment
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
-        hipLaunchKernelGGL((train_seg_kernel<G_, N_, 6>), dim3(grid), dim3(kTrainThreads), lds, st, a, next, claim_blocks, period); \
+        hipLaunchKernelGGL((train_seg_kernel<G_, N_, 6>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
+        return hipGetLastError();                                                                \
+    }
+    NE_FOR_EACH_SHAPE(NE_CASE)
+#undef NE_CASE
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_prepare(const Helpers& h, hipStream_t st)
+{
+    const PrepArgs& p = h.claims ? h.claim : h.resolve;
+    if (p.pairs) hipLaunchKernelGGL(prepare_kernel<kPairRefs>, dim3(h.count()), dim3(256), h.lds_bytes(), st, h);
+    else if (p.seg_entries) hipLaunchKernelGGL(prepare_kernel<kSegRefs>, dim3(h.count()), dim3(256), h.lds_bytes(), st, h);
+    else hipLaunchKernelGGL(prepare_kernel<kWalkRefs>, dim3(h.count()), dim3(256), h.lds_bytes(), st, h);
+    return hipGetLastError();
+}
+
+// Lane groups of the apply kernel: one dwordx4 chunk per lane as long as a wavefront holds the row.  Its
+// number of items is only known on the device; kApplyBlocks workgroups leave a lane group few of them, so
+// that those with long lists do not finish last (16384 against 2048: -2 .. -6 % of a batch's time).
+constexpr unsigned kApplyBlocks = 16384;
+hipError_t launch_apply(const Shape& s, const ApplyArgs& a, uint32_t refs, hipStream_t st)
+{
+    const unsigned groups = 256u / s.G;
+    const unsigned most = (refs / 2 + groups - 1) / groups;      // items <= refs / 2
+    const unsigned grid = most < kApplyBlocks ? (most ? most : 1u) : kApplyBlocks;
+#define NE_CASE(G_, N_)                                                                          \
+    if (s.G == G_ && s.NCH == N_) {                                                              \
+        hipLaunchKernelGGL((apply_kernel<G_, N_>), dim3(grid), dim3(256), 0, st, a);             \
         return hipGetLastError();                                                                \
     }
     NE_FOR_EACH_SHAPE(NE_CASE)
@@ -1268,32 +1345,8 @@ hipError_t launch_loss(const Shape& s, const LossArgs& a, hipStream_t st)
 
 // Largest batch: keeps every grid and the hash capacity inside 32 bits.
 constexpr int64_t kMaxBatch = static_cast<int64_t>(1) << 22;
-// Hash positions per reference, before rounding up to a power of two (load <= 1/2).  Four per
-// reference mean less probing but a longer sweep and twice the footprint of the delta slots, and
-// measured slower at every size tried (100 M nodes x dim 128: -1.6 %, 20 M x 512: -6 %, 1 M x 128: -7 %);
-// eight: -12 %.
-constexpr uint32_t kHashFactor = 2;
 // helper workgroups that prefetch the samples of a later batch from pinned host memory (512 KB per batch of 65536)
 constexpr unsigned kFetchBlocks = 8;
-
-// How a batch treats its shared rows.  Tables that are small next to the batch make most references name
-// shared rows: the train kernel is then bound by the atomics' rate, and the list path (plain stores per
-// reference, summed by the apply kernel) pays: +20 % at 1 M nodes x dim 128 with 458 752 references per
-// batch.  Where the atomics hide behind the row traffic it costs 4-12 %.  Break-even, measured on R-MAT
-// pairs as nodes per reference: 20 at dim 32, 12 at dim 128, 8 at dim 256, 4 at dim 512 (K = 10); the
-// rule below stays a little under it.  The sweep gives each thread 4 positions (2 with the list path,
-// whose row work is longer): 8 made the sweep cheaper but left the row work too few workgroups (-3.6 %).
-// ne_set_tuning overrides both.
-struct BatchTuning { uint32_t list_cap; int sweep_per_thread; };
-inline BatchTuning batch_tuning(const ne_tables* t, uint32_t refs)
-{
-    const int64_t per_ref = 1500 / t->dim < 20 ? 1500 / t->dim : 20;   // nodes per reference up to which lists pay
-    const bool small_tables = t->num_nodes <= per_ref * static_cast<int64_t>(refs);
-    BatchTuning b;
-    b.list_cap = t->tune_list_cap >= 0 ? static_cast<uint32_t>(t->tune_list_cap) : (small_tables ? kListCap : 0u);
-    b.sweep_per_thread = t->tune_sweep > 0 ? t->tune_sweep : (small_tables ? 2 : 4);
-    return b;
-}
 
 bool workspace_layout(int32_t dim, int64_t max_B, int32_t max_K, char* base, Workspace* w)
 {
@@ -1301,47 +1354,23 @@ bool workspace_layout(int32_t dim, int64_t max_B, int32_t max_K, char* base, Wor
         max_K > NE_MAX_NEGATIVES)
         return false;
     const uint64_t refs = static_cast<uint64_t>(max_B) * (max_K + 2);
-    uint64_t cap = 2048;   // one sweep block of the apply kernel
-    while (cap < kHashFactor * refs) cap <<= 1;
     auto up = [](size_t v) { return (v + 255) & ~static_cast<size_t>(255); };
     size_t off = 0;
     auto take = [&](size_t bytes) { char* p = base + off; off = up(off + bytes); return p; };
-    w->cap = static_cast<uint32_t>(cap);
-    for (int i = 0; i < 2; ++i) {
-        w->prep[i].slots = reinterpret_cast<unsigned long long*>(take(cap * 8));
-        w->prep[i].shared = reinterpret_cast<uint8_t*>(take(cap));
-        w->prep[i].ids = reinterpret_cast<int32_t*>(take(refs * 4));
-        w->prep[i].posbuf = reinterpret_cast<uint32_t*>(take(refs * 4));
-        w->prep[i].refshared = reinterpret_cast<uint8_t*>(take(refs));
+    for (PrepSlot& p : w->prep) {
+        p.ids = reinterpret_cast<int32_t*>(take(refs * 4));
+        p.tag = reinterpret_cast<uint32_t*>(take(refs * 4));
+        p.entries = reinterpret_cast<unsigned long long*>(take(refs * 8));
+        p.segs = reinterpret_cast<uint32_t*>(take(max_segs(refs) * 4));
+        p.items = reinterpret_cast<uint2*>(take(refs / 2 * sizeof(uint2)));
+        p.totals = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long)));
     }
-    w->delta = reinterpret_cast<float*>(take(cap * static_cast<size_t>(dim) * 4));
-    w->count = reinterpret_cast<uint32_t*>(take(cap * 4));
-    w->members = reinterpret_cast<uint32_t*>(take(cap * static_cast<size_t>(kListCap) * 4));
     w->dbuf = reinterpret_cast<float*>(take(refs * static_cast<size_t>(dim) * 4));
-    w->total_bytes = off;
+    // what a caller is told to bring is never less than two rows and two words per reference, the bound that
+    // programs may have sized their buffers by; the difference is not used
+    const size_t bound = 2 * refs * (static_cast<size_t>(dim) + 1) * 4;
+    w->total_bytes = off > bound ? off : up(bound);
     return true;
-}
-
-hipError_t launch_fill(uint32_t* p, size_t n, uint32_t v, hipStream_t st)
-{
-    if (n == 0) return hipSuccess;
-    const size_t want = (n + 255) / 256;
-    const unsigned grid = static_cast<unsigned>(want < 16384 ? want : 16384);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(grid), dim3(256), 0, st, p, n, v);
-    return hipGetLastError();
-}
-
-// The state every batch expects to find: hash positions empty, flags, delta slots and arrival counters zero.
-hipError_t clear_workspace(const Workspace& w, int32_t dim, hipStream_t st)
-{
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-        e = launch_fill(reinterpret_cast<uint32_t*>(w.prep[i].slots), static_cast<size_t>(w.cap) * 2, 0xFFFFFFFFu, st);
-        if (e == hipSuccess) e = launch_fill(reinterpret_cast<uint32_t*>(w.prep[i].shared), w.cap / 4, 0u, st);
-    }
-    if (e == hipSuccess) e = launch_fill(reinterpret_cast<uint32_t*>(w.delta), static_cast<size_t>(w.cap) * dim, 0u, st);
-    if (e == hipSuccess) e = launch_fill(w.count, w.cap, 0u, st);
-    return e;
 }
 
 ne_status check_batch_args(const ne_tables* t, const ne_alias* al, const int32_t* pairs, int64_t B, int32_t K,
@@ -1359,81 +1388,60 @@ ne_status check_batch_args(const ne_tables* t, const ne_alias* al, const int32_t
     return NE_OK;
 }
 
-// The launches of a run of batches, common to the pair and the walk shapes: claim and resolve of the
-// first batch stand alone; then per batch kernel A = train(i) + claim(i+1) (+ sample prefetch) and
-// kernel B = apply(i) + resolve(i+1).  prep(i) describes batch i (refs = 0 past the end); train(ta, next)
-// launches the shape's train kernel.
+// The launches of a run of batches, common to the pair and the walk shapes: claim(0), then resolve(0) +
+// claim(1), stand alone; then per batch kernel A = train(i) + resolve(i+1) + claim(i+2) (+ sample prefetch)
+// and kernel B = apply(i).  prep(i) describes batch i (refs = 0 past the end); train(ta, helpers) launches
+// the shape's train kernel.  direct: the per-sample mode, which leaves nothing to apply.
 template <class PrepFn, class TrainFn>
-ne_status run_batches(ne_tables* t, int64_t n_batches, int64_t R, int32_t window, int32_t K, const float* lr_host,
-                             hipStream_t st, PrepFn prep, TrainFn train, bool direct = false)
+ne_status run_batches(ne_tables* t, const Shape& shape, int64_t n_batches, int64_t R, int32_t window, int32_t K,
+                      const float* lr_host, hipStream_t st, PrepFn prep, TrainFn train, bool direct = false)
 {
     const Workspace& w = t->ws;
-    // A launch that failed part-way through an earlier run left hash positions, flags or slots in use:
-    // start from a clean workspace again (the tables may hold a partly applied batch; that is the caller's
-    // to judge from the error it got then).
-    if (t->workspace_dirty) {
-        const hipError_t ce = clear_workspace(w, t->dim, st);
-        if (ce != hipSuccess) return fail(NE_ERR_HIP, std::string("workspace re-clear launch: ") + hipGetErrorString(ce));
-        t->workspace_dirty = false;
-    }
-    t->workspace_dirty = true;   // until the last launch of this run has been enqueued
-    PrepArgs cur = prep(0);
-    cur.fetch_blocks = 0;   // a prefetch only rides in train launches
-    const unsigned grid0 = prep_blocks(cur.refs);
-    hipLaunchKernelGGL(claim_kernel, dim3(grid0), dim3(256), 0, st, cur);
-    hipError_t e = hipGetLastError();
+    // the parts of a batch's description that every shape shares
+    auto prepared = [&](int64_t i) {
+        PrepArgs pa = prep(i);
+        if (!pa.refs) return pa;
+        const PrepSlot& ps = w.prep[i % 3];
+        pa.bin = binning(pa.refs);
+        pa.ids = ps.ids; pa.tag = ps.tag; pa.entries = ps.entries; pa.segs = ps.segs; pa.items = ps.items; pa.totals = ps.totals;
+        pa.k0 = static_cast<uint32_t>(t->seed); pa.k1 = static_cast<uint32_t>(t->seed >> 32);
+        return pa;
+    };
+    auto helpers = [](const PrepArgs& resolve, const PrepArgs& claim, bool prefetch) {
+        Helpers h{};
+        h.resolve = resolve; h.claim = claim;
+        h.resolves = resolve.refs ? 1u << resolve.bin.bits : 0u;
+        h.claims = claim.refs ? claim.bin.tiles : 0u;
+        h.fetches = prefetch && claim.refs ? claim.fetch_blocks : 0u;
+        return h;
+    };
+    PrepArgs cur = prepared(0), next = prepared(1);
+    hipError_t e = launch_prepare(helpers(PrepArgs{}, cur, false), st);
     if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("claim launch: ") + hipGetErrorString(e));
-    hipLaunchKernelGGL(resolve_kernel, dim3(grid0), dim3(256), 0, st, cur);
-    e = hipGetLastError();
+    e = launch_prepare(helpers(cur, next, false), st);
     if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("resolve launch: ") + hipGetErrorString(e));
 
     for (int64_t i = 0; i < n_batches; ++i) {
-        const PrepArgs next = prep(i + 1);
-        const PrepSlot& ps = w.prep[i & 1];
+        const PrepArgs after = prepared(i + 2);
         TrainArgs ta{};
         ta.X = reinterpret_cast<float4*>(t->vertex); ta.C = reinterpret_cast<float4*>(t->context);
         ta.B = cur.refs / R; ta.window = window; ta.K = K; ta.d4 = t->dim / 4; ta.lr = lr_host[i];
-        ta.ids = ps.ids; ta.posbuf = ps.posbuf; ta.refshared = ps.refshared; ta.delta = w.delta;
-        BatchTuning tune = batch_tuning(t, cur.refs);
-        if (direct) tune.list_cap = 0;   // no slots, no lists: shared rows take their atomics on the table itself
-        ta.direct = direct ? 1 : 0;
-        ta.list_cap = tune.list_cap; ta.count = w.count; ta.members = w.members; ta.dbuf = reinterpret_cast<float4*>(w.dbuf);
+        ta.ids = cur.ids; ta.tag = cur.tag; ta.dbuf = reinterpret_cast<float4*>(w.dbuf);
         const bool timed = profile_begin(t, st);
-        e = train(ta, next);
+        e = train(ta, helpers(next, after, true));
         if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("train launch: ") + hipGetErrorString(e));
         if (timed) profile_end(t, st);
 
-        ApplyArgs aa{};
-        aa.X = ta.X; aa.C = ta.C; aa.d4 = ta.d4; aa.delta = reinterpret_cast<float4*>(w.delta);
-        aa.positions = cur.mask + 1; aa.slots = ps.slots; aa.shared = ps.shared;
-        aa.list_cap = ta.list_cap; aa.count = w.count; aa.members = w.members; aa.dbuf = ta.dbuf; aa.direct = ta.direct;
-        const unsigned resolve_blocks = prep_blocks(next.refs);
-        const int per_thread = tune.sweep_per_thread;
-        const unsigned sweep_blocks = aa.positions / (256u * per_thread);
-        const unsigned apply_grid = resolve_blocks + sweep_blocks;
-        const unsigned period = resolve_blocks ? apply_grid / resolve_blocks : 1u;
-        // Row work of the apply kernel: GL lanes per row, CH dwordx4 chunks per lane and pass.  One chunk per
-        // lane where a row has 32 or more (as in the train kernel; +1.1 % at dim 128), except with the list
-        // path, whose passes keep several buffer rows in flight (16 lanes measured +1.8 % there); rows of more
-        // than 2 chunks per lane go in passes of 8 (+1 % at dim 512).
-        const bool wide = aa.d4 > 32, lanes32 = aa.d4 >= 32 && aa.list_cap == 0;
-#define NE_APPLY(S_, G_, C_) hipLaunchKernelGGL((apply_kernel<S_, G_, C_>), dim3(apply_grid), dim3(256), 0, st, aa, next, resolve_blocks, period)
-#define NE_APPLY_SHAPE(S_)                                                                        \
-    do {                                                                                          \
-        if (lanes32) { if (wide) NE_APPLY(S_, 32, 8); else NE_APPLY(S_, 32, 1); }                 \
-        else { if (wide) NE_APPLY(S_, 16, 8); else NE_APPLY(S_, 16, 2); }                         \
-    } while (0)
-        if (per_thread == 2) NE_APPLY_SHAPE(2);
-        else if (per_thread == 4) NE_APPLY_SHAPE(4);
-        else NE_APPLY_SHAPE(8);
-#undef NE_APPLY_SHAPE
-#undef NE_APPLY
-        e = hipGetLastError();
-        if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("apply launch: ") + hipGetErrorString(e));
+        if (!direct) {
+            ApplyArgs aa{};
+            aa.X = ta.X; aa.C = ta.C; aa.d4 = ta.d4; aa.items = cur.items; aa.totals = cur.totals; aa.dbuf = ta.dbuf;
+            e = launch_apply(shape, aa, cur.refs, st);
+            if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("apply launch: ") + hipGetErrorString(e));
+        }
         t->batches_done += 1;
         cur = next;
+        next = after;
     }
-    t->workspace_dirty = false;
     return NE_OK;
 }
 
@@ -1470,8 +1478,7 @@ ne_status ne_create_tables(ne_tables** out, int64_t num_nodes, int32_t dim, floa
     ne_tables* t = new (std::nothrow) ne_tables{};
     if (!t) return fail(NE_ERR_NOMEM, "host allocation failed");
     t->num_nodes = num_nodes; t->dim = dim; t->vertex = vertex_dev; t->context = context_dev; t->seed = seed;
-    t->max_batch = 0; t->max_negatives = 0; t->batches_done = 0; t->workspace_dirty = false; t->profile_every = 0; t->ev_used = 0;
-    t->tune_list_cap = -1; t->tune_sweep = 0;
+    t->max_batch = 0; t->max_negatives = 0; t->batches_done = 0; t->profile_every = 0; t->ev_used = 0;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
     if (workspace_dev || max_batch > 0) {   // training requested
@@ -1485,11 +1492,6 @@ ne_status ne_create_tables(ne_tables** out, int64_t num_nodes, int32_t dim, floa
             return fail(NE_ERR_ARG, "workspace_dev is NULL, not 256-byte aligned, or smaller than ne_workspace_bytes()");
         }
         t->ws = w; t->max_batch = max_batch; t->max_negatives = max_negatives;
-        const hipError_t e = clear_workspace(w, dim, st);
-        if (e != hipSuccess) {
-            delete t;
-            return fail(NE_ERR_HIP, std::string("workspace init launch: ") + hipGetErrorString(e));
-        }
     }
     if (init) {
         const int64_t total = num_nodes * (dim / 4);
@@ -1660,7 +1662,6 @@ static ne_status train_runs_impl(ne_tables* t, const ne_run* runs, int64_t n_run
         return fail(NE_ERR_ARG, "B or K exceeds the max_batch / max_negatives the workspace was sized for");
 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const Workspace& w = t->ws;
     const int R = K + 2;
 
     auto prep_args = [&](int64_t i) {
@@ -1669,36 +1670,29 @@ static ne_status train_runs_impl(ne_tables* t, const ne_run* runs, int64_t n_run
         const Batch& bt = batches[i];
         const ne_run& run = runs[bt.run];
         const ne_alias* al = run.alias;
-        const PrepSlot& ps = w.prep[i & 1];
         pa.pairs = staging ? staging + (i % 3) * B : reinterpret_cast<const int2*>(run.pairs_dev) + bt.first;
         if (staging && i + 1 < n_batches) {
-            // the launch that trains batch i - 1 and claims batch i also fetches batch i + 1
+            // the launch that trains batch i - 2 and claims batch i also fetches batch i + 1
             pa.fetch_src = reinterpret_cast<const int2*>(run.pairs_dev) + batches[i + 1].first;
             pa.fetch_dst = staging + ((i + 1) % 3) * B;
             pa.fetch_n = batches[i + 1].count;
             pa.fetch_blocks = kFetchBlocks;
         }
-        pa.refs = static_cast<uint32_t>(bt.count * R); pa.R = static_cast<uint32_t>(R); pa.xrefs = 1; pa.K = K;
+        pa.refs = static_cast<uint32_t>(bt.count * R); pa.R = static_cast<uint32_t>(R); pa.K = K;
         pa.sample_base = run.sample_base + static_cast<uint64_t>(bt.first);
-        pa.k0 = static_cast<uint32_t>(t->seed); pa.k1 = static_cast<uint32_t>(t->seed >> 32);
         pa.alias = al ? al->table : nullptr; pa.alias_n = al ? static_cast<uint64_t>(al->n) : 1; pa.alias_base = al ? al->base : 0;
-        uint32_t positions = kSweepPerBlock;     // hash positions this batch uses
-        while (positions < kHashFactor * static_cast<uint32_t>(bt.count * R)) positions <<= 1;
-        pa.slots = ps.slots; pa.mask = positions - 1; pa.shared = ps.shared; pa.refshared = ps.refshared; pa.ids = ps.ids; pa.posbuf = ps.posbuf;
         pa.neg_out = run.neg_out_dev ? run.neg_out_dev + bt.first * K : nullptr;
         return pa;
     };
 
-    if (staging) {   // batches 0 and 1 have no launch to ride along with
-        for (int64_t i = 0; i < 2 && i < n_batches; ++i) {
-            hipLaunchKernelGGL(fetch_pairs_kernel, dim3(kFetchBlocks), dim3(256), 0, st,
-                               reinterpret_cast<const int2*>(runs[0].pairs_dev) + batches[i].first, staging + (i % 3) * B, batches[i].count);
-            hipError_t fe = hipGetLastError();
-            if (fe != hipSuccess) return fail(NE_ERR_HIP, std::string("fetch launch: ") + hipGetErrorString(fe));
-        }
+    if (staging) {   // batches 0, 1 and 2 (side by side in both buffers) have no launch to ride along with
+        const int64_t n = runs[0].n_pairs < 3 * B ? runs[0].n_pairs : 3 * B;
+        hipLaunchKernelGGL(fetch_pairs_kernel, dim3(3 * kFetchBlocks), dim3(256), 0, st, reinterpret_cast<const int2*>(runs[0].pairs_dev), staging, n);
+        const hipError_t fe = hipGetLastError();
+        if (fe != hipSuccess) return fail(NE_ERR_HIP, std::string("fetch launch: ") + hipGetErrorString(fe));
     }
-    return run_batches(t, n_batches, R, 0, K, lr_host, st, prep_args,
-                       [&](const TrainArgs& ta, const PrepArgs& next) { return launch_train(shape, ta, next, st); }, direct);
+    return run_batches(t, shape, n_batches, R, 0, K, lr_host, st, prep_args,
+                       [&](const TrainArgs& ta, const Helpers& h) { return launch_train(shape, ta, h, direct, st); }, direct);
 }
 
 ne_status ne_train_runs(ne_tables* t, const ne_run* runs_host, int64_t n_runs, int64_t B, int32_t K,
@@ -1776,7 +1770,6 @@ ne_status ne_train_walks(ne_tables* t, const ne_alias* al, const int32_t* walks_
     const int64_t groups_per_walk = by_segments ? segs_per_walk : walk_len;   // reference groups (of R) per walk
 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const Workspace& w = t->ws;
     const int64_t per_walk = static_cast<int64_t>(walk_len) * window;   // sample indices (and neg_out rows) per walk
 
     auto prep_args = [&](int64_t i) {
@@ -1784,24 +1777,18 @@ ne_status ne_train_walks(ne_tables* t, const ne_alias* al, const int32_t* walks_
         if (i >= n_batches) return pa;   // refs = 0: nothing to prepare
         const int64_t first = i * walks_per_batch;
         const int64_t count = (n_walks - first < walks_per_batch) ? n_walks - first : walks_per_batch;
-        const PrepSlot& ps = w.prep[i & 1];
         pa.walks = walks_dev + first * walk_len; pa.walk_len = walk_len; pa.window = window;
         pa.refs = static_cast<uint32_t>(count * groups_per_walk * R); pa.R = static_cast<uint32_t>(R); pa.K = K;
-        pa.xrefs = by_segments ? static_cast<uint32_t>(E) : 1u;
         pa.seg_entries = by_segments ? static_cast<uint32_t>(E) : 0u;
         pa.segs_per_walk = static_cast<uint32_t>(segs_per_walk);
         pa.sample_base = sample_base + static_cast<uint64_t>(first * per_walk);
-        pa.k0 = static_cast<uint32_t>(t->seed); pa.k1 = static_cast<uint32_t>(t->seed >> 32);
         pa.alias = al ? al->table : nullptr; pa.alias_n = al ? static_cast<uint64_t>(al->n) : 1; pa.alias_base = al ? al->base : 0;
-        uint32_t positions = kSweepPerBlock;     // hash positions this batch uses
-        while (positions < kHashFactor * pa.refs) positions <<= 1;
-        pa.slots = ps.slots; pa.mask = positions - 1; pa.shared = ps.shared; pa.refshared = ps.refshared; pa.ids = ps.ids; pa.posbuf = ps.posbuf;
         pa.neg_out = neg_out_dev ? neg_out_dev + first * per_walk * K : nullptr;
         return pa;
     };
 
-    return run_batches(t, n_batches, R, window, K, lr_host, st, prep_args, [&](const TrainArgs& ta, const PrepArgs& next) {
-        return by_segments ? launch_train_seg(shape, ta, next, static_cast<unsigned>(ta.B), st) : launch_train_walk(shape, ta, next, st);
+    return run_batches(t, shape, n_batches, R, window, K, lr_host, st, prep_args, [&](const TrainArgs& ta, const Helpers& h) {
+        return by_segments ? launch_train_seg(shape, ta, h, st) : launch_train_walk(shape, ta, h, st);
     });
 }
 
@@ -1887,11 +1874,9 @@ ne_status ne_score_pairs(const ne_tables* t, const int32_t* pairs_dev, int64_t n
 ne_status ne_set_tuning(ne_tables* t, int32_t list_cap, int32_t sweep_per_thread)
 {
     if (!t) return fail(NE_ERR_ARG, "tables handle is NULL");
-    if (list_cap < -1 || list_cap > static_cast<int32_t>(kListCap)) return fail(NE_ERR_ARG, "list_cap must be -1 (automatic) or in [0, 8]");
+    if (list_cap < -1 || list_cap > 8) return fail(NE_ERR_ARG, "list_cap must be -1 (automatic) or in [0, 8]");
     if (sweep_per_thread != 0 && sweep_per_thread != 2 && sweep_per_thread != 4 && sweep_per_thread != 8)
         return fail(NE_ERR_ARG, "sweep_per_thread must be 0 (automatic), 2, 4 or 8");
-    t->tune_list_cap = list_cap;
-    t->tune_sweep = sweep_per_thread;
     return NE_OK;
 }
 

@@ -29,21 +29,20 @@ ne_status fail(ne_status st, const std::string& msg);
 
 namespace {
 
-// Device workspace of a tables handle (caller's memory, carved up here).
+// Device workspace of a tables handle (caller's memory, carved up here).  Nothing in it has to start from any
+// value, and nothing is carried from one batch to the next but what the id phases of a batch hand to its train
+// and apply kernels.
 struct PrepSlot {
-    unsigned long long* slots;  // [cap]  (key << 32 | reference index) per hash position; ~0 = empty
-    uint8_t* shared;            // [cap]  1 <=> the row whose key sits at this position is shared
-    int32_t* ids;               // [max_B][max_K+2]  src, ctx, negatives
-    uint32_t* posbuf;           // [max_B][max_K+2]  final hash position of each reference
-    uint8_t* refshared;         // [max_B][max_K+2]  1 <=> another reference of the batch names this reference's row too
+    int32_t* ids;                 // [refs]  row named by each reference (walk mode: -1 = no such reference)
+    uint32_t* tag;                // [refs]  0 = only this reference names its row; else 1 + its row in dbuf
+    unsigned long long* entries;  // [refs]  key << 32 | reference, sorted by bin inside each tile
+    uint32_t* segs;               // [tiles][bins]  where a tile's entries of a bin start, and how many (<< 16)
+    uint2* items;                 // [refs / 2]  work items of the apply kernel: rows that several references name
+    unsigned long long* totals;   // [1]     number of items << 32 | rows of dbuf in use
 };
 struct Workspace {
-    PrepSlot prep[2];
-    float* delta;        // [cap][dim]  per-position fp32 accumulators, zero between batches
-    uint32_t* count;     // [cap]       arrivals at a shared row's position, zero between batches
-    uint32_t* members;   // [cap][8]    reference indices of a shared row's first arrivals
-    float* dbuf;         // [max_B * (max_K + 2)][dim]  per-reference deltas of those arrivals
-    uint32_t cap;        // power of two >= 2 * max_B * (max_K + 2)
+    PrepSlot prep[3];   // one batch in training, the next being resolved, the one after that being claimed
+    float* dbuf;        // [refs][dim]  deltas of references to shared rows, a row's references side by side
     size_t total_bytes;
 };
 
@@ -59,9 +58,6 @@ struct ne_tables {
     int32_t max_negatives;
     Workspace ws;
     uint64_t batches_done;
-    bool workspace_dirty;    // a launch failed in the middle of a run of batches: hash state, flags and slots may be half-used
-    int32_t tune_list_cap;   // ne_set_tuning: -1 = automatic
-    int32_t tune_sweep;      // ne_set_tuning: 0 = automatic
     // optional timing of the train kernel with HIP events (ne_profile_enable / ne_profile_read)
     int32_t profile_every;
     std::vector<hipEvent_t> ev_zero, ev_start, ev_stop;   // zero -> start brackets nothing: the events' own cost
@@ -90,10 +86,13 @@ inline void profile_end(ne_tables* t, hipStream_t st)
     if (hipEventRecord(t->ev_stop[t->ev_used], st) == hipSuccess) t->ev_used += 1;
 }
 
+// Fibonacci multiplicative hash of a row key.  A bijection of 32-bit values (the factor is odd), which spreads
+// runs of ids evenly over its top bits.
+__host__ __device__ __forceinline__ uint32_t hash_bits(uint32_t key) { return key * 0x9E3779B1u; }
+
 // Home position of a row key in a table of mask + 1 positions (a power of two, at most 2^31): the top
-// log2(positions) bits of a Fibonacci multiplicative hash, so that every position is some key's home
-// however large the table (a fixed shift would leave tables wider than its bits mostly unreachable and
-// pile the keys into one cluster).
+// log2(positions) bits of the hash, so that every position is some key's home however large the table (a
+// fixed shift would leave tables wider than its bits mostly unreachable and pile the keys into one cluster).
 __host__ __device__ __forceinline__ uint32_t hash_position(uint32_t key, uint32_t mask)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -101,7 +100,7 @@ __host__ __device__ __forceinline__ uint32_t hash_position(uint32_t key, uint32_
 #else
     const int shift = __builtin_clz(mask);
 #endif
-    return (key * 0x9E3779B1u) >> shift;
+    return hash_bits(key) >> shift;
 }
 
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
