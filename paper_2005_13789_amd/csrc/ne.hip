@@ -8,16 +8,18 @@
 //          tile by tile: draws the negatives (Philox + alias table) and writes the tile's (key,
 //          reference) entries sorted by a hash of the key into bins.  resolve takes one bin per
 //          workgroup: all entries of a row meet in one hash table in LDS.  A row with n > 1 references
-//          gets n consecutive rows of the delta buffer, one per reference (its tag), and ceil(n / 8)
+//          gets n consecutive places in a list, one per reference (its tag), and ceil(n / 8)
 //          work items for the apply kernel.  Nothing goes through atomics in memory but one counter
 //          per bin, and no state has to be cleared between batches.
 //   train  one lane group per pair: gathers x = vertex[src] and the K+1 context rows (dwordx4),
 //          reduces the K+1 dot products with DPP, forms g_j and the deltas.  A row that only this
 //          pair names is rewritten in place from registers (old + delta, one plain store: the row
 //          costs one read and one write).  A shared row is left untouched - other pairs must still
-//          read its pre-batch value - and the delta goes to the reference's row of the delta buffer.
-//   apply  one lane group per work item: sums up to 8 consecutive rows of the delta buffer and adds
-//          them to the table row (with atomics where a row has several items).
+//          read its pre-batch value.  A reference's delta to it is a coefficient times a row: lr g_j
+//          times the pair's source row, which is stored once for all of the pair's references, or one
+//          times a sum that is stored.  The reference's place in the list takes the two.
+//   apply  one lane group per work item: adds up to 8 consecutive entries of the list, coefficient times
+//          row, to the table row (with atomics where a row has several items).
 //
 // This is exactly minibatch-synchronous: no row that a second reference could read is written
 // before the apply phase, and all contributions to a row are summed.  fp32 atomics on gfx950
@@ -702,8 +704,9 @@ struct TrainArgs {
     int32_t d4;
     float lr;
     const int32_t* ids;
-    const uint32_t* tag;  // per reference: 0 = sole reference of its row, else 1 + its row in dbuf
-    float4* dbuf;         // [..][d4] deltas of references to shared rows
+    const uint32_t* tag;  // per reference: 0 = sole reference of its row, else 1 + its place in the list
+    uint2* list;          // (row of buf, coefficient)
+    float4* buf;          // [..][d4]
 };
 
 // Element e = lg + m*G of a row, for m < 4*NCH: the layout in which one atomic instruction of a lane
@@ -719,29 +722,51 @@ __device__ __forceinline__ void to_consecutive(const float4 (&v)[NCH], float (&o
     __builtin_amdgcn_wave_barrier();
 }
 
-// row += delta in place, or the delta to its place in the delta buffer.
+// row += delta in place, or the delta to row `spare` of buf and its place in the list.
 template <int G, int NCH>
-__device__ __forceinline__ void write_row(const TrainArgs& a, float4* row, uint32_t tag, const float4 (&old)[NCH],
+__device__ __forceinline__ void write_row(const TrainArgs& a, float4* row, uint32_t tag, uint32_t spare, const float4 (&old)[NCH],
                                           const float4 (&dv)[NCH], int lg, int d4)
 {
-    float4* out = tag ? a.dbuf + static_cast<int64_t>(tag - 1u) * d4 : row;
+    float4* out = tag ? a.buf + static_cast<int64_t>(spare) * d4 : row;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
         const int ci = lg + i * G;
         if (ci < d4) out[ci] = tag ? dv[i] : make_float4(old[i].x + dv[i].x, old[i].y + dv[i].y, old[i].z + dv[i].z, old[i].w + dv[i].w);
     }
+    if (tag && lg == 0) a.list[tag - 1u] = make_uint2(spare, __float_as_uint(1.0f));
+}
+
+// True for every lane of a lane group if it is for one of them.
+template <int G>
+__device__ __forceinline__ bool group_any(bool v)
+{
+    const unsigned long long all = __ballot(v);
+    return G == 64 ? all != 0ull : ((all >> (threadIdx.x & 63u & ~(G - 1u))) & ((1ull << (G & 63)) - 1ull)) != 0ull;
+}
+
+// The source row of a lane group to row `copy` of buf, where its references to shared rows point.
+template <int G, int NCH>
+__device__ __forceinline__ void write_copy(const TrainArgs& a, uint32_t copy, const float4 (&xr)[NCH], int lg, int d4)
+{
+    float4* out = a.buf + static_cast<int64_t>(copy) * d4;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const int ci = lg + i * G;
+        if (ci < d4) out[ci] = xr[i];
+    }
 }
 
 // K+1 context rows of one pair (rows 0..K; with POS_FIRST row 0 is the positive, every other row a
 // negative), JB at a time: gather, score against x, form g_j, add g_j c_j to dx, and update the row:
-// rewritten in place if only this reference names it, else its delta goes to the delta buffer (DIRECT:
-// to the row with atomics; xt is x in consecutive-dword layout).  Lane j + LANE0 of the group holds
-// reference j's id and tag.
+// rewritten in place if only this reference names it, else lr g_j and `copy`, the row of buf that gets x, go
+// to the reference's place in the list (DIRECT: the delta goes to the row with atomics; xt is x in
+// consecutive-dword layout).  Lane j + LANE0 of the group holds reference j's id and tag; other lanes' tags are 0.
 template <int G, int NCH, int JB, int LANE0, bool POS_FIRST = true, bool DIRECT = false>
 __device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, int d4, const float4 (&xr)[NCH],
                                                      const float (&xt)[4 * NCH], float4 (&dx)[NCH], int32_t id_mine,
-                                                     uint32_t tag_mine, int lg)
+                                                     uint32_t tag_mine, uint32_t copy, int lg)
 {
+    float g_mine = 0.0f;     // lr g_j of lane j + LANE0
     for (int j0 = 0; j0 <= K; j0 += JB) {
         float4 cr[JB][NCH];
         float part[JB];
@@ -783,12 +808,7 @@ __device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, 
                         if (e < d4 * 4) unsafeAtomicAdd(row + e, g * xt[m]);
                     }
                 } else if (tag) {
-                    float4* out = a.dbuf + static_cast<int64_t>(tag - 1u) * d4;
-#pragma unroll
-                    for (int i = 0; i < NCH; ++i) {
-                        const int ci = lg + i * G;
-                        if (ci < d4) out[ci] = make_float4(g * xr[i].x, g * xr[i].y, g * xr[i].z, g * xr[i].w);
-                    }
+                    if (lg == j + LANE0) g_mine = g;
                 } else {
 #pragma unroll
                     for (int i = 0; i < NCH; ++i) {
@@ -799,7 +819,7 @@ __device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, 
             }
         }
     }
-
+    if (!DIRECT && tag_mine) a.list[tag_mine - 1u] = make_uint2(copy, __float_as_uint(g_mine));
 }
 
 constexpr int kTrainThreads = 256;   // threads per block of the train kernels
@@ -841,7 +861,10 @@ __global__ __launch_bounds__(kTrainThreads) void train_kernel(TrainArgs a, Helpe
 #pragma unroll
     for (int i = 0; i < NCH; ++i) dx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 
-    context_rows_of_pair<G, NCH, JB, 1, true, DIRECT>(a, K, d4, xr, xt, dx, id_mine, tag_mine, lg);
+    const uint32_t copy = static_cast<uint32_t>(b), spare = static_cast<uint32_t>(a.B + b);   // rows of buf
+    const uint32_t tag_ctx = lg ? tag_mine : 0u;
+    context_rows_of_pair<G, NCH, JB, 1, true, DIRECT>(a, K, d4, xr, xt, dx, id_mine, tag_ctx, copy, lg);
+    if (!DIRECT && group_any<G>(tag_ctx != 0u)) write_copy<G, NCH>(a, copy, xr, lg, d4);
 
     if (DIRECT && tag0) {
         to_consecutive<G, NCH>(dx, xt, lds_row, lg);
@@ -851,7 +874,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_kernel(TrainArgs a, Helpe
             if (e < d4 * 4) unsafeAtomicAdd(reinterpret_cast<float*>(xrow) + e, xt[m]);
         }
     } else {
-        write_row<G, NCH>(a, xrow, tag0, xr, dx, lg, d4);
+        write_row<G, NCH>(a, xrow, tag0, spare, xr, dx, lg, d4);
     }
 }
 
@@ -892,6 +915,8 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
 #pragma unroll
     for (int i = 0; i < NCH; ++i) dx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 
+    const uint32_t copy = static_cast<uint32_t>(p), spare = static_cast<uint32_t>(a.B + p);   // rows of buf
+    bool copied = false;
     for (int j = 0; j < a.window; ++j) {
         // lane l <= K owns context reference l of pair j
         int32_t id_mine = -1;
@@ -902,9 +927,11 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
             tag_mine = a.tag[ref];
         }
         if (__shfl(id_mine, 0, G) < 0) continue;   // the walk has no pair j here; a pair's references exist together
-        context_rows_of_pair<G, NCH, JB, 0>(a, K, d4, xr, xt, dx, id_mine, tag_mine, lg);
+        context_rows_of_pair<G, NCH, JB, 0>(a, K, d4, xr, xt, dx, id_mine, tag_mine, copy, lg);
+        copied |= group_any<G>(tag_mine != 0u);
     }
-    write_row<G, NCH>(a, xrow, tag0, xr, dx, lg, d4);
+    if (copied) write_copy<G, NCH>(a, copy, xr, lg, d4);
+    write_row<G, NCH>(a, xrow, tag0, spare, xr, dx, lg, d4);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -919,8 +946,8 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
 //            entries of this segment: sums dc in registers.
 // The positive score of a sample is therefore computed twice (both ends need its coefficient); the
 // rows are what costs.  Every row is then written once: in place if no other reference names it,
-// else its delta to the delta buffer (the context rows next to a segment boundary get contributions
-// from both segments and are always of that kind).
+// else its delta goes to the list (the context rows next to a segment boundary get contributions from both
+// segments and are always of that kind).
 // ---------------------------------------------------------------------------------------------
 template <int G, int NCH, int JB>
 __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, Helpers helpers)
@@ -942,6 +969,8 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
     const int64_t R = E + CT + static_cast<int64_t>(E) * W * K;
     if (static_cast<int64_t>(block) >= a.B) return;             // a.B = segments of the batch (uniform over the workgroup)
     const int64_t ref0 = static_cast<int64_t>(block) * R;
+    // rows of buf: [E] deltas of vertex rows, [CT] deltas of context rows, [E] copies of vertex rows for the negatives
+    const uint32_t buf0 = block * static_cast<uint32_t>(E + CT + (K > 0 ? E : 0));
 
     // my entry's vertex row, and the context rows grp and grp + E of the segment's list
     const int32_t src = a.ids[ref0 + grp];
@@ -980,6 +1009,8 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
         float4 dx[NCH];
 #pragma unroll
         for (int i = 0; i < NCH; ++i) dx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        const uint32_t copy = buf0 + static_cast<uint32_t>(E + CT + grp);
+        bool copied = false;
         for (int j = 1; j <= W; ++j) {
             const int row = grp + j - 1;                      // context row of entry (mine + j)
             if (cid[row] < 0) continue;                       // no such sample (uniform over the group)
@@ -1003,10 +1034,12 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
                     id_mine = a.ids[ref];
                     tag_mine = a.tag[ref];
                 }
-                context_rows_of_pair<G, NCH, JB, 0, false>(a, K - 1, d4, xr, xt, dx, id_mine, tag_mine, lg);
+                context_rows_of_pair<G, NCH, JB, 0, false>(a, K - 1, d4, xr, xt, dx, id_mine, tag_mine, copy, lg);
+                copied |= group_any<G>(tag_mine != 0u);
             }
         }
-        write_row<G, NCH>(a, xrow, tag_x, xr, dx, lg, d4);
+        if (copied) write_copy<G, NCH>(a, copy, xr, lg, d4);
+        write_row<G, NCH>(a, xrow, tag_x, buf0 + grp, xr, dx, lg, d4);
     }
 
     // ---- context part: context row `row` is entry p0 + 1 + row; its sources in this segment are the
@@ -1036,14 +1069,20 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
 #pragma unroll
             for (int i = 0; i < NCH; ++i) dc[i] = axpy4(g0, xv[i], dc[i]);
         }
-        write_row<G, NCH>(a, a.C + static_cast<int64_t>(id) * d4, tag_c, cr, dc, lg, d4);
+        write_row<G, NCH>(a, a.C + static_cast<int64_t>(id) * d4, tag_c, buf0 + static_cast<uint32_t>(E + row), cr, dc, lg, d4);
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// apply kernel: one lane group per work item of the batch: up to 8 rows of the delta buffer, which lie
-// side by side, are summed and added to the table row.  A row with more references has several items,
-// which may meet: they use atomics.
+// apply kernel: one lane group per work item of the batch: the sum of up to 8 entries of the list, which lie
+// side by side, is added to the table row; an entry is a coefficient times a row of buf.  A row with more
+// references has several items, which may meet: they use atomics.
+// Bound by the rows it moves (two thirds of the rows have two references) and, in small batches, by its chain
+// of four dependent accesses: item, entries, rows, store.  The rows of buf are few (one or two per pair, however
+// many references share them) and mostly still in the last-level cache; per-reference deltas in memory order
+// instead cost here and in the train kernel 28 + 98 us at 32 M nodes x dim 128 (now 28 + 93), 47 + 94 at 1 M x
+// dim 128 (now 44 + 80) and 151 + 285 at 4 M x dim 512, K = 10 (now 96 + 218).  8 entries at a time against 4: -1 .. -2 % of a batch at dim <= 256,
+// +2 % at dim 512 (registers).
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
@@ -1053,60 +1092,71 @@ struct ApplyArgs {
     int32_t d4;
     const uint2* items;
     const unsigned long long* totals;
-    const float4* dbuf;
+    uint32_t most;        // items there can be
+    const uint2* list;
+    const float4* buf;
 };
 
 template <int GL, int CH>
 __global__ __launch_bounds__(256) void apply_kernel(ApplyArgs a)
 {
     constexpr uint32_t GROUPS = 256 / GL;
-    constexpr uint32_t MB = CH >= static_cast<int>(kItemRefs) ? 1 : kItemRefs / CH;   // delta rows in flight
-    const uint32_t n = static_cast<uint32_t>(*a.totals >> 32);
+    constexpr uint32_t MB = CH == 1 ? kItemRefs : kItemRefs / 2;   // entries whose rows travel together
+    __shared__ float lds[GROUPS][4 * GL * CH];     // layout change for the atomics
     const int lg = threadIdx.x & (GL - 1);
-    for (uint32_t e = blockIdx.x * GROUPS + threadIdx.x / GL; e < n; e += gridDim.x * GROUPS) {
-        const uint2 item = a.items[e];
-        float4* row = ((item.x & 0x80000000u) ? a.C : a.X) + static_cast<int64_t>(item.x & 0x7FFFFFFFu) * a.d4;
-        const float4* src = a.dbuf + static_cast<int64_t>(item.y >> 4) * a.d4;
+    const int grp = threadIdx.x / GL;
+    const int d4 = a.d4;
+    uint32_t e = blockIdx.x * GROUPS + grp;
+    uint2 item = a.items[min(e, a.most - 1u)];     // (in flight together with the count; what lies past it is not used)
+    const uint32_t n = static_cast<uint32_t>(*a.totals >> 32);
+    for (; e < n; e += gridDim.x * GROUPS, item = a.items[min(e, a.most - 1u)]) {
+        float4* row = ((item.x & 0x80000000u) ? a.C : a.X) + static_cast<int64_t>(item.x & 0x7FFFFFFFu) * d4;
+        const uint2* list = a.list + (item.y >> 4);
         const uint32_t refs = (item.y & 7u) + 1u;
-        if (item.y & 8u) {
-            // several items add to this row: consecutive dwords per atomic instruction
-            for (int c = lg; c < a.d4 * 4; c += GL) {
-                const float* s = reinterpret_cast<const float*>(src) + c;
-                float v[kItemRefs], sum = 0.0f;
+        const bool several = item.y & 8u;
+        float4 old[CH], sum[CH];
 #pragma unroll
-                for (uint32_t r = 0; r < kItemRefs; ++r) v[r] = r < refs ? s[static_cast<int64_t>(r) * (a.d4 * 4)] : 0.0f;
-#pragma unroll
-                for (uint32_t r = 0; r < kItemRefs; ++r) sum += v[r];
-                unsafeAtomicAdd(reinterpret_cast<float*>(row) + c, sum);
-            }
-            continue;
+        for (int i = 0; i < CH; ++i) {
+            const int ci = lg + GL * i;
+            old[i] = !several && ci < d4 ? row[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
+            sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        for (int c0 = 0; c0 < a.d4; c0 += GL * CH) {
-            float4 old[CH], sum[CH];
-            bool valid[CH];
+        for (uint32_t r0 = 0; r0 < refs; r0 += MB) {
+            uint2 entry[MB];
+            float4 v[MB][CH];
+#pragma unroll
+            for (uint32_t r = 0; r < MB; ++r) entry[r] = list[min(r0 + r, refs - 1u)];
+#pragma unroll
+            for (uint32_t r = 0; r < MB; ++r) {
+                const float4* src = a.buf + static_cast<int64_t>(entry[r].x) * d4;
+#pragma unroll
+                for (int i = 0; i < CH; ++i) {
+                    const int ci = lg + GL * i;
+                    v[r][i] = r0 + r < refs && ci < d4 ? src[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+            }
+#pragma unroll
+            for (uint32_t r = 0; r < MB; ++r) {
+                const float g = r0 + r < refs ? __uint_as_float(entry[r].y) : 0.0f;
+#pragma unroll
+                for (int i = 0; i < CH; ++i) sum[i] = axpy4(g, v[r][i], sum[i]);
+            }
+        }
+        if (!several) {
 #pragma unroll
             for (int i = 0; i < CH; ++i) {
-                const int ci = c0 + lg + GL * i;
-                valid[i] = ci < a.d4;
-                old[i] = valid[i] ? row[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
-                sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                const int ci = lg + GL * i;
+                if (ci < d4) row[ci] = add4(old[i], sum[i]);
             }
-            for (uint32_t r0 = 0; r0 < refs; r0 += MB) {
-                float4 dv[MB][CH];
+        } else {
+            // several items add to this row: consecutive dwords per atomic instruction
+            float t[4 * CH];
+            to_consecutive<GL, CH>(sum, t, lds[grp], lg);
 #pragma unroll
-                for (uint32_t r = 0; r < MB; ++r)
-#pragma unroll
-                    for (int i = 0; i < CH; ++i)
-                        dv[r][i] = (r0 + r < refs && valid[i]) ? src[static_cast<int64_t>(r0 + r) * a.d4 + c0 + lg + GL * i]
-                                                               : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                for (uint32_t r = 0; r < MB; ++r)
-#pragma unroll
-                    for (int i = 0; i < CH; ++i) sum[i] = add4(sum[i], dv[r][i]);
+            for (int m = 0; m < 4 * CH; ++m) {
+                const int c = lg + m * GL;
+                if (c < d4 * 4) unsafeAtomicAdd(reinterpret_cast<float*>(row) + c, t[m]);
             }
-#pragma unroll
-            for (int i = 0; i < CH; ++i)
-                if (valid[i]) row[c0 + lg + GL * i] = add4(old[i], sum[i]);
         }
     }
 }
@@ -1314,11 +1364,13 @@ hipError_t launch_prepare(const Helpers& h, hipStream_t st)
 // number of items is only known on the device; kApplyBlocks workgroups leave a lane group few of them, so
 // that those with long lists do not finish last (16384 against 2048: -2 .. -6 % of a batch's time).
 constexpr unsigned kApplyBlocks = 16384;
-hipError_t launch_apply(const Shape& s, const ApplyArgs& a, uint32_t refs, hipStream_t st)
+hipError_t launch_apply(const Shape& s, ApplyArgs a, uint32_t refs, hipStream_t st)
 {
+    a.most = refs / 2;                      // every item has two references or more to its row
+    if (a.most == 0) return hipSuccess;
     const unsigned groups = 256u / s.G;
-    const unsigned most = (refs / 2 + groups - 1) / groups;      // items <= refs / 2
-    const unsigned grid = most < kApplyBlocks ? (most ? most : 1u) : kApplyBlocks;
+    const unsigned want = (a.most + groups - 1) / groups;
+    const unsigned grid = want < kApplyBlocks ? want : kApplyBlocks;
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
         hipLaunchKernelGGL((apply_kernel<G_, N_>), dim3(grid), dim3(256), 0, st, a);             \
@@ -1365,7 +1417,9 @@ bool workspace_layout(int32_t dim, int64_t max_B, int32_t max_K, char* base, Wor
         p.items = reinterpret_cast<uint2*>(take(refs / 2 * sizeof(uint2)));
         p.totals = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long)));
     }
-    w->dbuf = reinterpret_cast<float*>(take(refs * static_cast<size_t>(dim) * 4));
+    w->list = reinterpret_cast<uint2*>(take(refs * sizeof(uint2)));
+    // two rows per pair or walk entry, a segment's entries twice and its context rows: never more than references
+    w->buf = reinterpret_cast<float*>(take(refs * static_cast<size_t>(dim) * 4));
     // what a caller is told to bring is never less than two rows and two words per reference, the bound that
     // programs may have sized their buffers by; the difference is not used
     const size_t bound = 2 * refs * (static_cast<size_t>(dim) + 1) * 4;
@@ -1426,7 +1480,7 @@ ne_status run_batches(ne_tables* t, const Shape& shape, int64_t n_batches, int64
         TrainArgs ta{};
         ta.X = reinterpret_cast<float4*>(t->vertex); ta.C = reinterpret_cast<float4*>(t->context);
         ta.B = cur.refs / R; ta.window = window; ta.K = K; ta.d4 = t->dim / 4; ta.lr = lr_host[i];
-        ta.ids = cur.ids; ta.tag = cur.tag; ta.dbuf = reinterpret_cast<float4*>(w.dbuf);
+        ta.ids = cur.ids; ta.tag = cur.tag; ta.list = w.list; ta.buf = reinterpret_cast<float4*>(w.buf);
         const bool timed = profile_begin(t, st);
         e = train(ta, helpers(next, after, true));
         if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("train launch: ") + hipGetErrorString(e));
@@ -1434,7 +1488,7 @@ ne_status run_batches(ne_tables* t, const Shape& shape, int64_t n_batches, int64
 
         if (!direct) {
             ApplyArgs aa{};
-            aa.X = ta.X; aa.C = ta.C; aa.d4 = ta.d4; aa.items = cur.items; aa.totals = cur.totals; aa.dbuf = ta.dbuf;
+            aa.X = ta.X; aa.C = ta.C; aa.d4 = ta.d4; aa.items = cur.items; aa.totals = cur.totals; aa.list = w.list; aa.buf = ta.buf;
             e = launch_apply(shape, aa, cur.refs, st);
             if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("apply launch: ") + hipGetErrorString(e));
         }

@@ -34,15 +34,16 @@ namespace {
 // and apply kernels.
 struct PrepSlot {
     int32_t* ids;                 // [refs]  row named by each reference (walk mode: -1 = no such reference)
-    uint32_t* tag;                // [refs]  0 = only this reference names its row; else 1 + its row in dbuf
+    uint32_t* tag;                // [refs]  0 = only this reference names its row; else 1 + its place in the list
     unsigned long long* entries;  // [refs]  key << 32 | reference, sorted by bin inside each tile
     uint32_t* segs;               // [tiles][bins]  where a tile's entries of a bin start, and how many (<< 16)
     uint2* items;                 // [refs / 2]  work items of the apply kernel: rows that several references name
-    unsigned long long* totals;   // [1]     number of items << 32 | rows of dbuf in use
+    unsigned long long* totals;   // [1]     number of items << 32 | places of the list in use
 };
 struct Workspace {
     PrepSlot prep[3];   // one batch in training, the next being resolved, the one after that being claimed
-    float* dbuf;        // [refs][dim]  deltas of references to shared rows, a row's references side by side
+    uint2* list;        // [refs]  (row of buf, coefficient) of each reference to a shared row, a row's references side by side
+    float* buf;         // [refs][dim]  rows that the list points to: copies of source rows, deltas
     size_t total_bytes;
 };
 
