@@ -1180,66 +1180,81 @@ struct LossArgs {
     double* loss;
 };
 
+// Lane groups go through the pairs with the grid's stride: a workgroup ends with one atomic add to the sum, and
+// adds to one address retire one after the other (one per 8 pairs took 116 us for 65 536 pairs, whatever the
+// rows cost).  The ids of a group's next pair travel while its rows do.
 template <int G, int NCH, int JB>
 __global__ __launch_bounds__(256) void loss_kernel(LossArgs a)
 {
     constexpr int GROUPS = 256 / G;
     const int lg = threadIdx.x & (G - 1);
-    const int64_t b_raw = static_cast<int64_t>(blockIdx.x) * GROUPS + (threadIdx.x / G);
-    const bool active = b_raw < a.B;
-    const int64_t b = active ? b_raw : a.B - 1;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * GROUPS;
     const int K = a.K;
     const int d4 = a.d4;
-    const int2 pr = a.pairs[b];
-
-    // lane lg owns context row j = lg of the pair: j = 0 the positive, j = 1..K negative j-1
-    int32_t id_mine = pr.y;
-    if (lg >= 1 && lg <= K) {
-        id_mine = draw_negative(a.sample_base + static_cast<uint64_t>(b), static_cast<uint32_t>(lg - 1), a.k0, a.k1,
-                                a.alias, a.alias_n, a.alias_base);
-        if (active && a.neg_out) a.neg_out[b * K + (lg - 1)] = id_mine;
-    }
-    float4 xr[NCH];
-    const float4* xrow = a.X + static_cast<int64_t>(pr.x) * d4;
+    // lane lg owns context row j = lg of a pair: j = 0 the positive, j = 1..K negative j-1
+    struct Ids { int32_t src, mine; };
+    auto ids_of = [&](int64_t b) {
+        const int2 pr = a.pairs[b];
+        Ids id{pr.x, pr.y};
+        if (lg >= 1 && lg <= K) {
+            id.mine = draw_negative(a.sample_base + static_cast<uint64_t>(b), static_cast<uint32_t>(lg - 1), a.k0, a.k1,
+                                    a.alias, a.alias_n, a.alias_base);
+            if (a.neg_out) a.neg_out[b * K + (lg - 1)] = id.mine;
+        }
+        return id;
+    };
+    double sum = 0.0;    // of lane lg's context row over the group's pairs
+    int64_t b = static_cast<int64_t>(blockIdx.x) * GROUPS + (threadIdx.x / G);
+    Ids next{0, 0};
+    if (b < a.B) next = ids_of(b);
+    for (; b < a.B; b += stride) {
+        const Ids id = next;
+        float4 xr[NCH];
+        const float4* xrow = a.X + static_cast<int64_t>(id.src) * d4;
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-        const int ci = lg + i * G;
-        xr[i] = (ci < d4) ? xrow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    float term_mine = 0.0f;   // lane j keeps the loss term of row j
-    for (int j0 = 0; j0 <= K; j0 += JB) {
-        float part[JB];
+        for (int i = 0; i < NCH; ++i) {
+            const int ci = lg + i * G;
+            xr[i] = (ci < d4) ? xrow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        float term_mine = 0.0f;   // lane j keeps the loss term of row j
+        for (int j0 = 0; j0 <= K; j0 += JB) {
+            float4 cr[JB][NCH];
 #pragma unroll
-        for (int jj = 0; jj < JB; ++jj) {
-            const int j = j0 + jj;
-            const int32_t id = __shfl(id_mine, j <= K ? j : K, G);
-            const float4* crow = a.C + static_cast<int64_t>(id) * d4;
-            float p = 0.0f;
+            for (int jj = 0; jj < JB; ++jj) {
+                const int j = j0 + jj;
+                const int32_t row = __shfl(id.mine, j <= K ? j : K, G);
+                const float4* crow = a.C + static_cast<int64_t>(row) * d4;
 #pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                const int ci = lg + i * G;
-                if (j <= K && ci < d4) p += dot4(xr[i], crow[ci]);
+                for (int i = 0; i < NCH; ++i) {
+                    const int ci = lg + i * G;
+                    cr[jj][i] = (j <= K && ci < d4) ? crow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
             }
-            part[jj] = p;
-        }
+            if (j0 == 0 && b + stride < a.B) next = ids_of(b + stride);
+            float part[JB];
 #pragma unroll
-        for (int jj = 0; jj < JB; ++jj) part[jj] = group_sum<G>(part[jj]);
+            for (int jj = 0; jj < JB; ++jj) {
+                float p = 0.0f;
 #pragma unroll
-        for (int jj = 0; jj < JB; ++jj) {
-            const int j = j0 + jj;
-            if (j <= K && lg == j) term_mine = softplusf(j == 0 ? -part[jj] : part[jj]);
+                for (int i = 0; i < NCH; ++i) p += dot4(xr[i], cr[jj][i]);
+                part[jj] = p;
+            }
+#pragma unroll
+            for (int jj = 0; jj < JB; ++jj) part[jj] = group_sum<G>(part[jj]);
+#pragma unroll
+            for (int jj = 0; jj < JB; ++jj) {
+                const int j = j0 + jj;
+                if (j <= K && lg == j) term_mine = j == 0 ? -part[jj] : part[jj];
+            }
         }
+        if (lg <= K) sum += static_cast<double>(softplusf(term_mine));
     }
-    float l = (active && lg <= K) ? term_mine : 0.0f;
-    l = group_sum<G>(l);
-    __shared__ double sh[GROUPS];
-    if (lg == 0) sh[threadIdx.x / G] = static_cast<double>(l);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    __shared__ double sh[4];
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int i = 0; i < GROUPS; ++i) t += sh[i];
-        atomicAdd(a.loss, t);
-    }
+    if (threadIdx.x == 0) atomicAdd(a.loss, sh[0] + sh[1] + sh[2] + sh[3]);
 }
 
 __global__ __launch_bounds__(256) void validate_pairs_kernel(const int32_t* __restrict__ ids, int64_t count,
@@ -1384,10 +1399,13 @@ hipError_t launch_apply(const Shape& s, ApplyArgs a, uint32_t refs, hipStream_t 
 hipError_t launch_loss(const Shape& s, const LossArgs& a, hipStream_t st)
 {
     const int groups = 256 / s.G;
-    const unsigned grid = static_cast<unsigned>((a.B + groups - 1) / groups);
+    // workgroups: enough to fill the chip, few enough for their atomic adds to one address to hide (65 536 pairs,
+    // dim 128, K = 5: 512 .. 1024 take 44 - 45 us with the caller's zero-fill, 2048 54, one per 8 pairs 118)
+    const int64_t want = (a.B + groups - 1) / groups;
+    const unsigned grid = static_cast<unsigned>(want < 768 ? want : 768);
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
-        hipLaunchKernelGGL((loss_kernel<G_, N_, 6>), dim3(grid), dim3(256), 0, st, a);           \
+        hipLaunchKernelGGL((loss_kernel<G_, N_, 3>), dim3(grid), dim3(256), 0, st, a);           \
         return hipGetLastError();                                                                \
     }
     NE_FOR_EACH_SHAPE(NE_CASE)

@@ -77,3 +77,4 @@ def test_rows_of_one_bin_beyond_its_table(distinct):
     pairs = np.stack([src, ctx], axis=1).astype(np.int32)
     t = make(V, d, pairs.shape[0], 0, seed)
     step_and_check(t, None, None, None, pairs, 0, seed, 1)
+
