@@ -230,9 +230,9 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(ScoresArgs a)
     constexpr int CB = D / 32;           // 32-column blocks of dX: wavefronts 0 .. CB-1 take one each
     constexpr int NCH = D / 64;          // float4 chunks of a row per lane of a pair's 16 lanes
     constexpr int kXsBytes = kPairTile * XP * 2, kGsBytes = kPairTile * GP * 2, kDxBytes = kPairTile * DP * 4;
-    __shared__ __align__(16) unsigned char lds_raw[(kXsBytes + kGsBytes > kDxBytes) ? kXsBytes + kGsBytes : kDxBytes];
+    __shared__ __align__(16) unsigned char lds_raw[(kXsBytes + 2 * kGsBytes > kDxBytes) ? kXsBytes + 2 * kGsBytes : kDxBytes];
     uint16_t* Xs = reinterpret_cast<uint16_t*>(lds_raw);                    // [32][XP]
-    uint16_t* Gs = reinterpret_cast<uint16_t*>(lds_raw + kXsBytes);         // [32][GP]
+    uint16_t* const Gs2 = reinterpret_cast<uint16_t*>(lds_raw + kXsBytes);  // [2][32][GP], passes alternate
     float* dXs = reinterpret_cast<float*>(lds_raw);                         // [32][DP], after the last pass
     const int tid = threadIdx.x;
     const int l = tid & 63, w = tid >> 6;
@@ -312,7 +312,6 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(ScoresArgs a)
     const int steps_all = a.N / 16;                                // contraction steps of dX over all negatives
     // A fragments of S: row l % 32, contraction indices 16 s + 8 (l / 32) ..; A fragments of dX: the same of G
     const uint16_t* xa = Xs + (l & 31) * XP + 8 * (l >> 5);
-    const uint16_t* ga = Gs + (l & 31) * GP + 8 * (l >> 5);
 
     // The operand fragments come straight from memory (L2: every workgroup streams the same 2 N d bytes), 1 KB per
     // wavefront and step, and each wavefront has only one other on its SIMD to hide their latency: so they are
@@ -325,6 +324,8 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(ScoresArgs a)
         for (int s = 0; s < KS; ++s) bS[s] = src[s * 64];
     }
     for (int n0 = 0; n0 < a.N; n0 += kNegChunk) {
+        uint16_t* const Gs = Gs2 + ((n0 / kNegChunk) & 1) * (kPairTile * GP);
+        const uint16_t* ga = Gs + (l & 31) * GP + 8 * (l >> 5);
         const int nblock = (n0 >> 5) + w;                 // this wavefront's block of 32 negatives (whole blocks: N % 128 == 0)
         const bool s_active = nblock * 32 < a.N;
         const bool x_active = w < CB;                     // this wavefront has a block of 32 columns of dX
@@ -388,8 +389,10 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(ScoresArgs a)
                     acc_dx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(ga + 16 * (8 + s))), as_bf16x8(bT1[s]), acc_dx, 0, 0, 0);
             }
         }
-        lds_barrier();   // G is rewritten by the next pass (and the rows' LDS by the epilogue)
+        // (the next pass writes the other G; the one after it writes this one behind a barrier that every
+        // wavefront reaches with its reads of this pass done)
     }
+    lds_barrier();       // the rows' and G's LDS is rewritten
 
     // ---- epilogue: dX to the pairs' lanes
     if (w < CB) {
@@ -426,8 +429,10 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(ScoresArgs a)
 // dctx kernel: dC = G^T . Xq.  Workgroup tile 128 negatives x TD columns (TD = 64 or 128), one share
 // of the batch (the contraction index) per blockIdx.z.  Both operands are contraction-contiguous in
 // memory (GT [N][Bp], XqT [d][Bp]); 64 contraction steps at a time are staged through LDS so that
-// the four wavefronts share them (operand traffic, not arithmetic, bounds this product), with the
-// next stage travelling into registers meanwhile.  Wavefront w: 64 negatives (w & 1) x TD/2 columns
+// the four wavefronts share them (operand traffic, not arithmetic, bounds this product), two stages
+// alternating, with the next one travelling into registers meanwhile: one barrier per stage, for LDS only
+// (two full barriers and one buffer: a step of 8192 pairs x 1024 negatives at dim 128 42.8 us, now 41.8; three or four
+// stages in flight instead of two gained nothing).  Wavefront w: 64 negatives (w & 1) x TD/2 columns
 // (w >> 1).
 // ---------------------------------------------------------------------------------------------
 struct DctxArgs {
@@ -441,8 +446,8 @@ __global__ __launch_bounds__(256) void dctx_kernel(DctxArgs a)
     constexpr int KP = 64 + 8;        // LDS pitch (bf16)
     constexpr int BT = TD / 64;       // column tiles per wavefront
     constexpr int BPT = TD * 8 / 256; // 16-byte pieces of the column operand per thread
-    __shared__ uint16_t As[128 * KP];
-    __shared__ uint16_t Bs[TD * KP];
+    __shared__ uint16_t As[2][128 * KP];
+    __shared__ uint16_t Bs[2][TD * KP];
     const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
     const int wr = w & 1, wc = w >> 1;
     const int64_t Bp = a.w.Bp;
@@ -457,42 +462,25 @@ __global__ __launch_bounds__(256) void dctx_kernel(DctxArgs a)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[r][t][i] = 0.0f;
 
-    // piece c: row c / 8, 16-byte column c % 8
-    const uint16_t* src_a[4];
-    const uint16_t* src_b[BPT];
-    u32x4 pa[4], pb[BPT];
+    // piece c of a stage: row c / 8, 16-byte column c % 8
+    struct Stage { u32x4 a[4], b[BPT]; };
+    const uint16_t* src_a = a.w.GT + static_cast<int64_t>(n0 + tid / 8) * Bp + kbeg + (tid % 8) * 8;
+    const uint16_t* src_b = a.w.XqT + static_cast<int64_t>(d0 + tid / 8) * Bp + kbeg + (tid % 8) * 8;
+    auto fetch = [&](int k0, Stage& s) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = tid + i * 256;
-        src_a[i] = a.w.GT + static_cast<int64_t>(n0 + c / 8) * Bp + kbeg + (c % 8) * 8;
-        pa[i] = *reinterpret_cast<const u32x4*>(src_a[i]);
-    }
+        for (int i = 0; i < 4; ++i) s.a[i] = *reinterpret_cast<const u32x4*>(src_a + static_cast<int64_t>(32 * i) * Bp + k0);
 #pragma unroll
-    for (int i = 0; i < BPT; ++i) {
-        const int c = tid + i * 256;
-        src_b[i] = a.w.XqT + static_cast<int64_t>(d0 + c / 8) * Bp + kbeg + (c % 8) * 8;
-        pb[i] = *reinterpret_cast<const u32x4*>(src_b[i]);
-    }
-    for (int k0 = 0; k0 < kc; k0 += 64) {
+        for (int i = 0; i < BPT; ++i) s.b[i] = *reinterpret_cast<const u32x4*>(src_b + static_cast<int64_t>(32 * i) * Bp + k0);
+    };
+    auto stage = [&](int buf, const Stage& s) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c = tid + i * 256;
-            *reinterpret_cast<u32x4*>(As + (c / 8) * KP + (c % 8) * 8) = pa[i];
-        }
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(As[buf] + (tid / 8 + 32 * i) * KP + (tid % 8) * 8) = s.a[i];
 #pragma unroll
-        for (int i = 0; i < BPT; ++i) {
-            const int c = tid + i * 256;
-            *reinterpret_cast<u32x4*>(Bs + (c / 8) * KP + (c % 8) * 8) = pb[i];
-        }
-        __syncthreads();
-        if (k0 + 64 < kc) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { src_a[i] += 64; pa[i] = *reinterpret_cast<const u32x4*>(src_a[i]); }
-#pragma unroll
-            for (int i = 0; i < BPT; ++i) { src_b[i] += 64; pb[i] = *reinterpret_cast<const u32x4*>(src_b[i]); }
-        }
-        const uint16_t* ar = As + (wr * 64 + (l & 31)) * KP + (l >> 5) * 8;
-        const uint16_t* br = Bs + (wc * (TD / 2) + (l & 31)) * KP + (l >> 5) * 8;
+        for (int i = 0; i < BPT; ++i) *reinterpret_cast<u32x4*>(Bs[buf] + (tid / 8 + 32 * i) * KP + (tid % 8) * 8) = s.b[i];
+    };
+    auto multiply = [&](int buf) {
+        const uint16_t* ar = As[buf] + (wr * 64 + (l & 31)) * KP + (l >> 5) * 8;
+        const uint16_t* br = Bs[buf] + (wc * (TD / 2) + (l & 31)) * KP + (l >> 5) * 8;
 #pragma unroll
         for (int kk = 0; kk < 64; kk += 16) {
             const bf16x8 a0 = as_bf16x8(*reinterpret_cast<const uint4*>(ar + kk));
@@ -504,7 +492,15 @@ __global__ __launch_bounds__(256) void dctx_kernel(DctxArgs a)
                 acc[1][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, bv, acc[1][t], 0, 0, 0);
             }
         }
-        __syncthreads();
+    };
+    Stage next;
+    fetch(0, next);
+    for (int k0 = 0; k0 < kc; k0 += 64) {
+        const int buf = (k0 >> 6) & 1;
+        stage(buf, next);
+        if (k0 + 64 < kc) fetch(k0 + 64, next);
+        lds_barrier();
+        multiply(buf);     // (the stage after the next overwrites this buffer behind another barrier)
     }
     float* out = a.w.dCp + static_cast<int64_t>(blockIdx.z) * a.N * a.D;
 #pragma unroll
