@@ -351,23 +351,24 @@ __device__ __forceinline__ void claim_seg_refs(const PrepArgs& a, uint32_t first
     }
 }
 
-// Exclusive prefix sum over the 256 threads of a workgroup; *total receives the sum.  part: 4 words of LDS.
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* part, uint32_t* total)
+// Exclusive prefix sum over the 256 threads of a workgroup; *total receives the sum.  part: 4 values in LDS.
+template <class T>
+__device__ __forceinline__ T block_exclusive_scan(T v, T* part, T* total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t inc = v;
+    T inc = v;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t o = __shfl_up(inc, off, 64);
+        const T o = __shfl_up(inc, off, 64);
         if (lane >= off) inc += o;
     }
     __syncthreads();            // part may still be read from an earlier scan
     if (lane == 63) part[wave] = inc;
     __syncthreads();
-    uint32_t before = 0, sum = 0;
+    T before = 0, sum = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        const uint32_t p = part[w];
+        const T p = part[w];
         if (w < wave) before += p;
         sum += p;
     }
@@ -458,9 +459,9 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
 // of 2^k values holds at most 2^k rows and the halving ends.
 constexpr uint32_t kItemRefs = 8;                        // references per work item
 struct ResolveLds {
-    uint32_t part[4];
-    uint32_t distinct, pad;
+    unsigned long long part[4];
     unsigned long long base;
+    uint32_t distinct, pad;
     // then key[slots], and cnt[slots]: references of the row; later its next place in the delta buffer (~0: not shared)
 };
 inline size_t resolve_lds_bytes(const Binning& b) { return sizeof(ResolveLds) + (static_cast<size_t>(8) << b.slot_bits); }
@@ -473,7 +474,8 @@ __device__ __forceinline__ uint2 make_item(uint32_t key, uint32_t begin, uint32_
 
 // A share of a bin's entries: 8 lanes per tile segment, kSegsPerLane segments each, the first 8 entries of
 // every segment in registers.  Fetching a share takes two dependent accesses, whatever its size; 256 tiles
-// are all there are up to 512 bins (with half as many, and so two fetches per pass: +1 .. 2 % of a batch).
+// are all there are up to 512 bins (with half as many, and so two fetches per pass: +1 .. 2 % of a batch; 16
+// lanes per segment: +2 % on batches of 90 000 references).
 constexpr int kSegsPerLane = 8;
 constexpr uint32_t kShareTiles = 32 * kSegsPerLane;      // tile segments per share
 struct BinShare {
@@ -570,19 +572,17 @@ __device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, uns
             continue;
         }
         // places and work items of the shared rows among my slots
-        uint32_t items = 0, rows = 0;
+        unsigned long long mine = 0, all;      // items << 32 | places of the list
         for (uint32_t i = 0; i < per; ++i) {
             const uint32_t n = scnt[tid * per + i];
-            if (n > 1) { items += (n + kItemRefs - 1) / kItemRefs; rows += n; }
+            if (n > 1) mine += (static_cast<unsigned long long>((n + kItemRefs - 1) / kItemRefs) << 32) | n;
         }
-        uint32_t items_all, rows_all;
-        uint32_t item = block_exclusive_scan(items, s.part, &items_all);
-        uint32_t row = block_exclusive_scan(rows, s.part, &rows_all);
-        if (rows_all) {                         // (uniform)
-            if (tid == 0) s.base = atomicAdd(a.totals, (static_cast<unsigned long long>(items_all) << 32) | rows_all);
+        unsigned long long at = block_exclusive_scan(mine, s.part, &all);
+        if (all) {                              // (uniform)
+            if (tid == 0) s.base = atomicAdd(a.totals, all);
             __syncthreads();
-            item += static_cast<uint32_t>(s.base >> 32);
-            row += static_cast<uint32_t>(s.base);
+            at += s.base;
+            uint32_t item = static_cast<uint32_t>(at >> 32), row = static_cast<uint32_t>(at);
             for (uint32_t i = 0; i < per; ++i) {
                 const uint32_t p = tid * per + i, n = scnt[p], key = skey[p];
                 scnt[p] = n > 1 ? row : kNoKey;
@@ -917,14 +917,20 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
 
     const uint32_t copy = static_cast<uint32_t>(p), spare = static_cast<uint32_t>(a.B + p);   // rows of buf
     bool copied = false;
+    // lane l <= K owns context reference l of pair j; the next pair's travel while this one's rows do
+    int32_t id_next = -1;
+    uint32_t tag_next = 0;
+    if (lg <= K) {
+        id_next = a.ids[ref0 + 1 + lg];
+        tag_next = a.tag[ref0 + 1 + lg];
+    }
     for (int j = 0; j < a.window; ++j) {
-        // lane l <= K owns context reference l of pair j
-        int32_t id_mine = -1;
-        uint32_t tag_mine = 0;
-        const int64_t ref = ref0 + 1 + static_cast<int64_t>(j) * (K + 1) + lg;
-        if (lg <= K) {
-            id_mine = a.ids[ref];
-            tag_mine = a.tag[ref];
+        const int32_t id_mine = id_next;
+        const uint32_t tag_mine = tag_next;
+        if (lg <= K && j + 1 < a.window) {
+            const int64_t ref = ref0 + 1 + static_cast<int64_t>(j + 1) * (K + 1) + lg;
+            id_next = a.ids[ref];
+            tag_next = a.tag[ref];
         }
         if (__shfl(id_mine, 0, G) < 0) continue;   // the walk has no pair j here; a pair's references exist together
         context_rows_of_pair<G, NCH, JB, 0>(a, K, d4, xr, xt, dx, id_mine, tag_mine, copy, lg);
@@ -1011,7 +1017,21 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
         for (int i = 0; i < NCH; ++i) dx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         const uint32_t copy = buf0 + static_cast<uint32_t>(E + CT + grp);
         bool copied = false;
+        // lane k < K owns negative k of a sample; the next sample's travel while this one's rows do
+        const int64_t ref_neg = ref0 + E + CT + static_cast<int64_t>(grp) * W * K + lg;
+        int32_t id_next = -1;
+        uint32_t tag_next = 0;
+        if (lg < K) {
+            id_next = a.ids[ref_neg];
+            tag_next = a.tag[ref_neg];
+        }
         for (int j = 1; j <= W; ++j) {
+            const int32_t id_mine = id_next;
+            const uint32_t tag_mine = tag_next;
+            if (lg < K && j < W) {
+                id_next = a.ids[ref_neg + static_cast<int64_t>(j) * K];
+                tag_next = a.tag[ref_neg + static_cast<int64_t>(j) * K];
+            }
             const int row = grp + j - 1;                      // context row of entry (mine + j)
             if (cid[row] < 0) continue;                       // no such sample (uniform over the group)
             float4 cr[NCH];
@@ -1026,14 +1046,6 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
 #pragma unroll
             for (int i = 0; i < NCH; ++i) dx[i] = axpy4(g0, cr[i], dx[i]);
             if (K > 0) {
-                // lane k < K owns negative k of this sample
-                int32_t id_mine = -1;
-                uint32_t tag_mine = 0;
-                const int64_t ref = ref0 + E + CT + (static_cast<int64_t>(grp) * W + (j - 1)) * K + lg;
-                if (lg < K) {
-                    id_mine = a.ids[ref];
-                    tag_mine = a.tag[ref];
-                }
                 context_rows_of_pair<G, NCH, JB, 0, false>(a, K - 1, d4, xr, xt, dx, id_mine, tag_mine, copy, lg);
                 copied |= group_any<G>(tag_mine != 0u);
             }
@@ -1320,11 +1332,14 @@ hipError_t launch_train(const Shape& s, const TrainArgs& a, const Helpers& h, bo
 {
     const int groups = kTrainThreads / s.G;
     const TrainGrid g = train_grid(h, (a.B + groups - 1) / groups, direct ? static_cast<size_t>(kTrainThreads) * s.NCH * sizeof(float4) : 0);
-    // context rows gathered together per lane group: 2, as 3 and more; one costs 1 - 2 % (dim 128)
+    // context rows gathered together per lane group: 6 where they come out nearly even (K = 5: 1.7 % ahead of 2 on
+    // 32 M nodes, dim 128), else 3 (K = 7: 6 would be 2 % behind); the per-sample mode's atomics leave 2 ahead by 1 - 2 %
+    const bool six = (a.K + 1) % 6 == 0 || (a.K + 1) % 6 >= 4;
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
         if (direct) hipLaunchKernelGGL((train_kernel<G_, N_, 2, true>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
-        else hipLaunchKernelGGL((train_kernel<G_, N_, 2, false>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
+        else if (six) hipLaunchKernelGGL((train_kernel<G_, N_, 6, false>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
+        else hipLaunchKernelGGL((train_kernel<G_, N_, 3, false>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
         return hipGetLastError();                                                                \
     }
     NE_FOR_EACH_SHAPE(NE_CASE)
