@@ -791,12 +791,20 @@ __device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, 
         }
 #pragma unroll
         for (int jj = 0; jj < JB; ++jj) part[jj] = group_sum<G>(part[jj]);
+        // every lane has every score: the lane that owns a reference forms its g_j, one exponential for all JB rows
+        // (one per row in every lane: up to 10 % slower where a walk entry has many rows, 1 % on pairs)
+        float score = 0.0f;
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj)
+            if (lg == j0 + jj + LANE0) score = part[jj];
+        const float sg = sigmoidf(score);
+        const float g_own = a.lr * ((POS_FIRST && lg == LANE0) ? 1.0f - sg : -sg);
+        if (lg >= j0 + LANE0 && lg < j0 + LANE0 + JB) g_mine = g_own;
 #pragma unroll
         for (int jj = 0; jj < JB; ++jj) {
             const int j = j0 + jj;
             if (j <= K) {
-                const float sg = sigmoidf(part[jj]);
-                const float g = a.lr * ((POS_FIRST && j == 0) ? 1.0f - sg : -sg);
+                const float g = __shfl(g_own, j + LANE0, G);
                 const uint32_t tag = __shfl(tag_mine, j + LANE0, G);
 #pragma unroll
                 for (int i = 0; i < NCH; ++i) dx[i] = axpy4(g, cr[jj][i], dx[i]);
@@ -807,9 +815,7 @@ __device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, 
                         const int e = lg + m * G;
                         if (e < d4 * 4) unsafeAtomicAdd(row + e, g * xt[m]);
                     }
-                } else if (tag) {
-                    if (lg == j + LANE0) g_mine = g;
-                } else {
+                } else if (!tag) {
 #pragma unroll
                     for (int i = 0; i < NCH; ++i) {
                         const int ci = lg + i * G;
@@ -881,7 +887,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_kernel(TrainArgs a, Helpe
 // ---------------------------------------------------------------------------------------------
 // train kernel of the walk mode: one lane group per walk position.  The source row is gathered once
 // and stays in registers for the position's `window` pairs; its delta is summed over all of them
-// and written once.  Each pair's K+1 context rows are handled exactly as in the pair mode.
+// and written once.  The pairs' context rows are handled as in the pair mode, as one list.
 // ---------------------------------------------------------------------------------------------
 template <int G, int NCH, int JB>
 __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, Helpers helpers)
@@ -909,31 +915,81 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
         const int ci = lg + i * G;
         xr[i] = (ci < d4) ? xrow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    const float xt[4 * NCH] = {};
-
     float4 dx[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) dx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 
     const uint32_t copy = static_cast<uint32_t>(p), spare = static_cast<uint32_t>(a.B + p);   // rows of buf
     bool copied = false;
-    // lane l <= K owns context reference l of pair j; the next pair's travel while this one's rows do
-    int32_t id_next = -1;
-    uint32_t tag_next = 0;
-    if (lg <= K) {
-        id_next = a.ids[ref0 + 1 + lg];
-        tag_next = a.tag[ref0 + 1 + lg];
-    }
-    for (int j = 0; j < a.window; ++j) {
+    // the context references of all pairs, JB at a time; lane l < JB owns reference j0 + l, and the next JB ids travel
+    // while these rows do.  (A pair that the walk does not have: its references have id -1.)
+    const int n = a.window * (K + 1);
+    auto fetch = [&](int j, int32_t& id, uint32_t& tag) {
+        id = -1;
+        tag = 0u;
+        if (lg < JB && j + lg < n) {
+            id = a.ids[ref0 + 1 + j + lg];
+            tag = a.tag[ref0 + 1 + j + lg];
+            if (id < 0) tag = 0u;
+        }
+    };
+    int32_t id_next;
+    uint32_t tag_next;
+    fetch(0, id_next, tag_next);
+    int phase = 0;                // j0 mod K + 1: reference 0 of a pair is its positive
+    for (int j0 = 0; j0 < n; j0 += JB) {
         const int32_t id_mine = id_next;
         const uint32_t tag_mine = tag_next;
-        if (lg <= K && j + 1 < a.window) {
-            const int64_t ref = ref0 + 1 + static_cast<int64_t>(j + 1) * (K + 1) + lg;
-            id_next = a.ids[ref];
-            tag_next = a.tag[ref];
+        float4 cr[JB][NCH];
+        int32_t id[JB];
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj) {
+            id[jj] = __shfl(id_mine, jj, G);
+            const float4* crow = a.C + static_cast<int64_t>(id[jj]) * d4;
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                const int ci = lg + i * G;
+                cr[jj][i] = (id[jj] >= 0 && ci < d4) ? crow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
         }
-        if (__shfl(id_mine, 0, G) < 0) continue;   // the walk has no pair j here; a pair's references exist together
-        context_rows_of_pair<G, NCH, JB, 0>(a, K, d4, xr, xt, dx, id_mine, tag_mine, copy, lg);
+        fetch(j0 + JB, id_next, tag_next);
+        float part[JB];
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj) {
+            float s = 0.0f;
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) s += dot4(xr[i], cr[jj][i]);
+            part[jj] = s;
+        }
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj) part[jj] = group_sum<G>(part[jj]);
+        // the lane that owns a reference forms its g_j
+        float score = 0.0f;
+        bool positive = false;
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj) {
+            if (lg == jj) { score = part[jj]; positive = phase == 0; }
+            phase = phase == K ? 0 : phase + 1;
+        }
+        const float sg = sigmoidf(score);
+        const float g_mine = a.lr * (positive ? 1.0f - sg : -sg);
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj) {
+            if (id[jj] >= 0) {
+                const float g = __shfl(g_mine, jj, G);
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) dx[i] = axpy4(g, cr[jj][i], dx[i]);
+                if (__shfl(tag_mine, jj, G) == 0u) {
+                    float4* crow = a.C + static_cast<int64_t>(id[jj]) * d4;
+#pragma unroll
+                    for (int i = 0; i < NCH; ++i) {
+                        const int ci = lg + i * G;
+                        if (ci < d4) crow[ci] = axpy4(g, xr[i], cr[jj][i]);
+                    }
+                }
+            }
+        }
+        if (tag_mine) a.list[tag_mine - 1u] = make_uint2(copy, __float_as_uint(g_mine));
         copied |= group_any<G>(tag_mine != 0u);
     }
     if (copied) write_copy<G, NCH>(a, copy, xr, lg, d4);
@@ -1351,9 +1407,15 @@ hipError_t launch_train_walk(const Shape& s, const TrainArgs& a, const Helpers& 
 {
     const int groups = kTrainThreads / s.G;
     const TrainGrid g = train_grid(h, (a.B + groups - 1) / groups, 0);
+    // context rows gathered together per lane group: 6; a batch of at most one workgroup per compute unit is bound by
+    // a group's chain of round trips, and takes up to 16 (880 entries, dim 64: 16 rows 2.5 % ahead; 6400 entries,
+    // dim 64: 2.7 % behind, from registers)
+    const bool wide = (a.B + groups - 1) / groups <= 256;
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
-        hipLaunchKernelGGL((train_walk_kernel<G_, N_, 6>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
+        constexpr int kWide = N_ > 1 ? 6 : G_ < 16 ? G_ : 16;                                    \
+        if (wide) hipLaunchKernelGGL((train_walk_kernel<G_, N_, kWide>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
+        else hipLaunchKernelGGL((train_walk_kernel<G_, N_, 6>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
         return hipGetLastError();                                                                \
     }
     NE_FOR_EACH_SHAPE(NE_CASE)
