@@ -84,9 +84,10 @@ __global__ __launch_bounds__(256) void init_tables_kernel(float4* __restrict__ X
 // that emptied the table again).  Here an entry is written once into a tile-local run of its bin and
 // read once from there, runs of a few entries are one transaction, and everything that needs an
 // atomic happens in LDS.  Bound by the latency of four dependent accesses per workgroup (segment words,
-// entries, the counter, nothing after it); riding in the train launch both phases together add 22 us to
-// its 76 us (32 M nodes, dim 128, 65 536 pairs), of which the random reads of the alias table are about half.
-// 65 536 pairs, K = 5: 1 M nodes 175 -> 140 us a batch, 32 M nodes 144 -> 126 us; 4096 pairs in one call 40 -> 33 us.
+// entries, the counter, nothing after it); riding in the train launch both phases together add 11 - 16 us to
+// its 77 us (32 M nodes, dim 128, 65 536 pairs), of which the random reads of the alias table are about half.
+// A batch of 65 536 pairs, K = 5, before and with this detection and the lists below: 1 M nodes 164 - 175 -> 119 us,
+// 32 M nodes 144 -> 122 us; 4096 pairs in one call 41 -> 29 us.
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
 // How the references of a batch are binned.
@@ -1148,8 +1149,8 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
 // Bound by the rows it moves (two thirds of the rows have two references) and, in small batches, by its chain
 // of four dependent accesses: item, entries, rows, store.  The rows of buf are few (one or two per pair, however
 // many references share them) and mostly still in the last-level cache; per-reference deltas in memory order
-// instead cost here and in the train kernel 28 + 98 us at 32 M nodes x dim 128 (now 28 + 93), 47 + 94 at 1 M x
-// dim 128 (now 44 + 80) and 151 + 285 at 4 M x dim 512, K = 10 (now 96 + 218).  8 entries at a time against 4: -1 .. -2 % of a batch at dim <= 256,
+// instead cost here and in the train kernel 28 + 98 us at 32 M nodes x dim 128 (now 28 + 91), 47 + 94 at 1 M x
+// dim 128 (now 43 + 76) and 151 + 285 at 4 M x dim 512, K = 10 (now 96 + 218).  8 entries at a time against 4: -1 .. -2 % of a batch at dim <= 256,
 // +2 % at dim 512 (registers).
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
