@@ -63,7 +63,9 @@ size_t ne_workspace_bytes(int32_t dim, int64_t max_batch, int32_t max_negatives)
  *   seed keys every random draw made through this handle.
  *   workspace_dev : device scratch for ne_train_batch, 256-byte aligned, at least
  *                   ne_workspace_bytes(dim, max_batch, max_negatives) bytes, caller-owned, used only
- *                   through this handle until the handle is destroyed; it needs no initialisation.  Pass NULL with max_batch = 0 for a handle that is only evaluated.
+ *                   through this handle until the handle is destroyed; the part of it that has to
+ *                   start from zero is cleared on the stream here.  Pass NULL with max_batch = 0 for a
+ *                   handle that is only evaluated.
  *   1 <= max_batch <= NE_MAX_BATCH, 0 <= max_negatives <= NE_MAX_NEGATIVES when training.
  * *out receives a handle to free with ne_destroy_tables.  Errors: NE_ERR_ARG, NE_ERR_NOMEM, NE_ERR_HIP.
  */
@@ -101,14 +103,13 @@ ne_status ne_build_neg_alias(ne_alias** out, const uint32_t* degree_host, int64_
  *   s_j = <x, c_j>,  g_0 = 1 - sigmoid(s_0),  g_k = -sigmoid(s_k),
  *   vertex[src] += lr * sum_j g_j c_j,   context[id_j] += lr * g_j x,
  * contributions to the same row summed (in fp32; the order of the sum is not fixed).
- * Accuracy: a row that one reference of the batch names is updated with one rounding per element.  A row
- * that n references name has their n deltas added in fp32, eight at a time and those sums one after the
- * other, so its update carries an accumulation error of up to about n / 8 * 2^-24 of the summed magnitudes:
- * typically sqrt(n / 8) * 2^-24, close to the bound when many of the contributions are identical (the same
- * source row against the same context row many times).  Up to n of about 13 000 that is inside a relative
- * error of 1e-4 per row.
- * Calls on one handle must be ordered by the stream and must not overlap: they use the handle's
- * workspace.  Errors: NE_ERR_ARG, NE_ERR_STATE, NE_ERR_HIP.  After NE_ERR_HIP from a training call (a kernel
+ * Accuracy: every row is rounded once per batch, when the sum of its deltas is added to it.  The deltas of a
+ * row that n references name are summed in fp32 before that, eight at a time, 32 or more at a time, and those
+ * sums one after the other: an accumulation error of up to about (n / 32 + 40) * 2^-24 of the deltas' summed
+ * magnitudes, which is approached when many of them are identical (the same source row against the same
+ * context row many times).
+ * Calls on one handle must be ordered by the stream and must not overlap: they use the handle's workspace,
+ * and every call leaves its accumulators at zero for the next.  Errors: NE_ERR_ARG, NE_ERR_STATE, NE_ERR_HIP.  After NE_ERR_HIP from a training call (a kernel
  * launch failed part-way through its batches) the handle stays usable; the tables may hold the batches
  * that were enqueued before the failure and part of the failing one.
  */

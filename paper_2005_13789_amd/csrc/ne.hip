@@ -9,8 +9,8 @@
 //          reference) entries sorted by a hash of the key into bins.  resolve takes one bin per
 //          workgroup: all entries of a row meet in one hash table in LDS.  A row with n > 1 references
 //          gets n consecutive places in a list, one per reference (its tag), and ceil(n / 8)
-//          work items for the apply kernel.  Nothing goes through atomics in memory but one counter
-//          per bin, and no state has to be cleared between batches.
+//          work items for the apply kernel.  Nothing goes through atomics in memory but an add or two
+//          per bin to the batch's totals, and no state has to be cleared between batches.
 //   train  one lane group per pair: gathers x = vertex[src] and the K+1 context rows (dwordx4),
 //          reduces the K+1 dot products with DPP, forms g_j and the deltas.  A row that only this
 //          pair names is rewritten in place from registers (old + delta, one plain store: the row
@@ -18,13 +18,15 @@
 //          read its pre-batch value.  A reference's delta to it is a coefficient times a row: lr g_j
 //          times the pair's source row, which is stored once for all of the pair's references, or one
 //          times a sum that is stored.  The reference's place in the list takes the two.
-//   apply  one lane group per work item: adds up to 8 consecutive entries of the list, coefficient times
-//          row, to the table row (with atomics where a row has several items).
+//   apply  one lane group per work item: sums up to 8 consecutive entries of the list, coefficient times
+//          row, and adds the sum to the table row.  A row with several items: their sums are summed in LDS
+//          and, where several workgroups hold them, in a row of zeros with atomics; who arrives last
+//          adds that to the table row.
 //
 // This is exactly minibatch-synchronous: no row that a second reference could read is written
 // before the apply phase, and all contributions to a row are summed.  fp32 atomics on gfx950
 // retire one dword per L2 channel clock, far below the rate of plain row stores, which is why only
-// rows with more than 8 references see any, one per element and 8 references.
+// rows whose references several workgroups of the apply kernel hold see any, one per element and workgroup.
 //
 // claim and resolve never touch the tables, so for a run of batches (ne_train_block) they ride
 // along in the train kernels of the batches before: kernel A = train(t) + resolve(t+1) + claim(t+2),
@@ -141,6 +143,7 @@ struct PrepArgs {
     int32_t* ids;
     uint32_t* tag;
     uint2* items;
+    uint4* hub_items;
     unsigned long long* totals;
     unsigned long long* entries;
     uint32_t* segs;
@@ -391,7 +394,7 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
     const unsigned tid = threadIdx.x;
     const uint32_t bits = a.bin.bits, bins = 1u << bits;
     uint32_t* part = hist + bins;
-    if (tile == 0 && tid == 0) *a.totals = 0ull;      // resolve, one launch later, counts from zero
+    if (tile == 0 && tid < 2) a.totals[tid] = 0ull;   // resolve, one launch later, counts from zero
     for (uint32_t i = tid; i < bins; i += 256) hist[i] = 0u;
     __syncthreads();
     const uint32_t first = tile * a.bin.tile;
@@ -462,16 +465,20 @@ constexpr uint32_t kItemRefs = 8;                        // references per work 
 struct ResolveLds {
     unsigned long long part[4];
     unsigned long long base;
-    uint32_t distinct, pad;
-    // then key[slots], and cnt[slots]: references of the row; later its next place in the delta buffer (~0: not shared)
+    uint32_t distinct;
+    uint32_t hub_items;       // of the bin's rows; later the number of the next one
+    // then key[slots], and cnt[slots]: references of the row; later its next place in the list (~0: not shared)
 };
 inline size_t resolve_lds_bytes(const Binning& b) { return sizeof(ResolveLds) + (static_cast<size_t>(8) << b.slot_bits); }
 
-// work item: x = key, y = first row in the delta buffer << 4 | (row has several items) << 3 | rows - 1
-__device__ __forceinline__ uint2 make_item(uint32_t key, uint32_t begin, uint32_t several, uint32_t n)
-{
-    return make_uint2(key, (begin << 4) | (several << 3) | (n - 1));
-}
+// Work item of a row with up to kItemRefs places in the list: x = key, y = first place << 3 | places - 1.  A row with
+// more (a hub) has several items with consecutive numbers in a list of their own: x, y as above, z = how many the row
+// has, w = which of them this is.
+__device__ __forceinline__ uint32_t item_places(uint32_t first, uint32_t n) { return (first << 3) | (n - 1u); }
+
+// Accumulator of a hub: the number of its first place, divided by kItemRefs and rounded up, which is no other hub's
+// because each has more than kItemRefs places.
+__device__ __forceinline__ uint32_t hub_accumulator(uint32_t first) { return (first + kItemRefs - 1u) / kItemRefs; }
 
 // A share of a bin's entries: 8 lanes per tile segment, kSegsPerLane segments each, the first 8 entries of
 // every segment in registers.  Fetching a share takes two dependent accesses, whatever its size; 256 tiles
@@ -543,7 +550,7 @@ __device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, uns
     };
     for (;;) {
         for (uint32_t i = tid; i < slots; i += 256) { skey[i] = kNoKey; scnt[i] = 0u; }
-        if (tid == 0) s.distinct = 0u;
+        if (tid == 0) { s.distinct = 0u; s.hub_items = 0u; }
         __syncthreads();
         auto home = [&](uint32_t key, uint32_t* pos) {
             const uint32_t x = (hash_bits(key) << a.bin.bits) - lo;
@@ -576,22 +583,30 @@ __device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, uns
         unsigned long long mine = 0, all;      // items << 32 | places of the list
         for (uint32_t i = 0; i < per; ++i) {
             const uint32_t n = scnt[tid * per + i];
-            if (n > 1) mine += (static_cast<unsigned long long>((n + kItemRefs - 1) / kItemRefs) << 32) | n;
+            if (n > kItemRefs) { atomicAdd(&s.hub_items, (n + kItemRefs - 1) / kItemRefs); mine += n; }
+            else if (n > 1) mine += (1ull << 32) | n;
         }
         unsigned long long at = block_exclusive_scan(mine, s.part, &all);
         if (all) {                              // (uniform)
-            if (tid == 0) s.base = atomicAdd(a.totals, all);
+            if (tid == 0) {
+                s.base = atomicAdd(a.totals, all);
+                if (s.hub_items) s.hub_items = static_cast<uint32_t>(atomicAdd(a.totals + 1, static_cast<unsigned long long>(s.hub_items)));
+            }
             __syncthreads();
             at += s.base;
             uint32_t item = static_cast<uint32_t>(at >> 32), row = static_cast<uint32_t>(at);
             for (uint32_t i = 0; i < per; ++i) {
                 const uint32_t p = tid * per + i, n = scnt[p], key = skey[p];
                 scnt[p] = n > 1 ? row : kNoKey;
-                if (n > 1) {
-                    for (uint32_t q = 0; q < n; q += kItemRefs)
-                        a.items[item++] = make_item(key, row + q, n > kItemRefs ? 1u : 0u, min(kItemRefs, n - q));
-                    row += n;
+                if (n > kItemRefs) {
+                    const uint32_t m = (n + kItemRefs - 1) / kItemRefs;
+                    uint4* hub = a.hub_items + atomicAdd(&s.hub_items, m);
+                    for (uint32_t q = 0; q < m; ++q)
+                        hub[q] = make_uint4(key, item_places(row + q * kItemRefs, min(kItemRefs, n - q * kItemRefs)), m, q);
+                } else if (n > 1) {
+                    a.items[item++] = make_uint2(key, item_places(row, n));
                 }
+                if (n > 1) row += n;
             }
             __syncthreads();
             for_bin_entries([&](uint32_t key, uint32_t ref) {
@@ -1144,8 +1159,11 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
 
 // ---------------------------------------------------------------------------------------------
 // apply kernel: one lane group per work item of the batch: the sum of up to 8 entries of the list, which lie
-// side by side, is added to the table row; an entry is a coefficient times a row of buf.  A row with more
-// references has several items, which may meet: they use atomics.
+// side by side, is added to the table row; an entry is a coefficient times a row of buf.
+// Hubs, rows with more references, are summed before they are added: the row is rounded once per batch however often the
+// batch names it, and eight deltas that are together below the row's last place are not lost.  Their items go to
+// workgroups of their own, which add up neighbouring items of a row in LDS; what several workgroups hold of a row meets
+// in an accumulator that starts from zero, and who arrives last adds it to the table row and leaves it zero again.
 // Bound by the rows it moves (two thirds of the rows have two references) and, in small batches, by its chain
 // of four dependent accesses: item, entries, rows, store.  The rows of buf are few (one or two per pair, however
 // many references share them) and mostly still in the last-level cache; per-reference deltas in memory order
@@ -1160,72 +1178,150 @@ struct ApplyArgs {
     float4* C;
     int32_t d4;
     const uint2* items;
+    const uint4* hub_items;
     const unsigned long long* totals;
     uint32_t most;        // items there can be
+    unsigned hub_blocks;  // workgroups, the first of the launch, that take the hubs' items
     const uint2* list;
     const float4* buf;
+    float* acc;           // accumulators, all zero
+    uint32_t* arrived;    // items whose sums have been added to each of them, all zero
 };
+
+// The entries of a work item, summed (item_places: y).
+template <int GL, int CH>
+__device__ __forceinline__ void sum_item(const ApplyArgs& a, uint32_t y, int lg, float4 (&sum)[CH])
+{
+    constexpr uint32_t MB = CH == 1 ? kItemRefs : kItemRefs / 2;   // entries whose rows travel together
+    const uint2* list = a.list + (y >> 3);
+    const uint32_t refs = (y & 7u) + 1u;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (uint32_t r0 = 0; r0 < refs; r0 += MB) {
+        uint2 entry[MB];
+        float4 v[MB][CH];
+#pragma unroll
+        for (uint32_t r = 0; r < MB; ++r) entry[r] = list[min(r0 + r, refs - 1u)];
+#pragma unroll
+        for (uint32_t r = 0; r < MB; ++r) {
+            const float4* src = a.buf + static_cast<int64_t>(entry[r].x) * a.d4;
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                const int ci = lg + GL * i;
+                v[r][i] = r0 + r < refs && ci < a.d4 ? src[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < MB; ++r) {
+            const float g = r0 + r < refs ? __uint_as_float(entry[r].y) : 0.0f;
+#pragma unroll
+            for (int i = 0; i < CH; ++i) sum[i] = axpy4(g, v[r][i], sum[i]);
+        }
+    }
+}
+
+__device__ __forceinline__ float4* row_of_key(const ApplyArgs& a, uint32_t key)
+{
+    return ((key & 0x80000000u) ? a.C : a.X) + static_cast<int64_t>(key & 0x7FFFFFFFu) * a.d4;
+}
+
+// Items of hubs, one lane group each, workgroup by workgroup.  All 256 threads call this together.
+template <int GL, int CH>
+__device__ __forceinline__ void apply_hubs(const ApplyArgs& a, float4 (&lds)[256 / GL][GL * CH])
+{
+    constexpr uint32_t GROUPS = 256 / GL;
+    const int lg = threadIdx.x & (GL - 1), d4 = a.d4;
+    const uint32_t grp = threadIdx.x / GL;
+    const uint32_t n = static_cast<uint32_t>(a.totals[1]);
+    for (uint32_t first = blockIdx.x * GROUPS; first < n; first += a.hub_blocks * GROUPS) {     // (uniform)
+        const bool live = first + grp < n;
+        uint4 item = make_uint4(0u, 0u, 0u, 0u);
+        float4 sum[CH];
+        if (live) {
+            item = a.hub_items[first + grp];
+            sum_item<GL, CH>(a, item.y, lg, sum);
+#pragma unroll
+            for (int i = 0; i < CH; ++i) lds[grp][lg + GL * i] = sum[i];
+        }
+        __syncthreads();
+        // the first of a row's items here adds up those that follow (its own sum is still in registers)
+        if (live && (grp == 0 || item.w == 0)) {
+            const uint32_t here = min(item.z - item.w, GROUPS - grp);
+            for (uint32_t q = 1; q < here; ++q)
+#pragma unroll
+                for (int i = 0; i < CH; ++i) sum[i] = add4(sum[i], lds[grp + q][lg + GL * i]);
+            bool last = here == item.z;
+            const uint32_t at = hub_accumulator((item.y >> 3) - item.w * kItemRefs);
+            float* acc = a.acc + static_cast<int64_t>(at) * (d4 * 4);
+            if (!last) {
+                float t[4 * CH];        // consecutive dwords per atomic instruction
+                to_consecutive<GL, CH>(sum, t, reinterpret_cast<float*>(lds[grp]), lg);
+#pragma unroll
+                for (int m = 0; m < 4 * CH; ++m) {
+                    const int c = lg + m * GL;
+                    if (c < d4 * 4) unsafeAtomicAdd(acc + c, t[m]);
+                }
+                // These adds are carried out before the arrival is counted: waiting for their acknowledgements is
+                // enough, and nothing has to be written back, because accumulators and counters are only ever
+                // touched by device-scope atomics in this launch (a release fence, which writes the whole L2 back,
+                // took five times as long as the rest of the launch).
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_s_waitcnt(0);
+                uint32_t before = 0u;
+                if (lg == 0) before = __hip_atomic_fetch_add(a.arrived + at, here, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                last = __shfl(before, 0, GL) + here == item.z;
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                if (last) {
+#pragma unroll
+                    for (int i = 0; i < CH; ++i) {
+                        const int ci = lg + GL * i;
+                        auto take = [&](int k) { return __hip_atomic_exchange(acc + 4 * ci + k, 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+                        if (ci < d4) sum[i] = make_float4(take(0), take(1), take(2), take(3));
+                    }
+                    if (lg == 0) a.arrived[at] = 0u;
+                }
+            }
+            if (last) {
+                float4* row = row_of_key(a, item.x);
+#pragma unroll
+                for (int i = 0; i < CH; ++i) {
+                    const int ci = lg + GL * i;
+                    if (ci < d4) row[ci] = add4(row[ci], sum[i]);
+                }
+            }
+        }
+        __syncthreads();        // the sums are overwritten
+    }
+}
 
 template <int GL, int CH>
 __global__ __launch_bounds__(256) void apply_kernel(ApplyArgs a)
 {
     constexpr uint32_t GROUPS = 256 / GL;
-    constexpr uint32_t MB = CH == 1 ? kItemRefs : kItemRefs / 2;   // entries whose rows travel together
-    __shared__ float lds[GROUPS][4 * GL * CH];     // layout change for the atomics
+    __shared__ float4 lds[GROUPS][GL * CH];
+    if (blockIdx.x < a.hub_blocks) {
+        apply_hubs<GL, CH>(a, lds);
+        return;
+    }
     const int lg = threadIdx.x & (GL - 1);
-    const int grp = threadIdx.x / GL;
-    const int d4 = a.d4;
-    uint32_t e = blockIdx.x * GROUPS + grp;
+    const uint32_t grp = threadIdx.x / GL;
+    const uint32_t step = (gridDim.x - a.hub_blocks) * GROUPS;
+    uint32_t e = (blockIdx.x - a.hub_blocks) * GROUPS + grp;
     uint2 item = a.items[min(e, a.most - 1u)];     // (in flight together with the count; what lies past it is not used)
     const uint32_t n = static_cast<uint32_t>(*a.totals >> 32);
-    for (; e < n; e += gridDim.x * GROUPS, item = a.items[min(e, a.most - 1u)]) {
-        float4* row = ((item.x & 0x80000000u) ? a.C : a.X) + static_cast<int64_t>(item.x & 0x7FFFFFFFu) * d4;
-        const uint2* list = a.list + (item.y >> 4);
-        const uint32_t refs = (item.y & 7u) + 1u;
-        const bool several = item.y & 8u;
+    for (; e < n; e += step, item = a.items[min(e, a.most - 1u)]) {
+        float4* row = row_of_key(a, item.x);
         float4 old[CH], sum[CH];
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int ci = lg + GL * i;
-            old[i] = !several && ci < d4 ? row[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
-            sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            old[i] = ci < a.d4 ? row[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        for (uint32_t r0 = 0; r0 < refs; r0 += MB) {
-            uint2 entry[MB];
-            float4 v[MB][CH];
+        sum_item<GL, CH>(a, item.y, lg, sum);
 #pragma unroll
-            for (uint32_t r = 0; r < MB; ++r) entry[r] = list[min(r0 + r, refs - 1u)];
-#pragma unroll
-            for (uint32_t r = 0; r < MB; ++r) {
-                const float4* src = a.buf + static_cast<int64_t>(entry[r].x) * d4;
-#pragma unroll
-                for (int i = 0; i < CH; ++i) {
-                    const int ci = lg + GL * i;
-                    v[r][i] = r0 + r < refs && ci < d4 ? src[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-            }
-#pragma unroll
-            for (uint32_t r = 0; r < MB; ++r) {
-                const float g = r0 + r < refs ? __uint_as_float(entry[r].y) : 0.0f;
-#pragma unroll
-                for (int i = 0; i < CH; ++i) sum[i] = axpy4(g, v[r][i], sum[i]);
-            }
-        }
-        if (!several) {
-#pragma unroll
-            for (int i = 0; i < CH; ++i) {
-                const int ci = lg + GL * i;
-                if (ci < d4) row[ci] = add4(old[i], sum[i]);
-            }
-        } else {
-            // several items add to this row: consecutive dwords per atomic instruction
-            float t[4 * CH];
-            to_consecutive<GL, CH>(sum, t, lds[grp], lg);
-#pragma unroll
-            for (int m = 0; m < 4 * CH; ++m) {
-                const int c = lg + m * GL;
-                if (c < d4 * 4) unsafeAtomicAdd(reinterpret_cast<float*>(row) + c, t[m]);
-            }
+        for (int i = 0; i < CH; ++i) {
+            const int ci = lg + GL * i;
+            if (ci < a.d4) row[ci] = add4(old[i], sum[i]);
         }
     }
 }
@@ -1455,15 +1551,21 @@ hipError_t launch_prepare(const Helpers& h, hipStream_t st)
 
 // Lane groups of the apply kernel: one dwordx4 chunk per lane as long as a wavefront holds the row.  Its
 // number of items is only known on the device; kApplyBlocks workgroups leave a lane group few of them, so
-// that those with long lists do not finish last (16384 against 2048: -2 .. -6 % of a batch's time).
+// that those with long lists do not finish last (16384 against 2048: -2 .. -6 % of a batch's time).  Up to
+// kHubBlocks more take the hubs' items, whose chains are the longest (512 take 6 % more of a batch of 65 536 pairs among
+// 1000 .. 10 000 nodes, 256 10 % more among a million; without hubs the 1024 are not seen).
 constexpr unsigned kApplyBlocks = 16384;
+constexpr unsigned kHubBlocks = 1024;
+inline uint64_t most_hub_items(uint64_t refs) { return refs * 2 / 9; }      // a hub of nine references has two
 hipError_t launch_apply(const Shape& s, ApplyArgs a, uint32_t refs, hipStream_t st)
 {
     a.most = refs / 2;                      // every item has two references or more to its row
     if (a.most == 0) return hipSuccess;
     const unsigned groups = 256u / s.G;
     const unsigned want = (a.most + groups - 1) / groups;
-    const unsigned grid = want < kApplyBlocks ? want : kApplyBlocks;
+    const unsigned hubs = static_cast<unsigned>((most_hub_items(refs) + groups - 1) / groups);
+    a.hub_blocks = hubs < kHubBlocks ? hubs : kHubBlocks;
+    const unsigned grid = (want < kApplyBlocks ? want : kApplyBlocks) + a.hub_blocks;
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
         hipLaunchKernelGGL((apply_kernel<G_, N_>), dim3(grid), dim3(256), 0, st, a);             \
@@ -1511,16 +1613,41 @@ bool workspace_layout(int32_t dim, int64_t max_B, int32_t max_K, char* base, Wor
         p.entries = reinterpret_cast<unsigned long long*>(take(refs * 8));
         p.segs = reinterpret_cast<uint32_t*>(take(max_segs(refs) * 4));
         p.items = reinterpret_cast<uint2*>(take(refs / 2 * sizeof(uint2)));
-        p.totals = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long)));
+        p.hub_items = reinterpret_cast<uint4*>(take(most_hub_items(refs) * sizeof(uint4)));
+        p.totals = reinterpret_cast<unsigned long long*>(take(2 * sizeof(unsigned long long)));
     }
     w->list = reinterpret_cast<uint2*>(take(refs * sizeof(uint2)));
     // two rows per pair or walk entry, a segment's entries twice and its context rows: never more than references
     w->buf = reinterpret_cast<float*>(take(refs * static_cast<size_t>(dim) * 4));
+    // (hub_accumulator)
+    w->accs = refs / kItemRefs + 1;
+    w->acc = reinterpret_cast<float*>(take(w->accs * static_cast<size_t>(dim) * 4));
+    w->arrived = reinterpret_cast<uint32_t*>(take(w->accs * 4));
     // what a caller is told to bring is never less than two rows and two words per reference, the bound that
     // programs may have sized their buffers by; the difference is not used
     const size_t bound = 2 * refs * (static_cast<size_t>(dim) + 1) * 4;
     w->total_bytes = off > bound ? off : up(bound);
     return true;
+}
+
+// (a kernel instead of hipMemsetAsync so that callers may capture the stream)
+__global__ __launch_bounds__(256) void clear_kernel(uint32_t* __restrict__ p, size_t n)
+{
+    const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
+    for (size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0u;
+}
+
+// The state every apply launch expects to find and leaves behind: accumulators and their counters zero.
+hipError_t clear_workspace(const Workspace& w, int32_t dim, hipStream_t st)
+{
+    const size_t floats = w.accs * static_cast<size_t>(dim);
+    const size_t want = (floats + 255) / 256;
+    const dim3 grid(static_cast<unsigned>(want < 16384 ? want : 16384));
+    hipLaunchKernelGGL(clear_kernel, grid, dim3(256), 0, st, reinterpret_cast<uint32_t*>(w.acc), floats);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(clear_kernel, grid, dim3(256), 0, st, w.arrived, w.accs);
+    return hipGetLastError();
 }
 
 ne_status check_batch_args(const ne_tables* t, const ne_alias* al, const int32_t* pairs, int64_t B, int32_t K,
@@ -1553,7 +1680,8 @@ ne_status run_batches(ne_tables* t, const Shape& shape, int64_t n_batches, int64
         if (!pa.refs) return pa;
         const PrepSlot& ps = w.prep[i % 3];
         pa.bin = binning(pa.refs);
-        pa.ids = ps.ids; pa.tag = ps.tag; pa.entries = ps.entries; pa.segs = ps.segs; pa.items = ps.items; pa.totals = ps.totals;
+        pa.ids = ps.ids; pa.tag = ps.tag; pa.entries = ps.entries; pa.segs = ps.segs; pa.items = ps.items;
+        pa.hub_items = ps.hub_items; pa.totals = ps.totals;
         pa.k0 = static_cast<uint32_t>(t->seed); pa.k1 = static_cast<uint32_t>(t->seed >> 32);
         return pa;
     };
@@ -1584,7 +1712,8 @@ ne_status run_batches(ne_tables* t, const Shape& shape, int64_t n_batches, int64
 
         if (!direct) {
             ApplyArgs aa{};
-            aa.X = ta.X; aa.C = ta.C; aa.d4 = ta.d4; aa.items = cur.items; aa.totals = cur.totals; aa.list = w.list; aa.buf = ta.buf;
+            aa.X = ta.X; aa.C = ta.C; aa.d4 = ta.d4; aa.items = cur.items; aa.hub_items = cur.hub_items; aa.totals = cur.totals; aa.list = w.list; aa.buf = ta.buf;
+            aa.acc = w.acc; aa.arrived = w.arrived;
             e = launch_apply(shape, aa, cur.refs, st);
             if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("apply launch: ") + hipGetErrorString(e));
         }
@@ -1642,6 +1771,11 @@ ne_status ne_create_tables(ne_tables** out, int64_t num_nodes, int32_t dim, floa
             return fail(NE_ERR_ARG, "workspace_dev is NULL, not 256-byte aligned, or smaller than ne_workspace_bytes()");
         }
         t->ws = w; t->max_batch = max_batch; t->max_negatives = max_negatives;
+        const hipError_t e = clear_workspace(w, dim, st);
+        if (e != hipSuccess) {
+            delete t;
+            return fail(NE_ERR_HIP, std::string("workspace clear launch: ") + hipGetErrorString(e));
+        }
     }
     if (init) {
         const int64_t total = num_nodes * (dim / 4);

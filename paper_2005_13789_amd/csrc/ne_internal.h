@@ -29,21 +29,25 @@ ne_status fail(ne_status st, const std::string& msg);
 
 namespace {
 
-// Device workspace of a tables handle (caller's memory, carved up here).  Nothing in it has to start from any
-// value, and nothing is carried from one batch to the next but what the id phases of a batch hand to its train
-// and apply kernels.
+// Device workspace of a tables handle (caller's memory, carved up here).  Nothing is carried from one batch to the
+// next but what the id phases of a batch hand to its train and apply kernels; acc and arrived are cleared with the
+// handle's creation and left zero by every apply launch, nothing else has to start from any value.
 struct PrepSlot {
     int32_t* ids;                 // [refs]  row named by each reference (walk mode: -1 = no such reference)
     uint32_t* tag;                // [refs]  0 = only this reference names its row; else 1 + its place in the list
     unsigned long long* entries;  // [refs]  key << 32 | reference, sorted by bin inside each tile
     uint32_t* segs;               // [tiles][bins]  where a tile's entries of a bin start, and how many (<< 16)
-    uint2* items;                 // [refs / 2]  work items of the apply kernel: rows that several references name
-    unsigned long long* totals;   // [1]     number of items << 32 | places of the list in use
+    uint2* items;                 // [refs / 2]  work items of the apply kernel: rows that 2 .. 8 references name
+    uint4* hub_items;             // [refs 2/9]  work items of the rows that more references name
+    unsigned long long* totals;   // [2]     number of items << 32 | places of the list in use; number of hub items
 };
 struct Workspace {
     PrepSlot prep[3];   // one batch in training, the next being resolved, the one after that being claimed
     uint2* list;        // [refs]  (row of buf, coefficient) of each reference to a shared row, a row's references side by side
     float* buf;         // [refs][dim]  rows that the list points to: copies of source rows, deltas
+    float* acc;         // [accs][dim]  sums of hubs, zero between batches
+    uint32_t* arrived;  // [accs]  how many of a hub's items its sum holds, zero between batches
+    size_t accs;
     size_t total_bytes;
 };
 
