@@ -98,25 +98,34 @@ constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 //          every workgroup without losing one; 2048 references and 4096 slots cost such a batch 6 %, 512 and
 //          1024 twice as many segments and 8 %); a smaller batch gets up to 256 bins, one per compute unit,
 //          of 128 .. 256 references, because a bin is one chain of dependent accesses (64 .. 128: 6 % slower
-//          on batches of 28 000 references).  More than 2^kMaxBinBits bins would make the claim phase's
-//          counters too large: the bins of batches beyond 4 M references are longer, and resolved in several
-//          ranges of the hash.
+//          on batches of 28 000 references), and below 64 bins they are shorter still (256 throughout: 2 .. 4 % slower on
+//          batches of 300 .. 4000 references, 10 % where such batches follow each other in one call).  Up to 256
+//          references are one bin, claimed and resolved in one launch (12 against 14.6 us for a call with one pair; of
+//          up to 512: the resolve phase takes 1 .. 2 us more than the launch it saves).  More than 2^kMaxBinBits bins
+//          would make the claim phase's counters too large: the bins of batches beyond 4 M references are longer, and
+//          resolved in several ranges of the hash.
 //   tile   references per claim workgroup: at least 4 per bin, so that runs of a bin's entries are worth an
 //          access and the segment table stays a quarter of the entries.
+//   lanes  per tile segment in the resolve phase: a power of two, half as many again as a segment has entries on
+//          average, so that most segments are one access (a fixed 8 took 43 us for a batch of 64 pairs, whose two
+//          bins are one segment of 224 entries each, where 1 pair takes 17).
 //   slots  of a bin's LDS table, and the distinct rows (full) at which it counts as too small: each of the
 //          256 threads may add one more after that, and one slot has to stay empty.
-struct Binning { uint32_t bits, tile, tiles, slot_bits, full; };
+struct Binning { uint32_t bits, tile, tiles, lane_bits, slot_bits, full; };
 constexpr uint32_t kMaxBinBits = 12;
 constexpr uint32_t kMinTile = 1024;
-constexpr uint64_t kFewRefs = 256, kManyRefs = 1024;   // most references per bin, on average, below and from 256 bins on
+constexpr uint64_t kOneBin = 256;
+constexpr struct { uint32_t bits; uint64_t refs; } kBinSteps[] = {{5, 64}, {6, 128}, {8, 256}, {kMaxBinBits, 1024}};   // most references per bin, up to 2^bits bins
 inline Binning binning(uint64_t refs)
 {
     Binning b;
     b.bits = 0;
-    while (b.bits < 8 && (kFewRefs << b.bits) < refs) ++b.bits;
-    while (b.bits < kMaxBinBits && (kManyRefs << b.bits) < refs) ++b.bits;
+    for (const auto& step : kBinSteps)
+        while (refs > kOneBin && b.bits < step.bits && (step.refs << b.bits) < refs) ++b.bits;
     b.tile = (4u << b.bits) > kMinTile ? (4u << b.bits) : kMinTile;
     b.tiles = static_cast<uint32_t>((refs + b.tile - 1) / b.tile);
+    b.lane_bits = 3;
+    while (b.lane_bits < 8 && (static_cast<uint64_t>(b.tiles) << (b.bits + b.lane_bits)) < refs + refs / 2) ++b.lane_bits;
     const uint64_t mean = refs >> b.bits;
     b.slot_bits = mean <= 128 ? 9 : mean <= 400 ? 10 : 11;
     b.full = b.slot_bits == 9 ? 255u : (5u << b.slot_bits) / 8u;
@@ -480,12 +489,12 @@ __device__ __forceinline__ uint32_t item_places(uint32_t first, uint32_t n) { re
 // because each has more than kItemRefs places.
 __device__ __forceinline__ uint32_t hub_accumulator(uint32_t first) { return (first + kItemRefs - 1u) / kItemRefs; }
 
-// A share of a bin's entries: 8 lanes per tile segment, kSegsPerLane segments each, the first 8 entries of
-// every segment in registers.  Fetching a share takes two dependent accesses, whatever its size; 256 tiles
+// A share of a bin's entries: 2^lane_bits lanes per tile segment, kSegsPerLane segments each, every segment's first
+// entries in registers.  Fetching a share takes two dependent accesses, whatever its size; 256 tiles
 // are all there are up to 512 bins (with half as many, and so two fetches per pass: +1 .. 2 % of a batch; 16
-// lanes per segment: +2 % on batches of 90 000 references).
+// lanes per segment: +2 % on batches of 90 000 references, whose segments have 4 entries).
 constexpr int kSegsPerLane = 8;
-constexpr uint32_t kShareTiles = 32 * kSegsPerLane;      // tile segments per share
+__device__ __forceinline__ uint32_t share_tiles(const PrepArgs& a) { return (256u * kSegsPerLane) >> a.bin.lane_bits; }
 struct BinShare {
     unsigned long long e[kSegsPerLane];
     uint32_t seg[kSegsPerLane];       // start in the tile | entries << 16
@@ -493,16 +502,17 @@ struct BinShare {
 
 __device__ __forceinline__ void fetch_share(const PrepArgs& a, uint32_t bin, uint32_t tile0, BinShare& s)
 {
-    const uint32_t g = threadIdx.x >> 3, l = threadIdx.x & 7;
+    const uint32_t lane_bits = a.bin.lane_bits, groups = 256u >> lane_bits;
+    const uint32_t g = threadIdx.x >> lane_bits, l = threadIdx.x & ((1u << lane_bits) - 1u);
     const uint32_t bins = 1u << a.bin.bits;
 #pragma unroll
     for (int i = 0; i < kSegsPerLane; ++i) {
-        const uint32_t t = tile0 + g + 32u * i;
+        const uint32_t t = tile0 + g + groups * i;
         s.seg[i] = t < a.bin.tiles ? a.segs[static_cast<size_t>(t) * bins + bin] : 0u;
     }
 #pragma unroll
     for (int i = 0; i < kSegsPerLane; ++i) {
-        const uint32_t t = tile0 + g + 32u * i;
+        const uint32_t t = tile0 + g + groups * i;
         s.e[i] = l < (s.seg[i] >> 16) ? a.entries[t * a.bin.tile + (s.seg[i] & 0xFFFFu) + l] : ~0ull;
     }
 }
@@ -511,17 +521,17 @@ __device__ __forceinline__ void fetch_share(const PrepArgs& a, uint32_t bin, uin
 template <class F>
 __device__ __forceinline__ void for_share(const PrepArgs& a, uint32_t tile0, const BinShare& s, F f)
 {
-    const uint32_t g = threadIdx.x >> 3, l = threadIdx.x & 7;
+    const uint32_t lane_bits = a.bin.lane_bits, lanes = 1u << lane_bits, groups = 256u >> lane_bits;
 #pragma unroll
     for (int i = 0; i < kSegsPerLane; ++i) {
-        if (tile0 + 32u * i >= a.bin.tiles) break;
+        if (tile0 + groups * i >= a.bin.tiles) break;
         // (opaque to the optimiser, which would otherwise keep every entry's hash and address from one pass to
         // the next: twice the registers, half the wavefronts of the kernel this rides in)
-        uint32_t key = static_cast<uint32_t>(s.e[i] >> 32), seg = s.seg[i], t = tile0 + g + 32u * i;
+        uint32_t key = static_cast<uint32_t>(s.e[i] >> 32), seg = s.seg[i], t = tile0 + (threadIdx.x >> lane_bits) + groups * i;
         asm volatile("" : "+v"(key), "+v"(seg), "+v"(t));
-        const uint32_t n = seg >> 16;
+        const uint32_t l = threadIdx.x & (lanes - 1u), n = seg >> 16;
         if (l < n) f(key, static_cast<uint32_t>(s.e[i]));
-        for (uint32_t q = l + 8; q < n; q += 8) {
+        for (uint32_t q = l + lanes; q < n; q += lanes) {
             const unsigned long long v = a.entries[t * a.bin.tile + (seg & 0xFFFFu) + q];
             f(static_cast<uint32_t>(v >> 32), static_cast<uint32_t>(v));
         }
@@ -537,12 +547,12 @@ __device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, uns
     uint32_t* scnt = skey + slots;
     uint32_t lo = 0, halvings = 0;      // range of the hash below the bin's bits: [lo, lo + 2^(32 - halvings))
     BinShare share;
-    if (a.bin.tiles <= kShareTiles) fetch_share(a, bin, 0, share);    // all there is, once
+    if (a.bin.tiles <= share_tiles(a)) fetch_share(a, bin, 0, share);    // all there is, once
     auto for_bin_entries = [&](auto f) {
-        if (a.bin.tiles <= kShareTiles) {
+        if (a.bin.tiles <= share_tiles(a)) {
             for_share(a, 0, share, f);
         } else {
-            for (uint32_t t0 = 0; t0 < a.bin.tiles; t0 += kShareTiles) {
+            for (uint32_t t0 = 0; t0 < a.bin.tiles; t0 += share_tiles(a)) {
                 fetch_share(a, bin, t0, share);
                 for_share(a, t0, share, f);
             }
@@ -701,10 +711,15 @@ __device__ __forceinline__ bool helper_block(const Helpers& h, unsigned* block)
     return false;
 }
 
-// The same work on its own, for the first batches of a call.
+// The same work on its own, for the first batches of a call.  A batch with one tile and one bin is claimed and resolved
+// by the same workgroup (claim_first: h.resolve).
 template <RefMode MODE>
-__global__ __launch_bounds__(256) void prepare_kernel(Helpers h)
+__global__ __launch_bounds__(256) void prepare_kernel(Helpers h, bool claim_first)
 {
+    if (claim_first && blockIdx.x == 0) {
+        claim_tile<MODE>(h.resolve, 0, reinterpret_cast<uint32_t*>(dynamic_lds));
+        __syncthreads();
+    }
     unsigned block;
     helper_block<MODE>(h, &block);
 }
@@ -1545,12 +1560,13 @@ hipError_t launch_train_seg(const Shape& s, const TrainArgs& a, const Helpers& h
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_prepare(const Helpers& h, hipStream_t st)
+hipError_t launch_prepare(const Helpers& h, bool claim_first, hipStream_t st)
 {
+    const size_t own = claim_first ? claim_lds_bytes(h.resolve.bin) : 0, lds = own > h.lds_bytes() ? own : h.lds_bytes();
     const PrepArgs& p = h.claims ? h.claim : h.resolve;
-    if (p.pairs) hipLaunchKernelGGL(prepare_kernel<kPairRefs>, dim3(h.count()), dim3(256), h.lds_bytes(), st, h);
-    else if (p.seg_entries) hipLaunchKernelGGL(prepare_kernel<kSegRefs>, dim3(h.count()), dim3(256), h.lds_bytes(), st, h);
-    else hipLaunchKernelGGL(prepare_kernel<kWalkRefs>, dim3(h.count()), dim3(256), h.lds_bytes(), st, h);
+    if (p.pairs) hipLaunchKernelGGL(prepare_kernel<kPairRefs>, dim3(h.count()), dim3(256), lds, st, h, claim_first);
+    else if (p.seg_entries) hipLaunchKernelGGL(prepare_kernel<kSegRefs>, dim3(h.count()), dim3(256), lds, st, h, claim_first);
+    else hipLaunchKernelGGL(prepare_kernel<kWalkRefs>, dim3(h.count()), dim3(256), lds, st, h, claim_first);
     return hipGetLastError();
 }
 
@@ -1671,7 +1687,7 @@ ne_status check_batch_args(const ne_tables* t, const ne_alias* al, const int32_t
 }
 
 // The launches of a run of batches, common to the pair and the walk shapes: claim(0), then resolve(0) +
-// claim(1), stand alone; then per batch kernel A = train(i) + resolve(i+1) + claim(i+2) (+ sample prefetch)
+// claim(1), stand alone (a first batch of one bin: both in one launch); then per batch kernel A = train(i) + resolve(i+1) + claim(i+2) (+ sample prefetch)
 // and kernel B = apply(i).  prep(i) describes batch i (refs = 0 past the end); train(ta, helpers) launches
 // the shape's train kernel.  direct: the per-sample mode, which leaves nothing to apply.
 template <class PrepFn, class TrainFn>
@@ -1699,9 +1715,10 @@ ne_status run_batches(ne_tables* t, const Shape& shape, int64_t n_batches, int64
         return h;
     };
     PrepArgs cur = prepared(0), next = prepared(1);
-    hipError_t e = launch_prepare(helpers(PrepArgs{}, cur, false), st);
+    const bool at_once = cur.refs <= kOneBin;
+    hipError_t e = at_once ? hipSuccess : launch_prepare(helpers(PrepArgs{}, cur, false), false, st);
     if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("claim launch: ") + hipGetErrorString(e));
-    e = launch_prepare(helpers(cur, next, false), st);
+    e = launch_prepare(helpers(cur, next, false), at_once, st);
     if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("resolve launch: ") + hipGetErrorString(e));
 
     for (int64_t i = 0; i < n_batches; ++i) {

@@ -42,9 +42,9 @@ def step_and_check(t, alias, thr, al, pairs, K, seed, batches, lr=0.02):
     assert np.array_equal(Cg[rest_c].view(np.uint32), C0[rest_c].view(np.uint32))
 
 
-# three references per pair; 256 << k references use k bin bits up to 256 bins, 1024 references fill a tile, from
-# 262 144 references on the number of bins follows 1024 references each
-@pytest.mark.parametrize("B", [1, 2, 85, 86, 170, 171, 341, 342, 683, 1366, 21845, 21846, 87381, 87382])
+# three references per pair; up to 256 are one bin, then 64, 128 and 256 each up to 32, 64 and 256 bins (2048, 8192 and
+# 65 536 references); 1024 references fill a tile, from 262 144 references on the number of bins follows 1024 references each
+@pytest.mark.parametrize("B", [1, 2, 85, 86, 170, 171, 341, 342, 682, 683, 1366, 2730, 2731, 21845, 21846, 87381, 87382])
 def test_tiles_and_bins(B):
     print(f"B={B}", flush=True)
     V, d, K, seed = 60_000, 8, 1, 11
@@ -60,17 +60,17 @@ def test_tiles_and_bins(B):
     step_and_check(t, alias, thr, al, pairs.astype(np.int32), K, seed, 3)
 
 
-@pytest.mark.parametrize("distinct", [600, 700, 4000])
-def test_rows_of_one_bin_beyond_its_table(distinct):
+@pytest.mark.parametrize("distinct,more", [(250, 1), (260, 1), (600, 1), (635, 3), (645, 3), (4000, 1)])
+def test_rows_of_one_bin_beyond_its_table(distinct, more):
     """All source rows share the top 10 bits of the hash, and so do all context rows: two bins hold everything.
-    The tables of this size take 640 distinct rows: just below, just above, and many times as many; each row is
-    named once, twice, 8, 9 or 17 times."""
-    print(f"distinct={distinct}", flush=True)
+    The tables take 255 distinct rows up to 8192 references, 640 with more: just below, just above, and many times
+    as many; each row is named once, twice, 8, 9 or 17 times, or 3 times as often."""
+    print(f"distinct={distinct} more={more}", flush=True)
     V, d, seed = 8_000_000, 4, 12
     ids = np.arange(V, dtype=np.uint64)
     same = ids[((ids * 0x9E3779B1) & 0xFFFFFFFF) >> 22 == 321][:distinct]
     assert same.size == distinct
-    times = np.array([1, 2, 1, 8, 1, 9, 1, 17])[np.arange(distinct) % 8]
+    times = np.array([1, 2, 1, 8, 1, 9, 1, 17])[np.arange(distinct) % 8] * more
     rng = np.random.default_rng(distinct)
     src = rng.permutation(np.repeat(same, times))
     ctx = rng.permutation(np.repeat(same, times))
