@@ -101,38 +101,45 @@ constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 //          on batches of 28 000 references), and below 64 bins they are shorter still (256 throughout: 2 .. 4 % slower on
 //          batches of 300 .. 4000 references, 10 % where such batches follow each other in one call).  Up to 256
 //          references are one bin, claimed and resolved in one launch (12 against 14.6 us for a call with one pair; of
-//          up to 512: the resolve phase takes 1 .. 2 us more than the launch it saves).  More than 2^kMaxBinBits bins
-//          would make the claim phase's counters too large: the bins of batches beyond 4 M references are longer, and
-//          resolved in several ranges of the hash.
+//          up to 512: the resolve phase takes 1 .. 2 us more than the launch it saves).  Beyond 1200 references per bin
+//          at 4096 bins (4.9 M references) up to 16 384 bins, as many as 16-bit counters of the claim phase in 32 KB of
+//          LDS allow; beyond that the bins get longer, and are resolved in several ranges of the hash.  (4096 bins
+//          throughout: 2^22 pairs with K = 5, dim 16 take 6.4 ms, in 8 ranges, instead of 3.9 in one; with K = 62, dim 4 147
+//          instead of 79, 64 ranges and 8.)
 //   tile   references per claim workgroup: at least 4 per bin, so that runs of a bin's entries are worth an
-//          access and the segment table stays a quarter of the entries.
+//          access and the segment table stays a quarter of the entries; 2 beyond 4096 bins, where tiles are few and long.
 //   lanes  per tile segment in the resolve phase: a power of two, half as many again as a segment has entries on
 //          average, so that most segments are one access (a fixed 8 took 43 us for a batch of 64 pairs, whose two
 //          bins are one segment of 224 entries each, where 1 pair takes 17).
-//   slots  of a bin's LDS table, and the distinct rows (full) at which it counts as too small: each of the
-//          256 threads may add one more after that, and one slot has to stay empty.
+//   slots  of a bin's LDS table (4096 only for the batches whose claim counters take 32 KB as well), and the distinct
+//          rows (full) at which it counts as too small: each of the 256 threads may add one more after that, and one
+//          slot has to stay empty.
 struct Binning { uint32_t bits, tile, tiles, lane_bits, slot_bits, full; };
-constexpr uint32_t kMaxBinBits = 12;
+constexpr uint32_t kWordBinBits = 12, kMaxBinBits = 14;      // most bins whose claim counters are whole words; most bins
 constexpr uint32_t kMinTile = 1024;
 constexpr uint64_t kOneBin = 256;
-constexpr struct { uint32_t bits; uint64_t refs; } kBinSteps[] = {{5, 64}, {6, 128}, {8, 256}, {kMaxBinBits, 1024}};   // most references per bin, up to 2^bits bins
+constexpr struct { uint32_t bits; uint64_t refs; } kBinSteps[] = {{5, 64}, {6, 128}, {8, 256}, {kWordBinBits, 1024}, {kMaxBinBits, 1200}};   // most references per bin, up to 2^bits bins
 inline Binning binning(uint64_t refs)
 {
     Binning b;
     b.bits = 0;
     for (const auto& step : kBinSteps)
         while (refs > kOneBin && b.bits < step.bits && (step.refs << b.bits) < refs) ++b.bits;
-    b.tile = (4u << b.bits) > kMinTile ? (4u << b.bits) : kMinTile;
+    b.tile = (b.bits > kWordBinBits ? 2u : 4u) << b.bits;
+    if (b.tile < kMinTile) b.tile = kMinTile;
     b.tiles = static_cast<uint32_t>((refs + b.tile - 1) / b.tile);
-    b.lane_bits = 3;
+    b.lane_bits = 2;
     while (b.lane_bits < 8 && (static_cast<uint64_t>(b.tiles) << (b.bits + b.lane_bits)) < refs + refs / 2) ++b.lane_bits;
     const uint64_t mean = refs >> b.bits;
-    b.slot_bits = mean <= 128 ? 9 : mean <= 400 ? 10 : 11;
+    b.slot_bits = mean <= 128 ? 9 : mean <= 400 ? 10 : mean <= 1200 ? 11 : 12;
     b.full = b.slot_bits == 9 ? 255u : (5u << b.slot_bits) / 8u;
     return b;
 }
 // Segment words that a batch of up to `refs` references can need.
-inline uint64_t max_segs(uint64_t refs) { return refs / 4 + (1u << kMaxBinBits); }
+inline uint64_t max_segs(uint64_t refs)
+{
+    return refs <= (kBinSteps[4].refs << kWordBinBits) ? refs / 4 + (1u << kWordBinBits) : refs / 2 + (1u << kMaxBinBits);
+}
 
 struct PrepArgs {
     const int2* pairs;    // pair mode: the batch's pairs
@@ -389,8 +396,9 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T* part, T* total)
     return before + inc - v;
 }
 
-// LDS of the claim phase: a counter per bin and the scan's four words.
-inline size_t claim_lds_bytes(const Binning& b) { return ((static_cast<size_t>(1) << b.bits) + 4) * sizeof(uint32_t); }
+// LDS of the claim phase: a counter per bin (beyond 2^kWordBinBits bins 16 bits each) and the scan's four words.
+__host__ __device__ inline uint32_t counter_words(uint32_t bits) { return bits > kWordBinBits ? 1u << (bits - 1u) : 1u << bits; }
+inline size_t claim_lds_bytes(const Binning& b) { return (static_cast<size_t>(counter_words(b.bits)) + 4) * sizeof(uint32_t); }
 
 // Layout of a batch's references.
 enum RefMode { kPairRefs, kWalkRefs, kSegRefs };
@@ -402,9 +410,15 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
 {
     const unsigned tid = threadIdx.x;
     const uint32_t bits = a.bin.bits, bins = 1u << bits;
-    uint32_t* part = hist + bins;
+    const uint32_t words = counter_words(bits), pack = bits > kWordBinBits ? 1u : 0u;
+    uint32_t* part = hist + words;
+    uint16_t* half = reinterpret_cast<uint16_t*>(hist);
+    auto count = [&](uint32_t p) {       // what the bin's counter was
+        const uint32_t shift = (p & pack) << 4, before = atomicAdd(&hist[p >> pack], 1u << shift) >> shift;
+        return pack ? before & 0xFFFFu : before;
+    };
     if (tile == 0 && tid < 2) a.totals[tid] = 0ull;   // resolve, one launch later, counts from zero
-    for (uint32_t i = tid; i < bins; i += 256) hist[i] = 0u;
+    for (uint32_t i = tid; i < words; i += 256) hist[i] = 0u;
     __syncthreads();
     const uint32_t first = tile * a.bin.tile;
     const uint32_t last = min(first + a.bin.tile, a.refs);   // (refs is at most 2^28)
@@ -418,7 +432,7 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
         for (int u = 0; u < kPrepUnroll; ++u) {
             const uint32_t t = step + u * 256u + tid;
             if (t < last) a.tag[t] = 0u;             // resolve overwrites it where the row is shared
-            if (key[u] != kNoKey) atomicAdd(&hist[bin_of(key[u], bits)], 1u);
+            if (key[u] != kNoKey) count(bin_of(key[u], bits));
         }
         if (step + 256 * kPrepUnroll >= last) break;
     }
@@ -428,16 +442,17 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
     uint32_t mine = 0;
     for (uint32_t i = 0; i < per; ++i) {
         const uint32_t p = tid * per + i;
-        if (p < bins) mine += hist[p];
+        if (p < bins) mine += pack ? half[p] : hist[p];
     }
     uint32_t total;
     uint32_t at = block_exclusive_scan(mine, part, &total);
     for (uint32_t i = 0; i < per; ++i) {
         const uint32_t p = tid * per + i;
         if (p < bins) {
-            const uint32_t n = hist[p];
+            const uint32_t n = pack ? half[p] : hist[p];
             a.segs[static_cast<size_t>(tile) * bins + p] = at | (n << 16);
-            hist[p] = at;
+            if (pack) half[p] = static_cast<uint16_t>(at);
+            else hist[p] = at;
             at += n;
         }
     }
@@ -448,7 +463,7 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
         for (int u = 0; u < kPrepUnroll; ++u) {
             if (key[u] != kNoKey) {
                 const uint32_t t = step + u * 256u + tid;
-                const uint32_t p = atomicAdd(&hist[bin_of(key[u], bits)], 1u);
+                const uint32_t p = count(bin_of(key[u], bits));
                 a.entries[first + p] = (static_cast<unsigned long long>(key[u]) << 32) | t;
             }
         }
@@ -555,6 +570,7 @@ __device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, uns
             for (uint32_t t0 = 0; t0 < a.bin.tiles; t0 += share_tiles(a)) {
                 fetch_share(a, bin, t0, share);
                 for_share(a, t0, share, f);
+                if (*const_cast<volatile uint32_t*>(&s.distinct) > a.bin.full) break;   // (a range that is given up)
             }
         }
     };

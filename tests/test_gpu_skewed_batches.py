@@ -43,18 +43,18 @@ def test_one_row_takes_many_references(B, share, side):
         assert e <= 1e-5 and eh <= (1.3e-4 if hub else 1e-5)
 
 
-def seconds(call):
-    """Median over seven rounds of 20 calls."""
-    for _ in range(5):
+def seconds(call, rounds=7, calls=20):
+    """Time of a call: the median over some rounds of several calls each."""
+    for _ in range(2):
         call()
     torch.cuda.synchronize()
     got = []
-    for _ in range(7):
+    for _ in range(rounds):
         t0 = time.perf_counter()
-        for _ in range(20):
+        for _ in range(calls):
             call()
         torch.cuda.synchronize()
-        got.append((time.perf_counter() - t0) / 20)
+        got.append((time.perf_counter() - t0) / calls)
     return statistics.median(got)
 
 
