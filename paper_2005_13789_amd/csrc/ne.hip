@@ -1586,18 +1586,21 @@ hipError_t launch_prepare(const Helpers& h, bool claim_first, hipStream_t st)
     return hipGetLastError();
 }
 
-// Lane groups of the apply kernel: one dwordx4 chunk per lane as long as a wavefront holds the row.  Its
-// number of items is only known on the device; kApplyBlocks workgroups leave a lane group few of them, so
+// Lane groups of the apply kernel: one dwordx4 chunk per lane as long as a wavefront holds the row, however many
+// references a pair has (the train kernel's groups, with a lane per reference, leave 63 of 64 lanes idle at dim 4,
+// K = 62: 32 768 pairs among a million nodes 465 us, now 316; 2^20 pairs among 64 million 19.3 ms, now 13.9).  Its number of items is only known on the device; kApplyBlocks workgroups leave a lane group few of them, so
 // that those with long lists do not finish last (16384 against 2048: -2 .. -6 % of a batch's time).  Up to
 // kHubBlocks more take the hubs' items, whose chains are the longest (512 take 6 % more of a batch of 65 536 pairs among
 // 1000 .. 10 000 nodes, 256 10 % more among a million; without hubs the 1024 are not seen).
 constexpr unsigned kApplyBlocks = 16384;
 constexpr unsigned kHubBlocks = 1024;
 inline uint64_t most_hub_items(uint64_t refs) { return refs * 2 / 9; }      // a hub of nine references has two
-hipError_t launch_apply(const Shape& s, ApplyArgs a, uint32_t refs, hipStream_t st)
+hipError_t launch_apply(ApplyArgs a, uint32_t refs, hipStream_t st)
 {
     a.most = refs / 2;                      // every item has two references or more to its row
     if (a.most == 0) return hipSuccess;
+    Shape s;
+    if (!pick_shape(a.d4, 0, &s)) return hipErrorInvalidValue;
     const unsigned groups = 256u / s.G;
     const unsigned want = (a.most + groups - 1) / groups;
     const unsigned hubs = static_cast<unsigned>((most_hub_items(refs) + groups - 1) / groups);
@@ -1707,7 +1710,7 @@ ne_status check_batch_args(const ne_tables* t, const ne_alias* al, const int32_t
 // and kernel B = apply(i).  prep(i) describes batch i (refs = 0 past the end); train(ta, helpers) launches
 // the shape's train kernel.  direct: the per-sample mode, which leaves nothing to apply.
 template <class PrepFn, class TrainFn>
-ne_status run_batches(ne_tables* t, const Shape& shape, int64_t n_batches, int64_t R, int32_t window, int32_t K,
+ne_status run_batches(ne_tables* t, int64_t n_batches, int64_t R, int32_t window, int32_t K,
                       const float* lr_host, hipStream_t st, PrepFn prep, TrainFn train, bool direct = false)
 {
     const Workspace& w = t->ws;
@@ -1752,7 +1755,7 @@ ne_status run_batches(ne_tables* t, const Shape& shape, int64_t n_batches, int64
             ApplyArgs aa{};
             aa.X = ta.X; aa.C = ta.C; aa.d4 = ta.d4; aa.items = cur.items; aa.hub_items = cur.hub_items; aa.totals = cur.totals; aa.list = w.list; aa.buf = ta.buf;
             aa.acc = w.acc; aa.arrived = w.arrived;
-            e = launch_apply(shape, aa, cur.refs, st);
+            e = launch_apply(aa, cur.refs, st);
             if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("apply launch: ") + hipGetErrorString(e));
         }
         t->batches_done += 1;
@@ -2013,7 +2016,7 @@ static ne_status train_runs_impl(ne_tables* t, const ne_run* runs, int64_t n_run
         const hipError_t fe = hipGetLastError();
         if (fe != hipSuccess) return fail(NE_ERR_HIP, std::string("fetch launch: ") + hipGetErrorString(fe));
     }
-    return run_batches(t, shape, n_batches, R, 0, K, lr_host, st, prep_args,
+    return run_batches(t, n_batches, R, 0, K, lr_host, st, prep_args,
                        [&](const TrainArgs& ta, const Helpers& h) { return launch_train(shape, ta, h, direct, st); }, direct);
 }
 
@@ -2109,7 +2112,7 @@ ne_status ne_train_walks(ne_tables* t, const ne_alias* al, const int32_t* walks_
         return pa;
     };
 
-    return run_batches(t, shape, n_batches, R, window, K, lr_host, st, prep_args, [&](const TrainArgs& ta, const Helpers& h) {
+    return run_batches(t, n_batches, R, window, K, lr_host, st, prep_args, [&](const TrainArgs& ta, const Helpers& h) {
         return by_segments ? launch_train_seg(shape, ta, h, st) : launch_train_walk(shape, ta, h, st);
     });
 }
