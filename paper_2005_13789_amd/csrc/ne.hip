@@ -542,9 +542,9 @@ __device__ __forceinline__ void for_share(const PrepArgs& a, uint32_t tile0, con
         if (tile0 + groups * i >= a.bin.tiles) break;
         // (opaque to the optimiser, which would otherwise keep every entry's hash and address from one pass to
         // the next: twice the registers, half the wavefronts of the kernel this rides in)
-        uint32_t key = static_cast<uint32_t>(s.e[i] >> 32), seg = s.seg[i], t = tile0 + (threadIdx.x >> lane_bits) + groups * i;
-        asm volatile("" : "+v"(key), "+v"(seg), "+v"(t));
-        const uint32_t l = threadIdx.x & (lanes - 1u), n = seg >> 16;
+        uint32_t key = static_cast<uint32_t>(s.e[i] >> 32), seg = s.seg[i], tid = threadIdx.x;
+        asm volatile("" : "+v"(key), "+v"(seg), "+v"(tid));
+        const uint32_t l = tid & (lanes - 1u), t = tile0 + (tid >> lane_bits) + groups * i, n = seg >> 16;
         if (l < n) f(key, static_cast<uint32_t>(s.e[i]));
         for (uint32_t q = l + lanes; q < n; q += lanes) {
             const unsigned long long v = a.entries[t * a.bin.tile + (seg & 0xFFFFu) + q];
@@ -614,9 +614,10 @@ __device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, uns
         }
         unsigned long long at = block_exclusive_scan(mine, s.part, &all);
         if (all) {                              // (uniform)
-            if (tid == 0) {
-                s.base = atomicAdd(a.totals, all);
-                if (s.hub_items) s.hub_items = static_cast<uint32_t>(atomicAdd(a.totals + 1, static_cast<unsigned long long>(s.hub_items)));
+            if (tid < 2) {      // (in one instruction: the adds of all bins to this line retire one after the other)
+                const unsigned long long before = atomicAdd(a.totals + tid, tid == 0 ? all : static_cast<unsigned long long>(s.hub_items));
+                if (tid == 0) s.base = before;
+                else s.hub_items = static_cast<uint32_t>(before);
             }
             __syncthreads();
             at += s.base;
