@@ -1658,16 +1658,14 @@ bool workspace_layout(int32_t dim, int64_t max_B, int32_t max_K, char* base, Wor
         p.totals = reinterpret_cast<unsigned long long*>(take(2 * sizeof(unsigned long long)));
     }
     w->list = reinterpret_cast<uint2*>(take(refs * sizeof(uint2)));
-    // two rows per pair or walk entry, a segment's entries twice and its context rows: never more than references
+    // two rows per pair or walk entry, a segment's entries twice and its context rows: never more than references, and as
+    // many where the batch is walks with window 1 and no negatives, which every handle accepts
     w->buf = reinterpret_cast<float*>(take(refs * static_cast<size_t>(dim) * 4));
     // (hub_accumulator)
     w->accs = refs / kItemRefs + 1;
     w->acc = reinterpret_cast<float*>(take(w->accs * static_cast<size_t>(dim) * 4));
     w->arrived = reinterpret_cast<uint32_t*>(take(w->accs * 4));
-    // what a caller is told to bring is never less than two rows and two words per reference, the bound that
-    // programs may have sized their buffers by; the difference is not used
-    const size_t bound = 2 * refs * (static_cast<size_t>(dim) + 1) * 4;
-    w->total_bytes = off > bound ? off : up(bound);
+    w->total_bytes = off;
     return true;
 }
 

@@ -135,8 +135,15 @@ def test_host_side_argument_errors():
 
 def test_workspace_bytes():
     w = ne.ne_workspace_bytes(128, 4096, 5)
-    refs = 4096 * 7
-    assert w >= 2 * refs * 128 * 4 + 2 * refs * 4
+    # per row reference: a buffer row, an eighth of an accumulator row and of its counter, a list entry, and three times
+    # its id, tag, bin entry, a quarter of a segment word, half a work item, 2/9 of a hub's work item; whatever is asked for
+    # beyond that is alignment and segment words of small batches
+    for dim, B, K in ((128, 4096, 5), (4, 65536, 0), (512, 32768, 10), (1024, 1, 0), (128, 65536, 5)):
+        refs = B * (K + 2)
+        laid_out = refs * (4 * dim + dim / 2 + 0.5 + 8 + 3 * (4 + 4 + 8 + 1 + 4 + 32 / 9))
+        assert 0.99 * laid_out <= ne.ne_workspace_bytes(dim, B, K) <= 1.01 * laid_out + 4 * dim + 65536
+    big = ne.NE_MAX_BATCH * 64      # 16 384 bins: half a segment word per reference
+    assert abs(ne.ne_workspace_bytes(4, ne.NE_MAX_BATCH, 62) / (big * (18.5 + 8 + 3 * (22 + 32 / 9))) - 1) < 0.01
     assert ne.ne_workspace_bytes(130, 4096, 5) == 0
     assert ne.ne_workspace_bytes(128, 0, 5) == 0
     assert ne.ne_workspace_bytes(128, 10, 63) == 0
