@@ -1,7 +1,6 @@
-"""Every setting of ne_set_tuning gives the oracle's result: rows that several references of a batch name
-collect their deltas through per-reference buffer rows (the first list_cap references), through atomics
-(the rest), or both, and the apply kernel sweeps 2, 4 or 8 positions per thread.  The inputs are hub-heavy so
-that rows with 1, 2..list_cap and more than list_cap references all occur in one batch."""
+"""Rows that several references of a batch name, on hub-heavy inputs: up to eight references of a row are one work item of
+the apply kernel, a row with more (a hub) has several, which one workgroup holds or several.  Every shape of the apply
+kernel, rows of both tables, pairs and walks, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -13,8 +12,6 @@ from test_gpu_walks import make, oracle_run
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-
-TUNINGS = [(0, 8), (0, 4), (0, 2), (1, 4), (3, 2), (8, 2), (8, 8), (-1, 0)]
 
 
 def say(msg):
@@ -30,14 +27,13 @@ def hub_ids(rng, V, shape):
     return ids.astype(np.int32).reshape(shape)
 
 
-@pytest.mark.parametrize("list_cap,sweep", TUNINGS)
-@pytest.mark.parametrize("V,d,K,B,n_pairs", [(3000, 128, 5, 700, 1900), (900, 512, 10, 150, 400), (400, 36, 2, 300, 300)])
-def test_pairs_with_tuning(V, d, K, B, n_pairs, list_cap, sweep):
-    say(f"pairs V={V} d={d} K={K} B={B} n={n_pairs} list_cap={list_cap} sweep={sweep}")
+@pytest.mark.parametrize("V,d,K,B,n_pairs", [(3000, 128, 5, 700, 1900), (900, 512, 10, 150, 400), (400, 36, 2, 300, 300),
+                                               (700, 1024, 2, 300, 800), (3000, 16, 62, 400, 900)])
+def test_pairs_among_hubs(V, d, K, B, n_pairs):
+    say(f"pairs V={V} d={d} K={K} B={B} n={n_pairs}")
     rng = np.random.default_rng(V + d + K)
     seed, base = 5, 77
     t = make(V, d, B, K, seed)
-    ne.ne_set_tuning(t, list_cap, sweep)
     deg = (rng.pareto(1.0, V) * 3).astype(np.uint32) + 1
     at = torch.empty((V, 2), dtype=torch.int32, device=DEV)
     alias = ne.ne_build_neg_alias(deg, 0, at)
@@ -62,7 +58,7 @@ def test_pairs_with_tuning(V, d, K, B, n_pairs, list_cap, sweep):
     named_c = np.zeros(V, bool); named_c[pairs[:, 1]] = True; named_c[neg.reshape(-1)] = True
     assert np.array_equal(Xg[~named_x].view(np.uint32), Xb[~named_x].view(np.uint32))
     assert np.array_equal(Cg[~named_c].view(np.uint32), Cb[~named_c].view(np.uint32))
-    # a second call on the same handle finds the hash state, the counters and the accumulators clean
+    # a second call on the same handle finds the accumulators clean
     ne.ne_train_block(t, alias, torch.from_numpy(pairs[:B]).to(DEV), B, K, lrs[:1], base)
     torch.cuda.synchronize()
     oracle.train_batch(Xo, Co, pairs[:B], neg[:B], lrs[0])
@@ -70,14 +66,13 @@ def test_pairs_with_tuning(V, d, K, B, n_pairs, list_cap, sweep):
     assert rowwise_rel_err(t.context.cpu().numpy(), Co) <= 1e-4 * (n_batches + 1)
 
 
-@pytest.mark.parametrize("list_cap,sweep", TUNINGS)
 @pytest.mark.parametrize("V,d,K,n,L,window,wpb", [
     (600, 128, 5, 30, 20, 5, 12),     # one lane group per walk entry
     (600, 128, 5, 30, 48, 5, 12),     # by segments of a workgroup's entries
     (500, 256, 3, 12, 32, 4, 5),
 ])
-def test_walks_with_tuning(V, d, K, n, L, window, wpb, list_cap, sweep):
-    say(f"walks V={V} d={d} K={K} n={n} L={L} window={window} per batch={wpb} list_cap={list_cap} sweep={sweep}")
+def test_walks_among_hubs(V, d, K, n, L, window, wpb):
+    say(f"walks V={V} d={d} K={K} n={n} L={L} window={window} per batch={wpb}")
     rng = np.random.default_rng(V + n + L)
     seed, sample_base = 22, 500
     deg = (rng.pareto(1.0, V) * 3).astype(np.uint32) + 1
@@ -85,7 +80,6 @@ def test_walks_with_tuning(V, d, K, n, L, window, wpb, list_cap, sweep):
     walks[0, L // 2:] = -1
     R = 1 + window * (K + 1)
     t = make(V, d, -(-(wpb * L * R) // (K + 2)), K, seed)
-    ne.ne_set_tuning(t, list_cap, sweep)
     at = torch.empty((V, 2), dtype=torch.int32, device=DEV)
     alias = ne.ne_build_neg_alias(deg, 0, at)
     thr, al, _ = oracle.build_alias(deg)
@@ -102,6 +96,7 @@ def test_walks_with_tuning(V, d, K, n, L, window, wpb, list_cap, sweep):
 
 
 def test_tuning_argument_errors():
+    """ne_set_tuning checks its arguments; they have no effect."""
     t = make(100, 8, 16, 2, 0)
     for bad in ((-2, 0), (9, 0), (0, 3), (0, 16), (0, -1)):
         with pytest.raises(ne.NeError):
@@ -109,27 +104,27 @@ def test_tuning_argument_errors():
     ne.ne_set_tuning(t, -1, 0)
 
 
-@pytest.mark.parametrize("list_cap", [0, 1, 2, 7, 8])
-@pytest.mark.parametrize("d", [128, 512])
-def test_exact_multiplicities_around_the_list_capacity(list_cap, d):
-    """Row k (k = 1..12) is named exactly k times as a source and row 100 + k exactly k times as a context, no
-    negatives: lists shorter than, as long as and one short of the number of references, in one batch."""
-    say(f"multiplicities 1..12, d={d}, list_cap={list_cap}")
-    V, K = 400, 0
-    src, ctx = [], []
-    for k in range(1, 13):
-        for i in range(k):
-            src.append(k); ctx.append(200 + 13 * k + i)          # source row k, k times, with distinct contexts
-            src.append(300 + (7 * k + i) % 90); ctx.append(100 + k)   # context row 100 + k, k times
-    rng = np.random.default_rng(d + list_cap)
-    order = rng.permutation(len(src))
-    pairs = np.stack([np.array(src)[order], np.array(ctx)[order]], axis=1).astype(np.int32)
+# work items hold 8 references; a workgroup's share of a hub is 8 per lane group: 256, 128, 64, 32, 32 and 32 references
+@pytest.mark.parametrize("d", [4, 64, 128, 256, 512, 1024])
+def test_multiplicities_around_the_work_items(d):
+    """Row i is named TIMES[i] times as a source and row 100 + i TIMES[i] times as a context, no negatives: one item, full and
+    not, several, as many as a workgroup takes and one more, and a hub of many workgroups, in one batch.
+
+    Bar: a row is a sum of n + 1 fp32 terms added at most 8, then 32, then n / 32 at a time; 1e-5 of its largest element
+    leaves a factor of two over the largest row's (n / 32 + 40) 2^-24 (here n = 4000)."""
+    times = [1, 2, 3, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 256, 257, 4000]
+    say(f"multiplicities up to {times[-1]}, d={d}")
+    n = sum(times)
+    V = 200 + 2 * n
+    hub = np.repeat(np.arange(len(times)), times)
+    other = 200 + np.arange(n)
+    pairs = np.concatenate([np.stack([hub, other], 1), np.stack([other + n, 100 + hub], 1)])
+    pairs = np.random.default_rng(d).permutation(pairs).astype(np.int32)
     B = pairs.shape[0]
-    t = make(V, d, B, K, 3)
-    ne.ne_set_tuning(t, list_cap, 0)
+    t = make(V, d, B, 0, 3)
     Xo, Co = t.vertex.cpu().numpy(), t.context.cpu().numpy()
-    for rep in range(2):       # the second batch finds counters, lists and accumulators clean
-        ne.ne_train_batch(t, None, torch.from_numpy(pairs).to(DEV), K, 0.05, 0)
+    for rep in range(2):       # the second batch finds the accumulators clean
+        ne.ne_train_batch(t, None, torch.from_numpy(pairs).to(DEV), 0, 0.05, 0)
         torch.cuda.synchronize()
         oracle.train_batch(Xo, Co, pairs, np.zeros((B, 0), np.int32), 0.05)
         ex = rowwise_rel_err(t.vertex.cpu().numpy(), Xo)

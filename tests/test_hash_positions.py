@@ -1,11 +1,12 @@
-"""Host-side check of the hash that the exact step's duplicate detection uses (ne_hash_position).
+"""Host-side check of the hash that the detection of rows named more than once uses (ne_hash_position).
 
-The detection stores each row key at its home position and resolves collisions by linear probing at load
-<= 1/2.  That only stays cheap if the home positions use the whole table: with B = 2^22 pairs and K = 10
-negatives a batch has 5e7 references and 2^27 positions.  The checks: the exported function equals the
-stated formula; for a 100 M-node id sample of that size the home positions cover the table evenly and a
-linear-probing insertion of all keys (simulated here, no GPU) has short probe sequences.  A hash of fixed
-width (for comparison: 25 bits, as an earlier version had) fails the same check by orders of magnitude.
+The exact step spreads a batch's references over bins by the hash's top bits and the rows of a bin over an LDS table by
+the bits below; the shared-negative step stores each row key at its home position in a table in memory.  Both
+resolve collisions by linear probing, which only stays cheap if bins and home positions are evenly used.  The checks:
+the exported function equals the stated formula; the distinct rows of a batch stay below what a bin's table takes;
+for a 100 M-node id sample the home positions cover a table of 2^27 evenly and a linear-probing insertion of all
+keys (simulated here, no GPU) has short probe sequences.  A hash of fixed width (for comparison: 25 bits) fails the
+same check by orders of magnitude.
 """
 import numpy as np
 import pytest
@@ -72,3 +73,27 @@ def test_small_tables_unchanged_in_quality():
     for positions in (1 << 20, 1 << 21):
         disp = probe_displacements(home_positions(ids, positions), positions)
         assert disp.max() < 64
+
+
+# bits of the bin, references per bin at most, distinct rows that a bin's table takes before it is gone through in ranges
+@pytest.mark.parametrize("bits,per_bin,full", [(5, 64, 255), (6, 128, 255), (8, 256, 640), (9, 1024, 1280), (12, 1024, 1280)])
+@pytest.mark.parametrize("ids", ["random", "run", "strided", "block"])
+def test_rows_per_bin_stay_below_its_table(bits, per_bin, full, ids):
+    """A batch whose references all name different rows, a third of them of the vertex table."""
+    n = per_bin << bits
+    rng = np.random.default_rng(bits)
+    rows = {"random": lambda m: rng.choice(100_000_000, m, replace=False),
+            "run": lambda m: 12_345 + np.arange(m),
+            "strided": lambda m: 16 * np.arange(m),
+            "block": lambda m: 25_000_000 + rng.choice(25_000_000, m, replace=False)}[ids]
+    x, c = rows(n // 3).astype(np.uint32), rows(n - n // 3).astype(np.uint32) | np.uint32(0x80000000)
+    keys = np.concatenate([x, c])
+    bins = home_positions(keys, 1 << bits)
+    most = np.bincount(bins, minlength=1 << bits).max()
+    assert most <= full, most
+    # inside a bin: the next bits spread its rows over twice as many slots or more
+    slots = 512 if full == 255 else 1024 if full == 640 else 2048
+    probe = ((keys.astype(np.uint64) * np.uint64(0x9E3779B1)) & np.uint64(0xFFFFFFFF)).astype(np.uint32)
+    home = (probe << np.uint32(bits)) >> np.uint32(32 - (slots.bit_length() - 1))
+    some = np.flatnonzero(bins == np.bincount(bins).argmax())
+    assert probe_displacements(home[some], slots).max() < slots // 2
