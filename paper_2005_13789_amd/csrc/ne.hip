@@ -1522,13 +1522,14 @@ hipError_t launch_train(const Shape& s, const TrainArgs& a, const Helpers& h, bo
 {
     const int groups = kTrainThreads / s.G;
     const TrainGrid g = train_grid(h, (a.B + groups - 1) / groups, direct ? static_cast<size_t>(kTrainThreads) * s.NCH * sizeof(float4) : 0);
-    // context rows gathered together per lane group: 6 where they come out nearly even (K = 5: 1.7 % ahead of 2 on
-    // 32 M nodes, dim 128), else 3 (K = 7: 6 would be 2 % behind); the per-sample mode's atomics leave 2 ahead by 1 - 2 %
-    const bool six = (a.K + 1) % 6 == 0 || (a.K + 1) % 6 >= 4;
+    // context rows gathered together per lane group: 6 where they come out nearly even and a lane has one chunk of a row
+    // (K = 5: 1.7 % ahead of 2 on 32 M nodes, dim 128; K 3 .. 10 at dim 64 .. 256: 2 % behind .. 5 % ahead of 3), else 3 (K = 7:
+    // 6 would be 2 % behind; dim 512 .. 1024: up to 4 % behind); the per-sample mode's atomics leave 2 ahead by 1 - 2 %
+    const bool six = s.NCH == 1 && ((a.K + 1) % 6 == 0 || (a.K + 1) % 6 >= 4);
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
         if (direct) hipLaunchKernelGGL((train_kernel<G_, N_, 2, true>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
-        else if (six) hipLaunchKernelGGL((train_kernel<G_, N_, 6, false>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
+        else if (six) hipLaunchKernelGGL((train_kernel<G_, N_, N_ == 1 ? 6 : 3, false>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
         else hipLaunchKernelGGL((train_kernel<G_, N_, 3, false>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
         return hipGetLastError();                                                                \
     }
@@ -1621,7 +1622,8 @@ hipError_t launch_loss(const Shape& s, const LossArgs& a, hipStream_t st)
 {
     const int groups = 256 / s.G;
     // workgroups: enough to fill the chip, few enough for their atomic adds to one address to hide (65 536 pairs,
-    // dim 128, K = 5: 512 .. 1024 take 44 - 45 us with the caller's zero-fill, 2048 54, one per 8 pairs 118)
+    // dim 128, K = 5: 512 .. 1024 take 44 - 45 us with the caller's zero-fill, 2048 54, one per 8 pairs 118; at dim
+    // 16 .. 1024 384 are up to 38 % behind on a million pairs and 23 % ahead on 4096, 1536 up to 40 % behind)
     const int64_t want = (a.B + groups - 1) / groups;
     const unsigned grid = static_cast<unsigned>(want < 768 ? want : 768);
 #define NE_CASE(G_, N_)                                                                          \
