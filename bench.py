@@ -166,7 +166,7 @@ def main():
         workspace = torch.empty(ne.ne_workspace_bytes(d, B, K), dtype=torch.uint8, device=dev)
 
     def fresh_tables():
-        """Both tables initialised again on the device (vertex uniform, context zero), workspace cleared."""
+        """Both tables initialised again on the device (vertex uniform, context zero), the workspace's accumulators cleared."""
         if N:
             return ne.ne_create_tables(vertex, context, seed, init=True)
         return ne.ne_create_tables(vertex, context, seed, init=True, max_batch=B, max_negatives=K, workspace=workspace)

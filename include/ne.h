@@ -313,7 +313,7 @@ ne_status ne_score_pairs(const ne_tables* tables, const int32_t* pairs_dev, int6
 /*
  * Former tuning of the exact step: how a row that several references of a batch name collected their
  * deltas (list_cap: -1 or 0..8) and how finely hash positions were swept (sweep_per_thread: 0, 2, 4 or 8).
- * Neither choice exists any more: such a row has one buffer row per reference, and nothing is swept.  The
+ * Neither choice exists any more: such a row has a list of coefficients and rows, and nothing is swept.  The
  * arguments are checked as before and change nothing.  Errors: NE_ERR_ARG.
  */
 ne_status ne_set_tuning(ne_tables* tables, int32_t list_cap, int32_t sweep_per_thread);

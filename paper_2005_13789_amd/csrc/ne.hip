@@ -86,10 +86,10 @@ __global__ __launch_bounds__(256) void init_tables_kernel(float4* __restrict__ X
 // that emptied the table again).  Here an entry is written once into a tile-local run of its bin and
 // read once from there, runs of a few entries are one transaction, and everything that needs an
 // atomic happens in LDS.  Bound by the latency of four dependent accesses per workgroup (segment words,
-// entries, the counter, nothing after it); riding in the train launch both phases together add 11 - 16 us to
+// entries, the totals, nothing after them); riding in the train launch both phases together add 11 - 16 us to
 // its 77 us (32 M nodes, dim 128, 65 536 pairs), of which the random reads of the alias table are about half.
 // A batch of 65 536 pairs, K = 5, before and with this detection and the lists below: 1 M nodes 164 - 175 -> 119 us,
-// 32 M nodes 144 -> 122 us; 4096 pairs in one call 41 -> 29 us.
+// 32 M nodes 144 -> 122 us; 4096 pairs in one call 41 -> 29.5 us.
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
 // How the references of a batch are binned.
@@ -481,7 +481,7 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
 }
 
 // One bin of references: all entries of a row are in it.  An LDS hash table counts each row's entries;
-// rows with more than one get their place in the delta buffer and their work items; then every entry of
+// rows with more than one get their places in the list and their work items; then every entry of
 // such a row takes the next of the row's places.  A bin whose distinct rows do not fit the table is
 // gone through in ranges of the hash, halved until they fit: the hash is a bijection of the key, so a range
 // of 2^k values holds at most 2^k rows and the halving ends.
@@ -658,7 +658,7 @@ __device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, uns
 // ---------------------------------------------------------------------------------------------
 // sample prefetch (ne_train_block_pinned): a few workgroups copy the pairs of a later batch from
 // pinned host memory, which they read directly, into a device staging ring.  They ride inside the
-// training launches; the first two batches of a call use the stand-alone kernel.
+// training launches; the first three batches of a call use the stand-alone kernel.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ void fetch_pairs(const int2* __restrict__ src, int2* __restrict__ dst, int64_t n, int64_t i0,
                                             int64_t stride)
@@ -745,7 +745,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(Helpers h, bool claim_firs
 // train kernel.  G lanes per pair, NCH float4 chunks per lane (chunk index = lg + i*G, valid while
 // < d4), JB context rows in flight at a time.
 // DIRECT: the per-sample mode (ne_train_block_async): a shared row's deltas go straight to the table row
-// with atomics instead of to the delta buffer, so pairs that read the row later see them, and nothing is
+// with atomics instead of to the list, so pairs that read the row later see them, and nothing is
 // left for the apply phase.
 // ---------------------------------------------------------------------------------------------
 struct TrainArgs {
@@ -1636,7 +1636,7 @@ hipError_t launch_loss(const Shape& s, const LossArgs& a, hipStream_t st)
     return hipErrorInvalidValue;
 }
 
-// Largest batch: keeps every grid and the hash capacity inside 32 bits.
+// Largest batch: its references stay below 2^28, so that places of the list fit a work item's 29 bits and grids 32.
 constexpr int64_t kMaxBatch = static_cast<int64_t>(1) << 22;
 // helper workgroups that prefetch the samples of a later batch from pinned host memory (512 KB per batch of 65536)
 constexpr unsigned kFetchBlocks = 8;
