@@ -1204,8 +1204,8 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
 // Bound by the rows it moves (two thirds of the rows have two references) and, in small batches, by its chain
 // of four dependent accesses: item, entries, rows, store.  The rows of buf are few (one or two per pair, however
 // many references share them) and mostly still in the last-level cache; per-reference deltas in memory order
-// instead cost here and in the train kernel 28 + 98 us at 32 M nodes x dim 128 (now 28 + 91), 47 + 94 at 1 M x
-// dim 128 (now 43 + 76) and 151 + 285 at 4 M x dim 512, K = 10 (now 96 + 218).  8 entries at a time against 4: -1 .. -2 % of a batch at dim <= 256,
+// instead cost here and in the train kernel 28 + 98 us at 32 M nodes x dim 128 (now 28 + 90), 47 + 94 at 1 M x
+// dim 128 (now 39 + 77) and 151 + 285 at 4 M x dim 512, K = 10 (now 99 + 216).  8 entries at a time against 4: -1 .. -2 % of a batch at dim <= 256,
 // +2 % at dim 512 (registers).
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
