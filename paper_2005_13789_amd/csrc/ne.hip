@@ -5,12 +5,12 @@
 //
 //   claim, resolve (ids only)  find out which rows several references of the batch name (a reference:
 //          the source, the context or one of the K negatives of a pair).  claim takes the references
-//          tile by tile: draws the negatives (Philox + alias table) and writes the tile's (key,
-//          reference) entries sorted by a hash of the key into bins.  resolve takes one bin per
+//          tile by tile: draws the negatives (Philox + alias table) and writes the tile's entries (a row's key, for one
+//          reference or for all that a tile has of a hub), sorted by a hash of the key into bins.  resolve takes one bin per
 //          workgroup: all entries of a row meet in one hash table in LDS.  A row with n > 1 references
-//          gets n consecutive places in a list, one per reference (its tag), and ceil(n / 8)
-//          work items for the apply kernel.  Nothing goes through atomics in memory but an add or two
-//          per bin to the batch's totals, and no state has to be cleared between batches.
+//          gets n consecutive places in a list, one per reference, and ceil(n / 8)
+//          work items for the apply kernel; an entry's place goes where the entry lies (its tag).  Nothing goes through atomics in
+//          memory but one add per bin to the batch's totals, and no state has to be cleared between batches.
 //   train  one lane group per pair: gathers x = vertex[src] and the K+1 context rows (dwordx4),
 //          reduces the K+1 dot products with DPP, forms g_j and the deltas.  A row that only this
 //          pair names is rewritten in place from registers (old + delta, one plain store: the row
@@ -85,11 +85,13 @@ __global__ __launch_bounds__(256) void init_tables_kernel(float4* __restrict__ X
 // for every lost position (measured at 458 752 references: 28 us of a 134 us batch, plus a linear pass
 // that emptied the table again).  Here an entry is written once into a tile-local run of its bin and
 // read once from there, runs of a few entries are one transaction, and everything that needs an
-// atomic happens in LDS.  Bound by the latency of four dependent accesses per workgroup (segment words,
-// entries, the totals, nothing after them); riding in the train launch both phases together add 11 - 16 us to
-// its 77 us (32 M nodes, dim 128, 65 536 pairs), of which the random reads of the alias table are about half.
-// A batch of 65 536 pairs, K = 5, before and with this detection and the lists below: 1 M nodes 164 - 175 -> 119 us,
-// 32 M nodes 144 -> 122 us; 4096 pairs in one call 41 -> 29.5 us.
+// atomic happens in LDS.  Riding in the train launch both phases together add 11 - 15 us to
+// its 61 us (1 M nodes, dim 128, 65 536 pairs) or 75 us (32 M).  What that is, found by leaving parts of one batch's resolve phase out
+// (its outputs were not needed): tags stored reference by reference, 4 bytes here and there, 4.5 us where as many side by
+// side take 0.4 (eight dies hold the same lines in part and each writes its part back), so a tag goes to its entry's place, and
+// the reference keeps where that is; a second add per bin to the line of the totals 2.5 us (adds to a line retire one after
+// the other, and rows behind the same channel wait); in the claim phase the alias table's random reads, 5 us (32 M nodes).
+// Entries, ids, Philox, LDS: written, read or done twice, they cost nothing more.
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
 // How the references of a batch are binned.
@@ -108,15 +110,11 @@ constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 //          instead of 79, 64 ranges and 8.)
 //   tile   references per claim workgroup: at least 4 per bin, so that runs of a bin's entries are worth an
 //          access and the segment table stays a quarter of the entries; 2 beyond 4096 bins, where tiles are few and long.
-//   lanes  per tile segment in the resolve phase: a power of two, half as many again as a segment has entries on
-//          average, so that most segments are one access (a fixed 8 took 43 us for a batch of 64 pairs, whose two
-//          bins are one segment of 224 entries each, where 1 pair takes 17).
 //   slots  of a bin's LDS table (4096 only for the batches whose claim counters take 32 KB as well), and the distinct
-//          rows (full) at which it counts as too small: each of the 256 threads may add one more after that, and one
-//          slot has to stay empty.
-struct Binning { uint32_t bits, tile, tiles, lane_bits, slot_bits, full; };
+//          rows (full) at which it counts as too small, where a bin is gone through in passes.
+struct Binning { uint32_t bits, tile, tiles, slot_bits, full; };
 constexpr uint32_t kWordBinBits = 12, kMaxBinBits = 14;      // most bins whose claim counters are whole words; most bins
-constexpr uint32_t kMinTile = 1024;
+constexpr uint32_t kMinTile = 256;
 constexpr uint64_t kOneBin = 256;
 constexpr struct { uint32_t bits; uint64_t refs; } kBinSteps[] = {{5, 64}, {6, 128}, {8, 256}, {kWordBinBits, 1024}, {kMaxBinBits, 1200}};   // most references per bin, up to 2^bits bins
 inline Binning binning(uint64_t refs)
@@ -128,8 +126,6 @@ inline Binning binning(uint64_t refs)
     b.tile = (b.bits > kWordBinBits ? 2u : 4u) << b.bits;
     if (b.tile < kMinTile) b.tile = kMinTile;
     b.tiles = static_cast<uint32_t>((refs + b.tile - 1) / b.tile);
-    b.lane_bits = 2;
-    while (b.lane_bits < 8 && (static_cast<uint64_t>(b.tiles) << (b.bits + b.lane_bits)) < refs + refs / 2) ++b.lane_bits;
     const uint64_t mean = refs >> b.bits;
     b.slot_bits = mean <= 128 ? 9 : mean <= 400 ? 10 : mean <= 1200 ? 11 : 12;
     b.full = b.slot_bits == 9 ? 255u : (5u << b.slot_bits) / 8u;
@@ -157,11 +153,12 @@ struct PrepArgs {
     int32_t alias_base;
     Binning bin;
     int32_t* ids;
-    uint32_t* tag;
+    uint32_t* where;
     uint2* items;
     uint4* hub_items;
     unsigned long long* totals;
-    unsigned long long* entries;
+    uint32_t* keys;
+    uint32_t* tags;
     uint32_t* segs;
     int32_t* neg_out;
     // sample prefetch riding along (ne_train_block_pinned): fetch_blocks helper workgroups copy fetch_n
@@ -174,49 +171,75 @@ struct PrepArgs {
 
 __device__ __forceinline__ uint32_t bin_of(uint32_t key, uint32_t bits) { return bits ? hash_bits(key) >> (32u - bits) : 0u; }
 
-// Drawing a reference's id is a chain of dependent memory accesses with next to no arithmetic, so each
-// thread runs kPrepUnroll references at once: 256 * kPrepUnroll consecutive references per step.
-constexpr int kPrepUnroll = 4;
+// Drawing a reference's id is a chain of dependent memory accesses with next to no arithmetic, so each thread
+// draws several references at once, all loads of which are issued before the first is waited for: the functions below
+// take U references per thread, first + u * T + tid < last for u < U, and return their keys (kNoKey where there is none);
+// ids and requested negatives go to memory.
+// Everything here comes for workgroups of T = 256 threads, which ride in train launches, and of 1024, for launches of its own
+// that leave most of the chip idle (launch_prepare).
+constexpr uint32_t kTileStep = 2048;       // references per workgroup and step, whose keys stay in registers
+template <uint32_t T> constexpr int kTileKeys = kTileStep / T;
 
-// The references first + u * 256 + tid < last, u < kPrepUnroll: their keys (kNoKey where there is none); ids and
-// requested negatives go to memory.
-__device__ __forceinline__ void claim_pair_refs(const PrepArgs& a, uint32_t first, uint32_t last, unsigned tid, uint32_t (&key)[kPrepUnroll])
+// Philox words of a negative: its slot of the alias table and the word that decides between slot and alias.
+__device__ __forceinline__ uint2 draw_slot(const PrepArgs& a, uint64_t sample, uint32_t k)
+{
+    const uint4 rnd = philox4x32_10(make_uint4(static_cast<uint32_t>(sample), static_cast<uint32_t>(sample >> 32), k, kStreamNegative), a.k0, a.k1);
+    const uint32_t n = static_cast<uint32_t>(a.alias_n);      // (below 2^31)
+    return make_uint2(static_cast<uint32_t>((static_cast<uint64_t>(rnd.x) * n + __umulhi(rnd.y, n)) >> 32), rnd.z);
+}
+__device__ __forceinline__ uint32_t drawn_id(const PrepArgs& a, uint2 draw, uint2 entry)
+{
+    return static_cast<uint32_t>(a.alias_base) + (draw.y < entry.x ? draw.x : entry.y);
+}
+
+template <int U, uint32_t T>
+__device__ __forceinline__ void claim_pair_refs(const PrepArgs& a, uint32_t first, uint32_t last, unsigned tid, uint32_t* key)
 {
     const uint32_t R = a.R;
-    // per reference: a negative's alias entry, slot and third Philox word; else the pair, and which half of it.
+    // per reference: a negative's alias entry and draw; else the pair, and which half of it.
     // (A wavefront has references of every kind, so all lanes draw, and one load serves both kinds.)
-    uint2 e[kPrepUnroll];
-    uint32_t slot[kPrepUnroll], keep[kPrepUnroll];
+    uint2 e[U], draw[U];
+    uint32_t sources = 0u, negatives = 0u;        // a bit per reference
+    const uint32_t step_b = T / R, step_j = T - step_b * R;
+    uint32_t t0 = min(first + tid, last - 1u), b = t0 / R, j = t0 - b * R;
 #pragma unroll
-    for (int u = 0; u < kPrepUnroll; ++u) {
-        const uint32_t t = min(first + u * 256u + tid, last - 1u);
-        const uint32_t b = t / R, j = t - b * R;
-        const uint64_t sample = a.sample_base + b;
-        const uint4 rnd = philox4x32_10(make_uint4(static_cast<uint32_t>(sample), static_cast<uint32_t>(sample >> 32),
-                                                   j - 2u, kStreamNegative), a.k0, a.k1);
-        slot[u] = static_cast<uint32_t>(__umul64hi((static_cast<uint64_t>(rnd.x) << 32) | rnd.y, a.alias_n));   // (n < 2^31)
-        keep[u] = rnd.z;
-        const uint2* from = j < 2u ? reinterpret_cast<const uint2*>(a.pairs) + b : a.alias + slot[u];
+    for (int u = 0; u < U; ++u) {
+        if (first + u * T >= last) break;         // (uniform)
+        draw[u] = draw_slot(a, a.sample_base + b, j - 2u);
+        const uint2* from = j < 2u ? reinterpret_cast<const uint2*>(a.pairs) + b : a.alias + draw[u].x;
         e[u] = *from;
+        sources |= static_cast<uint32_t>(j == 0u) << u;
+        negatives |= static_cast<uint32_t>(j >= 2u) << u;
+        if (first + (u + 1) * T + tid < last) {       // (else this one again)
+            b += step_b;
+            j += step_j;
+            if (j >= R) { j -= R; b += 1u; }
+        }
         __builtin_amdgcn_sched_barrier(0);   // one draw's registers at a time; the loads stay in flight
     }
 #pragma unroll
-    for (int u = 0; u < kPrepUnroll; ++u) {
-        const uint32_t t = first + u * 256u + tid;
+    for (int u = 0; u < U; ++u) {
+        const uint32_t t = first + u * T + tid;
         key[u] = kNoKey;
         if (t < last) {
-            const uint32_t b = t / R, j = t - b * R;
-            uint32_t id = j == 0u ? e[u].x : e[u].y;
-            if (j >= 2u) {
-                id = static_cast<uint32_t>(a.alias_base) + (keep[u] < e[u].x ? slot[u] : e[u].y);
-                if (a.neg_out) a.neg_out[static_cast<int64_t>(b) * a.K + (j - 2u)] = static_cast<int32_t>(id);
+            const bool source = sources >> u & 1u, negative = negatives >> u & 1u;
+            const uint32_t id = negative ? drawn_id(a, draw[u], e[u]) : source ? e[u].x : e[u].y;
+            if (negative && a.neg_out) {
+                uint32_t at = t;
+                asm volatile("" : "+v"(at));         // (the division is not worth a register each until here)
+                a.neg_out[static_cast<int64_t>(at) - 2 * static_cast<int64_t>(at / R) - 2] = static_cast<int32_t>(id);
             }
             a.ids[t] = static_cast<int32_t>(id);
-            key[u] = id | (j == 0u ? 0u : 0x80000000u);
+            key[u] = id | (source ? 0u : 0x80000000u);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 }
+
+// What a reference of the walk modes is: its kind (0 a source's row, 1 a context's row, 2 a negative), the walk, the two
+// entries of it that decide whether the reference exists (of a source's row the entry and the one after it, of a context's
+// row the last of its sources and itself), and a negative's sample of the batch and number.
+struct WalkRef { uint32_t kind, walk, i, c, sample, k; };
 
 // Walk mode (on-device augmentation, Algorithm 1 "network augmentation"): the batch is a set of
 // walks int32 [n][L]; position i of a walk is the source of the pairs (walk[i], walk[i+j]),
@@ -225,66 +248,13 @@ __device__ __forceinline__ void claim_pair_refs(const PrepArgs& a, uint32_t firs
 //   1 + (j-1)(K+1)             the context row of pair j
 //   1 + (j-1)(K+1) + 1 + k     negative k of pair j, drawn for sample index sample_base + p*window + (j-1)
 // Absent references get id -1 and no key.
-__device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, uint32_t first, uint32_t last, unsigned tid, uint32_t (&key)[kPrepUnroll])
+__device__ __forceinline__ WalkRef walk_ref(const PrepArgs& a, uint32_t t)
 {
-    const uint32_t R = a.R;
     const uint32_t L = static_cast<uint32_t>(a.walk_len), W = static_cast<uint32_t>(a.window), K1 = static_cast<uint32_t>(a.K + 1);
-    uint32_t t[kPrepUnroll], p[kPrepUnroll], jj[kPrepUnroll];
-    int kk[kPrepUnroll];     // -2: source, -1: context, >= 0: negative k
-    int32_t id[kPrepUnroll];
-    bool valid[kPrepUnroll];
-    uint32_t keep[kPrepUnroll];
-    uint2 entry[kPrepUnroll];
-    uint32_t draw_slot[kPrepUnroll];   // (the table has fewer than 2^31 entries)
-#pragma unroll
-    for (int u = 0; u < kPrepUnroll; ++u) {
-        t[u] = first + u * 256u + tid;
-        id[u] = -1;
-        valid[u] = false;
-        kk[u] = -2;
-        jj[u] = 0;
-        p[u] = 0;
-        if (t[u] < last) {
-            p[u] = t[u] / R;
-            const uint32_t q = t[u] - p[u] * R;
-            const uint32_t r = p[u] / L, i = p[u] - r * L;
-            const int32_t* wk = a.walks + static_cast<int64_t>(r) * L;
-            const int32_t src = wk[i];
-            if (q == 0) {
-                bool has = false;
-                for (uint32_t j = 1; j <= W && i + j < L; ++j) has = has || wk[i + j] >= 0;
-                valid[u] = src >= 0 && has;
-                id[u] = src;
-            } else {
-                jj[u] = (q - 1) / K1;
-                kk[u] = static_cast<int>(q - 1 - jj[u] * K1) - 1;
-                const uint32_t c = i + jj[u] + 1;
-                const int32_t ctx = c < L ? wk[c] : -1;
-                valid[u] = src >= 0 && ctx >= 0;
-                id[u] = ctx;
-                if (valid[u] && kk[u] >= 0) {
-                    const uint64_t sample = a.sample_base + static_cast<uint64_t>(p[u]) * W + jj[u];
-                    const uint4 rnd = philox4x32_10(make_uint4(static_cast<uint32_t>(sample), static_cast<uint32_t>(sample >> 32),
-                                                      static_cast<uint32_t>(kk[u]), kStreamNegative), a.k0, a.k1);
-                    draw_slot[u] = static_cast<uint32_t>(__umul64hi((static_cast<uint64_t>(rnd.x) << 32) | rnd.y, a.alias_n));
-                    keep[u] = rnd.z;
-                    entry[u] = a.alias[draw_slot[u]];
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < kPrepUnroll; ++u) {
-        key[u] = kNoKey;
-        if (t[u] >= last) continue;
-        if (valid[u] && kk[u] >= 0) {
-            id[u] = a.alias_base + static_cast<int32_t>(keep[u] < entry[u].x ? draw_slot[u] : entry[u].y);
-            if (a.neg_out) a.neg_out[(static_cast<int64_t>(p[u]) * W + jj[u]) * a.K + kk[u]] = id[u];
-        }
-        if (!valid[u]) id[u] = -1;
-        a.ids[t[u]] = id[u];
-        if (valid[u]) key[u] = static_cast<uint32_t>(id[u]) | (kk[u] == -2 ? 0u : 0x80000000u);
-    }
+    const uint32_t p = t / a.R, q = t - p * a.R, r = p / L, i = p - r * L;
+    if (q == 0) return {0u, r, i, i + 1, 0u, 0u};
+    const uint32_t j = (q - 1) / K1, k = q - 1 - j * K1;
+    return {k == 0u ? 1u : 2u, r, i, i + j + 1, p * W + j, k - 1u};
 }
 
 // Walk mode by segments: a walk is cut into segments of E = seg_entries consecutive entries, one
@@ -296,99 +266,90 @@ __device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, uint32_t firs
 //                            entries has it as a sample's context (the last window-1 of them belong
 //                            to the next segment's entries too: both segments name them)
 //   E + CT + (e*window + j-1)*K + k   negative k of sample (entry p0 + e, offset j)
-__device__ __forceinline__ void claim_seg_refs(const PrepArgs& a, uint32_t first, uint32_t last, unsigned tid, uint32_t (&key)[kPrepUnroll])
+__device__ __forceinline__ WalkRef seg_ref(const PrepArgs& a, uint32_t t)
 {
-    const uint32_t R = a.R, E = a.seg_entries;
     const uint32_t L = static_cast<uint32_t>(a.walk_len), W = static_cast<uint32_t>(a.window), K = static_cast<uint32_t>(a.K);
-    const uint32_t CT = E + W - 1;
-    uint32_t t[kPrepUnroll], samp[kPrepUnroll];
-    int kk[kPrepUnroll];     // -2: vertex row, -1: context row, >= 0: negative k
-    int32_t id[kPrepUnroll];
-    bool valid[kPrepUnroll];
-    uint32_t keep[kPrepUnroll];
-    uint2 entry[kPrepUnroll];
-    uint32_t draw_slot[kPrepUnroll];   // (the table has fewer than 2^31 entries)
+    const uint32_t E = a.seg_entries, CT = E + W - 1;
+    const uint32_t seg = t / a.R, q = t - seg * a.R, r = seg / a.segs_per_walk, p0 = (seg - r * a.segs_per_walk) * E;
+    if (q < E) return {0u, r, p0 + q, p0 + q + 1, 0u, 0u};
+    if (q < E + CT) {
+        const uint32_t c = p0 + 1 + (q - E);
+        return {1u, r, min(c - 1, p0 + E - 1), c, p0, 0u};       // (sample: the first entry that can be its source)
+    }
+    const uint32_t n = q - E - CT, pj = n / K, e = pj / W, j = pj - e * W;     // pj = e * W + (j - 1)
+    return {2u, r, p0 + e, p0 + e + j + 1, (r * L + p0 + e) * W + j, n - pj * K};
+}
+
+template <int U, bool SEG, uint32_t T>
+__device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, uint32_t first, uint32_t last, unsigned tid, uint32_t* key)
+{
+    const uint32_t L = static_cast<uint32_t>(a.walk_len), W = static_cast<uint32_t>(a.window);
+    auto ref = [&](uint32_t t) { return SEG ? seg_ref(a, t) : walk_ref(a, t); };
+    // the draw does not wait for the walk's entries, which say whether it is needed (when it did, four times in turn: 17
+    // instead of 22 us for the first claim of 170 walks of 80 entries, 5.6 instead of 4.8 for 22 of 40)
+    int32_t src[U], ctx[U];
+    uint2 e[U], draw[U];
 #pragma unroll
-    for (int u = 0; u < kPrepUnroll; ++u) {
-        t[u] = first + u * 256u + tid;
-        id[u] = -1;
-        valid[u] = false;
-        kk[u] = -2;
-        samp[u] = 0;
-        if (t[u] < last) {
-            const uint32_t seg = t[u] / R, q = t[u] - seg * R;
-            const uint32_t r = seg / a.segs_per_walk, p0 = (seg - r * a.segs_per_walk) * E;
-            const int32_t* wk = a.walks + static_cast<int64_t>(r) * L;
-            if (q < E) {
-                const uint32_t i = p0 + q;
-                if (i < L) {
-                    bool has = false;
-                    for (uint32_t j = 1; j <= W && i + j < L; ++j) has = has || wk[i + j] >= 0;
-                    id[u] = wk[i];
-                    valid[u] = id[u] >= 0 && has;
-                }
-            } else if (q < E + CT) {
-                kk[u] = -1;
-                const uint32_t c = p0 + 1 + (q - E);
-                if (c < L) {
-                    // sources of this segment that have entry c inside their window
-                    const uint32_t lo = c > p0 + W ? c - W : p0, hi = (c - 1 < p0 + E - 1) ? c - 1 : p0 + E - 1;
-                    bool has = false;
-                    for (uint32_t i = lo; i <= hi; ++i) has = has || wk[i] >= 0;
-                    id[u] = wk[c];
-                    valid[u] = id[u] >= 0 && has;
-                }
-            } else {
-                const uint32_t n = q - E - CT, pj = n / K;    // pj = e * W + (j - 1)
-                kk[u] = static_cast<int>(n - pj * K);
-                const uint32_t e = pj / W, j = pj - e * W + 1, i = p0 + e;
-                if (i + j < L) {
-                    valid[u] = wk[i] >= 0 && wk[i + j] >= 0;
-                    samp[u] = (r * L + i) * W + (j - 1);
-                    if (valid[u]) {
-                        const uint64_t sample = a.sample_base + samp[u];
-                        const uint4 rnd = philox4x32_10(make_uint4(static_cast<uint32_t>(sample), static_cast<uint32_t>(sample >> 32),
-                                                          static_cast<uint32_t>(kk[u]), kStreamNegative), a.k0, a.k1);
-                        draw_slot[u] = static_cast<uint32_t>(__umul64hi((static_cast<uint64_t>(rnd.x) << 32) | rnd.y, a.alias_n));
-                        keep[u] = rnd.z;
-                        entry[u] = a.alias[draw_slot[u]];
-                    }
-                }
-            }
+    for (int u = 0; u < U; ++u) {
+        if (first + u * T >= last) break;         // (uniform)
+        const WalkRef w = ref(min(first + u * T + tid, last - 1u));
+        const int32_t* wk = a.walks + static_cast<int64_t>(w.walk) * L;
+        src[u] = wk[min(w.i, L - 1u)];
+        ctx[u] = wk[min(w.c, L - 1u)];
+        if (w.i >= L) src[u] = -1;
+        if (w.c >= L) ctx[u] = -1;
+        if (a.K > 0) {
+            draw[u] = draw_slot(a, a.sample_base + w.sample, w.k);
+            e[u] = a.alias[w.kind == 2u ? draw[u].x : 0u];
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int u = 0; u < kPrepUnroll; ++u) {
+    for (int u = 0; u < U; ++u) {
+        const uint32_t t = first + u * T + tid;
         key[u] = kNoKey;
-        if (t[u] >= last) continue;
-        if (valid[u] && kk[u] >= 0) {
-            id[u] = a.alias_base + static_cast<int32_t>(keep[u] < entry[u].x ? draw_slot[u] : entry[u].y);
-            if (a.neg_out) a.neg_out[static_cast<int64_t>(samp[u]) * a.K + kk[u]] = id[u];
+        if (t < last) {
+            const WalkRef w = ref(t);
+            const int32_t* wk = a.walks + static_cast<int64_t>(w.walk) * L;
+            bool valid = src[u] >= 0 && ctx[u] >= 0;
+            int32_t id = ctx[u];
+            if (w.kind == 0u) {
+                id = src[u];
+                if (id >= 0)
+                    for (uint32_t c = w.i + 2; !valid && c <= w.i + W && c < L; ++c) valid = wk[c] >= 0;
+            } else if (w.kind == 1u) {
+                // (by segments) other entries of this segment that have c inside their window
+                if (SEG && ctx[u] >= 0)
+                    for (uint32_t i = w.c > w.sample + W ? w.c - W : w.sample; !valid && i < w.i; ++i) valid = wk[i] >= 0;
+            } else if (valid) {
+                id = static_cast<int32_t>(drawn_id(a, draw[u], e[u]));
+                if (a.neg_out) a.neg_out[static_cast<int64_t>(w.sample) * a.K + w.k] = id;
+            }
+            a.ids[t] = valid ? id : -1;
+            if (valid) key[u] = static_cast<uint32_t>(id) | (w.kind == 0u ? 0u : 0x80000000u);
         }
-        if (!valid[u]) id[u] = -1;
-        a.ids[t[u]] = id[u];
-        if (valid[u]) key[u] = static_cast<uint32_t>(id[u]) | (kk[u] == -2 ? 0u : 0x80000000u);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// Exclusive prefix sum over the 256 threads of a workgroup; *total receives the sum.  part: 4 values in LDS.
-template <class T>
-__device__ __forceinline__ T block_exclusive_scan(T v, T* part, T* total)
+// Exclusive prefix sum over the T threads of a workgroup; *total receives the sum.  part: T / 64 values in LDS.
+template <uint32_t T, class V>
+__device__ __forceinline__ V block_exclusive_scan(V v, V* part, V* total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    T inc = v;
+    V inc = v;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-        const T o = __shfl_up(inc, off, 64);
+        const V o = __shfl_up(inc, off, 64);
         if (lane >= off) inc += o;
     }
-    __syncthreads();            // part may still be read from an earlier scan
+    lds_barrier();              // part may still be read from an earlier scan
     if (lane == 63) part[wave] = inc;
-    __syncthreads();
-    T before = 0, sum = 0;
+    lds_barrier();
+    V before = 0, sum = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const T p = part[w];
+    for (int w = 0; w < static_cast<int>(T / 64); ++w) {
+        const V p = part[w];
         if (w < wave) before += p;
         sum += p;
     }
@@ -396,82 +357,267 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T* part, T* total)
     return before + inc - v;
 }
 
-// LDS of the claim phase: a counter per bin (beyond 2^kWordBinBits bins 16 bits each) and the scan's four words.
+// The same over v, and the sum of w beside it.  part: T / 32 values in LDS.
+template <uint32_t T>
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t w, uint32_t* part, uint32_t* total_v, uint32_t* total_w)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t inc = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(inc, off, 64);
+        w += __shfl_xor(w, off, 64);
+        if (lane >= off) inc += o;
+    }
+    lds_barrier();              // part may still be read from an earlier scan
+    if (lane == 63) { part[wave] = inc; part[T / 64 + wave] = w; }
+    lds_barrier();
+    uint32_t before = 0, sum_v = 0, sum_w = 0;
+#pragma unroll
+    for (int q = 0; q < static_cast<int>(T / 64); ++q) {
+        const uint32_t p = part[q];
+        if (q < wave) before += p;
+        sum_v += p;
+        sum_w += part[T / 64 + q];
+    }
+    *total_v = __builtin_amdgcn_readfirstlane(sum_v);
+    *total_w = __builtin_amdgcn_readfirstlane(sum_w);
+    return before + inc - v;
+}
+
+// LDS of the claim phase: a counter per bin (beyond 2^kWordBinBits bins 16 bits each), the scan's 32 words and, if they
+// are one step's, the tile's entries and what claim_rows needs to find them.
 __host__ __device__ inline uint32_t counter_words(uint32_t bits) { return bits > kWordBinBits ? 1u << (bits - 1u) : 1u << bits; }
-inline size_t claim_lds_bytes(const Binning& b) { return (static_cast<size_t>(counter_words(b.bits)) + 4) * sizeof(uint32_t); }
+inline size_t claim_lds_bytes(const Binning& b)
+{
+    const size_t rows = b.tile <= kTileStep ? b.tile * (2 * sizeof(uint32_t) + sizeof(uint16_t)) : 0;       // (claim_rows)
+    return (static_cast<size_t>(counter_words(b.bits)) + 32) * sizeof(uint32_t) + rows;
+}
 
 // Layout of a batch's references.
 enum RefMode { kPairRefs, kWalkRefs, kSegRefs };
 
-// One tile of references: draw, count by bin, then write the entries of each bin side by side.
-// All 256 threads of the workgroup call this together; hist: claim_lds_bytes() of LDS.
-template <RefMode MODE>
-__device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uint32_t* hist)
+// The ids and keys of a step's references.
+template <RefMode MODE, uint32_t T>
+__device__ __forceinline__ void claim_refs(const PrepArgs& a, uint32_t step, uint32_t last, uint32_t* key)
 {
+    constexpr int H = kTileKeys<T> / 2;       // (all eight of 256 threads at once take 95 registers)
     const unsigned tid = threadIdx.x;
-    const uint32_t bits = a.bin.bits, bins = 1u << bits;
-    const uint32_t words = counter_words(bits), pack = bits > kWordBinBits ? 1u : 0u;
-    uint32_t* part = hist + words;
-    uint16_t* half = reinterpret_cast<uint16_t*>(hist);
-    auto count = [&](uint32_t p) {       // what the bin's counter was
-        const uint32_t shift = (p & pack) << 4, before = atomicAdd(&hist[p >> pack], 1u << shift) >> shift;
-        return pack ? before & 0xFFFFu : before;
-    };
-    if (tile == 0 && tid < 2) a.totals[tid] = 0ull;   // resolve, one launch later, counts from zero
-    for (uint32_t i = tid; i < words; i += 256) hist[i] = 0u;
-    __syncthreads();
-    const uint32_t first = tile * a.bin.tile;
-    const uint32_t last = min(first + a.bin.tile, a.refs);   // (refs is at most 2^28)
-    uint32_t key[kPrepUnroll];
-    uint32_t step = first;
-    for (;; step += 256 * kPrepUnroll) {
-        if (MODE == kPairRefs) claim_pair_refs(a, step, last, tid, key);
-        else if (MODE == kSegRefs) claim_seg_refs(a, step, last, tid, key);
-        else claim_walk_refs(a, step, last, tid, key);
 #pragma unroll
-        for (int u = 0; u < kPrepUnroll; ++u) {
-            const uint32_t t = step + u * 256u + tid;
-            if (t < last) a.tag[t] = 0u;             // resolve overwrites it where the row is shared
-            if (key[u] != kNoKey) count(bin_of(key[u], bits));
-        }
-        if (step + 256 * kPrepUnroll >= last) break;
+    for (int h = 0; h < 2; ++h) {
+        if (MODE == kPairRefs) claim_pair_refs<H, T>(a, step + h * T * H, last, tid, key + h * H);
+        else claim_walk_refs<H, MODE == kSegRefs, T>(a, step + h * T * H, last, tid, key + h * H);
     }
-    __syncthreads();
-    // where each bin's entries start in the tile
-    const uint32_t per = (bins + 255u) >> 8;         // consecutive bins per thread
-    uint32_t mine = 0;
-    for (uint32_t i = 0; i < per; ++i) {
-        const uint32_t p = tid * per + i;
-        if (p < bins) mine += pack ? half[p] : hist[p];
-    }
-    uint32_t total;
-    uint32_t at = block_exclusive_scan(mine, part, &total);
+}
+
+// Where the entries of each bin start in the tile, to hist, and where they end, entries | references << 16, to the segment
+// table; *total: the last end.  hist holds the numbers: of entries | of references << 16 (with_refs), else of entries, which are one
+// reference each.  False, with nothing written, if a bin has more than `most` entries.
+template <uint32_t T>
+__device__ __forceinline__ bool start_bins(const PrepArgs& a, uint32_t tile, uint32_t* hist, bool with_refs, uint32_t most, uint32_t* total)
+{
+    const uint32_t tid = threadIdx.x, bits = a.bin.bits, bins = 1u << bits;
+    const bool pack = bits > kWordBinBits;
+    uint16_t* half = reinterpret_cast<uint16_t*>(hist);
+    const uint32_t per = (bins + T - 1u) / T;         // consecutive bins per thread
+    uint32_t mine = 0, over = 0;
     for (uint32_t i = 0; i < per; ++i) {
         const uint32_t p = tid * per + i;
         if (p < bins) {
             const uint32_t n = pack ? half[p] : hist[p];
-            a.segs[static_cast<size_t>(tile) * bins + p] = at | (n << 16);
-            if (pack) half[p] = static_cast<uint16_t>(at);
-            else hist[p] = at;
-            at += n;
+            mine += n;
+            over |= static_cast<uint32_t>(n > most);
         }
     }
-    __syncthreads();
+    uint32_t overs;
+    uint32_t at = block_exclusive_scan<T>(mine, over, hist + counter_words(bits), total, &overs);
+    if (overs) return false;                         // (uniform)
+    for (uint32_t i = 0; i < per; ++i) {
+        const uint32_t p = tid * per + i;
+        if (p < bins) {
+            const uint32_t end = at + (pack ? half[p] : hist[p]);
+            a.segs[static_cast<size_t>(tile) * bins + p] = with_refs ? end : end | (end << 16);
+            if (pack) half[p] = static_cast<uint16_t>(at);
+            else hist[p] = at & 0xFFFFu;
+            at = end;
+        }
+    }
+    lds_barrier();
+    return true;
+}
+
+// A tile of one step with many references in one bin, as a hub's.  One entry stands for all references to a row that find each
+// other: each leaves its number in a slot of its row's, and all whose slot was last written for the same row are that last one's;
+// who lost the slot to another row tries a second one (with as many slots as references 2 in 5 lose the first and 1 in 6 of
+// these the second one), and a row that lost both has an entry per reference.  So a hub is an entry or a few of each tile, however
+// many references name it, and its bin, which one workgroup resolves, does not hold the batch up: 4 x 65 536 pairs at dim 16 among
+// 50 / 1000 / 10 000 nodes 3170 / 574 / 282 us with an entry per reference, 264 / 163 / 155 with this; with one source row 1130 and
+// 190.  It takes the workgroup 3 .. 8 us more, so only tiles with such a bin do it (always: 1 - 5 % of batches without hubs).  A table
+// that settles every row takes up to 40 probes one after the other (two thirds full): 15 us more of a batch of 4096 pairs.
+template <uint32_t T>
+__device__ __forceinline__ void claim_rows(const PrepArgs& a, uint32_t tile, uint32_t first, uint32_t last, const uint32_t (&key)[kTileKeys<T>], uint32_t* hist)
+{
+    const uint32_t tid = threadIdx.x, bits = a.bin.bits, n = last - first, shift = __builtin_clz(a.bin.tile) + 1u;   // 32 - log2(tile)
+    uint32_t* keys = hist + (1u << bits) + 32;        // of the references; later of the entries, sorted by bin
+    uint32_t* count = keys + a.bin.tile;             // of the references that are this one's; later the number of their entry
+    uint16_t* slot = reinterpret_cast<uint16_t*>(count + a.bin.tile);       // later the entries' references
+    uint32_t at[kTileKeys<T>];                          // whose the reference is | its rank there << 16
+    uint32_t pending = 0u;
+    for (uint32_t i = tid; i < 1u << bits; i += T) hist[i] = 0u;
+#pragma unroll
+    for (int u = 0; u < kTileKeys<T>; ++u) {
+        if (u * T >= n) break;                    // (uniform)
+        at[u] = 0u;
+        if (u * T + tid >= n) continue;              // (T may be more than the tile has)
+        at[u] = u * T + tid;
+        keys[at[u]] = key[u];
+        count[at[u]] = 0u;
+        if (key[u] != kNoKey) pending |= 1u << u;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int round = 0; round < 2; ++round) {
+        auto slot_of = [&](uint32_t k) { return (round == 0 ? hash_bits(k) << bits : k * 0x85EBCA6Bu) >> shift; };    // (other bits than the bin's)
+#pragma unroll
+        for (int u = 0; u < kTileKeys<T>; ++u) {
+            if (u * T >= n) break;
+            if (pending >> u & 1u) slot[slot_of(key[u])] = static_cast<uint16_t>(u * T + tid);
+        }
+        lds_barrier();
+        uint32_t whose[kTileKeys<T>], row[kTileKeys<T>];
+#pragma unroll
+        for (int u = 0; u < kTileKeys<T>; ++u) {
+            if (u * T >= n) break;
+            whose[u] = at[u];
+            if (pending >> u & 1u) whose[u] = slot[slot_of(key[u])];
+        }
+#pragma unroll
+        for (int u = 0; u < kTileKeys<T>; ++u) {
+            if (u * T >= n) break;
+            row[u] = keys[whose[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kTileKeys<T>; ++u) {
+            if (u * T >= n) break;
+            if ((pending >> u & 1u) && row[u] == key[u]) {
+                at[u] = whose[u];
+                pending &= ~(1u << u);
+            }
+        }
+        lds_barrier();
+    }
+#pragma unroll
+    for (int u = 0; u < kTileKeys<T>; ++u) {
+        if (u * T >= n) break;
+        if (key[u] != kNoKey) at[u] |= atomicAdd(&count[at[u]], 1u) << 16;
+    }
+    lds_barrier();
+    uint32_t refs[kTileKeys<T>];                        // of the entries that this thread's references are the first ones of
+#pragma unroll
+    for (int u = 0; u < kTileKeys<T>; ++u) {
+        refs[u] = 0u;
+        if (u * T >= n) continue;
+        if (key[u] != kNoKey && at[u] < 0x10000u) {
+            refs[u] = count[at[u]];
+            atomicAdd(&hist[bin_of(key[u], bits)], 1u | (refs[u] << 16));
+        }
+    }
+    lds_barrier();
+    uint32_t total;
+    start_bins<T>(a, tile, hist, true, ~0u, &total);
+    total &= 0xFFFFu;
+#pragma unroll
+    for (int u = 0; u < kTileKeys<T>; ++u) {
+        if (u * T >= n) break;
+        if (refs[u]) {
+            const uint32_t p = atomicAdd(&hist[bin_of(key[u], bits)], 1u);
+            keys[p] = key[u];
+            slot[p] = static_cast<uint16_t>(refs[u]);
+            count[at[u]] = p;
+        }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int u = 0; u < kTileKeys<T>; ++u) {
+        const uint32_t t = first + u * T + tid;
+        if (t < last) a.where[t] = key[u] == kNoKey ? 0u : count[at[u] & 0xFFFFu] | (at[u] & 0xFFFF0000u);
+    }
+    for (uint32_t i = tid; i < total; i += T) {
+        a.keys[first + i] = keys[i];
+        a.tags[first + i] = slot[i];
+    }
+}
+
+// One tile of references: draw, count by bin, then write the entries of each bin side by side.
+// All T threads of the workgroup call this together; hist: claim_lds_bytes() of LDS.
+template <RefMode MODE, uint32_t T>
+__device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uint32_t* hist)
+{
+    const unsigned tid = threadIdx.x;
+    const uint32_t bits = a.bin.bits;
+    const uint32_t words = counter_words(bits), pack = bits > kWordBinBits ? 1u : 0u;
+    if (tile == 0 && tid == 0) *a.totals = 0ull;   // resolve, one launch later, counts from zero
+    for (uint32_t i = tid; i < words; i += T) hist[i] = 0u;
+    const uint32_t first = tile * a.bin.tile;
+    const uint32_t last = min(first + a.bin.tile, a.refs);   // (refs is at most 2^28)
+    uint32_t key[kTileKeys<T>];
+    // several steps: an entry per reference
+    auto count = [&](uint32_t p) {       // what the bin's counter was
+        const uint32_t shift = (p & pack) << 4, before = atomicAdd(&hist[p >> pack], 1u << shift) >> shift;
+        return pack ? before & 0xFFFFu : before;
+    };
+    lds_barrier();
+    uint32_t step = first;
+    for (;; step += kTileStep) {
+        claim_refs<MODE, T>(a, step, last, key);
+#pragma unroll
+        for (int u = 0; u < kTileKeys<T>; ++u)
+            if (key[u] != kNoKey) count(bin_of(key[u], bits));
+        if (step + kTileStep >= last) break;
+    }
+    lds_barrier();
+    uint32_t total;
+    if (a.bin.tile <= kTileStep) {                   // (uniform)
+        // (a bin whose rows are many has up to 13 references or so of the mean 4; where tiles are few, a bin's references stay few
+        // whatever one tile has of them)
+        if (!start_bins<T>(a, tile, hist, false, max(4u * (a.bin.tile >> bits) + 2u, kTileStep / a.bin.tiles), &total)) {
+            claim_rows<T>(a, tile, first, last, key, hist);
+            return;
+        }
+        uint32_t* keys = hist + words + 32;          // sorted in LDS, so that they leave side by side
+#pragma unroll
+        for (int u = 0; u < kTileKeys<T>; ++u) {
+            const uint32_t t = first + u * T + tid;
+            if (first + u * T >= last) break;        // (uniform)
+            uint32_t p = 0u;
+            if (key[u] != kNoKey) {
+                p = count(bin_of(key[u], bits));
+                keys[p] = key[u];
+            }
+            if (t < last) a.where[t] = p;
+        }
+        lds_barrier();
+        for (uint32_t i = tid; i < total; i += T) a.keys[first + i] = keys[i];
+        return;
+    }
+    start_bins<T>(a, tile, hist, false, ~0u, &total);
     // the last step's keys are still in registers; earlier ones are rebuilt from the ids
     for (;;) {
 #pragma unroll
-        for (int u = 0; u < kPrepUnroll; ++u) {
+        for (int u = 0; u < kTileKeys<T>; ++u) {
+            const uint32_t t = step + u * T + tid;
+            uint32_t p = 0u;
             if (key[u] != kNoKey) {
-                const uint32_t t = step + u * 256u + tid;
-                const uint32_t p = count(bin_of(key[u], bits));
-                a.entries[first + p] = (static_cast<unsigned long long>(key[u]) << 32) | t;
+                p = count(bin_of(key[u], bits));
+                a.keys[first + p] = key[u];
             }
+            if (t < last) a.where[t] = p;
         }
         if (step == first) break;
-        step -= 256 * kPrepUnroll;
+        step -= kTileStep;
 #pragma unroll
-        for (int u = 0; u < kPrepUnroll; ++u) {
-            const uint32_t t = step + u * 256u + tid;
+        for (int u = 0; u < kTileKeys<T>; ++u) {
+            const uint32_t t = step + u * T + tid;
             const int32_t id = a.ids[t];
             const uint32_t q = t % a.R;
             const bool vertex_row = q < (MODE == kSegRefs ? a.seg_entries : 1u);
@@ -480,18 +626,22 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
     }
 }
 
-// One bin of references: all entries of a row are in it.  An LDS hash table counts each row's entries;
+// One bin of references: all entries of a row are in it.  An LDS hash table counts each row's references;
 // rows with more than one get their places in the list and their work items; then every entry of
-// such a row takes the next of the row's places.  A bin whose distinct rows do not fit the table is
+// such a row takes the next of the row's places, as many as it has references.  A bin whose distinct rows do not fit the table is
 // gone through in ranges of the hash, halved until they fit: the hash is a bijection of the key, so a range
 // of 2^k values holds at most 2^k rows and the halving ends.
 constexpr uint32_t kItemRefs = 8;                        // references per work item
+// A place in memory (below 2^28), and a flag: some entry of the tile's segment is more than one reference, and their numbers are in tags.
+constexpr uint32_t kPlaceMask = 0x0FFFFFFFu, kCounted = 0x80000000u;
 struct ResolveLds {
-    unsigned long long part[4];
+    unsigned long long part[16];
     unsigned long long base;
     uint32_t distinct;
-    uint32_t hub_items;       // of the bin's rows; later the number of the next one
-    // then key[slots], and cnt[slots]: references of the row; later its next place in the list (~0: not shared)
+    uint32_t hub_items;       // of the range's rows; later the number of the next one
+    uint32_t first[256];      // of the 256 tiles at hand: number of the tile's first entry among theirs in this bin
+    uint32_t from[256];       // where entry 0 would be if the tile's entries began with it (kPlaceMask), and whether they have counts (kCounted)
+    // then the table, slot after slot: the row's key; its references, later its first, or next, place in the list (~0: not shared)
 };
 inline size_t resolve_lds_bytes(const Binning& b) { return sizeof(ResolveLds) + (static_cast<size_t>(8) << b.slot_bits); }
 
@@ -504,155 +654,297 @@ __device__ __forceinline__ uint32_t item_places(uint32_t first, uint32_t n) { re
 // because each has more than kItemRefs places.
 __device__ __forceinline__ uint32_t hub_accumulator(uint32_t first) { return (first + kItemRefs - 1u) / kItemRefs; }
 
-// A share of a bin's entries: 2^lane_bits lanes per tile segment, kSegsPerLane segments each, every segment's first
-// entries in registers.  Fetching a share takes two dependent accesses, whatever its size; 256 tiles
-// are all there are up to 512 bins (with half as many, and so two fetches per pass: +1 .. 2 % of a batch; 16
-// lanes per segment: +2 % on batches of 90 000 references, whose segments have 4 entries).
-constexpr int kSegsPerLane = 8;
-__device__ __forceinline__ uint32_t share_tiles(const PrepArgs& a) { return (256u * kSegsPerLane) >> a.bin.lane_bits; }
+// A bin's entries lie in up to one segment per tile.  A workgroup numbers those of 256 tiles through (a segment word per
+// thread, a prefix sum) and thread i takes the entries i, i + T, ...: every lane has one, and a thread's accesses to entries, hash table
+// and places are independent of one another and in flight together.  Up to 256 tiles and 2048 entries stay in registers,
+// which is every bin of up to 1024 references but for hubs' (1280: 1.5 % more of a batch among a million nodes, whose hubs'
+// bins are read in passes then).
+template <uint32_t T> constexpr int kShare = 2048 / T;
+template <uint32_t T>
 struct BinShare {
-    unsigned long long e[kSegsPerLane];
-    uint32_t seg[kSegsPerLane];       // start in the tile | entries << 16
+    uint32_t key[kShare<T>], from[kShare<T>];     // an entry's row, and where it lies
+    uint32_t refs[kShare<T>];    // its references
+    uint32_t at[kShare<T>];      // slot of the row, in bytes
 };
 
-__device__ __forceinline__ void fetch_share(const PrepArgs& a, uint32_t bin, uint32_t tile0, BinShare& s)
+// Numbers the entries of tiles [tile0, tile0 + 256) in the bin and returns how many they are; *before: these tiles' references in
+// lower bins.  All threads call this together.
+template <uint32_t T>
+__device__ __forceinline__ uint32_t number_entries(const PrepArgs& a, uint32_t bin, uint32_t tile0, ResolveLds& s, uint32_t* before)
 {
-    const uint32_t lane_bits = a.bin.lane_bits, groups = 256u >> lane_bits;
-    const uint32_t g = threadIdx.x >> lane_bits, l = threadIdx.x & ((1u << lane_bits) - 1u);
-    const uint32_t bins = 1u << a.bin.bits;
-#pragma unroll
-    for (int i = 0; i < kSegsPerLane; ++i) {
-        const uint32_t t = tile0 + g + groups * i;
-        s.seg[i] = t < a.bin.tiles ? a.segs[static_cast<size_t>(t) * bins + bin] : 0u;
+    const uint32_t t = tile0 + threadIdx.x;
+    uint32_t begin = 0u, end = 0u;       // entries | references << 16
+    if (threadIdx.x < 256u && t < a.bin.tiles) {
+        const uint32_t* ends = a.segs + (static_cast<size_t>(t) << a.bin.bits) + bin;
+        end = *ends;
+        if (bin) begin = ends[-1];
     }
-#pragma unroll
-    for (int i = 0; i < kSegsPerLane; ++i) {
-        const uint32_t t = tile0 + g + groups * i;
-        s.e[i] = l < (s.seg[i] >> 16) ? a.entries[t * a.bin.tile + (s.seg[i] & 0xFFFFu) + l] : ~0ull;
+    uint32_t total;
+    const uint32_t first = block_exclusive_scan<T>((end & 0xFFFFu) - (begin & 0xFFFFu), begin >> 16, reinterpret_cast<uint32_t*>(s.part), &total, before);
+    if (threadIdx.x < 256u) {
+        s.first[threadIdx.x] = first;
+        const uint32_t entries = (end & 0xFFFFu) - (begin & 0xFFFFu), refs = (end >> 16) - (begin >> 16);
+        s.from[threadIdx.x] = ((t * a.bin.tile + (begin & 0xFFFFu) - first) & kPlaceMask) | (refs != entries ? kCounted : 0u);
     }
+    lds_barrier();
+    return total;
 }
 
-// f(key, reference) for every entry of the share
-template <class F>
-__device__ __forceinline__ void for_share(const PrepArgs& a, uint32_t tile0, const BinShare& s, F f)
+template <uint32_t T>
+__device__ __forceinline__ void fetch_share(const PrepArgs& a, uint32_t total, const ResolveLds& s, BinShare<T>& e)
 {
-    const uint32_t lane_bits = a.bin.lane_bits, lanes = 1u << lane_bits, groups = 256u >> lane_bits;
+    const uint32_t k = threadIdx.x;
+    uint32_t (&tile)[kShare<T>] = e.at;                       // the last tile whose first entry is not behind the thread's
 #pragma unroll
-    for (int i = 0; i < kSegsPerLane; ++i) {
-        if (tile0 + groups * i >= a.bin.tiles) break;
-        // (opaque to the optimiser, which would otherwise keep every entry's hash and address from one pass to
-        // the next: twice the registers, half the wavefronts of the kernel this rides in)
-        uint32_t key = static_cast<uint32_t>(s.e[i] >> 32), seg = s.seg[i], tid = threadIdx.x;
-        asm volatile("" : "+v"(key), "+v"(seg), "+v"(tid));
-        const uint32_t l = tid & (lanes - 1u), t = tile0 + (tid >> lane_bits) + groups * i, n = seg >> 16;
-        if (l < n) f(key, static_cast<uint32_t>(s.e[i]));
-        for (uint32_t q = l + lanes; q < n; q += lanes) {
-            const unsigned long long v = a.entries[t * a.bin.tile + (seg & 0xFFFFu) + q];
-            f(static_cast<uint32_t>(v >> 32), static_cast<uint32_t>(v));
+    for (int u = 0; u < kShare<T>; ++u) tile[u] = 0u;
+    for (uint32_t step = a.bin.tiles > 128u ? 128u : 1u << (31 - __builtin_clz(a.bin.tiles)); step; step >>= 1) {
+        uint32_t begin[kShare<T>];
+#pragma unroll
+        for (int u = 0; u < kShare<T>; ++u) {
+            if (T * u >= total) break;          // (uniform)
+            begin[u] = s.first[tile[u] + step];
+        }
+#pragma unroll
+        for (int u = 0; u < kShare<T>; ++u) {
+            if (T * u >= total) break;
+            if (begin[u] <= k + T * u) tile[u] += step;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kShare<T>; ++u) {
+        if (T * u >= total) break;
+        if (k + T * u < total) {
+            const uint32_t from = s.from[tile[u]];
+            e.from[u] = (from + k + T * u) & kPlaceMask;
+            e.key[u] = a.keys[e.from[u]];
+            e.refs[u] = 1u;
+            if (from & kCounted) e.refs[u] = a.tags[e.from[u]];
         }
     }
 }
 
-__device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, unsigned char* lds)
+__device__ __forceinline__ uint32_t* key_of(uint2* table, uint32_t at) { return reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(table) + at); }
+__device__ __forceinline__ uint32_t* count_of(uint2* table, uint32_t at) { return key_of(table, at) + 1; }
+
+// The slots of the share's rows, which are added to the table where they are not there yet (it has as many slots as there are entries).
+template <uint32_t T>
+__device__ __forceinline__ void locate_share(const PrepArgs& a, uint32_t total, uint2* table, BinShare<T>& e)
 {
-    const unsigned tid = threadIdx.x;
-    ResolveLds& s = *reinterpret_cast<ResolveLds*>(lds);
-    const uint32_t slots = 1u << a.bin.slot_bits, mask = slots - 1u, per = slots >> 8;   // per: slots per thread
-    uint32_t* skey = reinterpret_cast<uint32_t*>(lds + sizeof(ResolveLds));
-    uint32_t* scnt = skey + slots;
-    uint32_t lo = 0, halvings = 0;      // range of the hash below the bin's bits: [lo, lo + 2^(32 - halvings))
-    BinShare share;
-    if (a.bin.tiles <= share_tiles(a)) fetch_share(a, bin, 0, share);    // all there is, once
-    auto for_bin_entries = [&](auto f) {
-        if (a.bin.tiles <= share_tiles(a)) {
-            for_share(a, 0, share, f);
-        } else {
-            for (uint32_t t0 = 0; t0 < a.bin.tiles; t0 += share_tiles(a)) {
-                fetch_share(a, bin, t0, share);
-                for_share(a, t0, share, f);
-                if (*const_cast<volatile uint32_t*>(&s.distinct) > a.bin.full) break;   // (a range that is given up)
+    const uint32_t mask = (sizeof(uint2) << a.bin.slot_bits) - 1u;
+    uint32_t pending = 0u;
+#pragma unroll
+    for (int u = 0; u < kShare<T>; ++u) {
+        if (T * u >= total) break;              // (uniform)
+        e.at[u] = ((hash_bits(e.key[u]) << a.bin.bits) >> (32u - a.bin.slot_bits)) * static_cast<uint32_t>(sizeof(uint2));
+        if (T * u + threadIdx.x < total) pending |= 1u << u;
+    }
+    while (__ballot(pending != 0u)) {
+        uint32_t there[kShare<T>];
+#pragma unroll
+        for (int u = 0; u < kShare<T>; ++u) {
+            if (T * u >= total) break;
+            if (pending >> u & 1u) there[u] = __hip_atomic_load(key_of(table, e.at[u]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+#pragma unroll
+        for (int u = 0; u < kShare<T>; ++u) {
+            if (T * u >= total) break;
+            if ((pending >> u & 1u) && there[u] == kNoKey) {
+                there[u] = atomicCAS(key_of(table, e.at[u]), kNoKey, e.key[u]);
+                if (there[u] == kNoKey) there[u] = e.key[u];
             }
         }
-    };
-    for (;;) {
-        for (uint32_t i = tid; i < slots; i += 256) { skey[i] = kNoKey; scnt[i] = 0u; }
-        if (tid == 0) { s.distinct = 0u; s.hub_items = 0u; }
-        __syncthreads();
-        auto home = [&](uint32_t key, uint32_t* pos) {
-            const uint32_t x = (hash_bits(key) << a.bin.bits) - lo;
-            if (halvings && (x >> (32u - halvings))) return false;     // another range's
-            *pos = (x << halvings) >> (32u - a.bin.slot_bits);
-            return true;
-        };
-        for_bin_entries([&](uint32_t key, uint32_t) {
-            uint32_t p;
-            if (!home(key, &p)) return;
-            while (true) {
-                // (no new row once the range is given up, so an empty slot is left and every probe ends)
-                uint32_t k = *const_cast<volatile uint32_t*>(&skey[p]);
-                if (k == kNoKey) {
-                    if (*const_cast<volatile uint32_t*>(&s.distinct) > a.bin.full) return;
-                    k = atomicCAS(&skey[p], kNoKey, key);
-                    if (k == kNoKey) { atomicAdd(&s.distinct, 1u); k = key; }
+#pragma unroll
+        for (int u = 0; u < kShare<T>; ++u) {
+            if (T * u >= total) break;
+            if (pending >> u & 1u) {
+                if (there[u] == e.key[u]) pending &= ~(1u << u);
+                else e.at[u] = (e.at[u] + static_cast<uint32_t>(sizeof(uint2))) & mask;
+            }
+        }
+    }
+}
+
+// The places and work items of the shared rows in the table, which holds every row's references on entry and, on
+// return, a shared row's first place, kNoKey for the others.  The rows take consecutive places from `row` on; returns how many.
+// All threads call this together.
+template <uint32_t T>
+__device__ __forceinline__ uint32_t place_rows(const PrepArgs& a, uint32_t row, ResolveLds& s, uint2* table)
+{
+    const uint32_t tid = threadIdx.x, slots = 1u << a.bin.slot_bits;
+    unsigned long long mine = 0, all;      // items << 32 | places of the list
+    for (uint32_t p = tid; p < slots; p += T) {
+        const uint32_t n = table[p].y;
+        if (n > kItemRefs) { atomicAdd(&s.hub_items, (n + kItemRefs - 1) / kItemRefs); mine += n; }
+        else if (n > 1) mine += (1ull << 32) | n;
+    }
+    const unsigned long long at = block_exclusive_scan<T>(mine, s.part, &all);
+    // (one add per bin: a second one cost 512 bins 1 .. 2 us of the train launch)
+    if (all && tid == 0) {
+        const unsigned long long before = atomicAdd(a.totals, (all >> 32) | (static_cast<unsigned long long>(s.hub_items) << 32));
+        s.base = static_cast<uint32_t>(before);
+        s.hub_items = static_cast<uint32_t>(before >> 32);
+    }
+    lds_barrier();
+    row += static_cast<uint32_t>(at);
+    uint32_t item = s.base + static_cast<uint32_t>(at >> 32);
+    for (uint32_t p = tid; p < slots; p += T) {
+        const uint2 slot = table[p];
+        const uint32_t n = slot.y;
+        table[p].y = n > 1 ? row : kNoKey;
+        if (n > 1 && n <= kItemRefs) a.items[item++] = make_uint2(slot.x, item_places(row, n));
+        // a hub's items by the whole wavefront: one lane takes 280 us for the 8192 of a row with 65 536 references
+        for (unsigned long long hubs = __ballot(n > kItemRefs); hubs; hubs &= hubs - 1ull) {
+            const int lane = __builtin_ctzll(hubs);
+            const uint32_t hub_key = __builtin_amdgcn_readlane(slot.x, lane), hub_n = __builtin_amdgcn_readlane(n, lane);
+            const uint32_t hub_row = __builtin_amdgcn_readlane(row, lane);
+            const uint32_t m = (hub_n + kItemRefs - 1) / kItemRefs;
+            uint32_t first = 0u;
+            if ((tid & 63u) == 0) first = atomicAdd(&s.hub_items, m);
+            uint4* hub = a.hub_items + static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(first));
+            for (uint32_t q = tid & 63u; q < m; q += 64u)
+                hub[q] = make_uint4(hub_key, item_places(hub_row + q * kItemRefs, min(kItemRefs, hub_n - q * kItemRefs)), m, q);
+        }
+        if (n > 1) row += n;
+    }
+    lds_barrier();
+    return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(all));
+}
+
+// f(key, references, place in memory) for every entry of the 256 tiles at hand: as many lanes per segment as it has entries on average,
+// four entries of each lane in flight; until stop().
+template <uint32_t T, class F, class S>
+__device__ __forceinline__ void for_entries(const PrepArgs& a, uint32_t tile0, uint32_t total, const ResolveLds& s, F f, S stop)
+{
+    const uint32_t tiles = min(a.bin.tiles - tile0, 256u), mean = (total + tiles - 1) / tiles;
+    const uint32_t lane_bits = mean <= 4u ? 2u : mean >= 256u ? 8u : 32u - __builtin_clz(mean - 1u), lanes = 1u << lane_bits;
+    for (uint32_t t = threadIdx.x >> lane_bits; t < tiles && !stop(); t += T >> lane_bits) {
+        const uint32_t begin = s.first[t], n = (t + 1u < 256u ? s.first[t + 1u] : total) - begin, counted = s.from[t] & kCounted, from = (s.from[t] + begin) & kPlaceMask;
+        for (uint32_t q = threadIdx.x & (lanes - 1u); q < n; q += 4u * lanes) {
+            uint32_t key[4], refs[4];
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i)
+                if (q + i * lanes < n) {
+                    key[i] = a.keys[from + q + i * lanes];
+                    refs[i] = counted ? a.tags[from + q + i * lanes] : 1u;
                 }
-                if (k == key) { atomicAdd(&scnt[p], 1u); return; }
-                p = (p + 1) & mask;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i)
+                if (q + i * lanes < n) f(key[i], refs[i], from + q + i * lanes);
+        }
+    }
+}
+
+template <uint32_t T>
+__device__ __forceinline__ void clear_table(const PrepArgs& a, ResolveLds& s, uint2* table)
+{
+    for (uint32_t i = threadIdx.x; i < 1u << a.bin.slot_bits; i += T) table[i] = make_uint2(kNoKey, 0u);
+    if (threadIdx.x == 0) { s.distinct = 0u; s.hub_items = 0u; }
+    lds_barrier();
+}
+
+// A bin whose entries stay in registers: `total` of them, all numbered, no more than the table takes.  Its rows take places from
+// first_place on.
+template <uint32_t T>
+__device__ __forceinline__ void resolve_share(const PrepArgs& a, uint32_t total, uint32_t first_place, ResolveLds& s, uint2* table)
+{
+    BinShare<T> e;
+    fetch_share<T>(a, total, s, e);
+    clear_table<T>(a, s, table);
+    locate_share<T>(a, total, table, e);
+#pragma unroll
+    for (int u = 0; u < kShare<T>; ++u) {
+        if (T * u >= total) break;              // (uniform)
+        if (T * u + threadIdx.x < total) e.refs[u] = atomicAdd(count_of(table, e.at[u]), e.refs[u]);     // the row's references in entries before this one
+    }
+    lds_barrier();
+    place_rows<T>(a, first_place, s, table);
+#pragma unroll
+    for (int u = 0; u < kShare<T>; ++u) {
+        if (T * u >= total) break;
+        if (T * u + threadIdx.x < total) {
+            const uint32_t row = *count_of(table, e.at[u]);
+            a.tags[e.from[u]] = row == kNoKey ? 0u : 1u + row + e.refs[u];
+        }
+    }
+}
+
+// Any bin: entries are read again for every pass, one after the other, and a bin whose rows do not fit the table is gone
+// through in ranges of the hash.  (total: the entries of the first 256 tiles, numbered; before: references there in lower bins.)
+template <uint32_t T>
+__device__ __forceinline__ void resolve_passes(const PrepArgs& a, uint32_t bin, uint32_t total, uint32_t before, ResolveLds& s, uint2* table)
+{
+    uint32_t lo = 0, halvings = 0;      // range of the hash below the bin's bits: [lo, lo + 2^(32 - halvings))
+    uint32_t placed = 0;
+    auto given_up = [&] { return __hip_atomic_load(&s.distinct, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > a.bin.full; };
+    auto home = [&](uint32_t key, uint32_t* at) {
+        const uint32_t x = (hash_bits(key) << a.bin.bits) - lo;
+        *at = ((x << halvings) >> (32u - a.bin.slot_bits)) * static_cast<uint32_t>(sizeof(uint2));
+        return !halvings || !(x >> (32u - halvings));      // (else another range's)
+    };
+    auto next = [&](uint32_t at) { return (at + static_cast<uint32_t>(sizeof(uint2))) & ((static_cast<uint32_t>(sizeof(uint2)) << a.bin.slot_bits) - 1u); };
+    for (;;) {
+        clear_table<T>(a, s, table);
+        uint32_t first_place = a.bin.tiles > 256u ? 0u : before;
+        for (uint32_t t0 = 0; t0 < a.bin.tiles; t0 += 256u) {
+            if (a.bin.tiles > 256u) {
+                lds_barrier();
+                if (given_up()) break;          // (uniform: nobody adds a row before the next barrier)
+                total = number_entries<T>(a, bin, t0, s, &before);
+                first_place += before;
             }
-        });
-        __syncthreads();
+            for_entries<T>(a, t0, total, s, [&](uint32_t key, uint32_t refs, uint32_t) {
+                uint32_t at;
+                if (!home(key, &at)) return;
+                for (;; at = next(at)) {
+                    uint32_t k = __hip_atomic_load(key_of(table, at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (k == kNoKey) {
+                        if (given_up()) return;
+                        k = atomicCAS(key_of(table, at), kNoKey, key);
+                        if (k == kNoKey) { atomicAdd(&s.distinct, 1u); k = key; }
+                    }
+                    if (k == key) break;
+                    if (given_up()) return;         // (no slot may be left: every row counts as soon as it has one)
+                }
+                atomicAdd(count_of(table, at), refs);
+            }, given_up);
+        }
+        lds_barrier();
         if (s.distinct > a.bin.full) {       // (uniform: nobody writes it between the barriers)
-            __syncthreads();
+            lds_barrier();
             halvings += 1;
             continue;
         }
-        // places and work items of the shared rows among my slots
-        unsigned long long mine = 0, all;      // items << 32 | places of the list
-        for (uint32_t i = 0; i < per; ++i) {
-            const uint32_t n = scnt[tid * per + i];
-            if (n > kItemRefs) { atomicAdd(&s.hub_items, (n + kItemRefs - 1) / kItemRefs); mine += n; }
-            else if (n > 1) mine += (1ull << 32) | n;
-        }
-        unsigned long long at = block_exclusive_scan(mine, s.part, &all);
-        if (all) {                              // (uniform)
-            if (tid < 2) {      // (in one instruction: the adds of all bins to this line retire one after the other)
-                const unsigned long long before = atomicAdd(a.totals + tid, tid == 0 ? all : static_cast<unsigned long long>(s.hub_items));
-                if (tid == 0) s.base = before;
-                else s.hub_items = static_cast<uint32_t>(before);
+        placed += place_rows<T>(a, first_place + placed, s, table);
+        for (uint32_t t0 = 0; t0 < a.bin.tiles; t0 += 256u) {
+            if (a.bin.tiles > 256u) {
+                lds_barrier();
+                total = number_entries<T>(a, bin, t0, s, &before);
             }
-            __syncthreads();
-            at += s.base;
-            uint32_t item = static_cast<uint32_t>(at >> 32), row = static_cast<uint32_t>(at);
-            for (uint32_t i = 0; i < per; ++i) {
-                const uint32_t p = tid * per + i, n = scnt[p];
-                scnt[p] = n > 1 ? row : kNoKey;
-                if (n > 1 && n <= kItemRefs) a.items[item++] = make_uint2(skey[p], item_places(row, n));
-                if (n > 1) row += n;
-                // a hub's items by the whole wavefront: one lane takes 280 us for the 8192 of a row with 65 536 references
-                for (unsigned long long hubs = __ballot(n > kItemRefs); hubs; hubs &= hubs - 1ull) {
-                    const int lane = __builtin_ctzll(hubs);
-                    const uint32_t at_p = __builtin_amdgcn_readlane(p, lane), hub_n = __builtin_amdgcn_readlane(n, lane);
-                    const uint32_t hub_key = __builtin_amdgcn_readfirstlane(skey[at_p]), hub_row = __builtin_amdgcn_readfirstlane(scnt[at_p]);
-                    const uint32_t m = (hub_n + kItemRefs - 1) / kItemRefs;
-                    uint32_t first = 0u;
-                    if ((tid & 63u) == 0) first = atomicAdd(&s.hub_items, m);
-                    uint4* hub = a.hub_items + static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(first));
-                    for (uint32_t q = tid & 63u; q < m; q += 64u)
-                        hub[q] = make_uint4(hub_key, item_places(hub_row + q * kItemRefs, min(kItemRefs, hub_n - q * kItemRefs)), m, q);
-                }
-            }
-            __syncthreads();
-            for_bin_entries([&](uint32_t key, uint32_t ref) {
-                uint32_t p;
-                if (!home(key, &p)) return;
-                while (skey[p] != key) p = (p + 1) & mask;
-                if (scnt[p] != kNoKey) a.tag[ref] = 1u + atomicAdd(&scnt[p], 1u);
-            });
+            for_entries<T>(a, t0, total, s, [&](uint32_t key, uint32_t refs, uint32_t from) {
+                uint32_t at;
+                if (!home(key, &at)) return;
+                while (*key_of(table, at) != key) at = next(at);
+                uint32_t tag = 0u;
+                if (*count_of(table, at) != kNoKey) tag = 1u + atomicAdd(count_of(table, at), refs);
+                a.tags[from] = tag;
+            }, [] { return false; });
         }
         if (halvings == 0) return;
         lo += 1u << (32u - halvings);
         if (lo == 0) return;
-        __syncthreads();
+        lds_barrier();
     }
+}
+
+template <uint32_t T>
+__device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, unsigned char* lds)
+{
+    ResolveLds& s = *reinterpret_cast<ResolveLds*>(lds);
+    uint2* table = reinterpret_cast<uint2*>(lds + sizeof(ResolveLds));
+    uint32_t before;
+    const uint32_t total = number_entries<T>(a, bin, 0, s, &before);
+    if (a.bin.tiles <= 256u && total <= min(T * kShare<T>, 1u << a.bin.slot_bits)) resolve_share<T>(a, total, before, s, table);      // (uniform)
+    else resolve_passes<T>(a, bin, total, before, s, table);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -706,39 +998,42 @@ struct Helpers {
 };
 
 // False for a workgroup that has other work to do; *block is then its index among those.
-template <RefMode MODE>
+template <RefMode MODE, uint32_t T = 256>
 __device__ __forceinline__ bool helper_block(const Helpers& h, unsigned* block)
 {
     unsigned i = blockIdx.x;
     if (i < h.resolves) {
         // neighbouring bins share cache lines (a tile's segment words and entries lie bin after bin), and
         // workgroups go to the eight dies in turn: each die takes a run of consecutive bins
-        resolve_bin(h.resolve, h.resolves >= 8 ? (i & 7u) * (h.resolves >> 3) + (i >> 3) : i, dynamic_lds);
+        resolve_bin<T>(h.resolve, h.resolves >= 8 ? (i & 7u) * (h.resolves >> 3) + (i >> 3) : i, dynamic_lds);
         return true;
     }
     i -= h.resolves;
-    if (i < h.claims) { claim_tile<MODE>(h.claim, i, reinterpret_cast<uint32_t*>(dynamic_lds)); return true; }
+    if (i < h.claims) { claim_tile<MODE, T>(h.claim, i, reinterpret_cast<uint32_t*>(dynamic_lds)); return true; }
     i -= h.claims;
     if (i < h.fetches) {
-        fetch_pairs(h.claim.fetch_src, h.claim.fetch_dst, h.claim.fetch_n, static_cast<int64_t>(i) * 256 + threadIdx.x,
-                    static_cast<int64_t>(h.fetches) * 256);
+        fetch_pairs(h.claim.fetch_src, h.claim.fetch_dst, h.claim.fetch_n, static_cast<int64_t>(i) * T + threadIdx.x,
+                    static_cast<int64_t>(h.fetches) * T);
         return true;
     }
-    *block = i - h.fetches;
+    i -= h.fetches;
+    // consecutive pairs on one die, which then shares the cache lines of their ids and tags
+    const unsigned blocks = gridDim.x - h.resolves - h.claims - h.fetches, share = blocks >> 3, rest = blocks & 7u, die = i & 7u;
+    *block = die * share + min(die, rest) + (i >> 3);
     return false;
 }
 
 // The same work on its own, for the first batches of a call.  A batch with one tile and one bin is claimed and resolved
 // by the same workgroup (claim_first: h.resolve).
-template <RefMode MODE>
-__global__ __launch_bounds__(256) void prepare_kernel(Helpers h, bool claim_first)
+template <RefMode MODE, uint32_t T>
+__global__ __launch_bounds__(T) void prepare_kernel(Helpers h, bool claim_first)
 {
     if (claim_first && blockIdx.x == 0) {
-        claim_tile<MODE>(h.resolve, 0, reinterpret_cast<uint32_t*>(dynamic_lds));
+        claim_tile<MODE, T>(h.resolve, 0, reinterpret_cast<uint32_t*>(dynamic_lds));
         __syncthreads();
     }
     unsigned block;
-    helper_block<MODE>(h, &block);
+    helper_block<MODE, T>(h, &block);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -757,10 +1052,23 @@ struct TrainArgs {
     int32_t d4;
     float lr;
     const int32_t* ids;
-    const uint32_t* tag;  // per reference: 0 = sole reference of its row, else 1 + its place in the list
+    const uint32_t* where;  // per reference: which entry of its tile names its row | how many of the tile's references come first << 16
+    const uint32_t* tags;   // per entry: 0 = one reference, and the only one of its row; else 1 + the first one's place in the list
+    uint32_t tile;          // references per tile, a power of two
     uint2* list;          // (row of buf, coefficient)
     float4* buf;          // [..][d4]
 };
+
+// Tag of a reference: 0 = the sole reference of its row, else 1 + its place in the list.  The entry's tag is on its way when this is
+// made, and only get() waits for it, once the rows are there.
+struct TagRef {
+    uint32_t first, rank;     // the entry's tag, and how many of its references come before this one
+    __device__ __forceinline__ uint32_t get() const { return first ? first + rank : 0u; }
+};
+__device__ __forceinline__ TagRef tag_of(const TrainArgs& a, int64_t t, uint32_t where)
+{
+    return {a.tags[(static_cast<uint32_t>(t) & ~(a.tile - 1u)) + (where & 0xFFFFu)], where >> 16};
+}
 
 // Element e = lg + m*G of a row, for m < 4*NCH: the layout in which one atomic instruction of a lane
 // group covers consecutive dwords.  The float4-chunk layout is turned into it through LDS.
@@ -813,13 +1121,15 @@ __device__ __forceinline__ void write_copy(const TrainArgs& a, uint32_t copy, co
 // negative), JB at a time: gather, score against x, form g_j, add g_j c_j to dx, and update the row:
 // rewritten in place if only this reference names it, else lr g_j and `copy`, the row of buf that gets x, go
 // to the reference's place in the list (DIRECT: the delta goes to the row with atomics; xt is x in
-// consecutive-dword layout).  Lane j + LANE0 of the group holds reference j's id and tag; other lanes' tags are 0.
+// consecutive-dword layout).  Lane j + LANE0 of the group holds reference j's id and tag, owns it (`own`) and returns whether its
+// row is shared; other lanes own nothing.
 template <int G, int NCH, int JB, int LANE0, bool POS_FIRST = true, bool DIRECT = false>
-__device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, int d4, const float4 (&xr)[NCH],
+__device__ __forceinline__ bool context_rows_of_pair(const TrainArgs& a, int K, int d4, const float4 (&xr)[NCH],
                                                      const float (&xt)[4 * NCH], float4 (&dx)[NCH], int32_t id_mine,
-                                                     uint32_t tag_mine, uint32_t copy, int lg)
+                                                     const TagRef& tag_ref, bool own, uint32_t copy, int lg)
 {
     float g_mine = 0.0f;     // lr g_j of lane j + LANE0
+    uint32_t tag_mine = 0u;
     for (int j0 = 0; j0 <= K; j0 += JB) {
         float4 cr[JB][NCH];
         float part[JB];
@@ -853,6 +1163,7 @@ __device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, 
         const float sg = sigmoidf(score);
         const float g_own = a.lr * ((POS_FIRST && lg == LANE0) ? 1.0f - sg : -sg);
         if (lg >= j0 + LANE0 && lg < j0 + LANE0 + JB) g_mine = g_own;
+        tag_mine = own ? tag_ref.get() : 0u;
 #pragma unroll
         for (int jj = 0; jj < JB; ++jj) {
             const int j = j0 + jj;
@@ -879,6 +1190,7 @@ __device__ __forceinline__ void context_rows_of_pair(const TrainArgs& a, int K, 
         }
     }
     if (!DIRECT && tag_mine) a.list[tag_mine - 1u] = make_uint2(copy, __float_as_uint(g_mine));
+    return tag_mine != 0u;
 }
 
 constexpr int kTrainThreads = 256;   // threads per block of the train kernels
@@ -898,13 +1210,9 @@ __global__ __launch_bounds__(kTrainThreads) void train_kernel(TrainArgs a, Helpe
     const int d4 = a.d4;
 
     // lane j < R owns reference j: id and tag
-    int32_t id_mine = 0;
-    uint32_t tag_mine = 0;
-    if (lg < R) {
-        id_mine = a.ids[b * R + lg];
-        tag_mine = a.tag[b * R + lg];
-    }
-    const uint32_t tag0 = __shfl(tag_mine, 0, G);
+    const int64_t ref = b * R + (lg < R ? lg : 0);
+    const int32_t id_mine = a.ids[ref];
+    const TagRef tag = tag_of(a, ref, a.where[ref]);
     float4* xrow = a.X + static_cast<int64_t>(__shfl(id_mine, 0, G)) * d4;
     float4 xr[NCH];
 #pragma unroll
@@ -921,9 +1229,9 @@ __global__ __launch_bounds__(kTrainThreads) void train_kernel(TrainArgs a, Helpe
     for (int i = 0; i < NCH; ++i) dx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 
     const uint32_t copy = static_cast<uint32_t>(b), spare = static_cast<uint32_t>(a.B + b);   // rows of buf
-    const uint32_t tag_ctx = lg ? tag_mine : 0u;
-    context_rows_of_pair<G, NCH, JB, 1, true, DIRECT>(a, K, d4, xr, xt, dx, id_mine, tag_ctx, copy, lg);
-    if (!DIRECT && group_any<G>(tag_ctx != 0u)) write_copy<G, NCH>(a, copy, xr, lg, d4);
+    const bool context = context_rows_of_pair<G, NCH, JB, 1, true, DIRECT>(a, K, d4, xr, xt, dx, id_mine, tag, lg > 0 && lg < R, copy, lg);
+    const uint32_t tag0 = __shfl(tag.get(), 0, G);
+    if (!DIRECT && group_any<G>(context)) write_copy<G, NCH>(a, copy, xr, lg, d4);
 
     if (DIRECT && tag0) {
         to_consecutive<G, NCH>(dx, xt, lds_row, lg);
@@ -959,7 +1267,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
 
     const int32_t src = a.ids[ref0];
     if (src < 0) return;    // no pair starts at this position (uniform over the group)
-    const uint32_t tag0 = a.tag[ref0];
+    const TagRef tag0 = tag_of(a, ref0, a.where[ref0]);
 
     float4* xrow = a.X + static_cast<int64_t>(src) * d4;
     float4 xr[NCH];
@@ -977,22 +1285,21 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
     // the context references of all pairs, JB at a time; lane l < JB owns reference j0 + l, and the next JB ids travel
     // while these rows do.  (A pair that the walk does not have: its references have id -1.)
     const int n = a.window * (K + 1);
-    auto fetch = [&](int j, int32_t& id, uint32_t& tag) {
+    auto fetch = [&](int j, int32_t& id, uint32_t& where) {
         id = -1;
-        tag = 0u;
+        where = 0u;
         if (lg < JB && j + lg < n) {
             id = a.ids[ref0 + 1 + j + lg];
-            tag = a.tag[ref0 + 1 + j + lg];
-            if (id < 0) tag = 0u;
+            where = a.where[ref0 + 1 + j + lg];
         }
     };
     int32_t id_next;
-    uint32_t tag_next;
-    fetch(0, id_next, tag_next);
+    uint32_t where_next;
+    fetch(0, id_next, where_next);
     int phase = 0;                // j0 mod K + 1: reference 0 of a pair is its positive
     for (int j0 = 0; j0 < n; j0 += JB) {
         const int32_t id_mine = id_next;
-        const uint32_t tag_mine = tag_next;
+        const TagRef tag_ref = tag_of(a, id_mine < 0 ? ref0 : ref0 + 1 + j0 + lg, id_mine < 0 ? 0u : where_next);
         float4 cr[JB][NCH];
         int32_t id[JB];
 #pragma unroll
@@ -1005,7 +1312,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
                 cr[jj][i] = (id[jj] >= 0 && ci < d4) ? crow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
             }
         }
-        fetch(j0 + JB, id_next, tag_next);
+        fetch(j0 + JB, id_next, where_next);
         float part[JB];
 #pragma unroll
         for (int jj = 0; jj < JB; ++jj) {
@@ -1026,6 +1333,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
         }
         const float sg = sigmoidf(score);
         const float g_mine = a.lr * (positive ? 1.0f - sg : -sg);
+        const uint32_t tag_mine = id_mine < 0 ? 0u : tag_ref.get();
 #pragma unroll
         for (int jj = 0; jj < JB; ++jj) {
             if (id[jj] >= 0) {
@@ -1046,7 +1354,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
         copied |= group_any<G>(tag_mine != 0u);
     }
     if (copied) write_copy<G, NCH>(a, copy, xr, lg, d4);
-    write_row<G, NCH>(a, xrow, tag0, spare, xr, dx, lg, d4);
+    write_row<G, NCH>(a, xrow, tag0.get(), spare, xr, dx, lg, d4);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1089,7 +1397,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
 
     // my entry's vertex row, and the context rows grp and grp + E of the segment's list
     const int32_t src = a.ids[ref0 + grp];
-    const uint32_t tag_x = a.tag[ref0 + grp];
+    const TagRef tag_x = tag_of(a, ref0 + grp, a.where[ref0 + grp]);
     float4 xr[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) xr[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1129,17 +1437,17 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
         // lane k < K owns negative k of a sample; the next sample's travel while this one's rows do
         const int64_t ref_neg = ref0 + E + CT + static_cast<int64_t>(grp) * W * K + lg;
         int32_t id_next = -1;
-        uint32_t tag_next = 0;
+        uint32_t where_next = 0;
         if (lg < K) {
             id_next = a.ids[ref_neg];
-            tag_next = a.tag[ref_neg];
+            where_next = a.where[ref_neg];
         }
         for (int j = 1; j <= W; ++j) {
             const int32_t id_mine = id_next;
-            const uint32_t tag_mine = tag_next;
+            const TagRef tag = tag_of(a, id_mine < 0 ? ref0 : ref_neg + static_cast<int64_t>(j - 1) * K, id_mine < 0 ? 0u : where_next);
             if (lg < K && j < W) {
                 id_next = a.ids[ref_neg + static_cast<int64_t>(j) * K];
-                tag_next = a.tag[ref_neg + static_cast<int64_t>(j) * K];
+                where_next = a.where[ref_neg + static_cast<int64_t>(j) * K];
             }
             const int row = grp + j - 1;                      // context row of entry (mine + j)
             if (cid[row] < 0) continue;                       // no such sample (uniform over the group)
@@ -1155,12 +1463,12 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
 #pragma unroll
             for (int i = 0; i < NCH; ++i) dx[i] = axpy4(g0, cr[i], dx[i]);
             if (K > 0) {
-                context_rows_of_pair<G, NCH, JB, 0, false>(a, K - 1, d4, xr, xt, dx, id_mine, tag_mine, copy, lg);
-                copied |= group_any<G>(tag_mine != 0u);
+                const bool shared = context_rows_of_pair<G, NCH, JB, 0, false>(a, K - 1, d4, xr, xt, dx, id_mine, tag, id_mine >= 0, copy, lg);
+                copied |= group_any<G>(shared);
             }
         }
         if (copied) write_copy<G, NCH>(a, copy, xr, lg, d4);
-        write_row<G, NCH>(a, xrow, tag_x, buf0 + grp, xr, dx, lg, d4);
+        write_row<G, NCH>(a, xrow, tag_x.get(), buf0 + grp, xr, dx, lg, d4);
     }
 
     // ---- context part: context row `row` is entry p0 + 1 + row; its sources in this segment are the
@@ -1168,7 +1476,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
     for (int row = grp; row < CT; row += E) {
         const int32_t id = cid[row];
         if (id < 0) continue;
-        const uint32_t tag_c = a.tag[ref0 + E + row];
+        const TagRef tag_c = tag_of(a, ref0 + E + row, a.where[ref0 + E + row]);
         float4 cr[NCH], dc[NCH];
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
@@ -1190,7 +1498,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
 #pragma unroll
             for (int i = 0; i < NCH; ++i) dc[i] = axpy4(g0, xv[i], dc[i]);
         }
-        write_row<G, NCH>(a, a.C + static_cast<int64_t>(id) * d4, tag_c, buf0 + static_cast<uint32_t>(E + row), cr, dc, lg, d4);
+        write_row<G, NCH>(a, a.C + static_cast<int64_t>(id) * d4, tag_c.get(), buf0 + static_cast<uint32_t>(E + row), cr, dc, lg, d4);
     }
 }
 
@@ -1216,7 +1524,7 @@ struct ApplyArgs {
     int32_t d4;
     const uint2* items;
     const uint4* hub_items;
-    const unsigned long long* totals;
+    const unsigned long long* totals;     // items | items of hubs << 32
     uint32_t most;        // items there can be
     unsigned hub_blocks;  // workgroups, the first of the launch, that take the hubs' items
     const uint2* list;
@@ -1269,7 +1577,7 @@ __device__ __forceinline__ void apply_hubs(const ApplyArgs& a, float4 (&lds)[256
     constexpr uint32_t GROUPS = 256 / GL;
     const int lg = threadIdx.x & (GL - 1), d4 = a.d4;
     const uint32_t grp = threadIdx.x / GL;
-    const uint32_t n = static_cast<uint32_t>(a.totals[1]);
+    const uint32_t n = static_cast<uint32_t>(*a.totals >> 32);
     for (uint32_t first = blockIdx.x * GROUPS; first < n; first += a.hub_blocks * GROUPS) {     // (uniform)
         const bool live = first + grp < n;
         uint4 item = make_uint4(0u, 0u, 0u, 0u);
@@ -1345,7 +1653,7 @@ __global__ __launch_bounds__(256) void apply_kernel(ApplyArgs a)
     const uint32_t step = (gridDim.x - a.hub_blocks) * GROUPS;
     uint32_t e = (blockIdx.x - a.hub_blocks) * GROUPS + grp;
     uint2 item = a.items[min(e, a.most - 1u)];     // (in flight together with the count; what lies past it is not used)
-    const uint32_t n = static_cast<uint32_t>(*a.totals >> 32);
+    const uint32_t n = static_cast<uint32_t>(*a.totals);
     for (; e < n; e += step, item = a.items[min(e, a.most - 1u)]) {
         float4* row = row_of_key(a, item.x);
         float4 old[CH], sum[CH];
@@ -1578,13 +1886,21 @@ hipError_t launch_train_seg(const Shape& s, const TrainArgs& a, const Helpers& h
     return hipErrorInvalidValue;
 }
 
+// Workgroups of 1024 threads where they all have a place at once and a tile has a reference for each: the first claim of a batch of
+// 65 536 pairs 14 instead of 20 us where tiles have hubs, a batch of 90 000 references 37.2 instead of 37.8, walks 394 and 401.
+// (Tiles of 512, half the threads idle: equal.  More workgroups, 736 of resolve and claim: 30 instead of 21 us.)
+constexpr uint32_t kWideTile = 1024;
+constexpr unsigned kWideBlocks = 512;
 hipError_t launch_prepare(const Helpers& h, bool claim_first, hipStream_t st)
 {
     const size_t own = claim_first ? claim_lds_bytes(h.resolve.bin) : 0, lds = own > h.lds_bytes() ? own : h.lds_bytes();
     const PrepArgs& p = h.claims ? h.claim : h.resolve;
-    if (p.pairs) hipLaunchKernelGGL(prepare_kernel<kPairRefs>, dim3(h.count()), dim3(256), lds, st, h, claim_first);
-    else if (p.seg_entries) hipLaunchKernelGGL(prepare_kernel<kSegRefs>, dim3(h.count()), dim3(256), lds, st, h, claim_first);
-    else hipLaunchKernelGGL(prepare_kernel<kWalkRefs>, dim3(h.count()), dim3(256), lds, st, h, claim_first);
+    const bool wide = p.bin.tile >= kWideTile && h.count() <= kWideBlocks;
+#define NE_CASE(M_)                                                                              \
+    if (wide) hipLaunchKernelGGL((prepare_kernel<M_, 1024>), dim3(h.count()), dim3(1024), lds, st, h, claim_first);  \
+    else hipLaunchKernelGGL((prepare_kernel<M_, 256>), dim3(h.count()), dim3(256), lds, st, h, claim_first);
+    if (p.pairs) { NE_CASE(kPairRefs) } else if (p.seg_entries) { NE_CASE(kSegRefs) } else { NE_CASE(kWalkRefs) }
+#undef NE_CASE
     return hipGetLastError();
 }
 
@@ -1652,12 +1968,13 @@ bool workspace_layout(int32_t dim, int64_t max_B, int32_t max_K, char* base, Wor
     auto take = [&](size_t bytes) { char* p = base + off; off = up(off + bytes); return p; };
     for (PrepSlot& p : w->prep) {
         p.ids = reinterpret_cast<int32_t*>(take(refs * 4));
-        p.tag = reinterpret_cast<uint32_t*>(take(refs * 4));
-        p.entries = reinterpret_cast<unsigned long long*>(take(refs * 8));
+        p.where = reinterpret_cast<uint32_t*>(take(refs * 4));
+        p.keys = reinterpret_cast<uint32_t*>(take(refs * 8));
+        p.tags = p.keys + refs;
         p.segs = reinterpret_cast<uint32_t*>(take(max_segs(refs) * 4));
         p.items = reinterpret_cast<uint2*>(take(refs / 2 * sizeof(uint2)));
         p.hub_items = reinterpret_cast<uint4*>(take(most_hub_items(refs) * sizeof(uint4)));
-        p.totals = reinterpret_cast<unsigned long long*>(take(2 * sizeof(unsigned long long)));
+        p.totals = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long)));
     }
     w->list = reinterpret_cast<uint2*>(take(refs * sizeof(uint2)));
     // two rows per pair or walk entry, a segment's entries twice and its context rows: never more than references, and as
@@ -1721,7 +2038,7 @@ ne_status run_batches(ne_tables* t, int64_t n_batches, int64_t R, int32_t window
         if (!pa.refs) return pa;
         const PrepSlot& ps = w.prep[i % 3];
         pa.bin = binning(pa.refs);
-        pa.ids = ps.ids; pa.tag = ps.tag; pa.entries = ps.entries; pa.segs = ps.segs; pa.items = ps.items;
+        pa.ids = ps.ids; pa.where = ps.where; pa.keys = ps.keys; pa.tags = ps.tags; pa.segs = ps.segs; pa.items = ps.items;
         pa.hub_items = ps.hub_items; pa.totals = ps.totals;
         pa.k0 = static_cast<uint32_t>(t->seed); pa.k1 = static_cast<uint32_t>(t->seed >> 32);
         return pa;
@@ -1746,7 +2063,7 @@ ne_status run_batches(ne_tables* t, int64_t n_batches, int64_t R, int32_t window
         TrainArgs ta{};
         ta.X = reinterpret_cast<float4*>(t->vertex); ta.C = reinterpret_cast<float4*>(t->context);
         ta.B = cur.refs / R; ta.window = window; ta.K = K; ta.d4 = t->dim / 4; ta.lr = lr_host[i];
-        ta.ids = cur.ids; ta.tag = cur.tag; ta.list = w.list; ta.buf = reinterpret_cast<float4*>(w.buf);
+        ta.ids = cur.ids; ta.where = cur.where; ta.tags = cur.tags; ta.tile = cur.bin.tile; ta.list = w.list; ta.buf = reinterpret_cast<float4*>(w.buf);
         const bool timed = profile_begin(t, st);
         e = train(ta, helpers(next, after, true));
         if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("train launch: ") + hipGetErrorString(e));

@@ -34,12 +34,14 @@ namespace {
 // handle's creation and left zero by every apply launch, nothing else has to start from any value.
 struct PrepSlot {
     int32_t* ids;                 // [refs]  row named by each reference (walk mode: -1 = no such reference)
-    uint32_t* tag;                // [refs]  0 = only this reference names its row; else 1 + its place in the list
-    unsigned long long* entries;  // [refs]  key << 32 | reference, sorted by bin inside each tile
-    uint32_t* segs;               // [tiles][bins]  where a tile's entries of a bin start, and how many (<< 16)
+    uint32_t* where;              // [refs]  the entry of the reference's tile that is its row's | its rank among the entry's references << 16
+    uint32_t* keys;               // [refs]  the entries, one per row and tile: keys, sorted by bin inside each tile
+    uint32_t* tags;               // [refs]  in the same order: references of the entry; later 0 = only one reference names the row, else
+                                  //         1 + the place in the list of the entry's first reference
+    uint32_t* segs;               // [tiles][bins]  where a tile's entries of a bin end | where its references do (<< 16)
     uint2* items;                 // [refs / 2]  work items of the apply kernel: rows that 2 .. 8 references name
     uint4* hub_items;             // [refs 2/9]  work items of the rows that more references name
-    unsigned long long* totals;   // [2]     number of items << 32 | places of the list in use; number of hub items
+    unsigned long long* totals;   // number of items | number of hub items << 32
 };
 struct Workspace {
     PrepSlot prep[3];   // one batch in training, the next being resolved, the one after that being claimed
@@ -124,9 +126,10 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
     constexpr uint32_t W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const uint32_t hi0 = __umulhi(M0, c.x), lo0 = M0 * c.x;
-        const uint32_t hi1 = __umulhi(M1, c.z), lo1 = M1 * c.z;
-        c = make_uint4(hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0);
+        // (both halves of a product in one multiply-add of 64 bits; multiplications are a quarter of the rate of anything else)
+        const uint64_t p0 = static_cast<uint64_t>(M0) * c.x, p1 = static_cast<uint64_t>(M1) * c.z;
+        c = make_uint4(static_cast<uint32_t>(p1 >> 32) ^ c.y ^ k0, static_cast<uint32_t>(p1),
+                       static_cast<uint32_t>(p0 >> 32) ^ c.w ^ k1, static_cast<uint32_t>(p0));
         k0 += W0;
         k1 += W1;
     }
@@ -149,6 +152,11 @@ __device__ __forceinline__ int32_t draw_negative(uint64_t sample, uint32_t k, ui
                                              kStreamNegative), k0, k1);
     return base + alias_draw(r, table, n);
 }
+
+// Workgroup barrier for data exchanged through LDS only: waits for this wavefront's LDS operations, not for its
+// global loads and stores.  (__syncthreads also drains those, which would undo every fetch issued ahead of its use and
+// expose the latency of every store.)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float v)

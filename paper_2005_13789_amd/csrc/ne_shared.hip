@@ -59,11 +59,6 @@ __device__ __forceinline__ float fast_sigmoidf(float z) { return __frcp_rn(1.0f 
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-// Workgroup barrier for data exchanged through LDS only: waits for this wavefront's LDS operations, not for its
-// global loads and stores.  (__syncthreads also drains those, which would undo every operand fetch issued ahead of
-// its use and expose the latency of every store.)
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // MFMA 32x32x16 operand layout (checked on hardware): lane l supplies row (A) / column (B) l%32 and the 8
 // consecutive contraction indices (l/32)*8..+7 of the step; accumulator element i is row
 // (i/4)*8 + (l/32)*4 + i%4, column l%32.  A "fragment" below is what the 64 lanes of a wavefront supply
