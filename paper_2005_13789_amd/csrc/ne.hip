@@ -332,57 +332,39 @@ __device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, uint32_t firs
     }
 }
 
-// Exclusive prefix sum over the T threads of a workgroup; *total receives the sum.  part: T / 64 values in LDS.
-template <uint32_t T, class V>
-__device__ __forceinline__ V block_exclusive_scan(V v, V* part, V* total)
+// Inclusive prefix sum over the 64 lanes of a wavefront, in registers (through LDS, one permutation after the other: 0.25 us, and
+// five of these lie in a batch's critical path).  All lanes call this together.
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    V inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const V o = __shfl_up(inc, off, 64);
-        if (lane >= off) inc += o;
-    }
-    lds_barrier();              // part may still be read from an earlier scan
-    if (lane == 63) part[wave] = inc;
-    lds_barrier();
-    V before = 0, sum = 0;
-#pragma unroll
-    for (int w = 0; w < static_cast<int>(T / 64); ++w) {
-        const V p = part[w];
-        if (w < wave) before += p;
-        sum += p;
-    }
-    *total = sum;
-    return before + inc - v;
+    v += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x111, 0xF, 0xF, false));    // row_shr 1, 2, 4, 8: inside 16 lanes
+    v += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x112, 0xF, 0xF, false));
+    v += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x114, 0xF, 0xF, false));
+    v += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x118, 0xF, 0xF, false));
+    v += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x142, 0xA, 0xF, false));    // lane 15 of a row to the next row
+    v += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x143, 0xC, 0xF, false));    // lane 31 to the upper half
+    return v;
 }
 
-// The same over v, and the sum of w beside it.  part: T / 32 values in LDS.
+// Exclusive prefix sums of v and w over the T threads of a workgroup, in place, and their totals.  part: T / 32 words of LDS.
 template <uint32_t T>
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t w, uint32_t* part, uint32_t* total_v, uint32_t* total_w)
+__device__ __forceinline__ void block_exclusive_scan(uint32_t& v, uint32_t& w, uint32_t* part, uint32_t* total_v, uint32_t* total_w)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t o = __shfl_up(inc, off, 64);
-        w += __shfl_xor(w, off, 64);
-        if (lane >= off) inc += o;
-    }
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t inc_v = wave_inclusive_scan(v), inc_w = wave_inclusive_scan(w);
     lds_barrier();              // part may still be read from an earlier scan
-    if (lane == 63) { part[wave] = inc; part[T / 64 + wave] = w; }
+    if (lane == 63u) { part[wave] = inc_v; part[T / 64u + wave] = inc_w; }
     lds_barrier();
-    uint32_t before = 0, sum_v = 0, sum_w = 0;
+    uint32_t before_v = 0, before_w = 0, sum_v = 0, sum_w = 0;
 #pragma unroll
-    for (int q = 0; q < static_cast<int>(T / 64); ++q) {
-        const uint32_t p = part[q];
-        if (q < wave) before += p;
-        sum_v += p;
-        sum_w += part[T / 64 + q];
+    for (uint32_t q = 0; q < T / 64u; ++q) {
+        if (q == wave) { before_v = sum_v; before_w = sum_w; }
+        sum_v += part[q];
+        sum_w += part[T / 64u + q];
     }
+    v = before_v + inc_v - v;
+    w = before_w + inc_w - w;
     *total_v = __builtin_amdgcn_readfirstlane(sum_v);
     *total_w = __builtin_amdgcn_readfirstlane(sum_w);
-    return before + inc - v;
 }
 
 // LDS of the claim phase: a counter per bin (beyond 2^kWordBinBits bins 16 bits each), the scan's 32 words and, if they
@@ -430,7 +412,8 @@ __device__ __forceinline__ bool start_bins(const PrepArgs& a, uint32_t tile, uin
         }
     }
     uint32_t overs;
-    uint32_t at = block_exclusive_scan<T>(mine, over, hist + counter_words(bits), total, &overs);
+    block_exclusive_scan<T>(mine, over, hist + counter_words(bits), total, &overs);
+    uint32_t at = mine;
     if (overs) return false;                         // (uniform)
     for (uint32_t i = 0; i < per; ++i) {
         const uint32_t p = tid * per + i;
@@ -635,8 +618,8 @@ constexpr uint32_t kItemRefs = 8;                        // references per work 
 // A place in memory (below 2^28), and a flag: some entry of the tile's segment is more than one reference, and their numbers are in tags.
 constexpr uint32_t kPlaceMask = 0x0FFFFFFFu, kCounted = 0x80000000u;
 struct ResolveLds {
-    unsigned long long part[16];
-    unsigned long long base;
+    uint32_t part[32];
+    uint32_t base;
     uint32_t distinct;
     uint32_t hub_items;       // of the range's rows; later the number of the next one
     uint32_t first[256];      // of the 256 tiles at hand: number of the tile's first entry among theirs in this bin
@@ -680,7 +663,8 @@ __device__ __forceinline__ uint32_t number_entries(const PrepArgs& a, uint32_t b
         if (bin) begin = ends[-1];
     }
     uint32_t total;
-    const uint32_t first = block_exclusive_scan<T>((end & 0xFFFFu) - (begin & 0xFFFFu), begin >> 16, reinterpret_cast<uint32_t*>(s.part), &total, before);
+    uint32_t first = (end & 0xFFFFu) - (begin & 0xFFFFu), refs_before = begin >> 16;
+    block_exclusive_scan<T>(first, refs_before, s.part, &total, before);
     if (threadIdx.x < 256u) {
         s.first[threadIdx.x] = first;
         const uint32_t entries = (end & 0xFFFFu) - (begin & 0xFFFFu), refs = (end >> 16) - (begin >> 16);
@@ -771,22 +755,22 @@ template <uint32_t T>
 __device__ __forceinline__ uint32_t place_rows(const PrepArgs& a, uint32_t row, ResolveLds& s, uint2* table)
 {
     const uint32_t tid = threadIdx.x, slots = 1u << a.bin.slot_bits;
-    unsigned long long mine = 0, all;      // items << 32 | places of the list
+    uint32_t item = 0, place = 0, items, places;
     for (uint32_t p = tid; p < slots; p += T) {
         const uint32_t n = table[p].y;
-        if (n > kItemRefs) { atomicAdd(&s.hub_items, (n + kItemRefs - 1) / kItemRefs); mine += n; }
-        else if (n > 1) mine += (1ull << 32) | n;
+        if (n > kItemRefs) atomicAdd(&s.hub_items, (n + kItemRefs - 1) / kItemRefs);
+        if (n > 1) { place += n; item += static_cast<uint32_t>(n <= kItemRefs); }
     }
-    const unsigned long long at = block_exclusive_scan<T>(mine, s.part, &all);
+    block_exclusive_scan<T>(item, place, s.part, &items, &places);
     // (one add per bin: a second one cost 512 bins 1 .. 2 us of the train launch)
-    if (all && tid == 0) {
-        const unsigned long long before = atomicAdd(a.totals, (all >> 32) | (static_cast<unsigned long long>(s.hub_items) << 32));
+    if (places && tid == 0) {
+        const unsigned long long before = atomicAdd(a.totals, items | (static_cast<unsigned long long>(s.hub_items) << 32));
         s.base = static_cast<uint32_t>(before);
         s.hub_items = static_cast<uint32_t>(before >> 32);
     }
     lds_barrier();
-    row += static_cast<uint32_t>(at);
-    uint32_t item = s.base + static_cast<uint32_t>(at >> 32);
+    row += place;
+    item += s.base;
     for (uint32_t p = tid; p < slots; p += T) {
         const uint2 slot = table[p];
         const uint32_t n = slot.y;
@@ -807,7 +791,7 @@ __device__ __forceinline__ uint32_t place_rows(const PrepArgs& a, uint32_t row, 
         if (n > 1) row += n;
     }
     lds_barrier();
-    return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(all));
+    return places;
 }
 
 // f(key, references, place in memory) for every entry of the 256 tiles at hand: as many lanes per segment as it has entries on average,
