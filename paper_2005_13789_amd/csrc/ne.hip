@@ -289,11 +289,13 @@ __device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, uint32_t firs
     // instead of 22 us for the first claim of 170 walks of 80 entries, 5.6 instead of 4.8 for 22 of 40)
     int32_t src[U], ctx[U];
     uint2 e[U], draw[U];
+    uint32_t kinds = 0u;          // two bits per reference
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         if (first + u * T >= last) break;         // (uniform)
         const WalkRef w = ref(min(first + u * T + tid, last - 1u));
         const int32_t* wk = a.walks + static_cast<int64_t>(w.walk) * L;
+        kinds |= w.kind << (2 * u);
         src[u] = wk[min(w.i, L - 1u)];
         ctx[u] = wk[min(w.c, L - 1u)];
         if (w.i >= L) src[u] = -1;
@@ -309,24 +311,30 @@ __device__ __forceinline__ void claim_walk_refs(const PrepArgs& a, uint32_t firs
         const uint32_t t = first + u * T + tid;
         key[u] = kNoKey;
         if (t < last) {
-            const WalkRef w = ref(t);
-            const int32_t* wk = a.walks + static_cast<int64_t>(w.walk) * L;
+            const uint32_t kind = kinds >> (2 * u) & 3u;
             bool valid = src[u] >= 0 && ctx[u] >= 0;
             int32_t id = ctx[u];
-            if (w.kind == 0u) {
-                id = src[u];
-                if (id >= 0)
-                    for (uint32_t c = w.i + 2; !valid && c <= w.i + W && c < L; ++c) valid = wk[c] >= 0;
-            } else if (w.kind == 1u) {
-                // (by segments) other entries of this segment that have c inside their window
-                if (SEG && ctx[u] >= 0)
-                    for (uint32_t i = w.c > w.sample + W ? w.c - W : w.sample; !valid && i < w.i; ++i) valid = wk[i] >= 0;
-            } else if (valid) {
-                id = static_cast<int32_t>(drawn_id(a, draw[u], e[u]));
-                if (a.neg_out) a.neg_out[static_cast<int64_t>(w.sample) * a.K + w.k] = id;
+            if (kind == 2u) {
+                if (valid) {
+                    id = static_cast<int32_t>(drawn_id(a, draw[u], e[u]));
+                    if (a.neg_out) {
+                        const WalkRef w = ref(t);
+                        a.neg_out[static_cast<int64_t>(w.sample) * a.K + w.k] = id;
+                    }
+                }
+            } else {
+                if (kind == 0u) id = src[u];
+                if (!valid && id >= 0 && (SEG || kind == 0u)) {      // by its other contexts, by (segments) its other sources
+                    const WalkRef w = ref(t);
+                    const int32_t* wk = a.walks + static_cast<int64_t>(w.walk) * L;
+                    if (kind == 0u)
+                        for (uint32_t c = w.i + 2; !valid && c <= w.i + W && c < L; ++c) valid = wk[c] >= 0;
+                    else
+                        for (uint32_t i = w.c > w.sample + W ? w.c - W : w.sample; !valid && i < w.i; ++i) valid = wk[i] >= 0;
+                }
             }
             a.ids[t] = valid ? id : -1;
-            if (valid) key[u] = static_cast<uint32_t>(id) | (w.kind == 0u ? 0u : 0x80000000u);
+            if (valid) key[u] = static_cast<uint32_t>(id) | (kind == 0u ? 0u : 0x80000000u);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -1232,16 +1240,19 @@ __global__ __launch_bounds__(kTrainThreads) void train_kernel(TrainArgs a, Helpe
 // ---------------------------------------------------------------------------------------------
 // train kernel of the walk mode: one lane group per walk position.  The source row is gathered once
 // and stays in registers for the position's `window` pairs; its delta is summed over all of them
-// and written once.  The pairs' context rows are handled as in the pair mode, as one list.
+// and written once.  The pairs' context rows are handled as in the pair mode, as one list, which P lane groups of one
+// wavefront share between them: a batch of few positions is bound by a group's chain of ids, rows and sums, and the chip idle
+// beside it (880 positions of 30 context rows at dim 64: 10.5 us with P = 1 and 16 rows at a time, 8.5 with P = 4 and 4 rows).
 // ---------------------------------------------------------------------------------------------
-template <int G, int NCH, int JB>
+template <int G, int NCH, int JB, int P>
 __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, Helpers helpers)
 {
-    constexpr int GROUPS = kTrainThreads / G;
+    static_assert(P == 1 || G * P == 64, "the groups of a position are a wavefront");
+    constexpr int GROUPS = kTrainThreads / (G * P);
     unsigned block;
     if (helper_block<kWalkRefs>(helpers, &block)) return;
     const int lg = threadIdx.x & (G - 1);
-    const int grp = threadIdx.x / G;
+    const int grp = threadIdx.x / (G * P), part = (threadIdx.x / G) & (P - 1);
     const int64_t p = static_cast<int64_t>(block) * GROUPS + grp;
     if (p >= a.B) return;   // whole groups leave together; groups never communicate below
     const int K = a.K;
@@ -1268,7 +1279,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
     bool copied = false;
     // the context references of all pairs, JB at a time; lane l < JB owns reference j0 + l, and the next JB ids travel
     // while these rows do.  (A pair that the walk does not have: its references have id -1.)
-    const int n = a.window * (K + 1);
+    const int all = a.window * (K + 1), share = (all + P - 1) / P, begin = part * share, n = min(all, begin + share);
     auto fetch = [&](int j, int32_t& id, uint32_t& where) {
         id = -1;
         where = 0u;
@@ -1279,9 +1290,9 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
     };
     int32_t id_next;
     uint32_t where_next;
-    fetch(0, id_next, where_next);
-    int phase = 0;                // j0 mod K + 1: reference 0 of a pair is its positive
-    for (int j0 = 0; j0 < n; j0 += JB) {
+    fetch(begin, id_next, where_next);
+    int phase = begin % (K + 1);                // j0 mod K + 1: reference 0 of a pair is its positive
+    for (int j0 = begin; j0 < n; j0 += JB) {
         const int32_t id_mine = id_next;
         const TagRef tag_ref = tag_of(a, id_mine < 0 ? ref0 : ref0 + 1 + j0 + lg, id_mine < 0 ? 0u : where_next);
         float4 cr[JB][NCH];
@@ -1336,6 +1347,16 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
         }
         if (tag_mine) a.list[tag_mine - 1u] = make_uint2(copy, __float_as_uint(g_mine));
         copied |= group_any<G>(tag_mine != 0u);
+    }
+    if (P > 1) {
+        copied = __ballot(copied) != 0ull;
+#pragma unroll
+        for (int off = G; off < G * P; off <<= 1)
+#pragma unroll
+            for (int i = 0; i < NCH; ++i)
+                dx[i] = make_float4(dx[i].x + __shfl_xor(dx[i].x, off, 64), dx[i].y + __shfl_xor(dx[i].y, off, 64),
+                                    dx[i].z + __shfl_xor(dx[i].z, off, 64), dx[i].w + __shfl_xor(dx[i].w, off, 64));
+        if (part) return;
     }
     if (copied) write_copy<G, NCH>(a, copy, xr, lg, d4);
     write_row<G, NCH>(a, xrow, tag0.get(), spare, xr, dx, lg, d4);
@@ -1833,16 +1854,17 @@ hipError_t launch_train(const Shape& s, const TrainArgs& a, const Helpers& h, bo
 hipError_t launch_train_walk(const Shape& s, const TrainArgs& a, const Helpers& h, hipStream_t st)
 {
     const int groups = kTrainThreads / s.G;
-    const TrainGrid g = train_grid(h, (a.B + groups - 1) / groups, 0);
-    // context rows gathered together per lane group: 6; a batch of at most one workgroup per compute unit is bound by
-    // a group's chain of round trips, and takes up to 16 (880 entries, dim 64: 16 rows 2.5 % ahead; 6400 entries,
-    // dim 64: 2.7 % behind, from registers)
+    // A batch of at most one workgroup per compute unit is bound by a position's chain of round trips: where a lane group is
+    // less than a wavefront, a position takes a whole one (880 positions, dim 64, K = 5, window 5: 275 us become 243 for 16 batches; 408,
+    // dim 48, K = 10, window 6: 88 and 58 for 3; up to 1024 workgroups: -5 .. +6 %).  Context rows gathered together per lane group: 6;
+    // in the former case 16 per position, at least 4 per group (8 per group of 16 lanes: 246).
     const bool wide = (a.B + groups - 1) / groups <= 256;
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
-        constexpr int kWide = N_ > 1 ? 6 : G_ < 16 ? G_ : 16;                                    \
-        if (wide) hipLaunchKernelGGL((train_walk_kernel<G_, N_, kWide>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
-        else hipLaunchKernelGGL((train_walk_kernel<G_, N_, 6>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
+        constexpr int kParts = 64 / G_, kWide = N_ > 1 ? 6 : kParts > 2 ? 4 : 16 / kParts;                \
+        const TrainGrid g = train_grid(h, wide ? (a.B * kParts + groups - 1) / groups : (a.B + groups - 1) / groups, 0);  \
+        if (wide) hipLaunchKernelGGL((train_walk_kernel<G_, N_, kWide, kParts>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
+        else hipLaunchKernelGGL((train_walk_kernel<G_, N_, 6, 1>), dim3(g.grid), dim3(kTrainThreads), g.lds, st, a, h); \
         return hipGetLastError();                                                                \
     }
     NE_FOR_EACH_SHAPE(NE_CASE)
