@@ -1294,7 +1294,6 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
     int phase = begin % (K + 1);                // j0 mod K + 1: reference 0 of a pair is its positive
     for (int j0 = begin; j0 < n; j0 += JB) {
         const int32_t id_mine = id_next;
-        const TagRef tag_ref = tag_of(a, id_mine < 0 ? ref0 : ref0 + 1 + j0 + lg, id_mine < 0 ? 0u : where_next);
         float4 cr[JB][NCH];
         int32_t id[JB];
 #pragma unroll
@@ -1307,6 +1306,8 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
                 cr[jj][i] = (id[jj] >= 0 && ci < d4) ? crow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
             }
         }
+        // (behind the rows: loads are waited for in the order in which they were issued)
+        const TagRef tag_ref = tag_of(a, id_mine < 0 ? ref0 : ref0 + 1 + j0 + lg, id_mine < 0 ? 0u : where_next);
         fetch(j0 + JB, id_next, where_next);
         float part[JB];
 #pragma unroll
