@@ -1,7 +1,7 @@
 """Rows that many references of one claim tile name: the tile then makes one entry of all its references to a row, unless
 they lose their slots to other rows, and several entries of one bin, tagged and untagged tiles side by side, share a row's places.
 
-Three references per pair (K = 1).  2730 pairs are 8190 references in 64 tiles of 128 or more, 21 840 pairs 65 520 references in
+Three references per pair (K = 1).  2730 pairs are 8190 references in 32 tiles of 256, 21 840 pairs 65 520 references in
 64 tiles of 1024, 130 000 pairs 390 000 references in 191 tiles of 2048, 200 000 pairs 600 000 references in 147 tiles of 4096, which
 are of several steps and have an entry per reference.  A tile counts as one with many at 4 references per bin + 2, or 2048 / tiles.
 
