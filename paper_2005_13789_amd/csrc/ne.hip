@@ -625,7 +625,7 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
 constexpr uint32_t kItemRefs = 8;                        // references per work item
 // A place in memory (below 2^28), and a flag: some entry of the tile's segment is more than one reference, and their numbers are in tags.
 constexpr uint32_t kPlaceMask = 0x0FFFFFFFu, kCounted = 0x80000000u;
-struct ResolveLds {
+struct alignas(16) ResolveLds {
     uint32_t part[32];
     uint32_t base;
     uint32_t distinct;
@@ -634,6 +634,7 @@ struct ResolveLds {
     uint32_t from[256];       // where entry 0 would be if the tile's entries began with it (kPlaceMask), and whether they have counts (kCounted)
     // then the table, slot after slot: the row's key; its references, later its first, or next, place in the list (~0: not shared)
 };
+static_assert(sizeof(ResolveLds) % alignof(uint2) == 0, "the table's slots are read and written whole");
 inline size_t resolve_lds_bytes(const Binning& b) { return sizeof(ResolveLds) + (static_cast<size_t>(8) << b.slot_bits); }
 
 // Work item of a row with up to kItemRefs places in the list: x = key, y = first place << 3 | places - 1.  A row with
