@@ -375,12 +375,13 @@ __device__ __forceinline__ void block_exclusive_scan(uint32_t& v, uint32_t& w, u
     *total_w = __builtin_amdgcn_readfirstlane(sum_w);
 }
 
-// LDS of the claim phase: a counter per bin (beyond 2^kWordBinBits bins 16 bits each), the scan's 32 words and, if they
-// are one step's, the tile's entries and what claim_rows needs to find them.
+// LDS of the claim phase: a counter per bin (beyond 2^kWordBinBits bins 16 bits each), the scan's 32 words and, if the tile is one
+// step, its entries and what claim_rows needs to find them, else a bit per bin and the table of claim_long_rows.
+constexpr uint32_t kLongRows = 512;        // (as many workgroups fit on a compute unit as without them)
 __host__ __device__ inline uint32_t counter_words(uint32_t bits) { return bits > kWordBinBits ? 1u << (bits - 1u) : 1u << bits; }
 inline size_t claim_lds_bytes(const Binning& b)
 {
-    const size_t rows = b.tile <= kTileStep ? b.tile * (2 * sizeof(uint32_t) + sizeof(uint16_t)) : 0;       // (claim_rows)
+    const size_t rows = b.tile <= kTileStep ? b.tile * (2 * sizeof(uint32_t) + sizeof(uint16_t)) : (1u << b.bits) / 8 + kLongRows * 2 * sizeof(uint32_t);
     return (static_cast<size_t>(counter_words(b.bits)) + 32) * sizeof(uint32_t) + rows;
 }
 
@@ -401,10 +402,13 @@ __device__ __forceinline__ void claim_refs(const PrepArgs& a, uint32_t step, uin
 }
 
 // Where the entries of each bin start in the tile, to hist, and where they end, entries | references << 16, to the segment
-// table; *total: the last end.  hist holds the numbers: of entries | of references << 16 (with_refs), else of entries, which are one
-// reference each.  False, with nothing written, if a bin has more than `most` entries.
+// table; *total: the last end.  hist holds the numbers: kSingles of entries, which are one reference each; kCounts of entries |
+// of references << 16; kEntries of entries, and only that half of the segment words is written.
+// False, with nothing written, if a bin has more than `most`; kRefs: then only the references' ends are written, to their half, and
+// the numbers stay, but for such bins, which start from zero and have a bit in `many`.
+enum BinCounts { kSingles, kCounts, kRefs, kEntries };
 template <uint32_t T>
-__device__ __forceinline__ bool start_bins(const PrepArgs& a, uint32_t tile, uint32_t* hist, bool with_refs, uint32_t most, uint32_t* total)
+__device__ __forceinline__ bool start_bins(const PrepArgs& a, uint32_t tile, uint32_t* hist, BinCounts what, uint32_t most, uint32_t* total, uint32_t* many = nullptr)
 {
     const uint32_t tid = threadIdx.x, bits = a.bin.bits, bins = 1u << bits;
     const bool pack = bits > kWordBinBits;
@@ -422,19 +426,24 @@ __device__ __forceinline__ bool start_bins(const PrepArgs& a, uint32_t tile, uin
     uint32_t overs;
     block_exclusive_scan<T>(mine, over, hist + counter_words(bits), total, &overs);
     uint32_t at = mine;
-    if (overs) return false;                         // (uniform)
+    if (overs && what != kRefs) return false;                         // (uniform)
     for (uint32_t i = 0; i < per; ++i) {
         const uint32_t p = tid * per + i;
         if (p < bins) {
-            const uint32_t end = at + (pack ? half[p] : hist[p]);
-            a.segs[static_cast<size_t>(tile) * bins + p] = with_refs ? end : end | (end << 16);
-            if (pack) half[p] = static_cast<uint16_t>(at);
-            else hist[p] = at & 0xFFFFu;
+            const uint32_t n = pack ? half[p] : hist[p], end = at + n;
+            uint32_t* seg = a.segs + static_cast<size_t>(tile) * bins + p;
+            const bool refs_only = what == kRefs && overs;
+            if (refs_only || what == kEntries) reinterpret_cast<uint16_t*>(seg)[refs_only] = static_cast<uint16_t>(end);
+            else *seg = what == kCounts ? end : end | (end << 16);
+            if (refs_only && n > most) atomicOr(&many[p >> 5], 1u << (p & 31u));
+            const uint32_t start = refs_only ? (n > most ? 0u : n) : at & 0xFFFFu;
+            if (pack) half[p] = static_cast<uint16_t>(start);
+            else hist[p] = start;
             at = end;
         }
     }
     lds_barrier();
-    return true;
+    return !overs;
 }
 
 // A tile of one step with many references in one bin, as a hub's.  One entry stands for all references to a row that find each
@@ -515,7 +524,7 @@ __device__ __forceinline__ void claim_rows(const PrepArgs& a, uint32_t tile, uin
     }
     lds_barrier();
     uint32_t total;
-    start_bins<T>(a, tile, hist, true, ~0u, &total);
+    start_bins<T>(a, tile, hist, kCounts, ~0u, &total);
     total &= 0xFFFFu;
 #pragma unroll
     for (int u = 0; u < kTileKeys<T>; ++u) {
@@ -539,6 +548,102 @@ __device__ __forceinline__ void claim_rows(const PrepArgs& a, uint32_t tile, uin
     }
 }
 
+// Key of a reference whose id is written.
+template <RefMode MODE>
+__device__ __forceinline__ uint32_t key_again(const PrepArgs& a, uint32_t t)
+{
+    const int32_t id = a.ids[t];
+    const bool vertex_row = t % a.R < (MODE == kSegRefs ? a.seg_entries : 1u);
+    return id < 0 ? kNoKey : static_cast<uint32_t>(id) | (vertex_row ? 0u : 0x80000000u);
+}
+
+// A tile of several steps with many references in some bins, which have a bit in `many` (start_bins, kRefs): the rows of these bins,
+// few as they are, find each other in a table; a row that finds no place near its home there has an entry per reference.  Three
+// passes over the tile's ids instead of two.  count_bin adds one to a bin's counter and returns what it was.
+// (With an entry per reference the one workgroup that resolves a hub's bin goes through all of them: 2 x 131 072 pairs, dim 16,
+// K = 5, among 4 M nodes, 5 / 30 % with one source row, 303 / 731 us, with this 200 / 204; 2 x 2^20 2030 / 3740 and 1817 / 1841;
+// 131 072 among 50 / 1000 / 10 000 nodes 2880 / 782 / 372 and 247 / 181 / 179.)
+template <RefMode MODE, uint32_t T, class F>
+__device__ __forceinline__ void claim_long_rows(const PrepArgs& a, uint32_t tile, uint32_t first, uint32_t last, uint32_t* hist, F count_bin)
+{
+    constexpr int U = T == 256 ? 4 : kTileKeys<T>;
+    constexpr uint32_t kAlone = 0x80000000u;
+    const uint32_t tid = threadIdx.x, bits = a.bin.bits;
+    uint32_t* many = hist + counter_words(bits) + 32;
+    uint32_t* row = many + ((1u << bits) >> 5);
+    uint32_t* count = row + kLongRows;          // of the row's references; later the number of its entry
+    auto of_many = [&](uint32_t key) { const uint32_t p = bin_of(key, bits); return key != kNoKey && (many[p >> 5] >> (p & 31u) & 1u); };
+    for (uint32_t i = tid; i < kLongRows; i += T) { row[i] = kNoKey; count[i] = 0u; }
+    __syncthreads();                            // (ids that other threads have written)
+    auto fetch = [&](uint32_t step, uint32_t (&key)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) key[u] = step + u * T + tid < last ? key_again<MODE>(a, step + u * T + tid) : kNoKey;
+    };
+    uint32_t next[U];
+    fetch(first, next);
+    for (uint32_t step = first; step < last; step += U * T) {
+        uint32_t key[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) key[u] = next[u];
+        fetch(step + U * T, next);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!of_many(key[u])) continue;
+            uint32_t at = (key[u] * 0x85EBCA6Bu) / (0xFFFFFFFFu / kLongRows + 1u), w = kAlone;
+            for (int probe = 0; probe < 8; ++probe, at = (at + 1u) & (kLongRows - 1u)) {
+                uint32_t k = __hip_atomic_load(row + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (k == kNoKey) k = atomicCAS(row + at, kNoKey, key[u]);
+                if (k == kNoKey || k == key[u]) { w = at | (atomicAdd(count + at, 1u) << 16); break; }
+            }
+            if (w == kAlone) count_bin(bin_of(key[u], bits));
+            a.where[step + u * T + tid] = w;
+        }
+    }
+    lds_barrier();
+    for (uint32_t i = tid; i < kLongRows; i += T)
+        if (row[i] != kNoKey) count_bin(bin_of(row[i], bits));
+    lds_barrier();
+    uint32_t total;
+    start_bins<T>(a, tile, hist, kEntries, ~0u, &total);
+    for (uint32_t i = tid; i < kLongRows; i += T)
+        if (row[i] != kNoKey) {
+            const uint32_t p = count_bin(bin_of(row[i], bits));
+            a.keys[first + p] = row[i];
+            a.tags[first + p] = count[i];
+            count[i] = p;
+        }
+    auto fetch_where = [&](uint32_t step, uint32_t (&w)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = step + u * T + tid < last ? a.where[step + u * T + tid] : 0u;
+    };
+    uint32_t next_w[U];
+    fetch(first, next);
+    fetch_where(first, next_w);
+    lds_barrier();
+    for (uint32_t step = first; step < last; step += U * T) {
+        uint32_t key[U], w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) { key[u] = next[u]; w[u] = next_w[u]; }
+        fetch(step + U * T, next);
+        fetch_where(step + U * T, next_w);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (step + u * T + tid >= last) continue;
+            uint32_t p = 0u;
+            if (key[u] != kNoKey) {
+                const bool rows = of_many(key[u]);
+                if (rows && w[u] != kAlone) p = count[w[u] & 0xFFFFu] | (w[u] & 0xFFFF0000u);
+                else {
+                    p = count_bin(bin_of(key[u], bits));
+                    a.keys[first + p] = key[u];
+                    if (rows) a.tags[first + p] = 1u;
+                }
+            }
+            a.where[step + u * T + tid] = p;
+        }
+    }
+}
+
 // One tile of references: draw, count by bin, then write the entries of each bin side by side.
 // All T threads of the workgroup call this together; hist: claim_lds_bytes() of LDS.
 template <RefMode MODE, uint32_t T>
@@ -552,7 +657,6 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
     const uint32_t first = tile * a.bin.tile;
     const uint32_t last = min(first + a.bin.tile, a.refs);   // (refs is at most 2^28)
     uint32_t key[kTileKeys<T>];
-    // several steps: an entry per reference
     auto count = [&](uint32_t p) {       // what the bin's counter was
         const uint32_t shift = (p & pack) << 4, before = atomicAdd(&hist[p >> pack], 1u << shift) >> shift;
         return pack ? before & 0xFFFFu : before;
@@ -568,10 +672,13 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
     }
     lds_barrier();
     uint32_t total;
+    // (a bin whose rows are many has up to 13 references or so of the mean 4; where tiles are few, a bin's references stay few
+    // whatever one tile has of them; the third pass over a long tile lengthens the claim phase, a launch's longest chain, where as
+    // many entries in the resolve phase still hide behind it: 2 x 262 144 pairs, dim 128, K = 10, 5 % with one source row, 68 of them a
+    // tile, 1896 us with it, 1824 without; 18 at all lengths also 2 x 2^22 pairs among 4 M nodes, 0.5 % with one, 8250 instead of 7710)
+    const uint32_t most = max(max(4u * (a.bin.tile >> bits) + 2u, a.bin.tile / 512u * 3u), kTileStep / a.bin.tiles);
     if (a.bin.tile <= kTileStep) {                   // (uniform)
-        // (a bin whose rows are many has up to 13 references or so of the mean 4; where tiles are few, a bin's references stay few
-        // whatever one tile has of them)
-        if (!start_bins<T>(a, tile, hist, false, max(4u * (a.bin.tile >> bits) + 2u, kTileStep / a.bin.tiles), &total)) {
+        if (!start_bins<T>(a, tile, hist, kSingles, most, &total)) {
             claim_rows<T>(a, tile, first, last, key, hist);
             return;
         }
@@ -591,7 +698,12 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
         for (uint32_t i = tid; i < total; i += T) a.keys[first + i] = keys[i];
         return;
     }
-    start_bins<T>(a, tile, hist, false, ~0u, &total);
+    uint32_t* many = hist + words + 32;
+    for (uint32_t i = tid; i < (1u << bits) >> 5; i += T) many[i] = 0u;        // (start_bins begins with a barrier)
+    if (!start_bins<T>(a, tile, hist, kRefs, most, &total, many)) {
+        claim_long_rows<MODE, T>(a, tile, first, last, hist, count);
+        return;
+    }
     // the last step's keys are still in registers; earlier ones are rebuilt from the ids
     for (;;) {
 #pragma unroll
@@ -609,10 +721,7 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
 #pragma unroll
         for (int u = 0; u < kTileKeys<T>; ++u) {
             const uint32_t t = step + u * T + tid;
-            const int32_t id = a.ids[t];
-            const uint32_t q = t % a.R;
-            const bool vertex_row = q < (MODE == kSegRefs ? a.seg_entries : 1u);
-            key[u] = id < 0 ? kNoKey : static_cast<uint32_t>(id) | (vertex_row ? 0u : 0x80000000u);
+            key[u] = key_again<MODE>(a, t);
         }
     }
 }
@@ -683,35 +792,37 @@ __device__ __forceinline__ uint32_t number_entries(const PrepArgs& a, uint32_t b
     return total;
 }
 
-template <uint32_t T>
-__device__ __forceinline__ void fetch_share(const PrepArgs& a, uint32_t total, const ResolveLds& s, BinShare<T>& e)
+// The entries first + T * u + tid < total of the 256 tiles at hand, u < U: their rows, where they lie, and their references.
+template <uint32_t T, int U>
+__device__ __forceinline__ void fetch_entries(const PrepArgs& a, uint32_t total, uint32_t first, const ResolveLds& s,
+                                              uint32_t (&key)[U], uint32_t (&from)[U], uint32_t (&refs)[U])
 {
-    const uint32_t k = threadIdx.x;
-    uint32_t (&tile)[kShare<T>] = e.at;                       // the last tile whose first entry is not behind the thread's
+    const uint32_t k = first + threadIdx.x;
+    uint32_t tile[U];                       // the last tile whose first entry is not behind the thread's
 #pragma unroll
-    for (int u = 0; u < kShare<T>; ++u) tile[u] = 0u;
+    for (int u = 0; u < U; ++u) tile[u] = 0u;
     for (uint32_t step = a.bin.tiles > 128u ? 128u : 1u << (31 - __builtin_clz(a.bin.tiles)); step; step >>= 1) {
-        uint32_t begin[kShare<T>];
+        uint32_t begin[U];
 #pragma unroll
-        for (int u = 0; u < kShare<T>; ++u) {
-            if (T * u >= total) break;          // (uniform)
+        for (int u = 0; u < U; ++u) {
+            if (first + T * u >= total) break;          // (uniform)
             begin[u] = s.first[tile[u] + step];
         }
 #pragma unroll
-        for (int u = 0; u < kShare<T>; ++u) {
-            if (T * u >= total) break;
+        for (int u = 0; u < U; ++u) {
+            if (first + T * u >= total) break;
             if (begin[u] <= k + T * u) tile[u] += step;
         }
     }
 #pragma unroll
-    for (int u = 0; u < kShare<T>; ++u) {
-        if (T * u >= total) break;
+    for (int u = 0; u < U; ++u) {
+        if (first + T * u >= total) break;
         if (k + T * u < total) {
-            const uint32_t from = s.from[tile[u]];
-            e.from[u] = (from + k + T * u) & kPlaceMask;
-            e.key[u] = a.keys[e.from[u]];
-            e.refs[u] = 1u;
-            if (from & kCounted) e.refs[u] = a.tags[e.from[u]];
+            const uint32_t place = s.from[tile[u]];
+            from[u] = (place + k + T * u) & kPlaceMask;
+            key[u] = a.keys[from[u]];
+            refs[u] = 1u;
+            if (place & kCounted) refs[u] = a.tags[from[u]];
         }
     }
 }
@@ -803,27 +914,20 @@ __device__ __forceinline__ uint32_t place_rows(const PrepArgs& a, uint32_t row, 
     return places;
 }
 
-// f(key, references, place in memory) for every entry of the 256 tiles at hand: as many lanes per segment as it has entries on average,
-// four entries of each lane in flight; until stop().
+// f(key, references, place in memory) for every entry of the 256 tiles at hand, four of a thread in flight (eight: 73 registers, a
+// wavefront less of the kernels this rides in), until stop().  Numbered through like a share's, because segments are short where tiles
+// are many: as many lanes per segment as it has entries on average, one segment after the other, took 5660 us for 3 x 2^21
+// pairs, dim 16, among 32 M nodes, this 5500 (2^22: 12 470 and 12 110).
 template <uint32_t T, class F, class S>
-__device__ __forceinline__ void for_entries(const PrepArgs& a, uint32_t tile0, uint32_t total, const ResolveLds& s, F f, S stop)
+__device__ __forceinline__ void for_entries(const PrepArgs& a, uint32_t total, const ResolveLds& s, F f, S stop)
 {
-    const uint32_t tiles = min(a.bin.tiles - tile0, 256u), mean = (total + tiles - 1) / tiles;
-    const uint32_t lane_bits = mean <= 4u ? 2u : mean >= 256u ? 8u : 32u - __builtin_clz(mean - 1u), lanes = 1u << lane_bits;
-    for (uint32_t t = threadIdx.x >> lane_bits; t < tiles && !stop(); t += T >> lane_bits) {
-        const uint32_t begin = s.first[t], n = (t + 1u < 256u ? s.first[t + 1u] : total) - begin, counted = s.from[t] & kCounted, from = (s.from[t] + begin) & kPlaceMask;
-        for (uint32_t q = threadIdx.x & (lanes - 1u); q < n; q += 4u * lanes) {
-            uint32_t key[4], refs[4];
+    constexpr int U = T == 256 ? 4 : kShare<T>;
+    for (uint32_t first = 0; first < total && !stop(); first += T * U) {
+        uint32_t key[U], from[U], refs[U];
+        fetch_entries<T>(a, total, first, s, key, from, refs);
 #pragma unroll
-            for (uint32_t i = 0; i < 4; ++i)
-                if (q + i * lanes < n) {
-                    key[i] = a.keys[from + q + i * lanes];
-                    refs[i] = counted ? a.tags[from + q + i * lanes] : 1u;
-                }
-#pragma unroll
-            for (uint32_t i = 0; i < 4; ++i)
-                if (q + i * lanes < n) f(key[i], refs[i], from + q + i * lanes);
-        }
+        for (int u = 0; u < U; ++u)
+            if (first + T * u + threadIdx.x < total) f(key[u], refs[u], from[u]);
     }
 }
 
@@ -841,7 +945,7 @@ template <uint32_t T>
 __device__ __forceinline__ void resolve_share(const PrepArgs& a, uint32_t total, uint32_t first_place, ResolveLds& s, uint2* table)
 {
     BinShare<T> e;
-    fetch_share<T>(a, total, s, e);
+    fetch_entries<T>(a, total, 0u, s, e.key, e.from, e.refs);
     clear_table<T>(a, s, table);
     locate_share<T>(a, total, table, e);
 #pragma unroll
@@ -885,7 +989,7 @@ __device__ __forceinline__ void resolve_passes(const PrepArgs& a, uint32_t bin, 
                 total = number_entries<T>(a, bin, t0, s, &before);
                 first_place += before;
             }
-            for_entries<T>(a, t0, total, s, [&](uint32_t key, uint32_t refs, uint32_t) {
+            for_entries<T>(a, total, s, [&](uint32_t key, uint32_t refs, uint32_t) {
                 uint32_t at;
                 if (!home(key, &at)) return;
                 for (;; at = next(at)) {
@@ -913,7 +1017,7 @@ __device__ __forceinline__ void resolve_passes(const PrepArgs& a, uint32_t bin, 
                 lds_barrier();
                 total = number_entries<T>(a, bin, t0, s, &before);
             }
-            for_entries<T>(a, t0, total, s, [&](uint32_t key, uint32_t refs, uint32_t from) {
+            for_entries<T>(a, total, s, [&](uint32_t key, uint32_t refs, uint32_t from) {
                 uint32_t at;
                 if (!home(key, &at)) return;
                 while (*key_of(table, at) != key) at = next(at);

@@ -35,7 +35,7 @@ namespace {
 struct PrepSlot {
     int32_t* ids;                 // [refs]  row named by each reference (walk mode: -1 = no such reference)
     uint32_t* where;              // [refs]  the entry of the reference's tile that is its row's | its rank among the entry's references << 16
-    uint32_t* keys;               // [refs]  the entries, one per row and tile: keys, sorted by bin inside each tile
+    uint32_t* keys;               // [refs]  the entries, one per reference or, of a hub, one or a few per tile: keys, sorted by bin inside each tile
     uint32_t* tags;               // [refs]  in the same order: references of the entry; later 0 = only one reference names the row, else
                                   //         1 + the place in the list of the entry's first reference
     uint32_t* segs;               // [tiles][bins]  where a tile's entries of a bin end | where its references do (<< 16)

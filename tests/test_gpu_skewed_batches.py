@@ -77,6 +77,18 @@ def test_a_dominant_row_does_not_hold_the_batch_up():
     assert star <= 12 * plain
 
 
+@pytest.mark.parametrize("B,K", [(131_072, 5), (65_536, 10)])
+def test_a_hub_does_not_hold_up_a_batch_of_long_tiles(B, K):
+    """Beyond 524 288 references a claim tile is of several steps.  30 % of the pairs with one source row against random
+    ones: 1.1 times as long (3 and 2 times while such a tile had an entry for each of the row's references)."""
+    pairs = np.random.default_rng(4).integers(0, 4_000_000, (B, 2))
+    plain = time_of_batch(4_000_000, 16, K, pairs)
+    pairs[np.random.default_rng(5).random(B) < 0.3, 0] = 9
+    star = time_of_batch(4_000_000, 16, K, pairs)
+    print(f"random sources {plain * 1e6:.1f} us, 30 % of one {star * 1e6:.1f} us: {star / plain:.2f}", flush=True)
+    assert star <= 1.5 * plain
+
+
 def test_narrow_rows_with_many_negatives():
     """32 768 pairs with 62 negatives at dim 4 against dim 128, whose rows are 32 times as long: 0.55 of the time
     (0.74 while the apply kernel gave a row 64 lanes there, one for each reference of a pair)."""
