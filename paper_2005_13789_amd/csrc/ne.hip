@@ -1383,7 +1383,10 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
     const uint32_t copy = static_cast<uint32_t>(p), spare = static_cast<uint32_t>(a.B + p);   // rows of buf
     bool copied = false;
     // the context references of all pairs, JB at a time; lane l < JB owns reference j0 + l, and the next JB ids travel
-    // while these rows do.  (A pair that the walk does not have: its references have id -1.)
+    // while these rows do.  (A pair that the walk does not have: its references have id -1.)  Where it costs no wavefront (4 more
+    // registers), ids travel two rounds ahead and their tags, one access further away, one: 4 x 4800 positions, dim 512, K = 5,
+    // 486 -> 475 us, 4 x 11 050, dim 144, 422 -> 417; at dim 64 it costs one (4 x 4800 positions, K = 10, 513 -> 556).
+    constexpr int AHEAD = G == 64 ? 2 : 1;
     const int all = a.window * (K + 1), share = (all + P - 1) / P, begin = part * share, n = min(all, begin + share);
     auto fetch = [&](int j, int32_t& id, uint32_t& where) {
         id = -1;
@@ -1393,12 +1396,19 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
             where = a.where[ref0 + 1 + j + lg];
         }
     };
-    int32_t id_next;
+    auto fetch_tag = [&](int j, int32_t id, uint32_t where) { return tag_of(a, id < 0 ? ref0 : ref0 + 1 + j + lg, id < 0 ? 0u : where); };
+    int32_t id_next, id_mine = -1;
     uint32_t where_next;
+    TagRef tag_ref{0u, 0u};
     fetch(begin, id_next, where_next);
+    if (AHEAD == 2) {
+        id_mine = id_next;
+        tag_ref = fetch_tag(begin, id_mine, where_next);
+        fetch(begin + JB, id_next, where_next);
+    }
     int phase = begin % (K + 1);                // j0 mod K + 1: reference 0 of a pair is its positive
     for (int j0 = begin; j0 < n; j0 += JB) {
-        const int32_t id_mine = id_next;
+        if (AHEAD == 1) id_mine = id_next;
         float4 cr[JB][NCH];
         int32_t id[JB];
 #pragma unroll
@@ -1412,8 +1422,10 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
             }
         }
         // (behind the rows: loads are waited for in the order in which they were issued)
-        const TagRef tag_ref = tag_of(a, id_mine < 0 ? ref0 : ref0 + 1 + j0 + lg, id_mine < 0 ? 0u : where_next);
-        fetch(j0 + JB, id_next, where_next);
+        const TagRef tag_next = fetch_tag(j0 + (AHEAD - 1) * JB, id_next, where_next);
+        const int32_t id_then = id_next;
+        fetch(j0 + AHEAD * JB, id_next, where_next);
+        if (AHEAD == 1) tag_ref = tag_next;
         float part[JB];
 #pragma unroll
         for (int jj = 0; jj < JB; ++jj) {
@@ -1453,6 +1465,10 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
         }
         if (tag_mine) a.list[tag_mine - 1u] = make_uint2(copy, __float_as_uint(g_mine));
         copied |= group_any<G>(tag_mine != 0u);
+        if (AHEAD == 2) {
+            id_mine = id_then;
+            tag_ref = tag_next;
+        }
     }
     if (P > 1) {
         copied = __ballot(copied) != 0ull;

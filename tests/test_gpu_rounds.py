@@ -97,3 +97,29 @@ def test_shared_passes(d, B, N):
         assert err <= 2e-4 * top + 2 ** -23
         idle = want.abs().sum(1) == 0
         assert torch.equal(got[idle], old[idle])
+
+
+@pytest.mark.parametrize("n_walks", [3, 80])
+@pytest.mark.parametrize("d,L", [(16, 9), (64, 5), (128, 3)])      # 8, 4 and 2 groups to a position, or fewer by K; by entries
+@pytest.mark.parametrize("window,K", [(1, 0), (5, 0), (3, 1), (1, 6), (3, 4), (4, 3), (1, 16), (4, 7), (3, 10), (2, 40)])
+def test_walk_rows_shared_out(n_walks, d, L, window, K):
+    """Positions whose rows several lane groups share: fewer rows than groups, shares that are no multiple of the rows in
+    flight, shares that begin inside a pair, holes and ends of walks.  Bar as above."""
+    print(f"walks n={n_walks} d={d} window={window} K={K}", flush=True)
+    V, seed = 4000, 9
+    rng = np.random.default_rng(n_walks + window + K)
+    deg = rng.integers(1, 9, V).astype(np.uint32)
+    walks = rng.integers(0, V, (n_walks, L)).astype(np.int32)
+    walks[0, L - 2:] = -1
+    walks[1, L // 2] = -1
+    R = 1 + window * (K + 1)
+    t = make(V, d, -(-(n_walks * L * R) // (K + 2)), K, seed)
+    alias = ne.ne_build_neg_alias(deg, 0, torch.empty((V, 2), dtype=torch.int32, device=DEV))
+    thr, al, _ = oracle.build_alias(deg)
+    X, C = t.vertex.cpu().numpy(), t.context.cpu().numpy()
+    ne.ne_train_walks(t, alias, torch.from_numpy(walks).to(DEV), n_walks, window, K, [0.02], 40)
+    torch.cuda.synchronize()
+    oracle_run(X, C, walks, n_walks, window, K, [0.02], seed, 40, thr, al)
+    ex, ec = rowwise_rel_err(t.vertex.cpu().numpy(), X), rowwise_rel_err(t.context.cpu().numpy(), C)
+    print(f"  row error X {ex:.2e} C {ec:.2e}", flush=True)
+    assert ex <= 1e-5 and ec <= 1e-5
