@@ -2016,14 +2016,18 @@ hipError_t launch_train_seg(const Shape& s, const TrainArgs& a, const Helpers& h
 
 // Workgroups of 1024 threads where they all have a place at once and a tile has a reference for each: the first claim of a batch of
 // 65 536 pairs 14 instead of 20 us where tiles have hubs, a batch of 90 000 references 37.2 instead of 37.8, walks 394 and 401.
-// (Tiles of 512, half the threads idle: equal.  More workgroups, 736 of resolve and claim: 30 instead of 21 us.)
+// (Tiles of 512, half the threads idle: equal.  More workgroups, 736 of resolve and claim: 30 instead of 21 us.)  Bins and tiles in
+// one launch: only where the bins are long, whose chain it shortens (2 x 4096 pairs, K = 9, dim 64, 144 references per bin, 43.8 us
+// with 256 threads and 46.3 with 1024; 2 x 16 384, K = 5, 448 of them, 56.1 and 57.6; 2 x 22 000, 601, level; 2 x 30 000, 820, 75 and 72.8).
 constexpr uint32_t kWideTile = 1024;
 constexpr unsigned kWideBlocks = 512;
+constexpr uint32_t kWideBin = 640;
 hipError_t launch_prepare(const Helpers& h, bool claim_first, hipStream_t st)
 {
     const size_t own = claim_first ? claim_lds_bytes(h.resolve.bin) : 0, lds = own > h.lds_bytes() ? own : h.lds_bytes();
     const PrepArgs& p = h.claims ? h.claim : h.resolve;
-    const bool wide = p.bin.tile >= kWideTile && h.count() <= kWideBlocks;
+    const bool one_kind = !h.claims || !h.resolves;
+    const bool wide = p.bin.tile >= kWideTile && h.count() <= kWideBlocks && (one_kind || (h.resolve.refs >> h.resolve.bin.bits) >= kWideBin);
 #define NE_CASE(M_)                                                                              \
     if (wide) hipLaunchKernelGGL((prepare_kernel<M_, 1024>), dim3(h.count()), dim3(1024), lds, st, h, claim_first);  \
     else hipLaunchKernelGGL((prepare_kernel<M_, 256>), dim3(h.count()), dim3(256), lds, st, h, claim_first);
