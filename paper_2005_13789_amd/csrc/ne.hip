@@ -1367,8 +1367,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
 
     const int32_t src = a.ids[ref0];
     if (src < 0) return;    // no pair starts at this position (uniform over the group)
-    const TagRef tag0 = tag_of(a, ref0, a.where[ref0]);
-
+    const uint32_t where0 = a.where[ref0];
     float4* xrow = a.X + static_cast<int64_t>(src) * d4;
     float4 xr[NCH];
 #pragma unroll
@@ -1376,6 +1375,7 @@ __global__ __launch_bounds__(kTrainThreads) void train_walk_kernel(TrainArgs a, 
         const int ci = lg + i * G;
         xr[i] = (ci < d4) ? xrow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
+    const TagRef tag0 = tag_of(a, ref0, where0);       // (behind the row: loads are waited for in the order in which they were issued)
     float4 dx[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) dx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
