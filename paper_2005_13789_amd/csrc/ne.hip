@@ -6,7 +6,7 @@
 //   claim, resolve (ids only)  find out which rows several references of the batch name (a reference:
 //          the source, the context or one of the K negatives of a pair).  claim takes the references
 //          tile by tile: draws the negatives (Philox + alias table) and writes the tile's entries (a row's key, for one
-//          reference or for all that a tile has of a hub), sorted by a hash of the key into bins.  resolve takes one bin per
+//          reference or for most or all that a tile has of a hub), sorted by a hash of the key into bins.  resolve takes one bin per
 //          workgroup: all entries of a row meet in one hash table in LDS.  A row with n > 1 references
 //          gets n consecutive places in a list, one per reference, and ceil(n / 8)
 //          work items for the apply kernel; an entry's place goes where the entry lies (its tag).  Nothing goes through atomics in
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void init_tables_kernel(float4* __restrict__ X
 // for every lost position (measured at 458 752 references: 28 us of a 134 us batch, plus a linear pass
 // that emptied the table again).  Here an entry is written once into a tile-local run of its bin and
 // read once from there, runs of a few entries are one transaction, and everything that needs an
-// atomic happens in LDS.  Riding in the train launch both phases together add 11 - 15 us to
+// atomic happens in LDS.  Riding in the train launch both phases together add 8 - 15 us to
 // its 61 us (1 M nodes, dim 128, 65 536 pairs) or 75 us (32 M).  What that is, found by leaving parts of one batch's resolve phase out
 // (its outputs were not needed): tags stored reference by reference, 4 bytes here and there, 4.5 us where as many side by
 // side take 0.4 (eight dies hold the same lines in part and each writes its part back), so a tag goes to its entry's place, and
