@@ -9,8 +9,8 @@
 //          reference or for most or all that a tile has of a hub), sorted by a hash of the key into bins.  resolve takes one bin per
 //          workgroup: all entries of a row meet in one hash table in LDS.  A row with n > 1 references
 //          gets n consecutive places in a list, one per reference, and ceil(n / 8)
-//          work items for the apply kernel; an entry's place goes where the entry lies (its tag).  Nothing goes through atomics in
-//          memory but one add per bin to the batch's totals, and no state has to be cleared between batches.
+//          work items for the apply kernel, which the batch's train launch moves together; an entry's place goes where the entry lies
+//          (its tag).  Nothing goes through atomics in memory, and no state has to be cleared between batches.
 //   train  one lane group per pair: gathers x = vertex[src] and the K+1 context rows (dwordx4),
 //          reduces the K+1 dot products with DPP, forms g_j and the deltas.  A row that only this
 //          pair names is rewritten in place from registers (old + delta, one plain store: the row
@@ -85,12 +85,13 @@ __global__ __launch_bounds__(256) void init_tables_kernel(float4* __restrict__ X
 // for every lost position (measured at 458 752 references: 28 us of a 134 us batch, plus a linear pass
 // that emptied the table again).  Here an entry is written once into a tile-local run of its bin and
 // read once from there, runs of a few entries are one transaction, and everything that needs an
-// atomic happens in LDS.  Riding in the train launch both phases together add 8 - 15 us to
-// its 61 us (1 M nodes, dim 128, 65 536 pairs) or 75 us (32 M).  What that is, found by leaving parts of one batch's resolve phase out
+// atomic happens in LDS.  Riding in the train launch both phases together add 8 - 13 us to
+// its 62 us (1 M nodes, dim 128, 65 536 pairs) or 75 us (32 M).  What that is, found by leaving parts of one batch's resolve phase out
 // (its outputs were not needed): tags stored reference by reference, 4 bytes here and there, 4.5 us where as many side by
 // side take 0.4 (eight dies hold the same lines in part and each writes its part back), so a tag goes to its entry's place, and
-// the reference keeps where that is; a second add per bin to the line of the totals 2.5 us (adds to a line retire one after
-// the other, and rows behind the same channel wait); in the claim phase the alias table's random reads, 5 us (32 M nodes).
+// the reference keeps where that is; an add per bin to a line of totals 2 - 3 us (adds to a line retire one after
+// the other, and rows behind the same channel wait), so the bins' work items are counted by who moves them together; in the claim phase
+// the alias table's random reads, 5 us (32 M nodes).
 // Entries, ids, Philox, LDS: written, read or done twice, they cost nothing more.
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
@@ -154,9 +155,9 @@ struct PrepArgs {
     Binning bin;
     int32_t* ids;
     uint32_t* where;
-    uint2* items;
+    uint2* items;         // of the bins, as are hub_items; nullptr: nothing is left to apply (per-sample mode)
     uint4* hub_items;
-    unsigned long long* totals;
+    uint4* bins;
     uint32_t* keys;
     uint32_t* tags;
     uint32_t* segs;
@@ -175,7 +176,7 @@ __device__ __forceinline__ uint32_t bin_of(uint32_t key, uint32_t bits) { return
 // draws several references at once, all loads of which are issued before the first is waited for: the functions below
 // take U references per thread, first + u * T + tid < last for u < U, and return their keys (kNoKey where there is none);
 // ids and requested negatives go to memory.
-// Everything here comes for workgroups of T = 256 threads, which ride in train launches, and of 1024, for launches of its own
+// Everything here comes for workgroups of T = 256 threads, which ride in train launches, and of 512, for launches of its own
 // that leave most of the chip idle (launch_prepare).
 constexpr uint32_t kTileStep = 2048;       // references per workgroup and step, whose keys stay in registers
 template <uint32_t T> constexpr int kTileKeys = kTileStep / T;
@@ -392,10 +393,10 @@ enum RefMode { kPairRefs, kWalkRefs, kSegRefs };
 template <RefMode MODE, uint32_t T>
 __device__ __forceinline__ void claim_refs(const PrepArgs& a, uint32_t step, uint32_t last, uint32_t* key)
 {
-    constexpr int H = kTileKeys<T> / 2;       // (all eight of 256 threads at once take 95 registers)
+    constexpr int H = T == 256 ? kTileKeys<T> / 2 : kTileKeys<T>;       // (all eight of 256 threads at once take 95 registers)
     const unsigned tid = threadIdx.x;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < kTileKeys<T> / H; ++h) {
         if (MODE == kPairRefs) claim_pair_refs<H, T>(a, step + h * T * H, last, tid, key + h * H);
         else claim_walk_refs<H, MODE == kSegRefs, T>(a, step + h * T * H, last, tid, key + h * H);
     }
@@ -652,7 +653,6 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
     const unsigned tid = threadIdx.x;
     const uint32_t bits = a.bin.bits;
     const uint32_t words = counter_words(bits), pack = bits > kWordBinBits ? 1u : 0u;
-    if (tile == 0 && tid == 0) *a.totals = 0ull;   // resolve, one launch later, counts from zero
     for (uint32_t i = tid; i < words; i += T) hist[i] = 0u;
     const uint32_t first = tile * a.bin.tile;
     const uint32_t last = min(first + a.bin.tile, a.refs);   // (refs is at most 2^28)
@@ -661,10 +661,10 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
         const uint32_t shift = (p & pack) << 4, before = atomicAdd(&hist[p >> pack], 1u << shift) >> shift;
         return pack ? before & 0xFFFFu : before;
     };
-    lds_barrier();
     uint32_t step = first;
     for (;; step += kTileStep) {
         claim_refs<MODE, T>(a, step, last, key);
+        if (step == first) lds_barrier();            // (the counters are zero)
 #pragma unroll
         for (int u = 0; u < kTileKeys<T>; ++u)
             if (key[u] != kNoKey) count(bin_of(key[u], bits));
@@ -735,12 +735,15 @@ constexpr uint32_t kItemRefs = 8;                        // references per work 
 // A place in memory (below 2^28), and a flag: some entry of the tile's segment is more than one reference, and their numbers are in tags.
 constexpr uint32_t kPlaceMask = 0x0FFFFFFFu, kCounted = 0x80000000u;
 struct alignas(16) ResolveLds {
-    uint32_t part[32];
-    uint32_t base;
+    unsigned long long taken; // by the bin's rows so far: places | work items << 32
+    uint32_t hub_items;       // work items of its hubs so far
     uint32_t distinct;
-    uint32_t hub_items;       // of the range's rows; later the number of the next one
+    uint32_t long_segments;   // some tile has more than kShortSegment entries in the bin
+    uint32_t unused[3];
+    uint32_t part[32];
     uint32_t first[256];      // of the 256 tiles at hand: number of the tile's first entry among theirs in this bin
     uint32_t from[256];       // where entry 0 would be if the tile's entries began with it (kPlaceMask), and whether they have counts (kCounted)
+    uint8_t tile_of[2048];    // of each entry of a share, if no segment is long
     // then the table, slot after slot: the row's key; its references, later its first, or next, place in the list (~0: not shared)
 };
 static_assert(sizeof(ResolveLds) % alignof(uint2) == 0, "the table's slots are read and written whole");
@@ -755,6 +758,35 @@ __device__ __forceinline__ uint32_t item_places(uint32_t first, uint32_t n) { re
 // because each has more than kItemRefs places.
 __device__ __forceinline__ uint32_t hub_accumulator(uint32_t first) { return (first + kItemRefs - 1u) / kItemRefs; }
 
+// A bin writes its items from where its references say, whatever other bins write: those of `refs` references are at most refs / 2
+// items and refs 2/9 items of hubs (one of nine references has two).  The batch's train launch moves them together (gather_items).
+// (One list for all bins, appended to with an add to the batch's totals: the add's round trip is a sixth of the chain of a batch of 28 672
+// references, and 512 of them behind one another hold up a channel's rows: 2 - 3 us of the train launch of 65 536 pairs.)
+__host__ __device__ inline uint64_t most_items(uint64_t refs) { return refs / 2u; }
+__host__ __device__ inline uint64_t most_hub_items(uint64_t refs) { return refs * 2u / 9u; }
+
+// The items of each lane's row, which has n references (up to 1: none) and places from `place` on, from numbers item and hub of the
+// batch's bins on, which are moved behind them.  All lanes call this together.
+__device__ __forceinline__ void write_items(const PrepArgs& a, uint32_t key, uint32_t n, uint32_t place, uint32_t& item, uint32_t& hub)
+{
+    constexpr uint32_t kAlone = 8 * kItemRefs;          // a lane writes up to eight items by itself
+    const uint32_t m = (n + kItemRefs - 1u) / kItemRefs;
+    auto write = [&](uint32_t at, uint32_t k, uint32_t refs, uint32_t first, uint32_t of, uint32_t q) {
+        a.hub_items[at + q] = make_uint4(k, item_places(first + q * kItemRefs, min(kItemRefs, refs - q * kItemRefs)), of, q);
+    };
+    if (n > 1 && n <= kItemRefs) a.items[item++] = make_uint2(key, item_places(place, n));
+    else if (n > kItemRefs && n <= kAlone)
+        for (uint32_t q = 0; q < m; ++q) write(hub, key, n, place, m, q);
+    // more by the whole wavefront: one lane takes 280 us for the 8192 of a row with 65 536 references
+    for (unsigned long long hubs = __ballot(n > kAlone); hubs; hubs &= hubs - 1ull) {
+        const int lane = __builtin_ctzll(hubs);
+        const uint32_t k = __builtin_amdgcn_readlane(key, lane), refs = __builtin_amdgcn_readlane(n, lane), first = __builtin_amdgcn_readlane(place, lane);
+        const uint32_t of = __builtin_amdgcn_readlane(m, lane), at = __builtin_amdgcn_readlane(hub, lane);
+        for (uint32_t q = threadIdx.x & 63u; q < of; q += 64u) write(at, k, refs, first, of, q);
+    }
+    if (n > kItemRefs) hub += m;
+}
+
 // A bin's entries lie in up to one segment per tile.  A workgroup numbers those of 256 tiles through (a segment word per
 // thread, a prefix sum) and thread i takes the entries i, i + T, ...: every lane has one, and a thread's accesses to entries, hash table
 // and places are independent of one another and in flight together.  Up to 256 tiles and 2048 entries stay in registers,
@@ -768,40 +800,61 @@ struct BinShare {
     uint32_t at[kShare<T>];      // slot of the row, in bytes
 };
 
-// Numbers the entries of tiles [tile0, tile0 + 256) in the bin and returns how many they are; *before: these tiles' references in
-// lower bins.  All threads call this together.
+// A tile's segment of the bin, for thread i that of tile tile0 + i, i < 256: begin and end, entries | references << 16.
 template <uint32_t T>
-__device__ __forceinline__ uint32_t number_entries(const PrepArgs& a, uint32_t bin, uint32_t tile0, ResolveLds& s, uint32_t* before)
+__device__ __forceinline__ uint2 fetch_segment(const PrepArgs& a, uint32_t bin, uint32_t tile0)
 {
     const uint32_t t = tile0 + threadIdx.x;
-    uint32_t begin = 0u, end = 0u;       // entries | references << 16
+    uint2 segment = make_uint2(0u, 0u);
     if (threadIdx.x < 256u && t < a.bin.tiles) {
         const uint32_t* ends = a.segs + (static_cast<size_t>(t) << a.bin.bits) + bin;
-        end = *ends;
-        if (bin) begin = ends[-1];
+        segment.y = *ends;
+        if (bin) segment.x = ends[-1];
     }
+    return segment;
+}
+
+// Numbers the entries of these tiles and returns how many they are; *before: the tiles' references in lower bins.  SHARE: if they
+// are a share, tile_of says whose each is (a search through 224 tiles is 8 accesses to LDS in turn).  All threads call this together.
+constexpr uint32_t kShortSegment = 16;
+template <uint32_t T, bool SHARE>
+__device__ __forceinline__ uint32_t number_entries(const PrepArgs& a, uint2 segment, uint32_t tile0, ResolveLds& s, uint32_t* before)
+{
+    const uint32_t begin = segment.x, end = segment.y, entries = (end & 0xFFFFu) - (begin & 0xFFFFu), refs = (end >> 16) - (begin >> 16);
+    if (SHARE && threadIdx.x == 0) s.long_segments = 0u;
     uint32_t total;
-    uint32_t first = (end & 0xFFFFu) - (begin & 0xFFFFu), refs_before = begin >> 16;
+    uint32_t first = entries, refs_before = begin >> 16;
     block_exclusive_scan<T>(first, refs_before, s.part, &total, before);
     if (threadIdx.x < 256u) {
         s.first[threadIdx.x] = first;
-        const uint32_t entries = (end & 0xFFFFu) - (begin & 0xFFFFu), refs = (end >> 16) - (begin >> 16);
-        s.from[threadIdx.x] = ((t * a.bin.tile + (begin & 0xFFFFu) - first) & kPlaceMask) | (refs != entries ? kCounted : 0u);
+        s.from[threadIdx.x] = (((tile0 + threadIdx.x) * a.bin.tile + (begin & 0xFFFFu) - first) & kPlaceMask) | (refs != entries ? kCounted : 0u);
+        if (SHARE && total <= sizeof s.tile_of) {
+            if (entries > kShortSegment) s.long_segments = 1u;
+            else for (uint32_t i = 0; i < entries; ++i) s.tile_of[first + i] = static_cast<uint8_t>(threadIdx.x);
+        }
     }
     lds_barrier();
     return total;
 }
 
 // The entries first + T * u + tid < total of the 256 tiles at hand, u < U: their rows, where they lie, and their references.
-template <uint32_t T, int U>
+// SHARE: tile_of is there for them unless some segment is long.
+template <uint32_t T, bool SHARE, int U>
 __device__ __forceinline__ void fetch_entries(const PrepArgs& a, uint32_t total, uint32_t first, const ResolveLds& s,
                                               uint32_t (&key)[U], uint32_t (&from)[U], uint32_t (&refs)[U])
 {
     const uint32_t k = first + threadIdx.x;
     uint32_t tile[U];                       // the last tile whose first entry is not behind the thread's
+    const bool search = !SHARE || s.long_segments;      // (uniform)
 #pragma unroll
     for (int u = 0; u < U; ++u) tile[u] = 0u;
-    for (uint32_t step = a.bin.tiles > 128u ? 128u : 1u << (31 - __builtin_clz(a.bin.tiles)); step; step >>= 1) {
+    if (!search) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (first + T * u >= total) break;          // (uniform)
+            if (k + T * u < total) tile[u] = s.tile_of[k + T * u];
+        }
+    } else for (uint32_t step = a.bin.tiles > 128u ? 128u : 1u << (31 - __builtin_clz(a.bin.tiles)); step; step >>= 1) {
         uint32_t begin[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -868,50 +921,38 @@ __device__ __forceinline__ void locate_share(const PrepArgs& a, uint32_t total, 
     }
 }
 
+// What the rows of a bin have taken: places of the list, and work items.
+struct Taken { uint32_t places, items, hub_items; };
+
 // The places and work items of the shared rows in the table, which holds every row's references on entry and, on
-// return, a shared row's first place, kNoKey for the others.  The rows take consecutive places from `row` on; returns how many.
-// All threads call this together.
+// return, a shared row's first place, kNoKey for the others.  The bin's first place is first_place, and earlier rows of it have taken
+// `taken`, which is moved.  All threads call this together.
 template <uint32_t T>
-__device__ __forceinline__ uint32_t place_rows(const PrepArgs& a, uint32_t row, ResolveLds& s, uint2* table)
+__device__ __forceinline__ void place_rows(const PrepArgs& a, uint32_t first_place, Taken& taken, ResolveLds& s, uint2* table)
 {
     const uint32_t tid = threadIdx.x, slots = 1u << a.bin.slot_bits;
-    uint32_t item = 0, place = 0, items, places;
+    uint32_t items = 0, places = 0, hubs = 0;
     for (uint32_t p = tid; p < slots; p += T) {
         const uint32_t n = table[p].y;
-        if (n > kItemRefs) atomicAdd(&s.hub_items, (n + kItemRefs - 1) / kItemRefs);
-        if (n > 1) { place += n; item += static_cast<uint32_t>(n <= kItemRefs); }
+        if (n > 1) { places += n; items += static_cast<uint32_t>(n <= kItemRefs); }
+        if (n > kItemRefs) hubs += (n + kItemRefs - 1) / kItemRefs;
     }
-    block_exclusive_scan<T>(item, place, s.part, &items, &places);
-    // (one add per bin: a second one cost 512 bins 1 .. 2 us of the train launch)
-    if (places && tid == 0) {
-        const unsigned long long before = atomicAdd(a.totals, items | (static_cast<unsigned long long>(s.hub_items) << 32));
-        s.base = static_cast<uint32_t>(before);
-        s.hub_items = static_cast<uint32_t>(before >> 32);
-    }
-    lds_barrier();
-    row += place;
-    item += s.base;
+    uint32_t all_items, all_places, all_hubs, none = 0, nothing;
+    block_exclusive_scan<T>(items, places, s.part, &all_items, &all_places);
+    block_exclusive_scan<T>(hubs, none, s.part, &all_hubs, &nothing);
+    uint32_t row = first_place + taken.places + places;
+    uint32_t item = static_cast<uint32_t>(most_items(first_place)) + taken.items + items;
+    uint32_t hub = static_cast<uint32_t>(most_hub_items(first_place)) + taken.hub_items + hubs;
     for (uint32_t p = tid; p < slots; p += T) {
         const uint2 slot = table[p];
-        const uint32_t n = slot.y;
-        table[p].y = n > 1 ? row : kNoKey;
-        if (n > 1 && n <= kItemRefs) a.items[item++] = make_uint2(slot.x, item_places(row, n));
-        // a hub's items by the whole wavefront: one lane takes 280 us for the 8192 of a row with 65 536 references
-        for (unsigned long long hubs = __ballot(n > kItemRefs); hubs; hubs &= hubs - 1ull) {
-            const int lane = __builtin_ctzll(hubs);
-            const uint32_t hub_key = __builtin_amdgcn_readlane(slot.x, lane), hub_n = __builtin_amdgcn_readlane(n, lane);
-            const uint32_t hub_row = __builtin_amdgcn_readlane(row, lane);
-            const uint32_t m = (hub_n + kItemRefs - 1) / kItemRefs;
-            uint32_t first = 0u;
-            if ((tid & 63u) == 0) first = atomicAdd(&s.hub_items, m);
-            uint4* hub = a.hub_items + static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(first));
-            for (uint32_t q = tid & 63u; q < m; q += 64u)
-                hub[q] = make_uint4(hub_key, item_places(hub_row + q * kItemRefs, min(kItemRefs, hub_n - q * kItemRefs)), m, q);
-        }
-        if (n > 1) row += n;
+        table[p].y = slot.y > 1 ? row : kNoKey;
+        if (a.items) write_items(a, slot.x, slot.y, row, item, hub);      // (uniform)
+        if (slot.y > 1) row += slot.y;
     }
+    taken.places += all_places;
+    taken.items += all_items;
+    taken.hub_items += all_hubs;
     lds_barrier();
-    return places;
 }
 
 // f(key, references, place in memory) for every entry of the 256 tiles at hand, four of a thread in flight (eight: 73 registers, a
@@ -924,41 +965,83 @@ __device__ __forceinline__ void for_entries(const PrepArgs& a, uint32_t total, c
     constexpr int U = T == 256 ? 4 : kShare<T>;
     for (uint32_t first = 0; first < total && !stop(); first += T * U) {
         uint32_t key[U], from[U], refs[U];
-        fetch_entries<T>(a, total, first, s, key, from, refs);
+        fetch_entries<T, false>(a, total, first, s, key, from, refs);
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (first + T * u + threadIdx.x < total) f(key[u], refs[u], from[u]);
     }
 }
 
+// (No barrier behind it.)
 template <uint32_t T>
 __device__ __forceinline__ void clear_table(const PrepArgs& a, ResolveLds& s, uint2* table)
 {
-    for (uint32_t i = threadIdx.x; i < 1u << a.bin.slot_bits; i += T) table[i] = make_uint2(kNoKey, 0u);
-    if (threadIdx.x == 0) { s.distinct = 0u; s.hub_items = 0u; }
-    lds_barrier();
+    for (uint32_t i = threadIdx.x; i < 1u << (a.bin.slot_bits - 1u); i += T) reinterpret_cast<uint4*>(table)[i] = make_uint4(kNoKey, 0u, kNoKey, 0u);
+    if (threadIdx.x == 0) { s.taken = 0ull; s.distinct = 0u; s.hub_items = 0u; }
 }
 
-// A bin whose entries stay in registers: `total` of them, all numbered, no more than the table takes.  Its rows take places from
-// first_place on.
+// A bin whose entries stay in registers: `total` of them, all numbered, no more than the table takes, which is empty.  Its rows take
+// places from first_place on: a row's first entry, the one that found its counter at zero, does that for it, so that the table is not
+// gone through.
+// A chain of dependent accesses from end to end, which is what a small batch waits for.  224 references, 56 tiles: 3.3 us, of which
+// the segments' words and the entries take 0.7 us each.  (5.8 with a search for every entry's tile, two passes over the table, rows placed by
+// a sum over the workgroup and the totals' round trip.)
 template <uint32_t T>
-__device__ __forceinline__ void resolve_share(const PrepArgs& a, uint32_t total, uint32_t first_place, ResolveLds& s, uint2* table)
+__device__ __forceinline__ void resolve_share(const PrepArgs& a, uint32_t bin, uint32_t total, uint32_t first_place, ResolveLds& s, uint2* table)
 {
+    const uint32_t tid = threadIdx.x;
     BinShare<T> e;
-    fetch_entries<T>(a, total, 0u, s, e.key, e.from, e.refs);
-    clear_table<T>(a, s, table);
+    fetch_entries<T, true>(a, total, 0u, s, e.key, e.from, e.refs);
     locate_share<T>(a, total, table, e);
+    uint32_t firsts = 0u;            // a bit per entry: its row's first
 #pragma unroll
     for (int u = 0; u < kShare<T>; ++u) {
         if (T * u >= total) break;              // (uniform)
-        if (T * u + threadIdx.x < total) e.refs[u] = atomicAdd(count_of(table, e.at[u]), e.refs[u]);     // the row's references in entries before this one
+        if (T * u + tid < total) {
+            e.refs[u] = atomicAdd(count_of(table, e.at[u]), e.refs[u]);     // the row's references in entries before this one
+            firsts |= static_cast<uint32_t>(e.refs[u] == 0u) << u;
+        }
     }
     lds_barrier();
-    place_rows<T>(a, first_place, s, table);
+    uint32_t places = 0u, items = 0u, hubs = 0u;
 #pragma unroll
     for (int u = 0; u < kShare<T>; ++u) {
         if (T * u >= total) break;
-        if (T * u + threadIdx.x < total) {
+        if (firsts >> u & 1u) {
+            const uint32_t n = *count_of(table, e.at[u]);
+            e.refs[u] = n;                                  // (of a first entry until its row is placed: the row's references)
+            if (n > 1) { places += n; items += static_cast<uint32_t>(n <= kItemRefs); }
+            if (n > kItemRefs) hubs += (n + kItemRefs - 1u) / kItemRefs;
+        }
+    }
+    const uint32_t last_place = wave_inclusive_scan(places), last_item = wave_inclusive_scan(items), last_hub = wave_inclusive_scan(hubs);
+    unsigned long long before = 0ull;
+    uint32_t hubs_before = 0u;
+    if ((tid & 63u) == 63u) {
+        before = atomicAdd(&s.taken, last_place | (static_cast<unsigned long long>(last_item) << 32));
+        if (last_hub) hubs_before = atomicAdd(&s.hub_items, last_hub);
+    }
+    uint32_t place = first_place + __builtin_amdgcn_readlane(static_cast<uint32_t>(before), 63) + last_place - places;
+    uint32_t item = static_cast<uint32_t>(most_items(first_place)) + __builtin_amdgcn_readlane(static_cast<uint32_t>(before >> 32), 63) + last_item - items;
+    uint32_t hub = static_cast<uint32_t>(most_hub_items(first_place)) + __builtin_amdgcn_readlane(hubs_before, 63) + last_hub - hubs;
+#pragma unroll
+    for (int u = 0; u < kShare<T>; ++u) {
+        if (T * u >= total) break;
+        const bool first = firsts >> u & 1u;
+        const uint32_t n = first ? e.refs[u] : 0u;
+        if (first) {
+            *count_of(table, e.at[u]) = n > 1 ? place : kNoKey;
+            e.refs[u] = 0u;
+        }
+        if (a.items) write_items(a, e.key[u], n, place, item, hub);     // (uniform)
+        if (n > 1) place += n;
+    }
+    lds_barrier();
+    if (a.items && tid == 0) a.bins[bin] = make_uint4(first_place, static_cast<uint32_t>(s.taken >> 32), s.hub_items, 0u);
+#pragma unroll
+    for (int u = 0; u < kShare<T>; ++u) {
+        if (T * u >= total) break;
+        if (T * u + tid < total) {
             const uint32_t row = *count_of(table, e.at[u]);
             a.tags[e.from[u]] = row == kNoKey ? 0u : 1u + row + e.refs[u];
         }
@@ -971,7 +1054,7 @@ template <uint32_t T>
 __device__ __forceinline__ void resolve_passes(const PrepArgs& a, uint32_t bin, uint32_t total, uint32_t before, ResolveLds& s, uint2* table)
 {
     uint32_t lo = 0, halvings = 0;      // range of the hash below the bin's bits: [lo, lo + 2^(32 - halvings))
-    uint32_t placed = 0;
+    Taken taken{0u, 0u, 0u};
     auto given_up = [&] { return __hip_atomic_load(&s.distinct, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > a.bin.full; };
     auto home = [&](uint32_t key, uint32_t* at) {
         const uint32_t x = (hash_bits(key) << a.bin.bits) - lo;
@@ -981,12 +1064,13 @@ __device__ __forceinline__ void resolve_passes(const PrepArgs& a, uint32_t bin, 
     auto next = [&](uint32_t at) { return (at + static_cast<uint32_t>(sizeof(uint2))) & ((static_cast<uint32_t>(sizeof(uint2)) << a.bin.slot_bits) - 1u); };
     for (;;) {
         clear_table<T>(a, s, table);
+        lds_barrier();
         uint32_t first_place = a.bin.tiles > 256u ? 0u : before;
         for (uint32_t t0 = 0; t0 < a.bin.tiles; t0 += 256u) {
             if (a.bin.tiles > 256u) {
                 lds_barrier();
                 if (given_up()) break;          // (uniform: nobody adds a row before the next barrier)
-                total = number_entries<T>(a, bin, t0, s, &before);
+                total = number_entries<T, false>(a, fetch_segment<T>(a, bin, t0), t0, s, &before);
                 first_place += before;
             }
             for_entries<T>(a, total, s, [&](uint32_t key, uint32_t refs, uint32_t) {
@@ -1011,11 +1095,11 @@ __device__ __forceinline__ void resolve_passes(const PrepArgs& a, uint32_t bin, 
             halvings += 1;
             continue;
         }
-        placed += place_rows<T>(a, first_place + placed, s, table);
+        place_rows<T>(a, first_place, taken, s, table);
         for (uint32_t t0 = 0; t0 < a.bin.tiles; t0 += 256u) {
             if (a.bin.tiles > 256u) {
                 lds_barrier();
-                total = number_entries<T>(a, bin, t0, s, &before);
+                total = number_entries<T, false>(a, fetch_segment<T>(a, bin, t0), t0, s, &before);
             }
             for_entries<T>(a, total, s, [&](uint32_t key, uint32_t refs, uint32_t from) {
                 uint32_t at;
@@ -1026,9 +1110,11 @@ __device__ __forceinline__ void resolve_passes(const PrepArgs& a, uint32_t bin, 
                 a.tags[from] = tag;
             }, [] { return false; });
         }
-        if (halvings == 0) return;
-        lo += 1u << (32u - halvings);
-        if (lo == 0) return;
+        if (halvings) lo += 1u << (32u - halvings);
+        if (lo == 0) {           // (the last range, or the only one)
+            if (a.items && threadIdx.x == 0) a.bins[bin] = make_uint4(first_place, taken.items, taken.hub_items, 0u);
+            return;
+        }
         lds_barrier();
     }
 }
@@ -1038,9 +1124,11 @@ __device__ __forceinline__ void resolve_bin(const PrepArgs& a, uint32_t bin, uns
 {
     ResolveLds& s = *reinterpret_cast<ResolveLds*>(lds);
     uint2* table = reinterpret_cast<uint2*>(lds + sizeof(ResolveLds));
+    const uint2 segment = fetch_segment<T>(a, bin, 0);
+    clear_table<T>(a, s, table);            // (while the segments' words travel)
     uint32_t before;
-    const uint32_t total = number_entries<T>(a, bin, 0, s, &before);
-    if (a.bin.tiles <= 256u && total <= min(T * kShare<T>, 1u << a.bin.slot_bits)) resolve_share<T>(a, total, before, s, table);      // (uniform)
+    const uint32_t total = number_entries<T, true>(a, segment, 0, s, &before);
+    if (a.bin.tiles <= 256u && total <= min(T * kShare<T>, 1u << a.bin.slot_bits)) resolve_share<T>(a, bin, total, before, s, table);      // (uniform)
     else resolve_passes<T>(a, bin, total, before, s, table);
 }
 
@@ -1077,20 +1165,58 @@ __global__ __launch_bounds__(256) void fetch_pairs_kernel(const int2* __restrict
                 static_cast<int64_t>(gridDim.x) * blockDim.x);
 }
 
+// The work items of a batch's bins, moved together for the apply kernel.  A few workgroups of the batch's own train launch, with
+// kGatherBins bins each or, of many, more: a workgroup adds up the bins before its own and copies what they have, a wavefront per bin.
+struct GatherArgs {
+    const uint4* bins;          // per bin: its first place, its items, its hubs' items
+    const uint2* from;
+    const uint4* hubs_from;
+    uint2* items;
+    uint4* hub_items;
+    unsigned long long* totals; // items | items of hubs << 32
+    uint32_t n_bins, share;     // bins in all and per workgroup, powers of two, share at most 256
+};
+constexpr uint32_t kGatherBins = 4, kGatherBlocks = 128;
+struct GatherLds { uint32_t part[32]; uint32_t item[256], hub[256]; };
+template <uint32_t T>
+__device__ __forceinline__ void gather_items(const GatherArgs& a, uint32_t block, unsigned char* lds)
+{
+    GatherLds& s = *reinterpret_cast<GatherLds*>(lds);
+    const uint32_t tid = threadIdx.x, first = block * a.share;
+    uint32_t items = 0u, hubs = 0u, own_items = 0u, own_hubs = 0u;
+    for (uint32_t b = tid; b < first; b += T) { const uint4 bin = a.bins[b]; items += bin.y; hubs += bin.z; }
+    if (tid < a.share) { const uint4 bin = a.bins[first + tid]; own_items = bin.y; own_hubs = bin.z; }
+    uint32_t items_before, hubs_before, items_here, hubs_here;
+    block_exclusive_scan<T>(items, hubs, s.part, &items_before, &hubs_before);
+    block_exclusive_scan<T>(own_items, own_hubs, s.part, &items_here, &hubs_here);
+    if (tid < a.share) { s.item[tid] = items_before + own_items; s.hub[tid] = hubs_before + own_hubs; }
+    if (tid == 0 && first + a.share == a.n_bins) *a.totals = (items_before + items_here) | (static_cast<unsigned long long>(hubs_before + hubs_here) << 32);
+    lds_barrier();
+    for (uint32_t b = tid >> 6; b < a.share; b += T / 64u) {
+        const uint4 bin = a.bins[first + b];
+        const uint2* from = a.from + most_items(bin.x);
+        for (uint32_t i = tid & 63u; i < bin.y; i += 64u) a.items[s.item[b] + i] = from[i];
+        const uint4* hubs_from = a.hubs_from + most_hub_items(bin.x);
+        for (uint32_t i = tid & 63u; i < bin.z; i += 64u) a.hub_items[s.hub[b] + i] = hubs_from[i];
+    }
+}
+
 // LDS of the kernels: counters of a claiming workgroup, hash table of a resolving one, staged rows of a training one.
 extern __shared__ __align__(16) unsigned char dynamic_lds[];
 
 // The id-only work for later batches that rides in a launch: the launch's first workgroups, because theirs are
 // chains of dependent accesses, which hide behind the other workgroups only if they start first.
 struct Helpers {
-    unsigned resolves, claims, fetches;   // workgroups of each kind: bins of `resolve`, tiles of `claim`
+    unsigned resolves, claims, fetches, gathers;   // workgroups of each kind: bins of `resolve`, tiles of `claim`
+    GatherArgs gather;    // the launch's own batch
     PrepArgs resolve;     // next batch
     PrepArgs claim;       // the one after that; its fetch fields: pairs of the batch after that one
-    unsigned count() const { return resolves + claims + fetches; }
+    unsigned count() const { return resolves + claims + fetches + gathers; }
     size_t lds_bytes() const
     {
         const size_t r = resolves ? resolve_lds_bytes(resolve.bin) : 0, c = claims ? claim_lds_bytes(claim.bin) : 0;
-        return r > c ? r : c;
+        const size_t g = gathers ? sizeof(GatherLds) : 0;
+        return std::max(std::max(r, c), g);
     }
 };
 
@@ -1114,8 +1240,10 @@ __device__ __forceinline__ bool helper_block(const Helpers& h, unsigned* block)
         return true;
     }
     i -= h.fetches;
+    if (i < h.gathers) { gather_items<T>(h.gather, i, dynamic_lds); return true; }
+    i -= h.gathers;
     // consecutive pairs on one die, which then shares the cache lines of their ids and tags
-    const unsigned blocks = gridDim.x - h.resolves - h.claims - h.fetches, share = blocks >> 3, rest = blocks & 7u, die = i & 7u;
+    const unsigned blocks = gridDim.x - h.resolves - h.claims - h.fetches - h.gathers, share = blocks >> 3, rest = blocks & 7u, die = i & 7u;
     *block = die * share + min(die, rest) + (i >> 3);
     return false;
 }
@@ -1123,7 +1251,7 @@ __device__ __forceinline__ bool helper_block(const Helpers& h, unsigned* block)
 // The same work on its own, for the first batches of a call.  A batch with one tile and one bin is claimed and resolved
 // by the same workgroup (claim_first: h.resolve).
 template <RefMode MODE, uint32_t T>
-__global__ __launch_bounds__(T) void prepare_kernel(Helpers h, bool claim_first)
+__global__ __launch_bounds__(T, T == 512 ? 6 : 1) void prepare_kernel(Helpers h, bool claim_first)
 {
     if (claim_first && blockIdx.x == 0) {
         claim_tile<MODE, T>(h.resolve, 0, reinterpret_cast<uint32_t*>(dynamic_lds));
@@ -2020,22 +2148,19 @@ hipError_t launch_train_seg(const Shape& s, const TrainArgs& a, const Helpers& h
     return hipErrorInvalidValue;
 }
 
-// Workgroups of 1024 threads where they all have a place at once and a tile has a reference for each: the first claim of a batch of
-// 65 536 pairs 14 instead of 20 us where tiles have hubs, a batch of 90 000 references 37.2 instead of 37.8, walks 394 and 401.
-// (Tiles of 512, half the threads idle: equal.  More workgroups, 736 of resolve and claim: 30 instead of 21 us.)  Bins and tiles in
-// one launch: only where the bins are long, whose chain it shortens (2 x 4096 pairs, K = 9, dim 64, 144 references per bin, 43.8 us
-// with 256 threads and 46.3 with 1024; 2 x 16 384, K = 5, 448 of them, 56.1 and 57.6; 2 x 22 000, 601, level; 2 x 30 000, 820, 75 and 72.8).
+// Workgroups of 512 threads where they all have a place at once (four on a compute unit) and a tile has two references for each.
+// 65 536 pairs, K = 5, among 1 M / 32 M nodes: the first claim 11.7 / 20.1 us, bins and the second claim together 12.3 / 18.4.
+// (1024 threads leave the bins and the second claim no place side by side: with both claims in the first launch 16.5 / 32.2 and
+// 10.6 / 13.0; 256 for bins and claim 19.6 / 24.8.)
 constexpr uint32_t kWideTile = 1024;
-constexpr unsigned kWideBlocks = 512;
-constexpr uint32_t kWideBin = 640;
+constexpr unsigned kWideBlocks = 1024;
 hipError_t launch_prepare(const Helpers& h, bool claim_first, hipStream_t st)
 {
     const size_t own = claim_first ? claim_lds_bytes(h.resolve.bin) : 0, lds = own > h.lds_bytes() ? own : h.lds_bytes();
     const PrepArgs& p = h.claims ? h.claim : h.resolve;
-    const bool one_kind = !h.claims || !h.resolves;
-    const bool wide = p.bin.tile >= kWideTile && h.count() <= kWideBlocks && (one_kind || (h.resolve.refs >> h.resolve.bin.bits) >= kWideBin);
+    const bool wide = p.bin.tile >= kWideTile && h.count() <= kWideBlocks;
 #define NE_CASE(M_)                                                                              \
-    if (wide) hipLaunchKernelGGL((prepare_kernel<M_, 1024>), dim3(h.count()), dim3(1024), lds, st, h, claim_first);  \
+    if (wide) hipLaunchKernelGGL((prepare_kernel<M_, 512>), dim3(h.count()), dim3(512), lds, st, h, claim_first);  \
     else hipLaunchKernelGGL((prepare_kernel<M_, 256>), dim3(h.count()), dim3(256), lds, st, h, claim_first);
     if (p.pairs) { NE_CASE(kPairRefs) } else if (p.seg_entries) { NE_CASE(kSegRefs) } else { NE_CASE(kWalkRefs) }
 #undef NE_CASE
@@ -2050,7 +2175,6 @@ hipError_t launch_prepare(const Helpers& h, bool claim_first, hipStream_t st)
 // 1000 .. 10 000 nodes, 256 10 % more among a million; without hubs the 1024 are not seen).
 constexpr unsigned kApplyBlocks = 16384;
 constexpr unsigned kHubBlocks = 1024;
-inline uint64_t most_hub_items(uint64_t refs) { return refs * 2 / 9; }      // a hub of nine references has two
 hipError_t launch_apply(ApplyArgs a, uint32_t refs, hipStream_t st)
 {
     a.most = refs / 2;                      // every item has two references or more to its row
@@ -2110,10 +2234,15 @@ bool workspace_layout(int32_t dim, int64_t max_B, int32_t max_K, char* base, Wor
         p.keys = reinterpret_cast<uint32_t*>(take(refs * 8));
         p.tags = p.keys + refs;
         p.segs = reinterpret_cast<uint32_t*>(take(max_segs(refs) * 4));
-        p.items = reinterpret_cast<uint2*>(take(refs / 2 * sizeof(uint2)));
-        p.hub_items = reinterpret_cast<uint4*>(take(most_hub_items(refs) * sizeof(uint4)));
-        p.totals = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long)));
     }
+    for (ItemSlot& p : w->item_slots) {
+        p.items = reinterpret_cast<uint2*>(take(most_items(refs) * sizeof(uint2)));
+        p.hub_items = reinterpret_cast<uint4*>(take(most_hub_items(refs) * sizeof(uint4)));
+        p.bins = reinterpret_cast<uint4*>(take(sizeof(uint4) << binning(refs).bits));      // (more references never have fewer bins)
+    }
+    w->items = reinterpret_cast<uint2*>(take(most_items(refs) * sizeof(uint2)));
+    w->hub_items = reinterpret_cast<uint4*>(take(most_hub_items(refs) * sizeof(uint4)));
+    w->totals = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long)));
     w->list = reinterpret_cast<uint2*>(take(refs * sizeof(uint2)));
     // two rows per pair or walk entry, a segment's entries twice and its context rows: never more than references, and as
     // many where the batch is walks with window 1 and no negatives, which every handle accepts
@@ -2175,9 +2304,10 @@ ne_status run_batches(ne_tables* t, int64_t n_batches, int64_t R, int32_t window
         PrepArgs pa = prep(i);
         if (!pa.refs) return pa;
         const PrepSlot& ps = w.prep[i % 3];
+        const ItemSlot& is = w.item_slots[i % 2];
         pa.bin = binning(pa.refs);
-        pa.ids = ps.ids; pa.where = ps.where; pa.keys = ps.keys; pa.tags = ps.tags; pa.segs = ps.segs; pa.items = ps.items;
-        pa.hub_items = ps.hub_items; pa.totals = ps.totals;
+        pa.ids = ps.ids; pa.where = ps.where; pa.keys = ps.keys; pa.tags = ps.tags; pa.segs = ps.segs;
+        pa.items = direct ? nullptr : is.items; pa.hub_items = is.hub_items; pa.bins = is.bins;
         pa.k0 = static_cast<uint32_t>(t->seed); pa.k1 = static_cast<uint32_t>(t->seed >> 32);
         return pa;
     };
@@ -2203,13 +2333,19 @@ ne_status run_batches(ne_tables* t, int64_t n_batches, int64_t R, int32_t window
         ta.B = cur.refs / R; ta.window = window; ta.K = K; ta.d4 = t->dim / 4; ta.lr = lr_host[i];
         ta.ids = cur.ids; ta.where = cur.where; ta.tags = cur.tags; ta.tile = cur.bin.tile; ta.list = w.list; ta.buf = reinterpret_cast<float4*>(w.buf);
         const bool timed = profile_begin(t, st);
-        e = train(ta, helpers(next, after, true));
+        Helpers h = helpers(next, after, true);
+        if (!direct) {
+            const uint32_t bins = 1u << cur.bin.bits, share = std::min(bins, std::max(kGatherBins, bins / kGatherBlocks));
+            h.gather = {cur.bins, cur.items, cur.hub_items, w.items, w.hub_items, w.totals, bins, share};
+            h.gathers = bins / share;
+        }
+        e = train(ta, h);
         if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("train launch: ") + hipGetErrorString(e));
         if (timed) profile_end(t, st);
 
         if (!direct) {
             ApplyArgs aa{};
-            aa.X = ta.X; aa.C = ta.C; aa.d4 = ta.d4; aa.items = cur.items; aa.hub_items = cur.hub_items; aa.totals = cur.totals; aa.list = w.list; aa.buf = ta.buf;
+            aa.X = ta.X; aa.C = ta.C; aa.d4 = ta.d4; aa.items = w.items; aa.hub_items = w.hub_items; aa.totals = w.totals; aa.list = w.list; aa.buf = ta.buf;
             aa.acc = w.acc; aa.arrived = w.arrived;
             e = launch_apply(aa, cur.refs, st);
             if (e != hipSuccess) return fail(NE_ERR_HIP, std::string("apply launch: ") + hipGetErrorString(e));

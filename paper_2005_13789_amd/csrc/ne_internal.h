@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -39,12 +40,18 @@ struct PrepSlot {
     uint32_t* tags;               // [refs]  in the same order: references of the entry; later 0 = only one reference names the row, else
                                   //         1 + the place in the list of the entry's first reference
     uint32_t* segs;               // [tiles][bins]  where a tile's entries of a bin end | where its references do (<< 16)
-    uint2* items;                 // [refs / 2]  work items of the apply kernel: rows that 2 .. 8 references name
-    uint4* hub_items;             // [refs 2/9]  work items of the rows that more references name
-    unsigned long long* totals;   // number of items | number of hub items << 32
+};
+struct ItemSlot {
+    uint2* items;                 // [refs / 2]  work items of each bin's rows that 2 .. 8 references name, from half its first place on
+    uint4* hub_items;             // [refs 2/9]  of the rows that more references name, from 2/9 of it on
+    uint4* bins;                  // [bins]  first place, items, hubs' items
 };
 struct Workspace {
     PrepSlot prep[3];   // one batch in training, the next being resolved, the one after that being claimed
+    ItemSlot item_slots[2];     // of the batch in training and the one being resolved
+    uint2* items;       // [refs / 2]  the work items of the batch in training, its bins' side by side
+    uint4* hub_items;   // [refs 2/9]
+    unsigned long long* totals;   // number of items | number of hub items << 32
     uint2* list;        // [refs]  (row of buf, coefficient) of each reference to a shared row, a row's references side by side
     float* buf;         // [refs][dim]  rows that the list points to: copies of source rows, deltas
     float* acc;         // [accs][dim]  sums of hubs, zero between batches
