@@ -42,20 +42,17 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPairTile = 32;      // pairs per workgroup in the scores kernel
-constexpr int kScoreThreads = 512; // 8 wavefronts: one 32-negative block of S each, one 32-column block of dX each
+constexpr int kScoreThreads = 512; // 8 wavefronts: one 32-negative block of S each, one 32-column block of dX over a share of the negatives each
 constexpr int kNegChunk = 256;     // negatives per pass of the scores kernel (8 wavefronts x 32)
-constexpr int kSplit = 16;         // partial sums of the dC product
-constexpr int kBatchPad = 1024;    // the padded batch is a multiple of this (kSplit shares of whole 64-pair steps)
-
-__device__ __forceinline__ uint16_t to_bf16(float x)
-{
-    uint32_t u = __float_as_uint(x);
-    u += 0x7FFFu + ((u >> 16) & 1u);   // round to nearest even
-    return static_cast<uint16_t>(u >> 16);
-}
+// Partial sums of the dC product.  With 8 instead of 16 of them, from tiles of 64 columns instead of 128, that product takes as long and 8 MB
+// less are written and read again: 8192 pairs x 1024 negatives at dim 256 dctx 10.9 us then, 11.5 now, update 14.8 and 12.6.  (Dim 64 has one
+// such tile: 8 would halve the workgroups.)
+constexpr int kMostSplit = 16;
+constexpr int split_of(int dim) { return dim == 64 ? kMostSplit : 8; }
+constexpr int kBatchPad = 1024;    // the padded batch is a multiple of this (shares of whole 64-pair stages)
 
 // sigmoid from the hardware exp2 and reciprocal (about 1 ulp each): the result is rounded to bf16 anyway
-__device__ __forceinline__ float fast_sigmoidf(float z) { return __frcp_rn(1.0f + __expf(-z)); }
+__device__ __forceinline__ float fast_sigmoidf(float z) { return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z * -1.44269504f)); }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -63,14 +60,18 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast
 // consecutive contraction indices (l/32)*8..+7 of the step; accumulator element i is row
 // (i/4)*8 + (l/32)*4 + i%4, column l%32.  A "fragment" below is what the 64 lanes of a wavefront supply
 // for one step: 64 x 8 bf16 = 1 KB, stored lane after lane.
+// The pairs of a step of dC are in the order in which a lane of the S product holds them, for both operands (pair_of_lane): its
+// coefficients leave the registers as the fragment they are, with no transpose through LDS.
+__device__ __forceinline__ int pair_of_lane(int l, int e) { return (e >> 2) * 8 + (l >> 5) * 4 + (e & 3); }
+
 struct SharedWs {
-    uint16_t* XqT;   // [d][Bp]   bf16 source rows, transposed (zero beyond B): operand of the dC product
+    uint16_t* XqP;   // [d/32][Bp/16][64][8]  bf16 source rows (zero beyond B) as B fragments of dC: block of 32 columns, step over pairs
     uint16_t* CqP;   // [N/32][d/16][64][8]  bf16 negative rows as B fragments of S: block of 32 negatives, step over d
     uint16_t* CqTP;  // [d/32][N/16][64][8]  the same rows as B fragments of dX: block of 32 columns, step over negatives
-    uint16_t* GT;    // [N][Bp]   bf16 coefficients, transposed
+    uint16_t* GP;    // [N/32][Bp/16][64][8]  bf16 coefficients as A fragments of dC: block of 32 negatives, step over pairs
     float* dxs;      // [Bp][d]   complete delta of pair b's source row: lr * (g0 * c_ctx + (G . Cq)_b)
     float* dcs;      // [Bp][d]   lr * g0 * x: delta of pair b's context row
-    float* dCp;      // [kSplit][N][d] partial sums of G^T . Xq
+    float* dCp;      // [split_of(d)][N][d] partial sums of G^T . Xq
     int32_t* negids; // [N]
     unsigned long long* slots;   // [hash_mask + 1]  (key << 32 | reference) of the reference that claimed a position last
     uint8_t* multi;              // [hash_mask + 1]  1 = the row that owns this position is named more than once
@@ -95,13 +96,13 @@ bool shared_layout(int32_t dim, int64_t B, int32_t N, char* base, SharedWs* w)
     auto take = [&](size_t bytes) { char* p = base + off; off = up(off + bytes); return p; };
     const size_t d = static_cast<size_t>(dim), n = static_cast<size_t>(N);
     w->Bp = static_cast<int64_t>(Bp);
-    w->XqT = reinterpret_cast<uint16_t*>(take(Bp * d * 2));
+    w->XqP = reinterpret_cast<uint16_t*>(take(Bp * d * 2));
     w->CqP = reinterpret_cast<uint16_t*>(take(n * d * 2));
     w->CqTP = reinterpret_cast<uint16_t*>(take(n * d * 2));
-    w->GT = reinterpret_cast<uint16_t*>(take(n * Bp * 2));
+    w->GP = reinterpret_cast<uint16_t*>(take(n * Bp * 2));
     w->dxs = reinterpret_cast<float*>(take(Bp * d * 4));
     w->dcs = reinterpret_cast<float*>(take(Bp * d * 4));
-    w->dCp = reinterpret_cast<float*>(take(static_cast<size_t>(kSplit) * n * d * 4));
+    w->dCp = reinterpret_cast<float*>(take(static_cast<size_t>(kMostSplit) * n * d * 4));
     w->negids = reinterpret_cast<int32_t*>(take(n * 4));
     size_t cap = 4096;
     while (cap < 4 * (2 * Bp + n)) cap <<= 1;
@@ -132,7 +133,12 @@ struct PrepNegArgs {
     int32_t* neg_out;
 };
 
-__device__ __forceinline__ uint32_t pack2(float a, float b) { return to_bf16(a) | (static_cast<uint32_t>(to_bf16(b)) << 16); }
+// two floats to bf16, to the nearest even
+__device__ __forceinline__ uint32_t pack2(float a, float b)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, (bf16x2){static_cast<__bf16>(a), static_cast<__bf16>(b)});
+}
 
 template <int D>
 __global__ __launch_bounds__(256) void prep_kernel(PrepNegArgs a)
@@ -193,15 +199,18 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepNegArgs a)
 // scores kernel: one workgroup (8 wavefronts) per 32 pairs, all N negatives.
 //   prologue   16 lanes per pair: gather x = vertex[src] and c = context[ctx] in fp32, positive score,
 //              g0 = lr (1 - sigma(s0)); lr g0 x goes to dcs, lr g0 c stays in registers; x rounded to bf16
-//              into LDS (and, transposed, to memory for the dC product); every wavefront then keeps the
-//              A fragments of the 32 rows (all of d) in registers.
+//              into LDS (and as fragments to memory for the dC product).
 //   per pass of 256 negatives
 //     S      wavefront w: 32 pairs x negatives block w of the pass; B fragments straight from memory.
-//            G = -neg_scale sigma(S) as bf16 into LDS [32][256].
-//     G^T    256 negatives x 32 pairs to memory, 64 contiguous bytes per negative.
-//     dX     wavefront w: 32 pairs x columns block w (32 of d): A fragments from G in LDS, B fragments
-//            straight from memory.
-//   epilogue   dX through LDS to the pairs' lanes: dxs = lr dX + lr g0 c.
+//            G = -neg_scale sigma(S) as bf16 to memory, in the fragments that the dC product wants, and into LDS [32][256].
+//     dX     wavefront w: 32 pairs x columns block w mod (d/32), over its share of the pass's negatives: A fragments from G in
+//            LDS, B fragments straight from memory.
+//   epilogue   dX through LDS, the shares added up, to the pairs' lanes: dxs = lr dX + lr g0 c.
+// Every workgroup streams all negatives twice, 2 N d x 2 bytes, which a compute unit takes in at 64 bytes a clock: 6.8 us at N = 1024, d =
+// 256 (a pass of 4096 clocks takes 5300), beside 3.4 us of MFMA and 2 of exponentials and reciprocals; the gather of the pairs' rows, which
+// nothing hides, 4 - 5.  8192 pairs: 23.0 us (27.5 with a phase's fragments requested when the last phase had ended, the
+// coefficients transposed through LDS and divisions rounded correctly before they are rounded to bf16).
+// (16 wavefronts, four per SIMD: 23.3 with whole phases requested ahead; 35 a quarter ahead, which takes more than their 128 registers.)
 // ---------------------------------------------------------------------------------------------
 struct ScoresArgs {
     const float4* X;
@@ -215,6 +224,12 @@ struct ScoresArgs {
     const int2* pairs;
 };
 
+__device__ __forceinline__ uint32_t key_of_ref(const ScoresArgs& a, int64_t r)
+{
+    const int32_t* id = r < 2 * a.B ? reinterpret_cast<const int32_t*>(a.pairs) + r : a.w.negids + (r - 2 * a.B);
+    return static_cast<uint32_t>(*id) | (r >= 2 * a.B || (r & 1) ? kContextKey : 0u);
+}
+
 template <int D, bool LOSS>
 __global__ __launch_bounds__(kScoreThreads) void scores_kernel(ScoresArgs a)
 {
@@ -222,167 +237,170 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(ScoresArgs a)
     constexpr int GP = kNegChunk + 8;    // pitch of G
     constexpr int DP = D + 4;            // pitch of the fp32 dX rows
     constexpr int KS = D / 16;           // contraction steps of S
-    constexpr int CB = D / 32;           // 32-column blocks of dX: wavefronts 0 .. CB-1 take one each
-    constexpr int NCH = D / 64;          // float4 chunks of a row per lane of a pair's 16 lanes
-    constexpr int kXsBytes = kPairTile * XP * 2, kGsBytes = kPairTile * GP * 2, kDxBytes = kPairTile * DP * 4;
+    constexpr int CB = D / 32;           // 32-column blocks of dX
+    constexpr int SHARES = kScoreThreads / 64 / CB;      // shares of a pass's negatives in the dX product
+    constexpr int XS = kNegChunk / 16 / SHARES;          // contraction steps of a share
+    constexpr int Q = KS / 4;                            // quarters: of the S product and, as many, of the dX product
+    static_assert(XS == KS, "both products of a pass take as many fragments per wavefront");
+    constexpr int LP = kScoreThreads / kPairTile;        // lanes per pair
+    constexpr int NCH = D / 4 / LP;                      // float4 chunks of a row per lane
+    constexpr int kXsBytes = kPairTile * XP * 2, kGsBytes = kPairTile * GP * 2, kDxBytes = SHARES * kPairTile * DP * 4;
     __shared__ __align__(16) unsigned char lds_raw[(kXsBytes + 2 * kGsBytes > kDxBytes) ? kXsBytes + 2 * kGsBytes : kDxBytes];
     uint16_t* Xs = reinterpret_cast<uint16_t*>(lds_raw);                    // [32][XP]
     uint16_t* const Gs2 = reinterpret_cast<uint16_t*>(lds_raw + kXsBytes);  // [2][32][GP], passes alternate
-    float* dXs = reinterpret_cast<float*>(lds_raw);                         // [32][DP], after the last pass
+    float* dXs = reinterpret_cast<float*>(lds_raw);                         // [SHARES][32][DP], after the last pass
     const int tid = threadIdx.x;
-    const int l = tid & 63, w = tid >> 6;
+    const int l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t b0 = static_cast<int64_t>(blockIdx.x) * kPairTile;
-    const int64_t Bp = a.w.Bp;
 
     // resolve (ids only, a by-product of this launch): a reference that finds its row's key at the
     // key's position under another reference's name flags the row as named more than once
-    {
-        const int64_t refs = 2 * a.B + a.N;
-        const int64_t stride = static_cast<int64_t>(gridDim.x) * kScoreThreads;
-        for (int64_t r = static_cast<int64_t>(blockIdx.x) * kScoreThreads + tid; r < refs; r += stride) {
-            uint32_t key;
-            if (r < 2 * a.B) {
-                const int2 pr = a.pairs[r >> 1];
-                key = (r & 1) ? (static_cast<uint32_t>(pr.y) | kContextKey) : static_cast<uint32_t>(pr.x);
-            } else {
-                key = static_cast<uint32_t>(a.w.negids[r - 2 * a.B]) | kContextKey;
-            }
-            const uint32_t pos = ref_hash(key, a.w.hash_mask);
-            const unsigned long long owner = a.w.slots[pos];
-            if (static_cast<uint32_t>(owner >> 32) == key && static_cast<uint32_t>(owner) != static_cast<uint32_t>(r)) a.w.multi[pos] = 1;
-        }
-    }
+    const int64_t refs = 2 * a.B + a.N, my_ref = static_cast<int64_t>(blockIdx.x) * kScoreThreads + tid;
+    auto flag = [&](int64_t r, uint32_t key, uint32_t pos, unsigned long long owner) {
+        if (static_cast<uint32_t>(owner >> 32) == key && static_cast<uint32_t>(owner) != static_cast<uint32_t>(r)) a.w.multi[pos] = 1;
+    };
+    uint32_t my_key = 0u, my_pos = 0u;
+    unsigned long long my_owner = 0ull;
 
-    // ---- prologue: the positive pairs, in fp32
-    const int p = tid >> 4, lp = tid & 15;           // pair of the tile, lane of the pair
+    // ---- prologue: the positive pairs, in fp32.  (Loads are waited for in the order in which they were issued: ids, rows, then the
+    // negatives' first fragments, which travel meanwhile.)
+    const int p = tid / LP, lp = tid % LP;           // pair of the tile, lane of the pair
     const int64_t b = b0 + p;
     const bool live = b < a.B;
     float4 dxp[NCH];                                 // lr g0 c
     float loss = 0.0f;
+    const uint4* SP = reinterpret_cast<const uint4*>(a.w.CqP);     // one uint4 per lane and fragment
+    const uint4* TP = reinterpret_cast<const uint4*>(a.w.CqTP);
+    const int nblocks = a.N / 32, steps_all = a.N / 16;            // blocks of negatives; contraction steps of dX over all negatives
+    const int cb = w % CB, share = w / CB;
+    // Fragments of the next S and the next dX product, which are on their way while this pass's are multiplied: a quarter is requested as
+    // soon as the last one has left its registers, so that a compute unit's intake never waits for a phase to end.
+    // (A wavefront whose block or share a later pass does not have fetches another's.)
+    uint4 rows[Q][4], columns[Q][4];
+    auto fetch = [&](uint4 (&frag)[4], const uint4* first) {        // (a uniform address and the lane's offset: no address registers)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) frag[s] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(first) + (static_cast<uint32_t>(l) * 16u + s * 1024u));
+    };
+    auto nothing = [&](uint4 (&frag)[4]) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) frag[s] = make_uint4(0u, 0u, 0u, 0u);
+    };
+    auto fetch_rows = [&](int q, int n0) { fetch(rows[q], SP + (static_cast<size_t>(min((n0 >> 5) + w, nblocks - 1)) * KS + 4 * q) * 64); };
+    auto fetch_columns = [&](int q, int n0) {
+        fetch(columns[q], TP + (static_cast<size_t>(cb) * steps_all + min((n0 >> 4) + share * XS + 4 * q, steps_all - 4)) * 64);
+    };
     {
         float4 x[NCH], c[NCH];
-        float s0 = 0.0f;
-        if (live) {
-            const int2 pr = a.pairs[b];
-            const float4* xrow = a.X + static_cast<int64_t>(pr.x) * (D / 4);
-            const float4* crow = a.C + static_cast<int64_t>(pr.y) * (D / 4);
+        const int2 pr = a.pairs[live ? b : 0];
+        my_key = key_of_ref(a, my_ref < refs ? my_ref : 0);
+        const float4* xrow = a.X + static_cast<int64_t>(pr.x) * (D / 4);
+        const float4* crow = a.C + static_cast<int64_t>(pr.y) * (D / 4);
 #pragma unroll
-            for (int i = 0; i < NCH; ++i) { x[i] = xrow[lp + 16 * i]; c[i] = crow[lp + 16 * i]; }
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) s0 += dot4(x[i], c[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) { x[i] = make_float4(0.f, 0.f, 0.f, 0.f); c[i] = x[i]; }
+        for (int i = 0; i < NCH; ++i) {
+            const int ci = lp + LP * i;
+            x[i] = live ? xrow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
+            c[i] = live ? crow[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        s0 = group_sum<16>(s0);
+        my_pos = ref_hash(my_key, a.w.hash_mask);
+        my_owner = a.w.slots[my_pos];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (w < nblocks) fetch_rows(q, 0);
+            else nothing(rows[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (share * XS + 4 * q < steps_all) fetch_columns(q, 0);
+            else nothing(columns[q]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        float s0 = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) s0 += dot4(x[i], c[i]);
+        s0 = group_sum<LP>(s0);
         const float g0 = live ? a.lr * (1.0f - sigmoidf(s0)) : 0.0f;
         if (LOSS && live && lp == 0) loss = softplusf(-s0);
         float4* dcs = reinterpret_cast<float4*>(a.w.dcs + b * D);
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
-            const int ci = lp + 16 * i;
+            const int ci = lp + LP * i;
             dxp[i] = make_float4(g0 * c[i].x, g0 * c[i].y, g0 * c[i].z, g0 * c[i].w);
             if (live) dcs[ci] = make_float4(g0 * x[i].x, g0 * x[i].y, g0 * x[i].z, g0 * x[i].w);
             *reinterpret_cast<uint2*>(Xs + p * XP + 4 * ci) = make_uint2(pack2(x[i].x, x[i].y), pack2(x[i].z, x[i].w));   // padding rows: zero
         }
+        if (my_ref < refs) flag(my_ref, my_key, my_pos, my_owner);
     }
-    __syncthreads();
-    // by-product: the transposed copy the dC product reads, 64 contiguous bytes per column
-    if (tid < D) {
-        uint4* out = reinterpret_cast<uint4*>(a.w.XqT + static_cast<int64_t>(tid) * Bp + b0);
+    lds_barrier();
+    const int64_t steps_pairs = a.w.Bp / 16, step0 = b0 / 16;      // of the dC product
+    // by-product: the fragments of the rows that the dC product reads: two steps of each block of 32 columns, 1 KB per wavefront
+    for (int f = w; f < 2 * CB; f += kScoreThreads / 64) {
+        const int cb = f >> 1, half = f & 1;
+        const uint16_t* col = Xs + half * 16 * XP + cb * 32 + (l & 31);
+        uint32_t v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint32_t v[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                v[i] = Xs[(8 * q + 2 * i) * XP + tid] | (static_cast<uint32_t>(Xs[(8 * q + 2 * i + 1) * XP + tid]) << 16);
-            out[q] = make_uint4(v[0], v[1], v[2], v[3]);
-        }
+        for (int i = 0; i < 4; ++i)
+            v[i] = col[pair_of_lane(l, 2 * i) * XP] | (static_cast<uint32_t>(col[pair_of_lane(l, 2 * i + 1) * XP]) << 16);
+        reinterpret_cast<uint4*>(a.w.XqP)[(cb * steps_pairs + step0 + half) * 64 + l] = make_uint4(v[0], v[1], v[2], v[3]);
     }
     f32x16 acc_dx;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc_dx[i] = 0.0f;
-    const uint4* SP = reinterpret_cast<const uint4*>(a.w.CqP);     // one uint4 per lane and fragment
-    const uint4* TP = reinterpret_cast<const uint4*>(a.w.CqTP);
-    const int steps_all = a.N / 16;                                // contraction steps of dX over all negatives
     // A fragments of S: row l % 32, contraction indices 16 s + 8 (l / 32) ..; A fragments of dX: the same of G
     const uint16_t* xa = Xs + (l & 31) * XP + 8 * (l >> 5);
+    const int live_rows = static_cast<int>(min(a.B - b0, static_cast<int64_t>(kPairTile)));    // (not positive in a tile of padding)
 
-    // The operand fragments come straight from memory (L2: every workgroup streams the same 2 N d bytes), 1 KB per
-    // wavefront and step, and each wavefront has only one other on its SIMD to hide their latency: so they are
-    // requested as early as their registers are free: those of a pass's dX product and those of the next pass's S
-    // product as soon as the S product has consumed its own.
-    uint4 bS[KS];
-    if (w * 32 < a.N) {
-        const uint4* src = SP + static_cast<size_t>(w) * KS * 64 + l;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) bS[s] = src[s * 64];
-    }
     for (int n0 = 0; n0 < a.N; n0 += kNegChunk) {
         uint16_t* const Gs = Gs2 + ((n0 / kNegChunk) & 1) * (kPairTile * GP);
-        const uint16_t* ga = Gs + (l & 31) * GP + 8 * (l >> 5);
+        const uint16_t* ga = Gs + (l & 31) * GP + share * (XS * 16) + 8 * (l >> 5);
         const int nblock = (n0 >> 5) + w;                 // this wavefront's block of 32 negatives (whole blocks: N % 128 == 0)
         const bool s_active = nblock * 32 < a.N;
-        const bool x_active = w < CB;                     // this wavefront has a block of 32 columns of dX
-        const int steps = min(kNegChunk / 16, steps_all - (n0 >> 4));   // 16, or 8 in a last pass of 128 negatives
-        const uint4* tsrc = TP + (static_cast<size_t>(w) * steps_all + (n0 >> 4)) * 64 + l;
-        uint4 bT0[8], bT1[8];
+        // steps of this wavefront's share of the pass: all XS, or, of d = 256, half of them, or none
+        const int xstep = (n0 >> 4) + share * XS, steps = max(0, min(XS, steps_all - xstep));
         f32x16 sacc;
-        if (s_active) {
+        const bool more = n0 + kNegChunk < a.N;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) sacc[i] = 0.0f;
+        for (int i = 0; i < 16; ++i) sacc[i] = 0.0f;
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
-                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(xa + 16 * s)), as_bf16x8(bS[s]), sacc, 0, 0, 0);
-        }
-        if (x_active) {                                   // (after the S product: waits on loads are in issue order)
+        for (int q = 0; q < Q; ++q) {
 #pragma unroll
-            for (int s = 0; s < 8; ++s) bT0[s] = tsrc[s * 64];
-            if (steps > 8) {
-#pragma unroll
-                for (int s = 0; s < 8; ++s) bT1[s] = tsrc[(8 + s) * 64];
-            }
-        }
-        if (n0 + kNegChunk + w * 32 < a.N) {              // the S operands of the next pass
-            const uint4* src = SP + static_cast<size_t>(nblock + kNegChunk / 32) * KS * 64 + l;
-#pragma unroll
-            for (int s = 0; s < KS; ++s) bS[s] = src[s * 64];
+            for (int s = 0; s < 4; ++s)
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(xa + 64 * q + 16 * s)), as_bf16x8(rows[q][s]), sacc, 0, 0, 0);
+            if (more) fetch_rows(q, n0 + kNegChunk);
         }
         if (s_active) {
-            // G = -neg_scale * sigmoid(S), zero for padding rows; into LDS as bf16
+            // G = -neg_scale * sigmoid(S), zero for padding rows
+            float g[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int row = (i >> 2) * 8 + (l >> 5) * 4 + (i & 3);
-                const bool valid = b0 + row < a.B;
-                const float g = valid ? -a.neg_scale * fast_sigmoidf(sacc[i]) : 0.0f;
-                if (LOSS && valid) loss += a.neg_scale * softplusf(sacc[i]);
-                Gs[row * GP + w * 32 + (l & 31)] = to_bf16(g);
+                g[i] = -a.neg_scale * fast_sigmoidf(sacc[i]);
+                if (LOSS && pair_of_lane(l, i) < live_rows) loss += a.neg_scale * softplusf(sacc[i]);
             }
+            if (live_rows < kPairTile) {                  // (uniform)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (pair_of_lane(l, i) >= live_rows) g[i] = 0.0f;
+            }
+            uint32_t v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = pack2(g[2 * i], g[2 * i + 1]);
+            char* out = reinterpret_cast<char*>(reinterpret_cast<uint4*>(a.w.GP) + (nblock * steps_pairs + step0) * 64);
+            *reinterpret_cast<uint4*>(out + static_cast<uint32_t>(l) * 16u) = make_uint4(v[0], v[1], v[2], v[3]);
+            *reinterpret_cast<uint4*>(out + (static_cast<uint32_t>(l) * 16u + 1024u)) = make_uint4(v[4], v[5], v[6], v[7]);
+            uint16_t* gs = Gs + w * 32 + (l & 31);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) gs[pair_of_lane(l, i) * GP] = static_cast<uint16_t>(i & 1 ? v[i >> 1] >> 16 : v[i >> 1]);
         }
         lds_barrier();
-        // G^T to memory: one negative of the pass per two threads, 16 pairs (32 bytes) each
-        {
-            const int neg = tid >> 1, half = tid & 1;
-            if (n0 + neg < a.N) {
-                uint32_t v[8];
+        // dX += G . Cq for this wavefront's block of 32 columns over its share of the pass's negatives
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    v[i] = Gs[(half * 16 + 2 * i) * GP + neg] | (static_cast<uint32_t>(Gs[(half * 16 + 2 * i + 1) * GP + neg]) << 16);
-                uint4* out = reinterpret_cast<uint4*>(a.w.GT + static_cast<int64_t>(n0 + neg) * Bp + b0 + half * 16);
-                out[0] = make_uint4(v[0], v[1], v[2], v[3]);
-                out[1] = make_uint4(v[4], v[5], v[6], v[7]);
+        for (int q = 0; q < Q; ++q) {
+            if (4 * q < steps) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    acc_dx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(ga + 64 * q + 16 * s)), as_bf16x8(columns[q][s]), acc_dx, 0, 0, 0);
             }
-        }
-        // dX += G . Cq for this wavefront's block of 32 columns over the negatives of the pass
-        if (x_active) {
-#pragma unroll
-            for (int s = 0; s < 8; ++s)
-                acc_dx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(ga + 16 * s)), as_bf16x8(bT0[s]), acc_dx, 0, 0, 0);
-            if (steps > 8) {
-#pragma unroll
-                for (int s = 0; s < 8; ++s)
-                    acc_dx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(ga + 16 * (8 + s))), as_bf16x8(bT1[s]), acc_dx, 0, 0, 0);
-            }
+            if (more) fetch_columns(q, n0 + kNegChunk);
         }
         // (the next pass writes the other G; the one after it writes this one behind a barrier that every
         // wavefront reaches with its reads of this pass done)
@@ -390,22 +408,30 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(ScoresArgs a)
     lds_barrier();       // the rows' and G's LDS is rewritten
 
     // ---- epilogue: dX to the pairs' lanes
-    if (w < CB) {
+    {
+        float* out = dXs + share * (kPairTile * DP) + cb * 32 + (l & 31);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int row = (i >> 2) * 8 + (l >> 5) * 4 + (i & 3);
-            dXs[row * DP + w * 32 + (l & 31)] = acc_dx[i];
-        }
+        for (int i = 0; i < 16; ++i) out[pair_of_lane(l, i) * DP] = acc_dx[i];
     }
     lds_barrier();
     if (live) {
         float4* dxs = reinterpret_cast<float4*>(a.w.dxs + b * D);
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
-            const int ci = lp + 16 * i;
-            const float4 n = *reinterpret_cast<const float4*>(dXs + p * DP + 4 * ci);
+            const int ci = lp + LP * i;
+            float4 n = *reinterpret_cast<const float4*>(dXs + p * DP + 4 * ci);
+#pragma unroll
+            for (int h = 1; h < SHARES; ++h) {
+                const float4 m = *reinterpret_cast<const float4*>(dXs + (h * kPairTile + p) * DP + 4 * ci);
+                n = make_float4(n.x + m.x, n.y + m.y, n.z + m.z, n.w + m.w);
+            }
             dxs[ci] = make_float4(fmaf(a.lr, n.x, dxp[i].x), fmaf(a.lr, n.y, dxp[i].y), fmaf(a.lr, n.z, dxp[i].z), fmaf(a.lr, n.w, dxp[i].w));
         }
+    }
+    // references beyond one per thread (many negatives, few pairs)
+    for (int64_t r = my_ref + static_cast<int64_t>(gridDim.x) * kScoreThreads; r < refs; r += static_cast<int64_t>(gridDim.x) * kScoreThreads) {
+        const uint32_t key = key_of_ref(a, r), pos = ref_hash(key, a.w.hash_mask);
+        flag(r, key, pos, a.w.slots[pos]);
     }
     if (LOSS) {
         __shared__ double sh[kScoreThreads / 64];
@@ -421,13 +447,14 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(ScoresArgs a)
 }
 
 // ---------------------------------------------------------------------------------------------
-// dctx kernel: dC = G^T . Xq.  Workgroup tile 128 negatives x TD columns (TD = 64 or 128), one share
-// of the batch (the contraction index) per blockIdx.z.  Both operands are contraction-contiguous in
-// memory (GT [N][Bp], XqT [d][Bp]); 64 contraction steps at a time are staged through LDS so that
-// the four wavefronts share them (operand traffic, not arithmetic, bounds this product), two stages
+// dctx kernel: dC = G^T . Xq.  Workgroup tile 128 negatives x 64 columns, one share
+// of the batch (the contraction index) per blockIdx.x, so that a die fetches the coefficients and rows of one or two shares only.
+// Both operands lie in memory as fragments, and four steps of them at a time are staged through LDS so that
+// the four wavefronts share them (operand traffic, not arithmetic, bounds this product: straight from memory into registers, eight
+// steps ahead, it takes 12.8 us instead of 10.9 at 8192 pairs x 1024 negatives x 256), two stages
 // alternating, with the next one travelling into registers meanwhile: one barrier per stage, for LDS only
-// (two full barriers and one buffer: a step of 8192 pairs x 1024 negatives at dim 128 42.8 us, now 41.8; three or four
-// stages in flight instead of two gained nothing).  Wavefront w: 64 negatives (w & 1) x TD/2 columns
+// (two full barriers and one buffer: a step of 8192 pairs x 1024 negatives at dim 128 42.8 us, so 41.8; three or four
+// stages in flight instead of two gained nothing).  Wavefront w: 64 negatives (w & 1) x 32 columns
 // (w >> 1).
 // ---------------------------------------------------------------------------------------------
 struct DctxArgs {
@@ -435,79 +462,67 @@ struct DctxArgs {
     int32_t N, D;
 };
 
-template <int TD>
+constexpr int kDctxColumns = 64;
+
+template <int SPLIT>
 __global__ __launch_bounds__(256) void dctx_kernel(DctxArgs a)
 {
-    constexpr int KP = 64 + 8;        // LDS pitch (bf16)
-    constexpr int BT = TD / 64;       // column tiles per wavefront
-    constexpr int BPT = TD * 8 / 256; // 16-byte pieces of the column operand per thread
-    __shared__ uint16_t As[2][128 * KP];
-    __shared__ uint16_t Bs[2][TD * KP];
+    constexpr int NB = kDctxColumns / 32;       // column blocks of the tile, one per pair of wavefronts
+    __shared__ u32x4 As[2][4][256];   // [block of 32 negatives][four steps of 64 lanes]
+    __shared__ u32x4 Bs[2][NB][256];
     const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
     const int wr = w & 1, wc = w >> 1;
-    const int64_t Bp = a.w.Bp;
-    const int kc = static_cast<int>(Bp / kSplit);
-    const int64_t kbeg = static_cast<int64_t>(blockIdx.z) * kc;
-    const int n0 = blockIdx.x * 128, d0 = blockIdx.y * TD;
-    f32x16 acc[2][BT];
+    const int64_t steps = a.w.Bp / 16;
+    const int stages = static_cast<int>(steps / SPLIT / 4);
+    const int nb0 = blockIdx.y * 4, cb0 = blockIdx.z * NB;
+    f32x16 acc[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
-        for (int t = 0; t < BT; ++t)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[r][t][i] = 0.0f;
+        for (int i = 0; i < 16; ++i) acc[r][i] = 0.0f;
 
-    // piece c of a stage: row c / 8, 16-byte column c % 8
-    struct Stage { u32x4 a[4], b[BPT]; };
-    const uint16_t* src_a = a.w.GT + static_cast<int64_t>(n0 + tid / 8) * Bp + kbeg + (tid % 8) * 8;
-    const uint16_t* src_b = a.w.XqT + static_cast<int64_t>(d0 + tid / 8) * Bp + kbeg + (tid % 8) * 8;
-    auto fetch = [&](int k0, Stage& s) {
+    struct Stage { u32x4 a[4], b[NB]; };
+    const int64_t first = blockIdx.x * (steps / SPLIT) * 64 + tid;
+    const u32x4* src_a = reinterpret_cast<const u32x4*>(a.w.GP) + nb0 * steps * 64 + first;
+    const u32x4* src_b = reinterpret_cast<const u32x4*>(a.w.XqP) + cb0 * steps * 64 + first;
+    auto fetch = [&](int k, Stage& s) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s.a[i] = *reinterpret_cast<const u32x4*>(src_a + static_cast<int64_t>(32 * i) * Bp + k0);
+        for (int i = 0; i < 4; ++i) s.a[i] = src_a[i * steps * 64 + k * 256];
 #pragma unroll
-        for (int i = 0; i < BPT; ++i) s.b[i] = *reinterpret_cast<const u32x4*>(src_b + static_cast<int64_t>(32 * i) * Bp + k0);
+        for (int i = 0; i < NB; ++i) s.b[i] = src_b[i * steps * 64 + k * 256];
     };
     auto stage = [&](int buf, const Stage& s) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(As[buf] + (tid / 8 + 32 * i) * KP + (tid % 8) * 8) = s.a[i];
+        for (int i = 0; i < 4; ++i) As[buf][i][tid] = s.a[i];
 #pragma unroll
-        for (int i = 0; i < BPT; ++i) *reinterpret_cast<u32x4*>(Bs[buf] + (tid / 8 + 32 * i) * KP + (tid % 8) * 8) = s.b[i];
+        for (int i = 0; i < NB; ++i) Bs[buf][i][tid] = s.b[i];
     };
     auto multiply = [&](int buf) {
-        const uint16_t* ar = As[buf] + (wr * 64 + (l & 31)) * KP + (l >> 5) * 8;
-        const uint16_t* br = Bs[buf] + (wc * (TD / 2) + (l & 31)) * KP + (l >> 5) * 8;
 #pragma unroll
-        for (int kk = 0; kk < 64; kk += 16) {
-            const bf16x8 a0 = as_bf16x8(*reinterpret_cast<const uint4*>(ar + kk));
-            const bf16x8 a1 = as_bf16x8(*reinterpret_cast<const uint4*>(ar + 32 * KP + kk));
-#pragma unroll
-            for (int t = 0; t < BT; ++t) {
-                const bf16x8 bv = as_bf16x8(*reinterpret_cast<const uint4*>(br + t * 32 * KP + kk));
-                acc[0][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, bv, acc[0][t], 0, 0, 0);
-                acc[1][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, bv, acc[1][t], 0, 0, 0);
-            }
+        for (int k = 0; k < 4; ++k) {
+            const bf16x8 a0 = __builtin_bit_cast(bf16x8, As[buf][2 * wr][k * 64 + l]);
+            const bf16x8 a1 = __builtin_bit_cast(bf16x8, As[buf][2 * wr + 1][k * 64 + l]);
+            const bf16x8 b = __builtin_bit_cast(bf16x8, Bs[buf][wc][k * 64 + l]);
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b, acc[1], 0, 0, 0);
         }
     };
     Stage next;
     fetch(0, next);
-    for (int k0 = 0; k0 < kc; k0 += 64) {
-        const int buf = (k0 >> 6) & 1;
-        stage(buf, next);
-        if (k0 + 64 < kc) fetch(k0 + 64, next);
+    for (int k = 0; k < stages; ++k) {
+        stage(k & 1, next);
+        if (k + 1 < stages) fetch(k + 1, next);
         lds_barrier();
-        multiply(buf);     // (the stage after the next overwrites this buffer behind another barrier)
+        multiply(k & 1);     // (the stage after the next overwrites this buffer behind another barrier)
     }
-    float* out = a.w.dCp + static_cast<int64_t>(blockIdx.z) * a.N * a.D;
+    float* out = a.w.dCp + static_cast<int64_t>(blockIdx.x) * a.N * a.D;
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
-        for (int t = 0; t < BT; ++t)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int row = n0 + wr * 64 + r * 32 + (i >> 2) * 8 + (l >> 5) * 4 + (i & 3);
-                const int col = d0 + wc * (TD / 2) + t * 32 + (l & 31);
-                out[static_cast<int64_t>(row) * a.D + col] = acc[r][t][i];
-            }
+        for (int i = 0; i < 16; ++i) {
+            const int row = (nb0 + 2 * wr + r) * 32 + (i >> 2) * 8 + (l >> 5) * 4 + (i & 3);
+            out[static_cast<int64_t>(row) * a.D + (cb0 + wc) * 32 + (l & 31)] = acc[r][i];
+        }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -600,7 +615,7 @@ __global__ __launch_bounds__(256) void update_shared_kernel(UpdateArgs a)
                 const int ci = lg + i * G;
                 float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-                for (int s = 0; s < kSplit; ++s)
+                for (int s = 0; s < split_of(D); ++s)
                     sum = add4(sum, reinterpret_cast<const float4*>(a.w.dCp + (static_cast<int64_t>(s) * a.N + j) * D)[ci]);
                 const float4 r = reinterpret_cast<const float4*>(crow)[ci];
                 c4[i] = make_float4(fmaf(a.lr, sum.x, r.x), fmaf(a.lr, sum.y, r.y), fmaf(a.lr, sum.z, r.z), fmaf(a.lr, sum.w, r.w));
@@ -614,7 +629,7 @@ __global__ __launch_bounds__(256) void update_shared_kernel(UpdateArgs a)
                 const int e = lg + m * G;
                 float sum = 0.0f;
 #pragma unroll
-                for (int s = 0; s < kSplit; ++s) sum += a.w.dCp[(static_cast<int64_t>(s) * a.N + j) * D + e];
+                for (int s = 0; s < split_of(D); ++s) sum += a.w.dCp[(static_cast<int64_t>(s) * a.N + j) * D + e];
                 c1[m] = a.lr * sum;
             }
 #pragma unroll
@@ -659,10 +674,7 @@ hipError_t run_shared(ne_tables* t, const ne_alias* al, const int32_t* pairs_dev
 
     DctxArgs da{};
     da.w = w; da.N = N; da.D = D;
-    if (D >= 128)
-        hipLaunchKernelGGL(dctx_kernel<128>, dim3(N / 128, D / 128, kSplit), dim3(256), 0, st, da);
-    else
-        hipLaunchKernelGGL(dctx_kernel<64>, dim3(N / 128, 1, kSplit), dim3(256), 0, st, da);
+    hipLaunchKernelGGL(dctx_kernel<split_of(D)>, dim3(split_of(D), N / 128, D / kDctxColumns), dim3(256), 0, st, da);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
 
