@@ -1771,7 +1771,8 @@ __global__ __launch_bounds__(kTrainThreads) void train_seg_kernel(TrainArgs a, H
 // workgroups of their own, which add up neighbouring items of a row in LDS; what several workgroups hold of a row meets
 // in an accumulator that starts from zero, and who arrives last adds it to the table row and leaves it zero again.
 // Bound by the rows it moves (two thirds of the rows have two references) and, in small batches, by its chain
-// of four dependent accesses: item, entries, rows, store.  The rows of buf are few (one or two per pair, however
+// of four dependent accesses: item, entries, rows, store, of which the first two go ahead of an item's turn (65 536 pairs, dim 128,
+// among 32 M / 1 M nodes 28.0 / 38.8 us with all of them in turn, 26.2 / 38.0; 20 000 nodes, 22 walks, dim 64 5.9 and 5.4).  The rows of buf are few (one or two per pair, however
 // many references share them) and mostly still in the last-level cache; per-reference deltas in memory order
 // instead cost here and in the train kernel 28 + 98 us at 32 M nodes x dim 128 (now 28 + 90), 47 + 94 at 1 M x
 // dim 128 (now 39 + 77) and 151 + 285 at 4 M x dim 512, K = 10 (now 99 + 216).  8 entries at a time against 4: -1 .. -2 % of a batch at dim <= 256,
@@ -1786,7 +1787,7 @@ struct ApplyArgs {
     const uint2* items;
     const uint4* hub_items;
     const unsigned long long* totals;     // items | items of hubs << 32
-    uint32_t most;        // items there can be
+    uint32_t most, most_hubs;        // items there can be, and items of hubs
     unsigned hub_blocks;  // workgroups, the first of the launch, that take the hubs' items
     const uint2* list;
     const float4* buf;
@@ -1794,23 +1795,24 @@ struct ApplyArgs {
     uint32_t* arrived;    // items whose sums have been added to each of them, all zero
 };
 
-// The entries of a work item, summed (item_places: y).
+// A work item's entries (item_places: y): lane r of the group fetches entry r, of the last one again past the end.
+__device__ __forceinline__ uint2 fetch_entry(const ApplyArgs& a, uint32_t y, int lg) { return a.list[(y >> 3) + min(static_cast<uint32_t>(lg) & 7u, y & 7u)]; }
+
+// The entries of a work item, summed.
 template <int GL, int CH>
-__device__ __forceinline__ void sum_item(const ApplyArgs& a, uint32_t y, int lg, float4 (&sum)[CH])
+__device__ __forceinline__ void sum_item(const ApplyArgs& a, uint32_t y, uint2 mine, int lg, float4 (&sum)[CH])
 {
     constexpr uint32_t MB = CH == 1 ? kItemRefs : kItemRefs / 2;   // entries whose rows travel together
-    const uint2* list = a.list + (y >> 3);
     const uint32_t refs = (y & 7u) + 1u;
 #pragma unroll
     for (int i = 0; i < CH; ++i) sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (uint32_t r0 = 0; r0 < refs; r0 += MB) {
-        uint2 entry[MB];
+#pragma unroll
+    for (uint32_t r0 = 0; r0 < kItemRefs; r0 += MB) {
+        if (r0 >= refs) break;
         float4 v[MB][CH];
 #pragma unroll
-        for (uint32_t r = 0; r < MB; ++r) entry[r] = list[min(r0 + r, refs - 1u)];
-#pragma unroll
         for (uint32_t r = 0; r < MB; ++r) {
-            const float4* src = a.buf + static_cast<int64_t>(entry[r].x) * a.d4;
+            const float4* src = a.buf + static_cast<int64_t>(__shfl(mine.x, r0 + r, GL)) * a.d4;
 #pragma unroll
             for (int i = 0; i < CH; ++i) {
                 const int ci = lg + GL * i;
@@ -1819,7 +1821,7 @@ __device__ __forceinline__ void sum_item(const ApplyArgs& a, uint32_t y, int lg,
         }
 #pragma unroll
         for (uint32_t r = 0; r < MB; ++r) {
-            const float g = r0 + r < refs ? __uint_as_float(entry[r].y) : 0.0f;
+            const float c = __uint_as_float(__shfl(mine.y, r0 + r, GL)), g = r0 + r < refs ? c : 0.0f;
 #pragma unroll
             for (int i = 0; i < CH; ++i) sum[i] = axpy4(g, v[r][i], sum[i]);
         }
@@ -1838,14 +1840,14 @@ __device__ __forceinline__ void apply_hubs(const ApplyArgs& a, float4 (&lds)[256
     constexpr uint32_t GROUPS = 256 / GL;
     const int lg = threadIdx.x & (GL - 1), d4 = a.d4;
     const uint32_t grp = threadIdx.x / GL;
+    auto fetch_item = [&](uint32_t first) { return a.hub_items[min(first + grp, a.most_hubs - 1u)]; };     // (what lies past the last one is not used)
+    uint4 item = fetch_item(blockIdx.x * GROUPS);          // (in flight together with the count)
     const uint32_t n = static_cast<uint32_t>(*a.totals >> 32);
-    for (uint32_t first = blockIdx.x * GROUPS; first < n; first += a.hub_blocks * GROUPS) {     // (uniform)
+    for (uint32_t first = blockIdx.x * GROUPS; first < n; first += a.hub_blocks * GROUPS, item = fetch_item(first)) {     // (uniform)
         const bool live = first + grp < n;
-        uint4 item = make_uint4(0u, 0u, 0u, 0u);
         float4 sum[CH];
         if (live) {
-            item = a.hub_items[first + grp];
-            sum_item<GL, CH>(a, item.y, lg, sum);
+            sum_item<GL, CH>(a, item.y, fetch_entry(a, item.y, lg), lg, sum);
 #pragma unroll
             for (int i = 0; i < CH; ++i) lds[grp][lg + GL * i] = sum[i];
         }
@@ -1913,9 +1915,13 @@ __global__ __launch_bounds__(256) void apply_kernel(ApplyArgs a)
     const uint32_t grp = threadIdx.x / GL;
     const uint32_t step = (gridDim.x - a.hub_blocks) * GROUPS;
     uint32_t e = (blockIdx.x - a.hub_blocks) * GROUPS + grp;
-    uint2 item = a.items[min(e, a.most - 1u)];     // (in flight together with the count; what lies past it is not used)
+    // an item's entries are requested an item ahead and its words two ahead, so that a group waits for its rows only
+    auto fetch_item = [&](uint32_t at) { return a.items[min(at, a.most - 1u)]; };     // (what lies past the last one is not used)
+    uint2 item = fetch_item(e), next = fetch_item(e + step);
     const uint32_t n = static_cast<uint32_t>(*a.totals);
-    for (; e < n; e += step, item = a.items[min(e, a.most - 1u)]) {
+    uint2 entry = make_uint2(0u, 0u);
+    if (e < n) entry = fetch_entry(a, item.y, lg);
+    for (; e < n; e += step) {
         float4* row = row_of_key(a, item.x);
         float4 old[CH], sum[CH];
 #pragma unroll
@@ -1923,12 +1929,18 @@ __global__ __launch_bounds__(256) void apply_kernel(ApplyArgs a)
             const int ci = lg + GL * i;
             old[i] = ci < a.d4 ? row[ci] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        sum_item<GL, CH>(a, item.y, lg, sum);
+        const uint2 then = fetch_item(e + 2 * step);
+        uint2 next_entry = make_uint2(0u, 0u);
+        if (e + step < n) next_entry = fetch_entry(a, next.y, lg);
+        sum_item<GL, CH>(a, item.y, entry, lg, sum);
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int ci = lg + GL * i;
             if (ci < a.d4) row[ci] = add4(old[i], sum[i]);
         }
+        item = next;
+        next = then;
+        entry = next_entry;
     }
 }
 
@@ -2169,11 +2181,13 @@ hipError_t launch_prepare(const Helpers& h, bool claim_first, hipStream_t st)
 
 // Lane groups of the apply kernel: one dwordx4 chunk per lane as long as a wavefront holds the row, however many
 // references a pair has (the train kernel's groups, with a lane per reference, leave 63 of 64 lanes idle at dim 4,
-// K = 62: 32 768 pairs among a million nodes 465 us, now 316; 2^20 pairs among 64 million 19.3 ms, now 13.9).  Its number of items is only known on the device; kApplyBlocks workgroups leave a lane group few of them, so
-// that those with long lists do not finish last (16384 against 2048: -2 .. -6 % of a batch's time).  Up to
-// kHubBlocks more take the hubs' items, whose chains are the longest (512 take 6 % more of a batch of 65 536 pairs among
-// 1000 .. 10 000 nodes, 256 10 % more among a million; without hubs the 1024 are not seen).
-constexpr unsigned kApplyBlocks = 16384;
+// K = 62: 32 768 pairs among a million nodes 465 us, now 316; 2^20 pairs among 64 million 19.3 ms, now 13.9).  Its number of items is only
+// known on the device; kApplyGroups lane groups leave each a few of them, of which all but the first find their entries there, and not so many
+// that those with long lists finish last (6 x 65 536 pairs, dim 128, 32 M / 1 M nodes, and 3 x 32 768, dim 512: 131 072 groups 693 / 625 /
+// 944 us, 57 344 692 / 622 / 945, 28 672 689 / 627 / 949, 14 336 694 / 627 / 962).  Up to
+// kHubBlocks workgroups more take the hubs' items, whose chains are the longest (512 take 6 % more of a batch of 65 536 pairs among
+// 1000 .. 10 000 nodes, 256 10 % more among a million; half as many as the items fill are level in small batches, a quarter take 9 - 14 % more).
+constexpr unsigned kApplyGroups = 57344;
 constexpr unsigned kHubBlocks = 1024;
 hipError_t launch_apply(ApplyArgs a, uint32_t refs, hipStream_t st)
 {
@@ -2184,8 +2198,9 @@ hipError_t launch_apply(ApplyArgs a, uint32_t refs, hipStream_t st)
     const unsigned groups = 256u / s.G;
     const unsigned want = (a.most + groups - 1) / groups;
     const unsigned hubs = static_cast<unsigned>((most_hub_items(refs) + groups - 1) / groups);
+    a.most_hubs = static_cast<uint32_t>(most_hub_items(refs));
     a.hub_blocks = hubs < kHubBlocks ? hubs : kHubBlocks;
-    const unsigned grid = (want < kApplyBlocks ? want : kApplyBlocks) + a.hub_blocks;
+    const unsigned grid = std::min(want, kApplyGroups / groups) + a.hub_blocks;
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
         hipLaunchKernelGGL((apply_kernel<G_, N_>), dim3(grid), dim3(256), 0, st, a);             \
