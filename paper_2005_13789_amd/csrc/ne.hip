@@ -921,7 +921,23 @@ __device__ __forceinline__ void locate_share(const PrepArgs& a, uint32_t total, 
     }
 }
 
-// What the rows of a bin have taken: places of the list, and work items.
+// What a thread's rows take, places of the list and work items, is added to what the bin's rows have taken, and becomes what others
+// took before.  All lanes call this together.
+__device__ __forceinline__ void take(ResolveLds& s, uint32_t& places, uint32_t& items, uint32_t& hubs)
+{
+    const uint32_t last_place = wave_inclusive_scan(places), last_item = wave_inclusive_scan(items), last_hub = wave_inclusive_scan(hubs);
+    unsigned long long before = 0ull;
+    uint32_t hubs_before = 0u;
+    if ((threadIdx.x & 63u) == 63u) {
+        before = atomicAdd(&s.taken, last_place | (static_cast<unsigned long long>(last_item) << 32));
+        if (last_hub) hubs_before = atomicAdd(&s.hub_items, last_hub);
+    }
+    places = __builtin_amdgcn_readlane(static_cast<uint32_t>(before), 63) + last_place - places;
+    items = __builtin_amdgcn_readlane(static_cast<uint32_t>(before >> 32), 63) + last_item - items;
+    hubs = __builtin_amdgcn_readlane(hubs_before, 63) + last_hub - hubs;
+}
+
+// What earlier rows of a bin have taken.
 struct Taken { uint32_t places, items, hub_items; };
 
 // The places and work items of the shared rows in the table, which holds every row's references on entry and, on
@@ -937,9 +953,7 @@ __device__ __forceinline__ void place_rows(const PrepArgs& a, uint32_t first_pla
         if (n > 1) { places += n; items += static_cast<uint32_t>(n <= kItemRefs); }
         if (n > kItemRefs) hubs += (n + kItemRefs - 1) / kItemRefs;
     }
-    uint32_t all_items, all_places, all_hubs, none = 0, nothing;
-    block_exclusive_scan<T>(items, places, s.part, &all_items, &all_places);
-    block_exclusive_scan<T>(hubs, none, s.part, &all_hubs, &nothing);
+    take(s, places, items, hubs);
     uint32_t row = first_place + taken.places + places;
     uint32_t item = static_cast<uint32_t>(most_items(first_place)) + taken.items + items;
     uint32_t hub = static_cast<uint32_t>(most_hub_items(first_place)) + taken.hub_items + hubs;
@@ -949,10 +963,10 @@ __device__ __forceinline__ void place_rows(const PrepArgs& a, uint32_t first_pla
         if (a.items) write_items(a, slot.x, slot.y, row, item, hub);      // (uniform)
         if (slot.y > 1) row += slot.y;
     }
-    taken.places += all_places;
-    taken.items += all_items;
-    taken.hub_items += all_hubs;
     lds_barrier();
+    taken.places += static_cast<uint32_t>(s.taken);
+    taken.items += static_cast<uint32_t>(s.taken >> 32);
+    taken.hub_items += s.hub_items;
 }
 
 // f(key, references, place in memory) for every entry of the 256 tiles at hand, four of a thread in flight (eight: 73 registers, a
@@ -1014,16 +1028,10 @@ __device__ __forceinline__ void resolve_share(const PrepArgs& a, uint32_t bin, u
             if (n > kItemRefs) hubs += (n + kItemRefs - 1u) / kItemRefs;
         }
     }
-    const uint32_t last_place = wave_inclusive_scan(places), last_item = wave_inclusive_scan(items), last_hub = wave_inclusive_scan(hubs);
-    unsigned long long before = 0ull;
-    uint32_t hubs_before = 0u;
-    if ((tid & 63u) == 63u) {
-        before = atomicAdd(&s.taken, last_place | (static_cast<unsigned long long>(last_item) << 32));
-        if (last_hub) hubs_before = atomicAdd(&s.hub_items, last_hub);
-    }
-    uint32_t place = first_place + __builtin_amdgcn_readlane(static_cast<uint32_t>(before), 63) + last_place - places;
-    uint32_t item = static_cast<uint32_t>(most_items(first_place)) + __builtin_amdgcn_readlane(static_cast<uint32_t>(before >> 32), 63) + last_item - items;
-    uint32_t hub = static_cast<uint32_t>(most_hub_items(first_place)) + __builtin_amdgcn_readlane(hubs_before, 63) + last_hub - hubs;
+    take(s, places, items, hubs);
+    uint32_t place = first_place + places;
+    uint32_t item = static_cast<uint32_t>(most_items(first_place)) + items;
+    uint32_t hub = static_cast<uint32_t>(most_hub_items(first_place)) + hubs;
 #pragma unroll
     for (int u = 0; u < kShare<T>; ++u) {
         if (T * u >= total) break;
@@ -1176,8 +1184,9 @@ struct GatherArgs {
     unsigned long long* totals; // items | items of hubs << 32
     uint32_t n_bins, share;     // bins in all and per workgroup, powers of two, share at most 256
 };
-constexpr uint32_t kGatherBins = 4, kGatherBlocks = 128;
-struct GatherLds { uint32_t part[32]; uint32_t item[256], hub[256]; };
+// A bin with many items of hubs is copied by all of them (by a wavefront: 4 x 65 536 pairs with one source row, dim 16, 264 us instead of 182).
+constexpr uint32_t kGatherBins = 4, kGatherBlocks = 128, kGatherAlone = 256;
+struct GatherLds { uint32_t part[32]; uint32_t item[256], hub[256]; uint32_t big[256]; uint32_t n_big; };
 template <uint32_t T>
 __device__ __forceinline__ void gather_items(const GatherArgs& a, uint32_t block, unsigned char* lds)
 {
@@ -1191,13 +1200,28 @@ __device__ __forceinline__ void gather_items(const GatherArgs& a, uint32_t block
     block_exclusive_scan<T>(own_items, own_hubs, s.part, &items_here, &hubs_here);
     if (tid < a.share) { s.item[tid] = items_before + own_items; s.hub[tid] = hubs_before + own_hubs; }
     if (tid == 0 && first + a.share == a.n_bins) *a.totals = (items_before + items_here) | (static_cast<unsigned long long>(hubs_before + hubs_here) << 32);
+    if (tid == 0) s.n_big = 0u;
     lds_barrier();
     for (uint32_t b = tid >> 6; b < a.share; b += T / 64u) {
         const uint4 bin = a.bins[first + b];
         const uint2* from = a.from + most_items(bin.x);
         for (uint32_t i = tid & 63u; i < bin.y; i += 64u) a.items[s.item[b] + i] = from[i];
         const uint4* hubs_from = a.hubs_from + most_hub_items(bin.x);
-        for (uint32_t i = tid & 63u; i < bin.z; i += 64u) a.hub_items[s.hub[b] + i] = hubs_from[i];
+        if (bin.z <= kGatherAlone)
+            for (uint32_t i = tid & 63u; i < bin.z; i += 64u) a.hub_items[s.hub[b] + i] = hubs_from[i];
+        else if ((tid & 63u) == 0u) s.big[atomicAdd(&s.n_big, 1u)] = b;
+    }
+    lds_barrier();
+    for (uint32_t k = 0; k < s.n_big; ++k) {
+        const uint32_t b = s.big[k];
+        const uint4 bin = a.bins[first + b];
+        const uint4* hubs_from = a.hubs_from + most_hub_items(bin.x);
+        for (uint32_t i = tid; i < bin.z; i += 4u * T) {
+            const uint32_t last = bin.z - 1u, i1 = min(i + T, last), i2 = min(i + 2u * T, last), i3 = min(i + 3u * T, last);     // (the last one several times)
+            const uint4 v0 = hubs_from[i], v1 = hubs_from[i1], v2 = hubs_from[i2], v3 = hubs_from[i3];
+            uint4* to = a.hub_items + s.hub[b];
+            to[i] = v0; to[i1] = v1; to[i2] = v2; to[i3] = v3;
+        }
     }
 }
 
