@@ -2208,10 +2208,11 @@ hipError_t launch_prepare(const Helpers& h, bool claim_first, hipStream_t st)
 // K = 62: 32 768 pairs among a million nodes 465 us, now 316; 2^20 pairs among 64 million 19.3 ms, now 13.9).  Its number of items is only
 // known on the device; kApplyGroups lane groups leave each a few of them, of which all but the first find their entries there, and not so many
 // that those with long lists finish last (6 x 65 536 pairs, dim 128, 32 M / 1 M nodes, and 3 x 32 768, dim 512: 131 072 groups 693 / 625 /
-// 944 us, 57 344 692 / 622 / 945, 28 672 689 / 627 / 949, 14 336 694 / 627 / 962).  Up to
+// 944 us, 57 344 692 / 622 / 945, 28 672 689 / 627 / 949, 14 336 694 / 627 / 962), but kApplyBlocks workgroups at least, where
+// groups are small (the apply launch of 2^22 pairs, dim 16, with a quarter of them 784 instead of 681 us).  Up to
 // kHubBlocks workgroups more take the hubs' items, whose chains are the longest (512 take 6 % more of a batch of 65 536 pairs among
 // 1000 .. 10 000 nodes, 256 10 % more among a million; half as many as the items fill are level in small batches, a quarter take 9 - 14 % more).
-constexpr unsigned kApplyGroups = 57344;
+constexpr unsigned kApplyGroups = 57344, kApplyBlocks = 7168;
 constexpr unsigned kHubBlocks = 1024;
 hipError_t launch_apply(ApplyArgs a, uint32_t refs, hipStream_t st)
 {
@@ -2224,7 +2225,7 @@ hipError_t launch_apply(ApplyArgs a, uint32_t refs, hipStream_t st)
     const unsigned hubs = static_cast<unsigned>((most_hub_items(refs) + groups - 1) / groups);
     a.most_hubs = static_cast<uint32_t>(most_hub_items(refs));
     a.hub_blocks = hubs < kHubBlocks ? hubs : kHubBlocks;
-    const unsigned grid = std::min(want, kApplyGroups / groups) + a.hub_blocks;
+    const unsigned grid = std::min(want, std::max(kApplyGroups / groups, kApplyBlocks)) + a.hub_blocks;
 #define NE_CASE(G_, N_)                                                                          \
     if (s.G == G_ && s.NCH == N_) {                                                              \
         hipLaunchKernelGGL((apply_kernel<G_, N_>), dim3(grid), dim3(256), 0, st, a);             \
