@@ -816,7 +816,7 @@ __device__ __forceinline__ uint2 fetch_segment(const PrepArgs& a, uint32_t bin, 
 
 // Numbers the entries of these tiles and returns how many they are; *before: the tiles' references in lower bins.  SHARE: if they
 // are a share, tile_of says whose each is (a search through 224 tiles is 8 accesses to LDS in turn).  All threads call this together.
-constexpr uint32_t kShortSegment = 16;
+constexpr uint32_t kShortSegment = 32;       // (tiles of one step have up to 18 references in a bin before equal rows are looked for)
 template <uint32_t T, bool SHARE>
 __device__ __forceinline__ uint32_t number_entries(const PrepArgs& a, uint2 segment, uint32_t tile0, ResolveLds& s, uint32_t* before)
 {

@@ -1,5 +1,5 @@
 """Work items of the shared rows: who writes them (a lane up to 64 references of a row, a wavefront beyond), how the bins'
-items are moved together (bins per workgroup), and the entries of a tile in one bin (up to 16 are listed, beyond that searched for).
+items are moved together (bins per workgroup), and the entries of a tile in one bin (up to 32 are listed, beyond that searched for).
 Every row is checked against the oracle.
 
 Bar: as in test_gpu_row_detection, rows of up to some hundred references."""
@@ -30,7 +30,7 @@ def test_multiplicities_and_bins(B):
 
 
 # 4096 references: 64 bins, tiles of 256 references with 4 per bin on average and up to 18 before equal rows are looked for
-@pytest.mark.parametrize("together", [15, 16, 17, 18, 19, 40])
+@pytest.mark.parametrize("together", [17, 18, 19, 31, 32, 33, 60])
 def test_entries_of_a_tile_in_one_bin(together):
     print(f"together={together}", flush=True)
     V, d, seed = 1_000_000, 4, 22
