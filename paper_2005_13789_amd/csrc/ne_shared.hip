@@ -16,7 +16,7 @@
 //           operand fragment later); claims every row reference of the batch (plain-store hashing).
 //   scores  one workgroup per 32 pairs, all N negatives: gathers its pairs' rows, does the positive
 //           pairs in fp32, S block by block on MFMA with the negatives' fragments streamed from
-//           memory (they stay in L2), sigmoid in registers, G to LDS (and transposed to memory for the
+//           memory (they stay in L2), sigmoid in registers, G to LDS (and as fragments to memory for the
 //           dC product), dX accumulated on MFMA over all negatives: a workgroup ends with the complete
 //           deltas of its pairs' source rows, no partial sums.  The resolve pass rides along.
 //   dctx    dC = G^T . Xq on MFMA, split over the batch dimension into partial sums.
