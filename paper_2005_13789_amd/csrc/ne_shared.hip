@@ -51,8 +51,16 @@ constexpr int kMostSplit = 16;
 constexpr int split_of(int dim) { return dim == 64 ? kMostSplit : 8; }
 constexpr int kBatchPad = 1024;    // the padded batch is a multiple of this (shares of whole 64-pair stages)
 
-// sigmoid from the hardware exp2 and reciprocal (about 1 ulp each): the result is rounded to bf16 anyway
-__device__ __forceinline__ float fast_sigmoidf(float z) { return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z * -1.44269504f)); }
+// sigmoid from the hardware exp2 (about 1 ulp) and a correctly rounded reciprocal: one Newton step from the hardware's, which is off by
+// a last bit for 11 % of the values in [1, 2^126] and after the step for none of them (all were compared with __frcp_rn).  y infinite: the
+// step's factor is NaN, fmaxf makes it -1, and the sigmoid is 0.  (A score of -87.3 or less, whose sigmoid is below 2^-126, may give 0 too.)
+// The scores kernel at 8192 pairs x 1024 negatives, dim 256 / 128 / 64: 22.2 / 16.1 / 15.4 us; 24.3 / 17.8 / 16.6 with __frcp_rn, a division;
+// 21.7 / 16.0 / 14.8 without the step.
+__device__ __forceinline__ float fast_sigmoidf(float z)
+{
+    const float y = 1.0f + __expf(-z), r = __builtin_amdgcn_rcpf(y);
+    return fmaf(fmaxf(fmaf(-y, r, 1.0f), -1.0f), r, r);
+}
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -208,8 +216,8 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepNegArgs a)
 //   epilogue   dX through LDS, the shares added up, to the pairs' lanes: dxs = lr dX + lr g0 c.
 // Every workgroup streams all negatives twice, 2 N d x 2 bytes, which a compute unit takes in at 64 bytes a clock: 6.8 us at N = 1024, d =
 // 256 (a pass of 4096 clocks takes 5300), beside 3.4 us of MFMA and 2 of exponentials and reciprocals; the gather of the pairs' rows, which
-// nothing hides, 4 - 5.  8192 pairs: 23.0 us (27.5 with a phase's fragments requested when the last phase had ended, the
-// coefficients transposed through LDS and divisions rounded correctly before they are rounded to bf16).
+// nothing hides, 4 - 5.  8192 pairs: 22.2 us (27.0 with a phase's fragments requested when the last phase had ended, the
+// coefficients transposed through LDS and the sigmoid's reciprocal as a division).
 // (16 wavefronts, four per SIMD: 23.3 with whole phases requested ahead; 35 a quarter ahead, which takes more than their 128 registers.)
 // ---------------------------------------------------------------------------------------------
 struct ScoresArgs {
