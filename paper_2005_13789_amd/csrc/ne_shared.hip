@@ -44,9 +44,10 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kPairTile = 32;      // pairs per workgroup in the scores kernel
 constexpr int kScoreThreads = 512; // 8 wavefronts: one 32-negative block of S each, one 32-column block of dX over a share of the negatives each
 constexpr int kNegChunk = 256;     // negatives per pass of the scores kernel (8 wavefronts x 32)
-// Partial sums of the dC product.  With 8 instead of 16 of them, from tiles of 64 columns instead of 128, that product takes as long and 8 MB
-// less are written and read again: 8192 pairs x 1024 negatives at dim 256 dctx 10.9 us then, 11.5 now, update 14.8 and 12.6.  (Dim 64 has one
-// such tile: 8 would halve the workgroups.)
+// Partial sums of the dC product: every sixteenth of the batch is summed by itself, and at dim 128 and 256 the two of a workgroup are added
+// before they are written, so that 8 MB less are written and read again: 8192 pairs x 1024 negatives, dim 256, dctx 11.3 us and update 12.1, with
+// 16 partial sums from tiles of 128 columns 11.8 and 15.1.  (One sum for both sixteenths takes as long, and its error is up to 26 % larger:
+// 16 384 pairs x 256, dim 128, 6.2e-8 of the deltas where two leave 4.9e-8.  Dim 64 has one tile of columns: 8 would halve the workgroups.)
 constexpr int kMostSplit = 16;
 constexpr int split_of(int dim) { return dim == 64 ? kMostSplit : 8; }
 constexpr int kBatchPad = 1024;    // the padded batch is a multiple of this (shares of whole 64-pair stages)
@@ -475,6 +476,8 @@ constexpr int kDctxColumns = 64;
 template <int SPLIT>
 __global__ __launch_bounds__(256) void dctx_kernel(DctxArgs a)
 {
+    constexpr int SUMS = kMostSplit / SPLIT;    // of a workgroup, side by side
+    static_assert(SUMS == 1 || SUMS == 2, "a share's stages are even (kBatchPad)");
     constexpr int NB = kDctxColumns / 32;       // column blocks of the tile, one per pair of wavefronts
     __shared__ u32x4 As[2][4][256];   // [block of 32 negatives][four steps of 64 lanes]
     __shared__ u32x4 Bs[2][NB][256];
@@ -483,11 +486,13 @@ __global__ __launch_bounds__(256) void dctx_kernel(DctxArgs a)
     const int64_t steps = a.w.Bp / 16;
     const int stages = static_cast<int>(steps / SPLIT / 4);
     const int nb0 = blockIdx.y * 4, cb0 = blockIdx.z * NB;
-    f32x16 acc[2];
+    f32x16 acc[SUMS][2];
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int h = 0; h < SUMS; ++h)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[r][i] = 0.0f;
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[h][r][i] = 0.0f;
 
     struct Stage { u32x4 a[4], b[NB]; };
     const int64_t first = blockIdx.x * (steps / SPLIT) * 64 + tid;
@@ -505,23 +510,26 @@ __global__ __launch_bounds__(256) void dctx_kernel(DctxArgs a)
 #pragma unroll
         for (int i = 0; i < NB; ++i) Bs[buf][i][tid] = s.b[i];
     };
-    auto multiply = [&](int buf) {
+    auto multiply = [&](int buf, f32x16 (&sum)[2]) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const bf16x8 a0 = __builtin_bit_cast(bf16x8, As[buf][2 * wr][k * 64 + l]);
             const bf16x8 a1 = __builtin_bit_cast(bf16x8, As[buf][2 * wr + 1][k * 64 + l]);
             const bf16x8 b = __builtin_bit_cast(bf16x8, Bs[buf][wc][k * 64 + l]);
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b, acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b, acc[1], 0, 0, 0);
+            sum[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b, sum[0], 0, 0, 0);
+            sum[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b, sum[1], 0, 0, 0);
         }
     };
     Stage next;
     fetch(0, next);
-    for (int k = 0; k < stages; ++k) {
-        stage(k & 1, next);
-        if (k + 1 < stages) fetch(k + 1, next);
-        lds_barrier();
-        multiply(k & 1);     // (the stage after the next overwrites this buffer behind another barrier)
+#pragma unroll
+    for (int h = 0; h < SUMS; ++h) {
+        for (int k = h * stages / SUMS; k < (h + 1) * stages / SUMS; ++k) {
+            stage(k & 1, next);
+            if (k + 1 < stages) fetch(k + 1, next);
+            lds_barrier();
+            multiply(k & 1, acc[h]);     // (the stage after the next overwrites this buffer behind another barrier)
+        }
     }
     float* out = a.w.dCp + static_cast<int64_t>(blockIdx.x) * a.N * a.D;
 #pragma unroll
@@ -529,7 +537,7 @@ __global__ __launch_bounds__(256) void dctx_kernel(DctxArgs a)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int row = (nb0 + 2 * wr + r) * 32 + (i >> 2) * 8 + (l >> 5) * 4 + (i & 3);
-            out[static_cast<int64_t>(row) * a.D + (cb0 + wc) * 32 + (l & 31)] = acc[r][i];
+            out[static_cast<int64_t>(row) * a.D + (cb0 + wc) * 32 + (l & 31)] = SUMS == 2 ? acc[0][r][i] + acc[SUMS - 1][r][i] : acc[0][r][i];
         }
 }
 

@@ -79,3 +79,32 @@ def test_coefficients_of_extreme_scores():
         ws = torch.empty(ne.ne_shared_workspace_bytes(d, 1, N), dtype=torch.uint8, device=DEV)
         ne.ne_train_batch_shared(t, alias, torch.tensor([[0, 1]], dtype=torch.int32, device=DEV), N, 1.0, 1.0, 0, ws)
         assert C[0, 1].item() == -N * want, (score, C[0, 1].item())
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("B", [1024, 8192])
+def test_every_sixteenth_of_a_batch_is_summed_by_itself(d, B):
+    """All scores are 0, so every coefficient is -2^-8.  One eighth of the batch has sources of 1 in its first half and of 1/64 of the
+    last place of that half's sum in its second, the rest of the batch sources of 0.  Added to the first half's sum, sixteen of the
+    small ones are a quarter of its last place and lost; summed by themselves they reach it (B = 1024) or eight times that."""
+    N, V, half = 128, 50_000, B // 16
+    small = float(np.spacing(np.float32(half))) / 64
+    want = -(2.0 ** -8) * (half + half * small)
+    assert float(np.float32(want)) == want != -(2.0 ** -8) * half
+    X = torch.zeros((V, d), dtype=torch.float32, device=DEV)
+    C = torch.zeros((V, d), dtype=torch.float32, device=DEV)
+    X[1, 0], X[2, 0] = 1.0, small
+    t = ne.ne_create_tables(X, C, 2, init=False)
+    alias = ne.ne_build_neg_alias(np.ones(V, np.uint32), 0, torch.empty((V, 2), dtype=torch.int32, device=DEV))
+    ws = torch.empty(ne.ne_shared_workspace_bytes(d, B, N), dtype=torch.uint8, device=DEV)
+    neg = torch.empty(N, dtype=torch.int32, device=DEV)
+    pairs = torch.zeros((B, 2), dtype=torch.int32, device=DEV)
+    pairs[10 * half:11 * half, 0] = 1
+    pairs[11 * half:12 * half, 0] = 2
+    ne.ne_train_batch_shared(t, alias, pairs, N, 1.0, 2.0 ** -7, 1, ws, neg)
+    named = torch.bincount(neg.long(), minlength=V)
+    named[0] = 0                     # the pairs' context row
+    got = C[named == 1, 0]
+    assert got.numel() > 100
+    print(f"d={d} B={B}: {got.min().item()!r} .. {got.max().item()!r}, wanted {want!r}", flush=True)
+    assert (got == want).all()
