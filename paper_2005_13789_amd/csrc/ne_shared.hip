@@ -111,7 +111,7 @@ bool shared_layout(int32_t dim, int64_t B, int32_t N, char* base, SharedWs* w)
     w->GP = reinterpret_cast<uint16_t*>(take(n * Bp * 2));
     w->dxs = reinterpret_cast<float*>(take(Bp * d * 4));
     w->dcs = reinterpret_cast<float*>(take(Bp * d * 4));
-    w->dCp = reinterpret_cast<float*>(take(static_cast<size_t>(kMostSplit) * n * d * 4));
+    w->dCp = reinterpret_cast<float*>(take(static_cast<size_t>(split_of(dim)) * n * d * 4));
     w->negids = reinterpret_cast<int32_t*>(take(n * 4));
     size_t cap = 4096;
     while (cap < 4 * (2 * Bp + n)) cap <<= 1;

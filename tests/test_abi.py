@@ -149,3 +149,20 @@ def test_workspace_bytes():
     assert ne.ne_workspace_bytes(128, 10, 63) == 0
     assert ne.ne_workspace_bytes(128, ne.NE_MAX_BATCH + 1, 5) == 0
     assert ne.ne_workspace_bytes(128, 8192, 5) > w
+
+
+def test_shared_workspace_bytes():
+    """Nothing is asked for that is not laid out: bf16 source rows and coefficients, the negatives' rows in two orders, two deltas
+    per pair, 16 partial sums of the negatives' deltas at dim 64 and 8 beyond, ids, nine bytes per position of the hash table."""
+    for dim, B, N in ((64, 8192, 1024), (128, 1500, 256), (256, 8192, 1024), (256, 1, 65536), (128, 1 << 20, 128)):
+        padded = -(-B // 1024) * 1024
+        positions = 4096
+        while positions < 4 * (2 * padded + N):
+            positions *= 2
+        laid_out = (2 * padded * dim + 2 * 2 * N * dim + 2 * N * padded + 2 * 4 * padded * dim + (16 if dim == 64 else 8) * 4 * N * dim
+                    + 4 * N + 9 * positions)
+        assert laid_out <= ne.ne_shared_workspace_bytes(dim, B, N) <= laid_out + 10 * 256
+    # the largest shapes with 1024 negatives that the header names for the static scratch
+    for dim, B in ((256, 4096), (128, 8192)):
+        assert ne.ne_shared_workspace_bytes(dim, B, 1024) <= ne.NE_SHARED_STATIC_SCRATCH_BYTES
+        assert ne.ne_shared_workspace_bytes(dim, B + 1, 1024) > ne.NE_SHARED_STATIC_SCRATCH_BYTES

@@ -109,3 +109,33 @@ def test_static_scratch_rejects_shapes_beyond_its_size():
     ne.ne_train_batch_shared_static(t, alias, pairs[:0], 128, 0.1, 0.1, 0)        # empty batch: no-op
     torch.cuda.synchronize()
     assert not vertex.any() and not context.any()
+
+
+@pytest.mark.parametrize("d,B", [(256, 4096), (128, 8192)])
+def test_static_scratch_at_its_largest_shapes(d, B):
+    """With 1024 negatives no more pairs fit.  Bars as above."""
+    say(f"static scratch, largest: d={d} B={B}")
+    L = ne.lib()
+    V, N, lr = 50_000, 1024, 0.05
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d)
+    X0 = torch.empty((V, d), dtype=torch.float32, device=DEV).normal_(0, 0.2, generator=gen)
+    C0 = torch.empty((V, d), dtype=torch.float32, device=DEV).normal_(0, 0.2, generator=gen)
+    pairs = torch.randint(V, (B, 2), generator=gen, device=DEV, dtype=torch.int32)
+    out = []
+    for static in (False, True):
+        X, C = X0.clone(), C0.clone()
+        t = ne.ne_create_tables(X, C, 5, init=False)
+        alias = ne.ne_build_neg_alias(np.ones(V, np.uint32), 0, torch.empty((V, 2), dtype=torch.int32, device=DEV))
+        neg = torch.empty(N, dtype=torch.int32, device=DEV)
+        loss = torch.zeros((), dtype=torch.float64, device=DEV)
+        if static:
+            assert raw_static(L, t, alias, pairs, N, lr, 5.0 / N, 9, neg, loss) == ne.NE_OK, ne.ne_last_error()
+        else:
+            ws = torch.empty(ne.ne_shared_workspace_bytes(d, B, N), dtype=torch.uint8, device=DEV)
+            ne.ne_train_batch_shared(t, alias, pairs, N, lr, 5.0 / N, 9, ws, neg, loss)
+        torch.cuda.synchronize()
+        out.append((X.cpu().numpy(), C.cpu().numpy(), neg.cpu().numpy(), loss.item()))
+    (xw, cw, nw, lw), (xs, cs, ns, ls) = out
+    assert np.array_equal(nw, ns) and abs(lw - ls) <= 1e-9 * abs(lw)
+    assert delta_err(X0.cpu().numpy(), xs, xw) <= 1e-5 and delta_err(C0.cpu().numpy(), cs, cw) <= 1e-5
