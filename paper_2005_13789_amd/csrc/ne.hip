@@ -2184,10 +2184,12 @@ hipError_t launch_train_seg(const Shape& s, const TrainArgs& a, const Helpers& h
     return hipErrorInvalidValue;
 }
 
-// Workgroups of 512 threads where they all have a place at once (four on a compute unit) and a tile has two references for each.
-// 65 536 pairs, K = 5, among 1 M / 32 M nodes: the first claim 11.7 / 20.1 us, bins and the second claim together 12.3 / 18.4.
+// Workgroups of 512 threads where a tile has two references for each and up to 1024 workgroups do.  Three have a place on a compute unit (their
+// 104 scalar registers leave seven wavefronts per SIMD), 768 on the chip, which is every launch of bins and tiles up to 512 of the one and 256
+// of the other.  65 536 pairs, K = 5, among 1 M / 32 M nodes: the first claim 11.7 / 20.1 us, bins and the second claim together 12.3 / 18.4.
 // (1024 threads leave the bins and the second claim no place side by side: with both claims in the first launch 16.5 / 32.2 and
-// 10.6 / 13.0; 256 for bins and claim 19.6 / 24.8.)
+// 10.6 / 13.0; 256 for bins and claim 19.6 / 24.8.)  Up to 1024, where some wait for a place: 512 against 256 threads, one call with one batch,
+// 896 tiles (2^22 pairs, dim 16, 8 M nodes) 4220 and 4306 us; 1024 bins, 130 000 pairs, dim 16, 94.3 and 95.3, 100 000, dim 128, 187.2 and 184.7.
 constexpr uint32_t kWideTile = 1024;
 constexpr unsigned kWideBlocks = 1024;
 hipError_t launch_prepare(const Helpers& h, bool claim_first, hipStream_t st)
