@@ -118,9 +118,9 @@ constexpr uint32_t kWordBinBits = 12, kMaxBinBits = 14;      // most bins whose 
 constexpr uint32_t kMinTile = 256;
 constexpr uint64_t kOneBin = 256;
 constexpr struct { uint32_t bits; uint64_t refs; } kBinSteps[] = {{5, 64}, {6, 128}, {8, 256}, {kWordBinBits, 1024}, {kMaxBinBits, 1200}};   // most references per bin, up to 2^bits bins
-inline Binning binning(uint64_t refs)
+constexpr Binning binning(uint64_t refs)
 {
-    Binning b;
+    Binning b{};
     b.bits = 0;
     for (const auto& step : kBinSteps)
         while (refs > kOneBin && b.bits < step.bits && (step.refs << b.bits) < refs) ++b.bits;
@@ -645,6 +645,18 @@ __device__ __forceinline__ void claim_long_rows(const PrepArgs& a, uint32_t tile
     }
 }
 
+// Most references of a tile in one bin for which each has an entry.
+// (A bin whose rows are many has up to 13 references or so of the mean 4; where tiles are few, a bin's references stay few
+// whatever one tile has of them; the third pass over a long tile lengthens the claim phase, a launch's longest chain, where as
+// many entries in the resolve phase still hide behind it: 2 x 262 144 pairs, dim 128, K = 10, 5 % with one source row, 68 of them a
+// tile, 1896 us with it, 1824 without; 18 at all lengths also 2 x 2^22 pairs among 4 M nodes, 0.5 % with one, 8250 instead of 7710)
+__host__ __device__ constexpr uint32_t most_singles(const Binning& b)
+{
+    const uint32_t by_mean = 4u * (b.tile >> b.bits) + 2u, by_tile = b.tile / 512u * 3u, by_tiles = kTileStep / b.tiles;
+    const uint32_t most = by_mean > by_tile ? by_mean : by_tile;
+    return most > by_tiles ? most : by_tiles;
+}
+
 // One tile of references: draw, count by bin, then write the entries of each bin side by side.
 // All T threads of the workgroup call this together; hist: claim_lds_bytes() of LDS.
 template <RefMode MODE, uint32_t T>
@@ -672,11 +684,7 @@ __device__ __forceinline__ void claim_tile(const PrepArgs& a, uint32_t tile, uin
     }
     lds_barrier();
     uint32_t total;
-    // (a bin whose rows are many has up to 13 references or so of the mean 4; where tiles are few, a bin's references stay few
-    // whatever one tile has of them; the third pass over a long tile lengthens the claim phase, a launch's longest chain, where as
-    // many entries in the resolve phase still hide behind it: 2 x 262 144 pairs, dim 128, K = 10, 5 % with one source row, 68 of them a
-    // tile, 1896 us with it, 1824 without; 18 at all lengths also 2 x 2^22 pairs among 4 M nodes, 0.5 % with one, 8250 instead of 7710)
-    const uint32_t most = max(max(4u * (a.bin.tile >> bits) + 2u, a.bin.tile / 512u * 3u), kTileStep / a.bin.tiles);
+    const uint32_t most = most_singles(a.bin);
     if (a.bin.tile <= kTileStep) {                   // (uniform)
         if (!start_bins<T>(a, tile, hist, kSingles, most, &total)) {
             claim_rows<T>(a, tile, first, last, key, hist);
@@ -816,7 +824,9 @@ __device__ __forceinline__ uint2 fetch_segment(const PrepArgs& a, uint32_t bin, 
 
 // Numbers the entries of these tiles and returns how many they are; *before: the tiles' references in lower bins.  SHARE: if they
 // are a share, tile_of says whose each is (a search through 224 tiles is 8 accesses to LDS in turn).  All threads call this together.
-constexpr uint32_t kShortSegment = 32;       // (tiles of one step have up to 18 references in a bin before equal rows are looked for)
+// (A tile of one step has up to most_singles references in a bin, 18 with 64 bins and 108 tiles or more, 2048 / tiles with fewer tiles, beyond
+// which equal rows share entries.  Batches of 257 .. 512 references, 8 bins and two tiles, have segments of 32 on average and mostly search.)
+constexpr uint32_t kShortSegment = 32;
 template <uint32_t T, bool SHARE>
 __device__ __forceinline__ uint32_t number_entries(const PrepArgs& a, uint2 segment, uint32_t tile0, ResolveLds& s, uint32_t* before)
 {

@@ -29,16 +29,31 @@ def test_multiplicities_and_bins(B):
     step_and_check(t, None, None, None, pairs.astype(np.int32), 0, seed, 1)
 
 
-# 4096 references: 64 bins, tiles of 256 references with 4 per bin on average and up to 18 before equal rows are looked for
-@pytest.mark.parametrize("together", [17, 18, 19, 31, 32, 33, 60])
-def test_entries_of_a_tile_in_one_bin(together):
-    print(f"together={together}", flush=True)
-    V, d, seed = 1_000_000, 4, 22
+# A chosen number of references of some tiles in one bin.  (tests/test_lds_layout.py has the compiler check these batches' bins and tiles.)
+#   2100 pairs     64 bins, tiles of 128 pairs with 4 references per bin on average: segments of up to 32 entries are listed, beyond that searched
+#   60 000 pairs  256 bins, tiles of 512 pairs with 4 per bin: up to 18 references of a tile in a bin have an entry each, beyond that
+#                 equal rows are looked for; `rows` of them, the others' equals
+@pytest.mark.parametrize("B,bits,tile_pairs,tiles,together,rows",
+                         [(2100, 6, 128, (0, 3, 15), n, n) for n in (17, 31, 32, 33, 60)]
+                         + [(60_000, 8, 512, (0, 50, 116), n, m) for n, m in ((18, 18), (19, 19), (18, 9), (19, 10), (33, 33))])
+def test_entries_of_a_tile_in_one_bin(B, bits, tile_pairs, tiles, together, rows):
+    print(f"B={B} together={together} rows={rows}", flush=True)
+    V, d, seed, bin = 1_000_000, 4, 22, 5
     rng = np.random.default_rng(together)
     ids = np.arange(V, dtype=np.uint64)
-    same = ids[((ids * 0x9E3779B1) & 0xFFFFFFFF) >> 26 == 5]
-    pairs = rng.integers(0, V, (2048, 2))
-    for tile in (0, 3, 15):          # 128 pairs each
-        pairs[tile * 128:tile * 128 + together, 0] = same[tile * 60:tile * 60 + together]
-    t = make(V, d, 2048, 0, seed)
+
+    def bin_of(keys):
+        return ((keys * 0x9E3779B1) & 0xFFFFFFFF) >> (32 - bits)
+
+    # sources, and contexts, whose key has the top bit, of other bins; then the chosen sources
+    sources, contexts = ids[bin_of(ids) != bin], ids[bin_of(ids | 0x80000000) != bin]
+    same = rng.permutation(ids[bin_of(ids) == bin])
+    pairs = np.stack([rng.choice(sources, B), rng.choice(contexts, B)], axis=1)
+    for k, tile in enumerate(tiles):
+        named = np.resize(same[k * rows:(k + 1) * rows], together)
+        pairs[tile * tile_pairs + rng.permutation(tile_pairs)[:together], 0] = named
+    in_bin = (bin_of(pairs[:, 0]) == bin).astype(int) + (bin_of(pairs[:, 1] | 0x80000000) == bin)
+    for tile in range(-(-B // tile_pairs)):
+        assert in_bin[tile * tile_pairs:(tile + 1) * tile_pairs].sum() == (together if tile in tiles else 0)
+    t = make(V, d, B, 0, seed)
     step_and_check(t, None, None, None, pairs.astype(np.int32), 0, seed, 1)
