@@ -754,7 +754,7 @@ struct alignas(16) ResolveLds {
     uint8_t tile_of[2048];    // of each entry of a share, if no segment is long
     // then the table, slot after slot: the row's key; its references, later its first, or next, place in the list (~0: not shared)
 };
-static_assert(sizeof(ResolveLds) % alignof(uint2) == 0, "the table's slots are read and written whole");
+static_assert(sizeof(ResolveLds) % alignof(uint4) == 0, "the table is cleared two slots at a time");
 inline size_t resolve_lds_bytes(const Binning& b) { return sizeof(ResolveLds) + (static_cast<size_t>(8) << b.slot_bits); }
 
 // Work item of a row with up to kItemRefs places in the list: x = key, y = first place << 3 | places - 1.  A row with

@@ -1,7 +1,7 @@
 """LDS areas that a kernel lays out by hand start at the alignment of what they hold.
 
-The dynamic LDS of a workgroup is 16-byte aligned; the resolve phase puts its table of uint2 right behind ResolveLds, whose
-size is therefore checked (by the compiler, in a translation unit that sees the kernels' source)."""
+The dynamic LDS of a workgroup is 16-byte aligned; the resolve phase puts its table of uint2, which it clears two slots at a time,
+right behind ResolveLds, whose size is therefore checked (by the compiler, in a translation unit that sees the kernels' source)."""
 import os
 import shutil
 import subprocess
@@ -12,7 +12,7 @@ from paper_2005_13789_amd import build as ne_build
 
 SRC = """
 #include "{src}"
-static_assert(sizeof(ResolveLds) % alignof(uint2) == 0, "the resolve table's slots are read and written whole");
+static_assert(sizeof(ResolveLds) % alignof(uint4) == 0, "the resolve table is cleared two slots at a time");
 static_assert(alignof(ResolveLds) <= 16, "dynamic LDS");
 """
 
