@@ -61,7 +61,7 @@ def test_loss_rounds(B, K):
     assert abs(loss.item() - want) <= 1e-6 * want
 
 
-@pytest.mark.parametrize("d", [64, 256])
+@pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("B,N", [(1, 128), (33, 256), (1024, 384), (1025, 512), (2049, 640), (5000, 1152)])
 def test_shared_passes(d, B, N):
     """Half a pass of 256 negatives, whole ones and both; one and several stages of the dC product.  Bars: a
