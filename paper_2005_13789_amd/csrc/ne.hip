@@ -2219,7 +2219,7 @@ hipError_t launch_prepare(const Helpers& h, bool claim_first, hipStream_t st)
 // references a pair has (the train kernel's groups, with a lane per reference, leave 63 of 64 lanes idle at dim 4,
 // K = 62: 32 768 pairs among a million nodes 465 us, now 316; 2^20 pairs among 64 million 19.3 ms, now 13.9).  Its number of items is only
 // known on the device; kApplyGroups lane groups leave each a few of them, of which all but the first find their entries there, and not so many
-// that those with long lists finish last (6 x 65 536 pairs, dim 128, 32 M / 1 M nodes, and 3 x 32 768, dim 512: 131 072 groups 693 / 625 /
+// that those with long lists finish last (level but for the fewest of dim 512: 6 x 65 536 pairs, dim 128, 32 M / 1 M nodes, and 3 x 32 768, dim 512: 131 072 groups 693 / 625 /
 // 944 us, 57 344 692 / 622 / 945, 28 672 689 / 627 / 949, 14 336 694 / 627 / 962), but kApplyBlocks workgroups at least, where
 // groups are small (the apply launch of 2^22 pairs, dim 16, with a quarter of them 784 instead of 681 us).  Up to
 // kHubBlocks workgroups more take the hubs' items, whose chains are the longest (512 take 6 % more of a batch of 65 536 pairs among

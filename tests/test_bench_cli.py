@@ -21,7 +21,7 @@ def test_more_than_one_gpu_is_refused():
 
 def test_no_gpu_no_fallback():
     if torch.cuda.is_available():
-        return                                        # on a GPU machine the benchmark itself is the test
+        return                                        # with a GPU the benchmark itself is the test
     r = run("--steps", "1", "--warmup", "0")
     assert r.returncode == 1
     assert "no GPU" in r.stderr and r.stdout.strip() == ""
